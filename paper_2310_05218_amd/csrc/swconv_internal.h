@@ -154,6 +154,12 @@ bool       mfma_f32_dma_supported(const Conv2dShape& s, const float* x, const fl
 hipError_t launch_mfma_f32_dma(const float* x, const float* w, float* y, const Conv2dShape& s, hipStream_t st,
                                const Epilogue& ep = Epilogue{nullptr, 0});
 
+// ---- multi-channel fp32, nine taps, any stride / padding / dilation: operands as sums of three bf16 values on the bf16
+// matrix instructions (tensors below 2 GiB, a tile of output rows and its window within LDS)
+bool       mfma_f32_split_supported(const Conv2dShape& s);
+hipError_t launch_mfma_f32_split(const float* x, const float* w, float* y, const Conv2dShape& s, hipStream_t st,
+                                 const Epilogue& ep = Epilogue{nullptr, 0});
+
 // ---- fp32 / bf16 / half multi-channel convolution on channel-last tensors ------------------------------------
 enum Elem { kElemF32 = 0, kElemBF16 = 1, kElemF16 = 2 };      // element format of x, w and y
 constexpr int elem_size(int ek) { return ek == kElemF32 ? 4 : 2; }
