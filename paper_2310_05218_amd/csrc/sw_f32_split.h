@@ -14,7 +14,7 @@
 // bf16 range) are reported by split_f32 through `tiny`.  Kernels compute what either can reach by plain fp32 multiply-adds.
 #pragma once
 
-#include <hip/hip_runtime.h>
+#include "swconv_internal.h"
 
 namespace swconv {
 
@@ -63,22 +63,44 @@ __device__ __forceinline__ Split8 split_f32(const float (&v)[8], unsigned& tiny)
 }
 constexpr unsigned kTinyBits = 0x0c800000u << 1;        // 2^-102, as `tiny` counts
 
-// An accumulator that may have lost something the operands had: not finite, or so small that partial products underflowed.
-__device__ __forceinline__ bool split_suspect(float acc)
+// Accumulators that may have lost something the operands had: not finite, or so small (below 2^-100, but not zero) that
+// partial products underflowed.  (In integer minima and maxima: as sixteen comparisons the compiler gathers them bit by bit.)
+__device__ __forceinline__ bool split_suspect(const splitx16& acc)
 {
-    const unsigned a = __float_as_uint(acc) & 0x7fffffffu;
-    return a >= 0x7f800000u || (a != 0 && a < 0x0d800000u);        // (2^-100)
+    unsigned hi = 0, lo = ~0u;
+#pragma unroll
+    for (int v = 0; v < 16; ++v) {
+        const unsigned a = __float_as_uint(acc[v]) << 1;
+        hi = max(hi, a);
+        lo = min(lo, a - 1u);
+    }
+    return hi >= 0x7f800000u << 1 || lo < (0x0d800000u << 1) - 1u;
 }
 
-// acc += a x b, the six products in ascending order of magnitude
-__device__ __forceinline__ splitx16 mfma_split(const Split8& a, const Split8& b, splitx16 acc)
+// Stores a block's 32 output channels x 32 pixels: register v of a lane is output channel co + 8 (v / 4) + v % 4 of its pixel
+// (co: the lane's first channel, yp: its place), channels HoWo floats apart; nontemporal, because a launch's last lines would
+// otherwise wait in L2 for its end.  Whole blocks without a test per value: sixteen of them, each with the tests of the
+// epilogue, cost more than the stores.
+__device__ __forceinline__ void store_block(splitx16 acc, float* yp, int HoWo, int co, int C_out, bool whole, const Epilogue& ep)
 {
-    acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a.l, b.h, acc, 0, 0, 0);
-    acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a.h, b.l, acc, 0, 0, 0);
-    acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a.m, b.m, acc, 0, 0, 0);
-    acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a.m, b.h, acc, 0, 0, 0);
-    acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a.h, b.m, acc, 0, 0, 0);
-    return __builtin_amdgcn_mfma_f32_32x32x16_bf16(a.h, b.h, acc, 0, 0, 0);
+    if (whole) {
+        if (ep.bias) {
+#pragma unroll
+            for (int v = 0; v < 16; ++v) acc[v] += ep.bias[co + 8 * (v >> 2) + (v & 3)];
+        }
+        if (ep.relu) {
+#pragma unroll
+            for (int v = 0; v < 16; ++v) acc[v] = fmaxf(acc[v], 0.f);
+        }
+#pragma unroll
+        for (int v = 0; v < 16; ++v) __builtin_nontemporal_store(acc[v], yp + (int64_t)(8 * (v >> 2) + (v & 3)) * HoWo);
+    } else {
+#pragma unroll
+        for (int v = 0; v < 16; ++v) {
+            const int c = 8 * (v >> 2) + (v & 3);
+            if (co + c < C_out) __builtin_nontemporal_store(apply_epilogue(acc[v], co + c, ep), yp + (int64_t)c * HoWo);
+        }
+    }
 }
 
 // One output by plain fp32 multiply-adds, taps in the padding as zeros: what an accumulator that is no use is replaced by.

@@ -318,7 +318,7 @@ __global__ __launch_bounds__(64 * (CW + 4), CW / 4 + 1) void mfma_f32_split_kern
         for (int b = 0; b < PB; ++b) acc[b] += low[b];
 
         // ---- store: register v of a lane is output channel 8 (v / 4) + 4 kk + v % 4, pixel lj
-        const bool again = *reinterpret_cast<volatile int*>(flag) != 0;
+        const bool again = *flag != 0;                  // (not volatile: that would be a flat load, and wait for the stores)
 #pragma unroll
         for (int b = 0; b < PB; ++b) {
             const int p = 32 * (CW * b + wave) + lj;
@@ -326,10 +326,7 @@ __global__ __launch_bounds__(64 * (CW + 4), CW / 4 + 1) void mfma_f32_split_kern
             const int im = fast_div(p, P.by_thwo), rem = p - im * thwo;
             const int ol = fast_div(rem, P.by_Wo), ow = rem - ol * P.Wo;
             float* yp = y + ((int64_t)(n0 + im) * P.C_out + co0) * HoWo + (row0 + ol) * P.Wo + ow;
-            bool bad = again;
-#pragma unroll
-            for (int v = 0; v < 16; ++v) bad |= split_suspect(acc[b][v]);
-            if (__builtin_expect(bad, 0)) {
+            if (__builtin_expect(again || split_suspect(acc[b]), 0)) {
 #pragma unroll 1
                 for (int v = 0; v < 16; ++v) {
                     const int co = 8 * (v >> 2) + 4 * kk + (v & 3);
@@ -339,11 +336,7 @@ __global__ __launch_bounds__(64 * (CW + 4), CW / 4 + 1) void mfma_f32_split_kern
                 }
                 continue;
             }
-#pragma unroll
-            for (int v = 0; v < 16; ++v) {
-                const int co = 8 * (v >> 2) + 4 * kk + (v & 3);
-                if (co0 + co < P.C_out) __builtin_nontemporal_store(apply_epilogue(acc[b][v], co0 + co, P.ep), yp + (int64_t)co * HoWo);
-            }
+            store_block(acc[b], yp + (int64_t)(4 * kk) * HoWo, HoWo, co0 + 4 * kk, P.C_out, co0 + 32 <= P.C_out, P.ep);
         }
     }
 }

@@ -242,6 +242,9 @@ static int run_conv2d(const float* x, const float* w, float* y, const Conv2dShap
             return launch_status(launch_mfma_f32_pointwise(x, w, y, s, st, ep));
         if (s.R * s.S >= 25 && s.C_in >= 8 && mfma_f32_rows_supported(s, x))
             return launch_status(launch_mfma_f32_rows(x, w, y, s, st, ep));
+        // Few channels at an even stride (the first layer of an image network): K along the filter rows
+        // (7 x 7 stride 2, 3 -> 64 at 224 x 224: 162 -> 71 us; 3 x 3 stride 2: 52 -> 50, 9.2 -> 6 for one image)
+        if (mfma_f32_stem_supported(s)) return launch_status(launch_mfma_f32_stem(x, w, y, s, st, ep));
         // Nine taps: operands as sums of three bf16 values.  Faster than the kernels below on every such layer timed (us, one
         // image, 56 x 56 -> 64 channels: 16 channels 9.8 -> 6.8, 32 13.4 -> 8.6, 64 20.2 -> 11.1; 32 images 25.7 -> 25.1,
         // 41.4 -> 36.5, 75.0 -> 62.8); up to 32 channels the direct-to-LDS kernel keeps the plans its tests assert.

@@ -160,6 +160,12 @@ bool       mfma_f32_split_supported(const Conv2dShape& s);
 hipError_t launch_mfma_f32_split(const float* x, const float* w, float* y, const Conv2dShape& s, hipStream_t st,
                                  const Epilogue& ep = Epilogue{nullptr, 0});
 
+// ---- multi-channel fp32, few input channels (2 .. 7), even stride, rows of at most 8 taps, at most 22 (row, channel) pairs:
+// K along the filter rows, operands as sums of three bf16 values
+bool       mfma_f32_stem_supported(const Conv2dShape& s);
+hipError_t launch_mfma_f32_stem(const float* x, const float* w, float* y, const Conv2dShape& s, hipStream_t st,
+                                const Epilogue& ep = Epilogue{nullptr, 0});
+
 // ---- fp32 / bf16 / half multi-channel convolution on channel-last tensors ------------------------------------
 enum Elem { kElemF32 = 0, kElemBF16 = 1, kElemF16 = 2 };      // element format of x, w and y
 constexpr int elem_size(int ek) { return ek == kElemF32 ? 4 : 2; }

@@ -102,3 +102,68 @@ def test_split_kernel_small_values(torch, sw, oracle, exponent):
     y = sw.sw_conv2d(torch.from_numpy(x).cuda(), torch.from_numpy(w).cuda(), 1, 1)
     assert sw.sw_last_kernel().startswith("mfma_f32_split_kernel")
     assert_f32_parity(y.cpu().numpy(), y_ref, d, f"2^{exponent}")
+
+
+STEM_CASES = [
+    # N, C_in, C_out, H, W, R, S, stride, pad, kernel (steps of two filter rows, output rows per tile)
+    (2, 3, 64, 33, 47, 7, 7, 2, 3, "mfma_f32_stem_kernel<11,"),     # odd plane, rows of 24 outputs
+    (1, 3, 32, 32, 32, 7, 7, 2, 3, "mfma_f32_stem_kernel<11,"),     # one block of output channels: every wavefront takes it
+    (1, 3, 70, 19, 300, 7, 7, 2, 3, "mfma_f32_stem_kernel<11,"),    # two channel groups, the second with six channels; long rows
+    (9, 3, 48, 61, 75, 7, 7, 2, 3, "mfma_f32_stem_kernel<11,"),     # a group of 48 channels; the last row tile short
+    (40, 3, 64, 56, 56, 7, 7, 2, 3, "mfma_f32_stem_kernel<11,"),    # several tiles per workgroup
+    (1, 3, 48, 20, 20, 3, 3, 2, 1, "mfma_f32_stem_kernel<5,"),      # nine row pairs
+    (1, 5, 70, 30, 31, 3, 3, 2, 0, "mfma_f32_stem_kernel<8,"),      # fifteen, no padding
+    (2, 2, 64, 40, 41, 5, 5, 4, 2, "mfma_f32_stem_kernel<5,"),      # stride 4
+    (1, 4, 64, 24, 26, 4, 2, 2, 1, "mfma_f32_stem_kernel<8,"),      # rectangular, even extents
+    (1, 2, 64, 12, 40, 11, 8, 2, 4, "mfma_f32_stem_kernel<11,"),    # rows of eight taps, 22 pairs
+    (1, 3, 8, 7, 7, 7, 7, 2, 0, "mfma_f32_stem_kernel<11,"),        # a single output pixel
+]
+
+
+@pytest.mark.parametrize("case", STEM_CASES, ids=lambda c: "x".join(map(str, c[:9])))
+@pytest.mark.parametrize("shift", [0, 1], ids=["aligned", "4-byte"])
+def test_few_channels_kernel(torch, sw, oracle, case, shift):
+    """Few input channels at an even stride: K along the filter rows.  The input and the filters also from views that are only
+    4-byte aligned (the loads are 16 bytes wide), followed by NaN that must not be reached."""
+    N, Ci, Co, H, W, R, S, st, pad, kernel = case
+    x = inputs.normal_f32((N, Ci, H, W), 5400 + H)
+    w = inputs.normal_f32((Co, Ci, R, S), 5500 + Co, (2.0 / (Ci * R * S)) ** 0.5)
+    b = inputs.normal_f32((Co,), 5600, 0.5)
+    y_ref, d = oracle.conv2d(x, w, st, pad)
+
+    def view(a):
+        buf = torch.full((a.size + 8,), float("nan"), device="cuda")
+        buf[shift:shift + a.size] = torch.from_numpy(a).cuda().reshape(-1)
+        return buf[shift:shift + a.size].view(a.shape)
+
+    xd, wd = view(x), view(w)
+    buf, out, front, n, guard = guarded_empty(torch, y_ref.shape, torch.float32)
+    sw.sw_conv2d(xd, wd, st, pad, out=out)
+    assert sw.sw_last_kernel().startswith(kernel), sw.sw_last_kernel()
+    assert_f32_parity(out.cpu().numpy(), y_ref, d, str(case))
+    assert_guards_intact(buf, front, n, guard)
+    y = sw.sw_conv2d_bias_relu(xd, wd, torch.from_numpy(b).cuda(), st, pad, True)
+    yr, dr = oracle.conv2d_bias_relu(x, w, b, st, pad, True)
+    assert_f32_parity(y.cpu().numpy(), yr, np.maximum(dr, 1e-30), f"{case} bias, rectifier")
+
+
+@pytest.mark.parametrize("value", [np.inf, np.nan, 3.4028234e38, 2.0 ** -120], ids=str)
+@pytest.mark.parametrize("where", ["x", "w"])
+def test_few_channels_kernel_special_values(torch, sw, value, where):
+    rng = np.random.default_rng(8)
+    x = rng.uniform(0.5, 1.0, (1, 3, 20, 22)).astype(np.float32)
+    w = rng.uniform(0.001, 0.002, (32, 3, 7, 7)).astype(np.float32)
+    if value < 1e-30:       # a value whose parts leave the bf16 range, alone under a weight that lifts it back
+        (x if where == "x" else w)[:] = 0.0
+        (w if where == "x" else x)[:] *= np.float32(2.0 ** 100)
+        value = np.float32(value) * np.float32(1.2345678)
+    elif where == "w":
+        x *= 0.125
+    (x if where == "x" else w).flat[633 if where == "x" else 700] = value
+    y = sw.sw_conv2d(torch.from_numpy(x).cuda(), torch.from_numpy(w).cuda(), 2, 0).cpu().numpy()
+    assert sw.sw_last_kernel().startswith("mfma_f32_stem_kernel")
+    ref = torch.nn.functional.conv2d(torch.from_numpy(x).double(), torch.from_numpy(w).double(), stride=2).numpy()
+    with np.errstate(all="ignore"):
+        _same_but_finite(y, ref.astype(np.float32) if not np.isfinite(value) else ref, f"{value} in {where}")
+        ok = np.isfinite(ref)
+        assert np.all(np.abs(y[ok] - ref[ok]) <= 2e-5 * np.abs(ref[ok]))
