@@ -23,6 +23,7 @@
 // Measured on 32 x 256 x 56 x 56 -> 64 (784 tiles of 128 pixels, one per wavefront): filters in LDS 3.5 us after the
 // start, 33.8 us in the loop (65536 cycles of matrix instructions at the 1.94 GHz the chip holds under them: the loop
 // runs at the rate of the matrix pipe), 3.8 us of stores; 46 us per launch, where the window kernels take 71.
+#include "sw_f32_split.h"
 #include "swconv_internal.h"
 
 namespace swconv {
@@ -33,6 +34,7 @@ typedef float floatx4 __attribute__((ext_vector_type(4)));
 typedef float floatx16 __attribute__((ext_vector_type(16)));
 
 constexpr size_t kPwLdsMax = 150 * 1024;
+constexpr size_t kPwLdsSplit = 156 * 1024;    // of split filters
 constexpr int kRing = 3;      // register sets of B operands (measured: 4 and 6 are no faster)
 
 struct PwParams {
@@ -41,6 +43,8 @@ struct PwParams {
     int tiles;        // of 32 * QB pixels
     int wpitch;       // floats between filter rows in LDS
     FastDiv by_c4;    // 16-byte groups per filter row
+    int flag_off;     // (split) of four words, one per wavefront: a filter value too small to split
+    FastDiv by_oct;   // (split) groups of eight channels, rounded up to whole steps
     Epilogue ep;
 };
 
@@ -212,9 +216,251 @@ __global__ __launch_bounds__(256, 2) void mfma_f32_pointwise_kernel(const float*
     }
 }
 
+// The same walk on the bf16 matrix instructions, each fp32 operand as a sum of three bf16 values (sw_f32_split.h: six products
+// of K = 16 take 0.375 of the fp32 instruction's time).  A K step is 16 channels, 8 kk + j for element j of lane half kk: a lane
+// splits the eight values it loaded for one of its pixels, between the matrix instructions of the pixel before.  The filters
+// (zeros up to the next 16 channels) are split into LDS once, before the first tile: [step][h, m, l][lane half][output channel]
+// of 16 bytes.  Both kernels report one name: block and pixel counts are chosen the same way for both.
+// Measured (us per launch, fp32 matrix instructions -> split): 32 x 256 x 56 x 56 -> 64 48.6 -> 37.2, 64 -> 256 53.5 -> 47.1,
+// 256 -> 256 at 28 x 28 44.5 -> 33, 512 -> 512 at 14 x 14 42.5 -> 37, 24 x 136 x 58 x 58 -> 16 26.0 -> 20.5; error against
+// 64 bits 2.9e-7 -> 2.4e-7.  128 MB are 23 us at the rate of a large copy; the products are 13 us, one wavefront per SIMD.
+template <int CB, int QB, int NB>
+__global__ __launch_bounds__(256, CB * QB == 8 ? 1 : 2) void mfma_f32_pointwise_split_kernel(const float* __restrict__ x, const float* __restrict__ w,
+                                                                                       float* __restrict__ y, const PwParams P)
+{
+    typedef float bvec __attribute__((ext_vector_type(QB)));
+    extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
+    constexpr int kRow = CB * 32 + 1;                        // 16-byte units of a (step, part, lane half): odd, spreads the writes
+    int* flag = reinterpret_cast<int*>(smem + P.flag_off);
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, lj = lane & 31, kk = lane >> 5;
+    const int co0 = blockIdx.y * (CB * 32);
+    const int HW = P.HW;
+
+    const int T = (P.C_in + 15) >> 4;                        // steps of sixteen channels
+    const int nwaves = (int)gridDim.x * 4;
+    int tile = (int)blockIdx.x * 4 + wave;
+
+    // the lane's QB pixels of a tile (a lane beyond the last pixel computes on pixel 0 and stores nothing)
+    struct Place {
+        bool live;
+        int n, pix;
+    };
+    auto place = [&](int tl) __attribute__((always_inline)) {
+        const int pg = tl * (32 * QB) + QB * lj;
+        Place p;
+        p.live = tl < P.tiles && pg < P.total_px;
+        const int pgc = p.live ? pg : 0;
+        p.n = pgc / HW;
+        p.pix = pgc - p.n * HW;
+        return p;
+    };
+    auto x_of = [&](const Place& p) __attribute__((always_inline)) { return x + (int64_t)p.n * P.C_in * HW + p.pix; };
+
+    bvec b[NB][8];
+    // step g of the tile whose lane pointer is src0, into register set `buf`; a lane half without channels in the last step
+    // loads the other half's (its filters are zeros)
+    auto fetch = [&](int buf, const float* src0, int g) __attribute__((always_inline)) {
+        const int gc = g < T ? g : T - 1;
+        const int c = 16 * gc + 8 * kk;
+        const float* src = src0 + (int64_t)(c < P.C_in ? c : 16 * gc) * HW;
+#pragma unroll
+        for (int j = 0; j < 8; ++j) b[buf][j] = *reinterpret_cast<const bvec*>(src + (int64_t)j * HW);
+    };
+
+    // the first tile's first steps are on their way while the filters are brought into LDS
+    Place cur = place(tile);
+    const float* xp = x_of(cur);
+#pragma unroll
+    for (int i = 0; i < NB; ++i) fetch(i, xp, i);
+
+    // filters: rows co0 .. co0 + CB * 32 - 1 (zeros beyond C_out and C_in), eight channels at a time, two in flight per thread
+    unsigned tiny = ~0u;
+    {
+        const int octs = 2 * T, total = CB * 32 * octs;
+#pragma unroll 1
+        for (int i0 = tid; i0 < total; i0 += 2 * 256) {
+            floatx4 v[2][2];
+#pragma unroll
+            for (int u = 0; u < 2; ++u) {
+                const int i = i0 + 256 * u;
+                const int row = fast_div(i, P.by_oct), o = i - row * octs;
+                const bool in = i < total && co0 + row < P.C_out && 8 * o < P.C_in;
+                const floatx4* src = reinterpret_cast<const floatx4*>(w + (in ? (int64_t)(co0 + row) * P.C_in + 8 * o : 0));
+                v[u][0] = src[0];
+                v[u][1] = src[1];
+                if (!in) v[u][0] = v[u][1] = floatx4{0.f, 0.f, 0.f, 0.f};
+            }
+#pragma unroll
+            for (int u = 0; u < 2; ++u) {
+                const int i = i0 + 256 * u;
+                const int row = fast_div(i, P.by_oct), o = i - row * octs;
+                if (i >= total) break;
+                const float f[8] = {v[u][0][0], v[u][0][1], v[u][0][2], v[u][0][3], v[u][1][0], v[u][1][1], v[u][1][2], v[u][1][3]};
+                const Split8 s = split_f32(f, tiny);
+                bf16x8* d = reinterpret_cast<bf16x8*>(smem) + ((o >> 1) * 6 + (o & 1)) * kRow + row;
+                d[0] = s.h;
+                d[2 * kRow] = s.m;
+                d[4 * kRow] = s.l;
+            }
+        }
+        const bool any = __ballot(tiny < kTinyBits) != 0;
+        if (lane == 0) flag[wave] = any;
+    }
+    __syncthreads();
+    const bool again_w = (flag[0] | flag[1] | flag[2] | flag[3]) != 0;
+
+    const int T3 = T - T % NB;          // steps taken by whole trips of the main loop
+#pragma unroll 1
+    for (; tile < P.tiles; tile += nwaves) {
+        // the wavefront's next tile: its first steps are requested while this one's last products run and its
+        // results leave, so the register sets are full again when the next turn starts
+        const Place nxt = place(tile + nwaves);
+        const float* xq = x_of(nxt);
+        tiny = ~0u;
+
+        splitx16 acc[CB][QB];
+#pragma unroll
+        for (int cb = 0; cb < CB; ++cb)
+#pragma unroll
+            for (int q = 0; q < QB; ++q)
+#pragma unroll
+                for (int v = 0; v < 16; ++v) acc[cb][q][v] = 0.f;
+
+        auto split_pixel = [&](int buf, int q) __attribute__((always_inline)) {
+            const float v[8] = {b[buf][0][q], b[buf][1][q], b[buf][2][q], b[buf][3][q], b[buf][4][q], b[buf][5][q], b[buf][6][q], b[buf][7][q]};
+            return split_f32(v, tiny);
+        };
+        auto multiply = [&](int buf, int t) __attribute__((always_inline)) {
+            Split8 a[CB], sb[2];
+#pragma unroll
+            for (int cb = 0; cb < CB; ++cb) {
+                const bf16x8* s = reinterpret_cast<const bf16x8*>(smem) + (t * 6 + kk) * kRow + 32 * cb + lj;
+                a[cb].h = s[0];
+                a[cb].m = s[2 * kRow];
+                a[cb].l = s[4 * kRow];
+            }
+            sb[0] = split_pixel(buf, 0);
+#pragma unroll
+            for (int q = 0; q < QB; ++q) {
+                if (q + 1 < QB) sb[(q + 1) & 1] = split_pixel(buf, q + 1);
+                const Split8& c = sb[q & 1];
+#pragma unroll
+                for (int cb = 0; cb < CB; ++cb) acc[cb][q] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[cb].l, c.h, acc[cb][q], 0, 0, 0);
+#pragma unroll
+                for (int cb = 0; cb < CB; ++cb) acc[cb][q] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[cb].h, c.l, acc[cb][q], 0, 0, 0);
+#pragma unroll
+                for (int cb = 0; cb < CB; ++cb) acc[cb][q] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[cb].m, c.m, acc[cb][q], 0, 0, 0);
+#pragma unroll
+                for (int cb = 0; cb < CB; ++cb) acc[cb][q] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[cb].m, c.h, acc[cb][q], 0, 0, 0);
+#pragma unroll
+                for (int cb = 0; cb < CB; ++cb) acc[cb][q] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[cb].h, c.m, acc[cb][q], 0, 0, 0);
+#pragma unroll
+                for (int cb = 0; cb < CB; ++cb) acc[cb][q] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[cb].h, c.h, acc[cb][q], 0, 0, 0);
+            }
+            // the splitting of pixel q + 1 between the matrix instructions of pixel q
+#pragma unroll
+            for (int i = 0; i < 6 * CB * QB; ++i) {
+                __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
+                __builtin_amdgcn_sched_group_barrier(0x002, CB == 2 ? 5 : 10, 0);
+            }
+        };
+        // step t of this tile, or, past its last one, step `buf` of the next tile (when the step count is a multiple of NB
+        // that is exactly what set `buf` has to hold next; otherwise the steps left over after the loop still need the
+        // first sets, and the next tile is requested behind them)
+        auto fetch_on = [&](int buf, int t) __attribute__((always_inline)) {
+            if (T3 == T && t >= T) fetch(buf, xq, buf);
+            else fetch(buf, xp, t);
+        };
+
+        // NB steps per trip, so that the register sets keep their names
+#pragma unroll 1
+        for (int t = 0; t < T3; t += NB) {
+            // (the fences keep each step's loads where they are written: right behind the products that freed their
+            // registers, NB - 1 steps ahead of their use)
+#pragma unroll
+            for (int i = 0; i < NB; ++i) {
+                multiply(i, t + i);
+                __builtin_amdgcn_sched_barrier(0);
+                fetch_on(i, t + NB + i);
+                __builtin_amdgcn_sched_barrier(0);
+            }
+        }
+        if (T3 < T) {
+#pragma unroll
+            for (int i = 0; i < NB - 1; ++i)
+                if (T3 + i < T) multiply(i, T3 + i);
+            __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+            for (int i = 0; i < NB; ++i) fetch(i, xq, i);
+            __builtin_amdgcn_sched_barrier(0);
+        }
+
+        // register v of a lane is output channel 8 (v / 4) + 4 kk + v % 4 of the block, pixels QB lj .. QB lj + QB - 1
+        bool again = again_w || __ballot(tiny < kTinyBits) != 0;       // (a pixel's channels are spread over two lanes)
+        if (cur.live) {
+#pragma unroll
+            for (int cb = 0; cb < CB; ++cb)
+#pragma unroll
+                for (int q = 0; q < QB; ++q) again |= split_suspect(acc[cb][q]);
+            // (the store addresses are computed here, per tile, not kept in registers the products need: the empty
+            // statement hides from the compiler that they are the same for every tile)
+            int pix_out = cur.pix, kk_out = kk;
+            asm volatile("" : "+v"(pix_out), "+v"(kk_out));
+            float* yp = y + (int64_t)cur.n * P.C_out * HW + pix_out;
+            if (__builtin_expect(again, 0)) {
+                // what the bf16 parts could not hold: plain multiply-adds
+#pragma unroll 1
+                for (int i = 0; i < 16 * CB * QB; ++i) {
+                    const int v = i / QB, q = i - v * QB;
+                    const int co = co0 + 32 * (v >> 4) + 8 * ((v & 15) >> 2) + 4 * kk_out + (v & 3);
+                    if (co >= P.C_out) continue;
+                    const float* xs = x + (int64_t)cur.n * P.C_in * HW + pix_out + q;
+                    const float* ws = w + (int64_t)co * P.C_in;
+                    float t = 0.f;
+#pragma unroll 1
+                    for (int ci = 0; ci < P.C_in; ++ci) t = fmaf(xs[(int64_t)ci * HW], ws[ci], t);
+                    yp[(int64_t)co * HW + q] = apply_epilogue(t, co, P.ep);
+                }
+            } else {
+                const bool whole = co0 + 32 * CB <= P.C_out;
+#pragma unroll
+                for (int cb = 0; cb < CB; ++cb) {
+                    if (whole && P.ep.bias) {
+#pragma unroll
+                        for (int v = 0; v < 16; ++v) {
+                            const float bias = P.ep.bias[co0 + cb * 32 + 8 * (v >> 2) + 4 * kk_out + (v & 3)];
+#pragma unroll
+                            for (int q = 0; q < QB; ++q) acc[cb][q][v] += bias;
+                        }
+                    }
+                    if (whole && P.ep.relu) {
+#pragma unroll
+                        for (int q = 0; q < QB; ++q)
+#pragma unroll
+                            for (int v = 0; v < 16; ++v) acc[cb][q][v] = fmaxf(acc[cb][q][v], 0.f);
+                    }
+#pragma unroll
+                    for (int v = 0; v < 16; ++v) {
+                        const int co = co0 + cb * 32 + 8 * (v >> 2) + 4 * kk_out + (v & 3);
+                        if (whole || co < P.C_out) {
+                            bvec o;
+#pragma unroll
+                            for (int q = 0; q < QB; ++q) o[q] = whole ? acc[cb][q][v] : apply_epilogue(acc[cb][q][v], co, P.ep);
+                            __builtin_nontemporal_store(o, reinterpret_cast<bvec*>(yp + (int64_t)co * HW));
+                        }
+                    }
+                }
+            }
+        }
+        cur = nxt;
+        xp = xq;
+    }
+}
+
 struct PwPlan {
     bool ok = false;
     int CB = 0, QB = 0;
+    bool split = false;
     size_t lds = 0;
 };
 
@@ -243,6 +489,13 @@ PwPlan plan_pointwise(const Conv2dShape& s, const float* x, const float* w, cons
         if (units(v[0], v[1]) >= 700) break;
     }
     if (a.ok) a.lds = (size_t)a.CB * 32 * (s.C_in + 4) * sizeof(float);
+    // Split operands where their filters fit LDS, but not where the last, half empty step of 16 channels is a large part of few
+    // (8 -> 32 at 256 x 256, 5 images: 15.4 us against 25.1; 72 -> 248 at 66 x 65, 7 images: 20.7 against 21.8), nor for
+    // launches of a few short tiles, where the splitting before the first product shows (32 -> 64 at 28 x 28, 2 images: 5.4
+    // against 5.7; 16 -> 7, 270 pixels: 3.9 against 4.8).
+    const size_t steps = (s.C_in + 15) / 16, split_lds = steps * 96 * (a.CB * 32 + 1) + 16;
+    a.split = a.ok && split_lds <= kPwLdsSplit && (s.C_in % 16 == 0 || s.C_in >= 128) && (s.C_in >= 64 || units(a.CB, a.QB) >= 700);
+    if (a.split) a.lds = split_lds;
     return a;
 }
 
@@ -252,7 +505,9 @@ hipError_t launch_pw(const float* x, const float* w, float* y, const Conv2dShape
 {
     static const hipError_t attr = hipFuncSetAttribute(reinterpret_cast<const void*>(mfma_f32_pointwise_kernel<CB, QB, NB>),
                                                        hipFuncAttributeMaxDynamicSharedMemorySize, (int)kPwLdsMax);
-    if (attr != hipSuccess) return attr;
+    static const hipError_t attr_split = hipFuncSetAttribute(reinterpret_cast<const void*>(mfma_f32_pointwise_split_kernel<CB, QB, NB>),
+                                                             hipFuncAttributeMaxDynamicSharedMemorySize, (int)kPwLdsSplit);
+    if (attr != hipSuccess || attr_split != hipSuccess) return attr != hipSuccess ? attr : attr_split;
     PwParams P;
     P.C_in = s.C_in;
     P.C_out = s.C_out;
@@ -261,6 +516,8 @@ hipError_t launch_pw(const float* x, const float* w, float* y, const Conv2dShape
     P.tiles = (P.total_px + 32 * QB - 1) / (32 * QB);
     P.wpitch = s.C_in + 4;
     P.by_c4 = make_fastdiv(s.C_in / 4);
+    P.flag_off = (int)a.lds - 16;
+    P.by_oct = make_fastdiv(2 * ((s.C_in + 15) / 16));
     P.ep = ep;
     const int gy = (s.C_out + CB * 32 - 1) / (CB * 32);
     // persistent: at most two workgroups per CU (one when the filters take more than half of its LDS)
@@ -268,6 +525,11 @@ hipError_t launch_pw(const float* x, const float* w, float* y, const Conv2dShape
     int gx = (P.tiles + 3) / 4;
     const int cap = (256 * per_cu + gy - 1) / gy;
     if (gx > cap) gx = cap;
+    if (a.split) {
+        SW_NOTED_LAUNCH(note_kernel("mfma_f32_pointwise_kernel", CB, QB), (mfma_f32_pointwise_split_kernel<CB, QB, NB>),
+                        dim3((unsigned)gx, (unsigned)gy), dim3(256), a.lds, st, x, w, y, P);
+        return hipGetLastError();
+    }
     SW_NOTED_LAUNCH(note_kernel("mfma_f32_pointwise_kernel", CB, QB), (mfma_f32_pointwise_kernel<CB, QB, NB>), dim3((unsigned)gx, (unsigned)gy),
                     dim3(256), a.lds, st, x, w, y, P);
     return hipGetLastError();

@@ -167,3 +167,48 @@ def test_few_channels_kernel_special_values(torch, sw, value, where):
         _same_but_finite(y, ref.astype(np.float32) if not np.isfinite(value) else ref, f"{value} in {where}")
         ok = np.isfinite(ref)
         assert np.all(np.abs(y[ok] - ref[ok]) <= 2e-5 * np.abs(ref[ok]))
+
+
+# N, C_in, C_out, H, W: 1 x 1 layers whose operands are split, one per (channel blocks, pixels per lane) and remainder
+POINTWISE_CASES = [(2, 64, 100, 28, 28), (32, 48, 64, 56, 56), (32, 152, 40, 30, 32), (30, 64, 128, 33, 34), (1, 136, 7, 9, 10),
+                   (8, 256, 64, 40, 40), (3, 384, 33, 12, 12), (40, 512, 512, 8, 8)]
+
+
+@pytest.mark.parametrize("case", POINTWISE_CASES, ids=lambda c: "x".join(map(str, c)))
+def test_split_pointwise(torch, sw, oracle, case):
+    N, Ci, Co, H, W = case
+    x = inputs.normal_f32((N, Ci, H, W), 5700 + Ci)
+    w = inputs.normal_f32((Co, Ci, 1, 1), 5800 + Co, (2.0 / Ci) ** 0.5)
+    b = inputs.normal_f32((Co,), 5900, 0.5)
+    xd, wd = torch.from_numpy(x).cuda(), torch.from_numpy(w).cuda()
+    y_ref, d = oracle.conv2d(x, w, 1, 0)
+    buf, out, front, n, guard = guarded_empty(torch, y_ref.shape, torch.float32)
+    sw.sw_conv2d(xd, wd, 1, 0, out=out)
+    assert sw.sw_last_kernel().startswith("mfma_f32_pointwise_kernel"), sw.sw_last_kernel()
+    assert_f32_parity(out.cpu().numpy(), y_ref, d, str(case))
+    assert_guards_intact(buf, front, n, guard)
+    y = sw.sw_conv2d_bias_relu(xd, wd, torch.from_numpy(b).cuda(), 1, 0, True)
+    yr, dr = oracle.conv2d_bias_relu(x, w, b, 1, 0, True)
+    assert_f32_parity(y.cpu().numpy(), yr, np.maximum(dr, 1e-30), f"{case} bias, rectifier")
+
+
+@pytest.mark.parametrize("value", [np.inf, np.nan, 3.4028234e38, 2.0 ** -120], ids=str)
+@pytest.mark.parametrize("where", ["x", "w"])
+def test_split_pointwise_special_values(torch, sw, value, where):
+    rng = np.random.default_rng(9)
+    x = rng.uniform(0.5, 1.0, (1, 136, 9, 10)).astype(np.float32)
+    w = rng.uniform(0.001, 0.002, (40, 136, 1, 1)).astype(np.float32)
+    if value < 1e-30:
+        (x if where == "x" else w)[:] = 0.0
+        (w if where == "x" else x)[:] *= np.float32(2.0 ** 100)
+        value = np.float32(value) * np.float32(1.2345678)
+    elif where == "w":
+        x *= 0.125
+    (x if where == "x" else w).flat[7777 if where == "x" else 700] = value
+    y = sw.sw_conv2d(torch.from_numpy(x).cuda(), torch.from_numpy(w).cuda(), 1, 0).cpu().numpy()
+    assert sw.sw_last_kernel().startswith("mfma_f32_pointwise_kernel")
+    ref = torch.nn.functional.conv2d(torch.from_numpy(x).double(), torch.from_numpy(w).double()).numpy()
+    with np.errstate(all="ignore"):
+        _same_but_finite(y, ref.astype(np.float32) if not np.isfinite(value) else ref, f"{value} in {where}")
+        ok = np.isfinite(ref)
+        assert np.all(np.abs(y[ok] - ref[ok]) <= 2e-5 * np.abs(ref[ok]))
