@@ -16,16 +16,17 @@
 //            A lane loads eight channels of one cell (consecutive lanes: consecutive pixels).
 //
 // Both layouts give the matrix operands as conflict-free 16-byte reads; tap shift, stride and dilation are in the address.
-// Wavefronts 0 .. 7 multiply, 8 .. 7 + PH split filters, the other 4 - PH split windows.  There are two window stages and PH + 1
+// The first eight (PH = 3: four) wavefronts multiply, the next PH split filters, the other 4 - PH split windows.  There are two window stages and PH + 1
 // filter stages: a filter wavefront has PH chunk periods for its chunk (PH chunks are under way at a time), which is what
 // keeps small tiles, whose periods are short, supplied; large windows leave room for PH = 1 only.  One barrier per chunk.
 //
-// Measured (us per launch, batch 32 unless said, the fp32-instruction kernels -> this one): 64 -> 64 at 56 x 56 75.0 -> 62.8,
-// 128 -> 128 at 28 x 28 86.9 -> 56.4, 256 -> 256 at 14 x 14 92.5 -> 53.5, 512 -> 512 at 7 x 7 109.8 -> 70.6, one image of
-// 256 -> 256 at 14 x 14 45.9 -> 26.2, 64 -> 64 at 56 x 56 20.2 -> 11.1, five of 96 -> 136 at 35 x 35 40.3 -> 22.5.
+// Measured (us per launch, batch 32 unless said, the fp32-instruction kernels -> this one): 64 -> 64 at 56 x 56 75.0 -> 60.3,
+// 128 -> 128 at 28 x 28 86.9 -> 53.2, 256 -> 256 at 14 x 14 92.5 -> 54.5, 512 -> 512 at 7 x 7 109.8 -> 69.0, one image of
+// 256 -> 256 at 14 x 14 45.9 -> 23.6, 64 -> 64 at 56 x 56 20.2 -> 10.7, five of 96 -> 136 at 35 x 35 40.3 -> 21.0.
 // What bounds it: 256 pixels x PB of a tile are never quite full (13 of 16 blocks in the first case), the first chunk's way
-// through LDS (7 us) and the stores of a tile (3 us: all workgroups store at once) that nothing overlaps, and 40 cycles per
-// matrix instruction with its operand reads where the instruction takes 32.
+// through LDS (7 us) and the stores of a tile that nothing overlaps, 40 cycles per matrix instruction with its operand reads
+// where the instruction takes 32, and a clock of 1.8-1.9 GHz under the bf16 instructions.  In the one-image case a single
+// wavefront has the tile's only block: 54 matrix instructions in a row per chunk, 2.5 k ticks.
 #include <algorithm>
 
 #include "sw_f32_split.h"
@@ -42,7 +43,9 @@ constexpr unsigned kBeyond = 0x80000000u;               // a byte offset no tens
 constexpr int kTaps = 9;
 constexpr int kFilterStage = kTaps * 3 * 2 * 32 * 16;   // 27 KB
 
-constexpr int CW = 8;                                   // multiplying wavefronts: two per SIMD, one reads operands while the other multiplies
+// Multiplying wavefronts: two per SIMD, so that one reads operands while the other multiplies; with PH = 3, whose tiles have few
+// blocks, one per SIMD, which leaves the filter wavefronts registers for a second chunk in flight.
+constexpr int mul_waves(int PH) { return PH == 3 ? 4 : 8; }
 
 // cells of a window that fit beside PH + 1 filter stages
 constexpr int max_cells(int PH) { return PH == 1 ? 528 : PH == 2 ? 400 : 256; }
@@ -66,9 +69,10 @@ struct SplitParams {
 __device__ __forceinline__ void chunk_barrier() { asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory"); }
 
 template <int PH, int PB>
-__global__ __launch_bounds__(64 * (CW + 4), CW / 4 + 1) void mfma_f32_split_kernel(const float* __restrict__ x, const float* __restrict__ w,
+__global__ __launch_bounds__(64 * (mul_waves(PH) + 4), mul_waves(PH) / 4 + 1) void mfma_f32_split_kernel(const float* __restrict__ x, const float* __restrict__ w,
                                                                 float* __restrict__ y, const SplitParams P)
 {
+    constexpr int CW = mul_waves(PH);
     constexpr int CELLS = max_cells(PH);
     constexpr int OCT = CELLS * 16, PLANE = 2 * OCT, WSTAGE = 3 * PLANE;
     constexpr int WIN0 = (PH + 1) * kFilterStage;
@@ -180,18 +184,20 @@ __global__ __launch_bounds__(64 * (CW + 4), CW / 4 + 1) void mfma_f32_split_kern
         const int f = wave - CW;
         const int co = lane & 31, oct = lane >> 5;
         const __amdgpu_buffer_rsrc_t wr = __builtin_amdgcn_make_buffer_rsrc(const_cast<float*>(w), 0, P.w_bytes, 0x00020000);
-        floatx4 raw[18];
+        constexpr bool kAhead = PH == 3;
+        floatx4 raw0[18], raw1[kAhead ? 18 : 1];
         unsigned tiny = ~0u;
-        auto load = [&](int i) __attribute__((always_inline)) {
+        // pieces first .. last - 1 of the 18 of this lane's run of chunk i
+        auto load = [&](int i, auto& raw, int first, int last) __attribute__((always_inline)) {
             const int k = i / P.chunks, c = i - k * P.chunks;
             const int t = blockIdx.x + k * gridDim.x;
             const int cog = 32 * fast_div(t, P.by_px_tiles) + co, ci = 16 * c + 8 * oct;
-            const unsigned off = cog < P.C_out && ci < P.C_in ? (unsigned)((cog * P.C_in + ci) * (kTaps * 4)) : kBeyond;
+            const unsigned off = i < T && cog < P.C_out && ci < P.C_in ? (unsigned)((cog * P.C_in + ci) * (kTaps * 4)) : kBeyond;
 #pragma unroll
-            for (int k4 = 0; k4 < 18; ++k4)
+            for (int k4 = first; k4 < last; ++k4)
                 raw[k4] = __builtin_bit_cast(floatx4, __builtin_amdgcn_raw_buffer_load_b128(wr, off + 16 * k4, 0, 0));
         };
-        auto chunk = [&](int i) __attribute__((always_inline)) {
+        auto chunk = [&](int i, floatx4 (&raw)[18], auto& next) __attribute__((always_inline)) {
             unsigned char* sf = smem + (i % (PH + 1)) * kFilterStage + oct * 512 + co * 16;
             const int c = i - (i / P.chunks) * P.chunks;
             const int lim = P.C_in - 16 * c - 8 * oct;
@@ -216,12 +222,23 @@ __global__ __launch_bounds__(64 * (CW + 4), CW / 4 + 1) void mfma_f32_split_kern
                     *reinterpret_cast<bf16x8*>(sf + tap * 3072 + 2048) = s.l;
                 }
                 if (tiny < kTinyBits) *flag = 1;
+                // the next chunk's loads: 64 lanes 288 bytes apart take 64 ticks a load to issue; in one piece they made every
+                // third period of a small tile twice as long
+                if constexpr (kAhead) load(i + PH, next, 18 * ph / PH, 18 * (ph + 1) / PH);
             }
-            if (i + PH < T) load(i + PH);
+            if constexpr (!kAhead) load(i + PH, raw, 0, 18);
         };
-        if (f < T) load(f);
+        load(f, raw0, 0, 18);
+        if constexpr (kAhead) {
 #pragma unroll 1
-        for (int i = f; i < T; i += PH) chunk(i);
+            for (int i = f; i < T; i += 2 * PH) {
+                chunk(i, raw0, raw1);
+                if (i + PH < T) chunk(i + PH, raw1, raw0);
+            }
+        } else {
+#pragma unroll 1
+            for (int i = f; i < T; i += PH) chunk(i, raw0, raw1);
+        }
         // (chunk i of this wavefront passed the barriers up to i - 1)
         const int last = f < T ? f + ((T - 1 - f) / PH) * PH : 0;
 #pragma unroll 1
@@ -364,8 +381,8 @@ SplitPlan search_split(const Conv2dShape& s)
         const int64_t px = (int64_t)NI * TH * s.Wo;
         const int64_t IH = (int64_t)(TH - 1) * s.stride + (int64_t)(s.R - 1) * s.dil + 1;
         const int64_t WC = NI * IH * IW;
-        const int64_t blocks = (px + 31) / 32, PB = (blocks + CW - 1) / CW;
-        if (PB > 2) return;
+        const int64_t blocks = (px + 31) / 32;
+        if (blocks > 16) return;
         const int64_t px_tiles = (int64_t)((s.N + NI - 1) / NI) * tiles_y, tiles = px_tiles * co_blocks;
         if (tiles * px_tiles >= (1LL << 32)) return;        // (fast_div's range)
         // A stride-2 window holds four cells per output pixel, and splitting those takes longer than multiplying: with one
@@ -373,12 +390,13 @@ SplitPlan search_split(const Conv2dShape& s)
         // not (64 -> 128, 32 images: 58 against 51).
         if (s.stride > 1 && tiles > 256) return;
         for (int PH = 1; PH <= 3; ++PH) {
-            if (WC > max_cells(PH) || (PH > 1 && PB > 1)) continue;
+            const int64_t PB = (blocks + mul_waves(PH) - 1) / mul_waves(PH);
+            if (WC > max_cells(PH) || PB > (PH == 1 ? 2 : 1)) continue;
             // ticks of a chunk: the matrix instructions of a SIMD (40 each with their operand reads), a filter wavefront's
             // share, a window wavefront's items of 64 cells -- as time stamps showed them
             const int NW = 4 - PH, per_simd = (int)((blocks + 3) / 4);
             const double mul = 40.0 * 6 * kTaps * per_simd + 300;
-            const double fil = 6100.0 / PH, win = (double)((2 * WC + 64 * NW - 1) / (64 * NW)) * 950 + 600;
+            const double fil = PH == 3 ? 1700.0 : 6100.0 / PH, win = (double)((2 * WC + 64 * NW - 1) / (64 * NW)) * 950 + 600;
             const double per = std::max(mul, std::max(fil, win)) * chunks;
             const double est = (double)((tiles + 255) / 256) * (per + 1500.0 * per_simd) + 12000;
             if (best.ok && est >= best.est) continue;
@@ -399,7 +417,7 @@ SplitPlan search_split(const Conv2dShape& s)
             P.by_thwo = make_fastdiv(TH * s.Wo); P.by_Wo = make_fastdiv(s.Wo);
         }
     };
-    for (int NI = 2; NI <= s.N && (int64_t)NI * s.Ho * s.Wo <= 64 * CW; ++NI) consider(NI, 1);
+    for (int NI = 2; NI <= s.N && (int64_t)NI * s.Ho * s.Wo <= 512; ++NI) consider(NI, 1);
     for (int ty = 1; ty <= s.Ho; ++ty) consider(1, ty);
     return best;
 }
@@ -417,7 +435,7 @@ hipError_t launch_one(const float* x, const float* w, float* y, const SplitPlan&
                                                        hipFuncAttributeMaxDynamicSharedMemorySize, lds_bytes(PH));
     if (attr != hipSuccess) return attr;
     SW_NOTED_LAUNCH(note_kernel("mfma_f32_split_kernel", 10 * PH + PB, a.P.NI, a.P.TH), (mfma_f32_split_kernel<PH, PB>),
-                    dim3(a.grid), dim3(64 * (CW + 4)), lds_bytes(PH), st, x, w, y, a.P);
+                    dim3(a.grid), dim3(64 * (mul_waves(PH) + 4)), lds_bytes(PH), st, x, w, y, a.P);
     return hipGetLastError();
 }
 
