@@ -378,6 +378,9 @@ static int run_s8_nhwc(const int8_t* x, const int8_t* w, const int32_t* bias, co
             return SW_ERR_ALIAS;
     }
     hipStream_t st = static_cast<hipStream_t>(hip_stream);
+    // one tap, int8 out: the pixels straight from x, their channels all in flight at once
+    if (!force_direct() && y8 && mfma_s8_pointwise_nhwc_supported(x, w, y8, s))
+        return launch_status(launch_mfma_s8_pointwise_nhwc(x, w, y8, rq, s, st));
     if (!force_direct() && mfma_s8_nhwc_lds_supported(x, w, y8 ? static_cast<const void*>(y8) : static_cast<const void*>(y), y8 != nullptr, s))
         return launch_status(launch_mfma_s8_nhwc_lds(x, w, y8 ? static_cast<void*>(y8) : static_cast<void*>(y), y8 ? &rq : nullptr, s, st));
     if (!force_direct() && mfma_s8_nhwc_supported(x, w, s))
