@@ -104,14 +104,21 @@ int sw_pool2d(const float* x, float* y, int N, int C, int H, int W, int R, int S
  *     y[n,co,i,j] = sum_{ci,r,s} w[co,ci,r,s] * xz[n,ci,i*stride+r-pad, j*stride+s-pad]
  * x: [N,C_in,H,W] fp32;  w: [C_out,C_in,R,S] fp32;  y: [N,C_out,H_out,W_out] fp32.
  * Supported: any shape with R,S <= 64 (SW_ERR_UNSUPPORTED beyond).  C_in >= 2
- * runs on the matrix cores: 3x3 and 5x5 at stride 1 with C_in % 16 == 0,
- * C_out % 64 == 0 and 16-byte aligned w in a large-tile kernel when the problem
- * fills the chip with such tiles, 1x1 at stride 1 without padding (C_in % 8 == 0,
- * an even number of pixels per plane, x and y aligned to 8 bytes, w to 16) in a
- * kernel that reads its operands straight from x, every other extent, stride,
- * padding and channel count in an any-shape kernel (one thread per output only
- * when its window or filter does not fit 64 KB of LDS).  C_in == 1 runs the
- * one-filter-per-plane kernels of sw_conv2d_depthwise.
+ * runs on the matrix cores.  Nine taps over more than 32 channels (stride 1, or any
+ * stride while the launch is one tile per workgroup), few channels at an even stride
+ * (2 to 7, rows of at most 8 taps, R * C_in <= 22) and 1x1 at stride 1 without padding
+ * (C_in % 16 == 0 or >= 128, see the source for small launches) take every fp32 operand
+ * as a sum of three bf16 values on the bf16 matrix instructions: six of nine products,
+ * fp32 sums, errors against 64-bit sums below those of the fp32 instructions; operands
+ * that are no such sum (infinities, NaN, beyond the largest bf16, below 2^-102) are
+ * multiplied in plain fp32.  3x3 and 5x5 at stride 1 with C_in % 16 == 0,
+ * C_out % 64 == 0 and 16-byte aligned w run in a large-tile fp32 kernel when the problem
+ * fills the chip with such tiles, other 1x1 layers (C_in % 8 == 0, an even number of
+ * pixels per plane, x and y aligned to 8 bytes, w to 16) in a kernel that reads its
+ * operands straight from x, every other extent, stride, padding and channel count in
+ * few-tap, compound or any-shape kernels (one thread per output only when the window or
+ * filter does not fit 64 KB of LDS).  C_in == 1 runs the one-filter-per-plane kernels
+ * of sw_conv2d_depthwise.
  */
 int sw_conv2d(const float* x, const float* w, float* y,
               int N, int C_in, int C_out, int H, int W, int R, int S,
@@ -140,9 +147,10 @@ int sw_conv2d_depthwise_bias_relu(const float* x, const float* w, const float* b
  *     y[n,c,i,j] = sum_{r,s} w[c,0,r,s] * xz[n,c,i*stride+r-pad, j*stride+s-pad]
  * x: [N,C,H,W];  w: [C,1,R,S];  y: [N,C,H_out,W_out].
  * Supported: any shape with R,S <= 64 (SW_ERR_UNSUPPORTED beyond).  3x3, 5x5
- * and 7x7 at stride 1, and 3x3 and 5x5 at stride 2, have fixed-size kernels (the
- * paper's "custom" kernels, section 2); other extents up to 51 x 51 at stride 1
- * run the generic sliding kernel; every other case one thread per output.
+ * and 7x7 at strides 1 and 2 have fixed-size kernels (the paper's "custom" kernels,
+ * section 2), for any width; other extents up to 51 x 51 at stride 1 run the generic
+ * sliding kernel; every other case bands of output rows with the taps in loops, or one
+ * thread per output where four output rows of a plane do not fit LDS.
  */
 int sw_conv2d_depthwise(const float* x, const float* w, float* y,
                         int N, int C, int H, int W, int R, int S,
@@ -239,8 +247,8 @@ int sw_dw_pw_block(const float* x, const float* w_dw, const float* b_dw,
  * x: [N,C,H,W] bf16;  w: [C,1,R,S] fp32;  y: [N,C,H_out,W_out] bf16.
  * x and y must be 2-byte aligned, w 4-byte aligned; errors as sw_conv2d_depthwise.
  * 3x3, 5x5, 7x7 at stride 1 on planes up to 56 x 56 with W and W_out multiples of
- * 8 and 16-byte aligned x, y run the sliding whole-plane kernel; every other
- * valid shape one thread per output.
+ * 8 and 16-byte aligned x, y run the sliding whole-plane kernel; other shapes bands of
+ * output rows, or one thread per output on planes with little to do.
  */
 int sw_conv2d_depthwise_bf16(const uint16_t* x, const float* w, uint16_t* y,
                              int N, int C, int H, int W, int R, int S,
@@ -332,6 +340,8 @@ int sw_jit_cached_kernels(void);
  * this layout are 16 consecutive bytes: nothing is transposed on the way.  Note the
  * argument order (H, W before the channel counts).  Errors as the channel-first
  * calls.  C_in a multiple of 32 and 16-byte aligned x and w run on the matrix cores:
+ * requantised 1x1 layers at stride 1 over at least 128 channels (C_out % 16 == 0) on a
+ * kernel that reads the pixels straight from x; else,
  * with C_out % 4 == 0, y aligned to four elements, tensors below 2 GiB and tiles of
  * output rows (at most 256 outputs wide) whose windows fit LDS, on the kernel that
  * brings the windows in by direct-to-LDS loads a tile ahead (the one the channel-last
