@@ -70,7 +70,7 @@ TRAFFIC_SOURCE = ("rocprofv3 --pmc FETCH_SIZE / WRITE_SIZE runs made by the buil
 TRAFFIC = {
     "depthwise_3x3": (207413237, "sw_sliding_plane.hip", "1d24ebdfa6df1cef"),
     "depthwise_7x7": (206183315, "sw_sliding_plane.hip", "1d24ebdfa6df1cef"),
-    "conv2d_64x64_3x3": (86019000, "sw_mfma_f32_split.hip", "30e35709d6431d56"),
+    "conv2d_64x64_3x3": (86019000, "sw_mfma_f32_split.hip", "378765b1b0f8346a"),
     "conv2d_s8_128x128_3x3": (22096535, "sw_mfma_s8_band.hip", "efae7346fdd97c23"),
     "conv1d_k9": (33974646, "sw_sliding1d.hip", "b574d6ab8949af6c"),
     "avgpool1d_w8": (34237947, "sw_sliding1d.hip", "b574d6ab8949af6c"),

@@ -16,17 +16,18 @@
 //            A lane loads eight channels of one cell (consecutive lanes: consecutive pixels).
 //
 // Both layouts give the matrix operands as conflict-free 16-byte reads; tap shift, stride and dilation are in the address.
-// The first eight (PH = 3: four) wavefronts multiply, the next PH split filters, the other 4 - PH split windows.  There are two window stages and PH + 1
+// The first eight (PH = 4: three) wavefronts multiply, the next PH split filters, the last 4 - PH (PH = 4: one) split windows.  There are two window stages and PH + 1
 // filter stages: a filter wavefront has PH chunk periods for its chunk (PH chunks are under way at a time), which is what
 // keeps small tiles, whose periods are short, supplied; large windows leave room for PH = 1 only.  One barrier per chunk.
 //
 // Measured (us per launch, batch 32 unless said, the fp32-instruction kernels -> this one): 64 -> 64 at 56 x 56 75.0 -> 60.3,
 // 128 -> 128 at 28 x 28 86.9 -> 53.2, 256 -> 256 at 14 x 14 92.5 -> 54.5, 512 -> 512 at 7 x 7 109.8 -> 69.0, one image of
-// 256 -> 256 at 14 x 14 45.9 -> 23.6, 64 -> 64 at 56 x 56 20.2 -> 10.7, five of 96 -> 136 at 35 x 35 40.3 -> 21.0.
+// 256 -> 256 at 14 x 14 45.9 -> 23.1, of 512 -> 512 at 7 x 7 85.0 -> 31.3, 64 -> 64 at 56 x 56 20.2 -> 10.6, five of 96 -> 136 at 35 x 35 40.3 -> 21.0.
 // What bounds it: 256 pixels x PB of a tile are never quite full (13 of 16 blocks in the first case), the first chunk's way
 // through LDS (7 us) and the stores of a tile that nothing overlaps, 40 cycles per matrix instruction with its operand reads
-// where the instruction takes 32, and a clock of 1.8-1.9 GHz under the bf16 instructions.  In the one-image case a single
-// wavefront has the tile's only block: 54 matrix instructions in a row per chunk, 2.5 k ticks.
+// where the instruction takes 32, and a clock of 1.8-1.9 GHz under the bf16 instructions.  Single images: about 2 k ticks a
+// chunk, most of it the filter loads (64 lanes 288 bytes apart are 64 lines a load, 1.2 k ticks a chunk).  Before the taps
+// were shared (one wavefront had a tile's only block) 512 -> 512 at 7 x 7 took 40.2 us, 3 x 344 -> 88 at 9 x 9 28.2, now 23.2.
 #include <algorithm>
 
 #include "sw_f32_split.h"
@@ -43,15 +44,17 @@ constexpr unsigned kBeyond = 0x80000000u;               // a byte offset no tens
 constexpr int kTaps = 9;
 constexpr int kFilterStage = kTaps * 3 * 2 * 32 * 16;   // 27 KB
 
-// Multiplying wavefronts: two per SIMD, so that one reads operands while the other multiplies; with PH = 3, whose tiles have few
-// blocks, one per SIMD, which leaves the filter wavefronts registers for a second chunk in flight.
-constexpr int mul_waves(int PH) { return PH == 3 ? 4 : 8; }
+// Multiplying wavefronts: two per SIMD, so that one reads operands while the other multiplies.  With PH = 4, for launches of at
+// most one tile of one block per workgroup, three share the block, a third of the taps each, and the filter wavefronts have
+// registers for a second chunk in flight (eight wavefronts instead of twelve).
+constexpr int mul_waves(int PH) { return PH == 4 ? 3 : 8; }
+constexpr int win_waves(int PH) { return PH == 4 ? 1 : 4 - PH; }
 
 // cells of a window that fit beside PH + 1 filter stages
-constexpr int max_cells(int PH) { return PH == 1 ? 528 : PH == 2 ? 400 : 256; }
+constexpr int max_cells(int PH) { return PH == 1 ? 528 : PH == 2 ? 400 : 112; }
 // cells of a window lane's items: its byte offsets wait in LDS for the rolled loop that computes them
-constexpr int lane_items(int PH) { return (2 * max_cells(PH) + 64 * (4 - PH) - 1) / (64 * (4 - PH)); }
-constexpr int lds_bytes(int PH) { return (PH + 1) * kFilterStage + 2 * 96 * max_cells(PH) + 64 + 256 * (4 - PH) * lane_items(PH); }
+constexpr int lane_items(int PH) { return (2 * max_cells(PH) + 64 * win_waves(PH) - 1) / (64 * win_waves(PH)); }
+constexpr int lds_bytes(int PH) { return (PH + 1) * kFilterStage + 2 * 96 * max_cells(PH) + 64 + 256 * win_waves(PH) * lane_items(PH); }
 
 struct SplitParams {
     Epilogue ep;
@@ -69,10 +72,11 @@ struct SplitParams {
 __device__ __forceinline__ void chunk_barrier() { asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory"); }
 
 template <int PH, int PB>
-__global__ __launch_bounds__(64 * (mul_waves(PH) + 4), mul_waves(PH) / 4 + 1) void mfma_f32_split_kernel(const float* __restrict__ x, const float* __restrict__ w,
+__global__ __launch_bounds__(64 * (mul_waves(PH) + PH + win_waves(PH)), mul_waves(PH) == 8 ? 3 : 2) void mfma_f32_split_kernel(const float* __restrict__ x, const float* __restrict__ w,
                                                                 float* __restrict__ y, const SplitParams P)
 {
     constexpr int CW = mul_waves(PH);
+    constexpr bool kShared = PH == 4;                   // one block per tile: the multiplying wavefronts share it, a row of taps each
     constexpr int CELLS = max_cells(PH);
     constexpr int OCT = CELLS * 16, PLANE = 2 * OCT, WSTAGE = 3 * PLANE;
     constexpr int WIN0 = (PH + 1) * kFilterStage;
@@ -91,7 +95,7 @@ __global__ __launch_bounds__(64 * (mul_waves(PH) + 4), mul_waves(PH) / 4 + 1) vo
     if (wave >= CW) __builtin_amdgcn_s_setprio(3);
     if (wave >= CW + PH) {
         // ------------------------------------------------------------------------------------------ windows
-        constexpr int NW = 4 - PH, IT = lane_items(PH);
+        constexpr int NW = win_waves(PH), IT = lane_items(PH);
         const int q0 = (wave - CW - PH) * 64 + lane;
         unsigned* table = reinterpret_cast<unsigned*>(smem + FLAG0 + 64) + (wave - CW - PH) * 64 * IT + lane;
         const int items = 2 * P.WC;
@@ -176,6 +180,10 @@ __global__ __launch_bounds__(64 * (mul_waves(PH) + 4), mul_waves(PH) / 4 + 1) vo
                 load_next(raw1);
             }
         }
+        if constexpr (kShared) {                        // (the barriers around the partial sums)
+            chunk_barrier();
+            chunk_barrier();
+        }
         return;
     }
 
@@ -184,7 +192,7 @@ __global__ __launch_bounds__(64 * (mul_waves(PH) + 4), mul_waves(PH) / 4 + 1) vo
         const int f = wave - CW;
         const int co = lane & 31, oct = lane >> 5;
         const __amdgpu_buffer_rsrc_t wr = __builtin_amdgcn_make_buffer_rsrc(const_cast<float*>(w), 0, P.w_bytes, 0x00020000);
-        constexpr bool kAhead = PH == 3;
+        constexpr bool kAhead = PH == 4;
         floatx4 raw0[18], raw1[kAhead ? 18 : 1];
         unsigned tiny = ~0u;
         // pieces first .. last - 1 of the 18 of this lane's run of chunk i
@@ -243,6 +251,10 @@ __global__ __launch_bounds__(64 * (mul_waves(PH) + 4), mul_waves(PH) / 4 + 1) vo
         const int last = f < T ? f + ((T - 1 - f) / PH) * PH : 0;
 #pragma unroll 1
         for (int b = last; b < T; ++b) chunk_barrier();
+        if constexpr (kShared) {
+            chunk_barrier();
+            chunk_barrier();
+        }
         return;
     }
 
@@ -260,8 +272,8 @@ __global__ __launch_bounds__(64 * (mul_waves(PH) + 4), mul_waves(PH) / 4 + 1) vo
         int nlive = 0;
 #pragma unroll
         for (int b = 0; b < PB; ++b) {
-            const int p = 32 * (CW * b + wave) + lj;
-            if (32 * (CW * b + wave) < valid_px) nlive = b + 1;
+            const int first = kShared ? 0 : 32 * (CW * b + wave), p = first + lj;
+            if (first < valid_px) nlive = b + 1;
             const int im = fast_div(p, P.by_thwo), rem = p - im * thwo;
             const int ol = fast_div(rem, P.by_Wo), ow = rem - ol * P.Wo;
             pix[b] = (p < valid_px ? 16 * (im * P.cells_img + (ol * P.IW + ow) * P.stride) : 0) + kk * OCT;
@@ -311,7 +323,13 @@ __global__ __launch_bounds__(64 * (mul_waves(PH) + 4), mul_waves(PH) / 4 + 1) vo
 #pragma unroll
                 for (int b = 0; b < PB; ++b) acc[b] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(o.a.h, o.b[b].h, acc[b], 0, 0, 0);
             };
-            if constexpr (PB == 2) {
+            if constexpr (kShared) {
+                Ops o[3];
+#pragma unroll
+                for (int j = 0; j < 3; ++j) fetch(o[j], 3 * wave + j);
+#pragma unroll
+                for (int j = 0; j < 3; ++j) mul(o[j]);
+            } else if constexpr (PB == 2) {
                 // (registers for one set of operands: the other wavefront of the SIMD covers the reads)
 #pragma unroll
                 for (int tap = 0; tap < kTaps; ++tap) {
@@ -333,12 +351,27 @@ __global__ __launch_bounds__(64 * (mul_waves(PH) + 4), mul_waves(PH) / 4 + 1) vo
         }
 #pragma unroll
         for (int b = 0; b < PB; ++b) acc[b] += low[b];
+        if constexpr (kShared) {
+            // the parts meet in LDS, over stages that everybody has left (one tile per workgroup)
+            chunk_barrier();
+            float* part = reinterpret_cast<float*>(smem);
+            if (wave > 0) {
+#pragma unroll
+                for (int v = 0; v < 16; ++v) part[((wave - 1) * 16 + v) * 64 + lane] = acc[0][v];
+            }
+            chunk_barrier();
+            if (wave > 0) return;
+#pragma unroll
+            for (int q = 0; q < CW - 1; ++q)
+#pragma unroll
+                for (int v = 0; v < 16; ++v) acc[0][v] += part[(q * 16 + v) * 64 + lane];
+        }
 
         // ---- store: register v of a lane is output channel 8 (v / 4) + 4 kk + v % 4, pixel lj
         const bool again = *flag != 0;                  // (not volatile: that would be a flat load, and wait for the stores)
 #pragma unroll
         for (int b = 0; b < PB; ++b) {
-            const int p = 32 * (CW * b + wave) + lj;
+            const int p = (kShared ? 0 : 32 * (CW * b + wave)) + lj;
             if (p >= valid_px) continue;
             const int im = fast_div(p, P.by_thwo), rem = p - im * thwo;
             const int ol = fast_div(rem, P.by_Wo), ow = rem - ol * P.Wo;
@@ -389,14 +422,17 @@ SplitPlan search_split(const Conv2dShape& s)
         // tile per workgroup still the faster kernel (128 -> 128 at 56 x 56, 8 images: 30.6 us against 41.0), beyond that
         // not (64 -> 128, 32 images: 58 against 51).
         if (s.stride > 1 && tiles > 256) return;
-        for (int PH = 1; PH <= 3; ++PH) {
+        for (int PH : {1, 2, 4}) {
+            // PH = 4 adds up one block of one tile per workgroup.  Measured on single images against PH = 3 and a block per
+            // wavefront: 256 -> 256 at 14 x 14 23.6 -> 23.1, 512 -> 512 at 7 x 7 40.2 -> 31.3, 16 x 128 -> 32 at 17 x 17 14.6 -> 12.7.
+            if (PH == 4 && (blocks > 1 || tiles > 256)) continue;
             const int64_t PB = (blocks + mul_waves(PH) - 1) / mul_waves(PH);
             if (WC > max_cells(PH) || PB > (PH == 1 ? 2 : 1)) continue;
             // ticks of a chunk: the matrix instructions of a SIMD (40 each with their operand reads), a filter wavefront's
             // share, a window wavefront's items of 64 cells -- as time stamps showed them
-            const int NW = 4 - PH, per_simd = (int)((blocks + 3) / 4);
-            const double mul = 40.0 * 6 * kTaps * per_simd + 300;
-            const double fil = PH == 3 ? 1700.0 : 6100.0 / PH, win = (double)((2 * WC + 64 * NW - 1) / (64 * NW)) * 950 + 600;
+            const int NW = win_waves(PH), per_simd = (int)((blocks + 3) / 4);
+            const double mul = 40.0 * 6 * (PH == 4 ? 3 : kTaps) * per_simd + 300;
+            const double fil = PH == 4 ? 1500.0 : 6100.0 / PH, win = (double)((2 * WC + 64 * NW - 1) / (64 * NW)) * (PH == 4 ? 600 : 950) + (PH == 4 ? 400 : 600);
             const double per = std::max(mul, std::max(fil, win)) * chunks;
             const double est = (double)((tiles + 255) / 256) * (per + 1500.0 * per_simd) + 12000;
             if (best.ok && est >= best.est) continue;
@@ -435,7 +471,7 @@ hipError_t launch_one(const float* x, const float* w, float* y, const SplitPlan&
                                                        hipFuncAttributeMaxDynamicSharedMemorySize, lds_bytes(PH));
     if (attr != hipSuccess) return attr;
     SW_NOTED_LAUNCH(note_kernel("mfma_f32_split_kernel", 10 * PH + PB, a.P.NI, a.P.TH), (mfma_f32_split_kernel<PH, PB>),
-                    dim3(a.grid), dim3(64 * (mul_waves(PH) + 4)), lds_bytes(PH), st, x, w, y, a.P);
+                    dim3(a.grid), dim3(64 * (mul_waves(PH) + PH + win_waves(PH))), lds_bytes(PH), st, x, w, y, a.P);
     return hipGetLastError();
 }
 
@@ -452,7 +488,7 @@ hipError_t launch_mfma_f32_split(const float* x, const float* w, float* y, const
         case 11: return launch_one<1, 1>(x, w, y, a, st);
         case 12: return launch_one<1, 2>(x, w, y, a, st);
         case 21: return launch_one<2, 1>(x, w, y, a, st);
-        default: return launch_one<3, 1>(x, w, y, a, st);
+        default: return launch_one<4, 1>(x, w, y, a, st);
     }
 }
 

@@ -23,17 +23,18 @@ def sw():
 
 CASES = [
     # N, C_in, C_out, H, W, R, S, stride, pad, dilation, kernel
-    (1, 48, 32, 9, 9, 3, 3, 1, 1, 1, "mfma_f32_split_kernel<31,1,3>"),      # three chunks, tiles of three rows
+    (1, 48, 32, 9, 9, 3, 3, 1, 1, 1, "mfma_f32_split_kernel<41,1,3>"),      # three chunks, tiles of three rows
     (2, 64, 70, 35, 35, 3, 3, 1, 1, 1, "mfma_f32_split_kernel<21,1,1>"),           # ragged channel block
     (3, 53, 77, 23, 41, 3, 3, 2, 1, 1, "mfma_f32_split_kernel<21,1,1>"),           # five of sixteen channels in the last chunk, stride 2
-    (1, 57, 33, 12, 12, 3, 3, 1, 0, 1, "mfma_f32_split_kernel<31,1,3>"),           # nine of sixteen: the second octet holds one channel
-    (45, 48, 40, 7, 7, 3, 3, 1, 1, 1, "mfma_f32_split_kernel<31,1,4>"),            # whole small images, the last tile short
+    (1, 57, 33, 12, 12, 3, 3, 1, 0, 1, "mfma_f32_split_kernel<41,1,3>"),           # nine of sixteen: the second octet holds one channel
+    (45, 48, 40, 7, 7, 3, 3, 1, 1, 1, "mfma_f32_split_kernel<41,1,4>"),            # row tiles of small images, the last one short
+    (4, 48, 64, 6, 6, 3, 3, 1, 1, 1, "mfma_f32_split_kernel<"),            # several whole images per tile where the planner takes them
     (12, 48, 64, 56, 56, 3, 3, 1, 1, 1, "mfma_f32_split_kernel<12,1,6>"),          # large windows
     (12, 48, 96, 56, 56, 3, 3, 1, 1, 1, "mfma_f32_split_kernel<11,1,4>"),          # more tiles than workgroups
     (1, 48, 40, 30, 31, 3, 3, 1, 2, 2, "mfma_f32_split_kernel<21,1,1>"),           # dilation 2
     (1, 64, 64, 40, 40, 3, 3, 2, 3, 3, "mfma_f32_split_kernel<21,1,1>"),           # dilation 3 with stride 2
-    (2, 50, 64, 20, 24, 1, 9, 1, 4, 1, "mfma_f32_split_kernel<31,1,1>"),           # a row of nine taps
-    (1, 48, 8, 3, 3, 3, 3, 1, 0, 1, "mfma_f32_split_kernel<31,1,1>"),              # a single output pixel
+    (2, 50, 64, 20, 24, 1, 9, 1, 4, 1, "mfma_f32_split_kernel<41,1,1>"),           # a row of nine taps
+    (1, 48, 8, 3, 3, 3, 3, 1, 0, 1, "mfma_f32_split_kernel<41,1,1>"),              # a single output pixel
 ]
 
 
