@@ -43,7 +43,6 @@ struct PwParams {
     int tiles;        // of 32 * QB pixels
     int wpitch;       // floats between filter rows in LDS
     FastDiv by_c4;    // 16-byte groups per filter row
-    int flag_off;     // (split) of four words, one per wavefront: a filter value too small to split
     FastDiv by_oct;   // (split) groups of eight channels, rounded up to whole steps
     Epilogue ep;
 };
@@ -231,7 +230,6 @@ __global__ __launch_bounds__(256, CB * QB == 8 ? 1 : 2) void mfma_f32_pointwise_
     typedef float bvec __attribute__((ext_vector_type(QB)));
     extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
     constexpr int kRow = CB * 32 + 1;                        // 16-byte units of a (step, part, lane half): odd, spreads the writes
-    int* flag = reinterpret_cast<int*>(smem + P.flag_off);
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, lj = lane & 31, kk = lane >> 5;
     const int co0 = blockIdx.y * (CB * 32);
     const int HW = P.HW;
@@ -274,7 +272,6 @@ __global__ __launch_bounds__(256, CB * QB == 8 ? 1 : 2) void mfma_f32_pointwise_
     for (int i = 0; i < NB; ++i) fetch(i, xp, i);
 
     // filters: rows co0 .. co0 + CB * 32 - 1 (zeros beyond C_out and C_in), eight channels at a time, two in flight per thread
-    unsigned tiny = ~0u;
     {
         const int octs = 2 * T, total = CB * 32 * octs;
 #pragma unroll 1
@@ -296,18 +293,15 @@ __global__ __launch_bounds__(256, CB * QB == 8 ? 1 : 2) void mfma_f32_pointwise_
                 const int row = fast_div(i, P.by_oct), o = i - row * octs;
                 if (i >= total) break;
                 const float f[8] = {v[u][0][0], v[u][0][1], v[u][0][2], v[u][0][3], v[u][1][0], v[u][1][1], v[u][1][2], v[u][1][3]};
-                const Split8 s = split_f32(f, tiny);
+                const Split8 s = split_f32(f);
                 bf16x8* d = reinterpret_cast<bf16x8*>(smem) + ((o >> 1) * 6 + (o & 1)) * kRow + row;
                 d[0] = s.h;
                 d[2 * kRow] = s.m;
                 d[4 * kRow] = s.l;
             }
         }
-        const bool any = __ballot(tiny < kTinyBits) != 0;
-        if (lane == 0) flag[wave] = any;
     }
     __syncthreads();
-    const bool again_w = (flag[0] | flag[1] | flag[2] | flag[3]) != 0;
 
     const int T3 = T - T % NB;          // steps taken by whole trips of the main loop
 #pragma unroll 1
@@ -316,7 +310,6 @@ __global__ __launch_bounds__(256, CB * QB == 8 ? 1 : 2) void mfma_f32_pointwise_
         // results leave, so the register sets are full again when the next turn starts
         const Place nxt = place(tile + nwaves);
         const float* xq = x_of(nxt);
-        tiny = ~0u;
 
         splitx16 acc[CB][QB];
 #pragma unroll
@@ -328,7 +321,7 @@ __global__ __launch_bounds__(256, CB * QB == 8 ? 1 : 2) void mfma_f32_pointwise_
 
         auto split_pixel = [&](int buf, int q) __attribute__((always_inline)) {
             const float v[8] = {b[buf][0][q], b[buf][1][q], b[buf][2][q], b[buf][3][q], b[buf][4][q], b[buf][5][q], b[buf][6][q], b[buf][7][q]};
-            return split_f32(v, tiny);
+            return split_f32(v);
         };
         auto multiply = [&](int buf, int t) __attribute__((always_inline)) {
             Split8 a[CB], sb[2];
@@ -396,60 +389,73 @@ __global__ __launch_bounds__(256, CB * QB == 8 ? 1 : 2) void mfma_f32_pointwise_
         }
 
         // register v of a lane is output channel 8 (v / 4) + 4 kk + v % 4 of the block, pixels QB lj .. QB lj + QB - 1
-        bool again = again_w || __ballot(tiny < kTinyBits) != 0;       // (a pixel's channels are spread over two lanes)
+        unsigned beyond = 0;                    // a bit per (channel block, pixel) whose accumulators hold no finite number
         if (cur.live) {
-#pragma unroll
-            for (int cb = 0; cb < CB; ++cb)
-#pragma unroll
-                for (int q = 0; q < QB; ++q) again |= split_suspect(acc[cb][q]);
             // (the store addresses are computed here, per tile, not kept in registers the products need: the empty
             // statement hides from the compiler that they are the same for every tile)
             int pix_out = cur.pix, kk_out = kk;
             asm volatile("" : "+v"(pix_out), "+v"(kk_out));
             float* yp = y + (int64_t)cur.n * P.C_out * HW + pix_out;
-            if (__builtin_expect(again, 0)) {
-                // what the bf16 parts could not hold: plain multiply-adds
-#pragma unroll 1
-                for (int i = 0; i < 16 * CB * QB; ++i) {
-                    const int v = i / QB, q = i - v * QB;
-                    const int co = co0 + 32 * (v >> 4) + 8 * ((v & 15) >> 2) + 4 * kk_out + (v & 3);
-                    if (co >= P.C_out) continue;
-                    const float* xs = x + (int64_t)cur.n * P.C_in * HW + pix_out + q;
-                    const float* ws = w + (int64_t)co * P.C_in;
-                    float t = 0.f;
-#pragma unroll 1
-                    for (int ci = 0; ci < P.C_in; ++ci) t = fmaf(xs[(int64_t)ci * HW], ws[ci], t);
-                    yp[(int64_t)co * HW + q] = apply_epilogue(t, co, P.ep);
-                }
-            } else {
-                const bool whole = co0 + 32 * CB <= P.C_out;
+            const bool whole = co0 + 32 * CB <= P.C_out;
 #pragma unroll
-                for (int cb = 0; cb < CB; ++cb) {
+            for (int cb = 0; cb < CB; ++cb) {
+#pragma unroll
+                for (int q = 0; q < QB; ++q)
+                    if (split_overflow(acc[cb][q])) beyond |= 1u << (QB * cb + q);
+                if constexpr (CB * QB == 8) {
+                    // (accumulators in the other half of the register file: each read once)
+                    float bias[16];
+#pragma unroll
+                    for (int v = 0; v < 16; ++v) bias[v] = 0.f;
                     if (whole && P.ep.bias) {
 #pragma unroll
-                        for (int v = 0; v < 16; ++v) {
-                            const float bias = P.ep.bias[co0 + cb * 32 + 8 * (v >> 2) + 4 * kk_out + (v & 3)];
-#pragma unroll
-                            for (int q = 0; q < QB; ++q) acc[cb][q][v] += bias;
-                        }
+                        for (int v = 0; v < 16; ++v) bias[v] = P.ep.bias[co0 + cb * 32 + 8 * (v >> 2) + 4 * kk_out + (v & 3)];
                     }
-                    if (whole && P.ep.relu) {
 #pragma unroll
-                        for (int q = 0; q < QB; ++q)
+                    for (int q = 0; q < QB; ++q)
 #pragma unroll
-                            for (int v = 0; v < 16; ++v) acc[cb][q][v] = fmaxf(acc[cb][q][v], 0.f);
-                    }
+                        for (int v = 0; v < 16; ++v) acc[cb][q][v] = fmaf(acc[cb][q][v], kSplitUnscale, bias[v]);
+                } else if (whole && P.ep.bias) {
 #pragma unroll
                     for (int v = 0; v < 16; ++v) {
-                        const int co = co0 + cb * 32 + 8 * (v >> 2) + 4 * kk_out + (v & 3);
-                        if (whole || co < P.C_out) {
-                            bvec o;
+                        const float bias = P.ep.bias[co0 + cb * 32 + 8 * (v >> 2) + 4 * kk_out + (v & 3)];
 #pragma unroll
-                            for (int q = 0; q < QB; ++q) o[q] = whole ? acc[cb][q][v] : apply_epilogue(acc[cb][q][v], co, P.ep);
-                            __builtin_nontemporal_store(o, reinterpret_cast<bvec*>(yp + (int64_t)co * HW));
-                        }
+                        for (int q = 0; q < QB; ++q) acc[cb][q][v] = fmaf(acc[cb][q][v], kSplitUnscale, bias);
+                    }
+                } else {
+#pragma unroll
+                    for (int q = 0; q < QB; ++q) split_unscale(acc[cb][q]);
+                }
+                if (whole && P.ep.relu) {
+#pragma unroll
+                    for (int q = 0; q < QB; ++q)
+#pragma unroll
+                        for (int v = 0; v < 16; ++v) acc[cb][q][v] = fmaxf(acc[cb][q][v], 0.f);
+                }
+#pragma unroll
+                for (int v = 0; v < 16; ++v) {
+                    const int co = co0 + cb * 32 + 8 * (v >> 2) + 4 * kk_out + (v & 3);
+                    if (whole || co < P.C_out) {
+                        bvec o;
+#pragma unroll
+                        for (int q = 0; q < QB; ++q) o[q] = whole ? acc[cb][q][v] : apply_epilogue(acc[cb][q][v], co, P.ep);
+                        __builtin_nontemporal_store(o, reinterpret_cast<bvec*>(yp + (int64_t)co * HW));
                     }
                 }
+            }
+        }
+        if (__builtin_expect(__ballot(beyond != 0) != 0, 0)) {
+            int channels = P.C_in, outs = P.C_out, px = HW;         // (in vector registers: the scalar ones spilled)
+            asm volatile("" : "+v"(channels), "+v"(outs), "+v"(px));
+            const float* xs = x + ((int64_t)cur.n * channels + kk * (channels >> 1)) * px + cur.pix;
+#pragma unroll 1
+            for (int i = 0; i < CB * QB; ++i) {
+                const bool mine = beyond >> i & 1;
+                if (!__ballot(mine)) continue;
+                const int co = co0 + 32 * (i / QB), q = i % QB;
+                const splitx16 again = multiply_f32<4>(w, channels, co + lj, outs, kk, ColumnInputs{xs + q, px});
+                if (mine)
+                    store_outputs(again, y + ((int64_t)cur.n * outs + co + 4 * kk) * px + cur.pix + q, px, co + 4 * kk, outs, P.ep);
             }
         }
         cur = nxt;
@@ -493,7 +499,7 @@ PwPlan plan_pointwise(const Conv2dShape& s, const float* x, const float* w, cons
     // (8 -> 32 at 256 x 256, 5 images: 15.4 us against 25.1; 72 -> 248 at 66 x 65, 7 images: 20.7 against 21.8), nor for
     // launches of a few short tiles, where the splitting before the first product shows (32 -> 64 at 28 x 28, 2 images: 5.4
     // against 5.7; 16 -> 7, 270 pixels: 3.9 against 4.8).
-    const size_t steps = (s.C_in + 15) / 16, split_lds = steps * 96 * (a.CB * 32 + 1) + 16;
+    const size_t steps = (s.C_in + 15) / 16, split_lds = steps * 96 * (a.CB * 32 + 1);
     a.split = a.ok && split_lds <= kPwLdsSplit && (s.C_in % 16 == 0 || s.C_in >= 128) && (s.C_in >= 64 || units(a.CB, a.QB) >= 700);
     if (a.split) a.lds = split_lds;
     return a;
@@ -516,7 +522,6 @@ hipError_t launch_pw(const float* x, const float* w, float* y, const Conv2dShape
     P.tiles = (P.total_px + 32 * QB - 1) / (32 * QB);
     P.wpitch = s.C_in + 4;
     P.by_c4 = make_fastdiv(s.C_in / 4);
-    P.flag_off = (int)a.lds - 16;
     P.by_oct = make_fastdiv(2 * ((s.C_in + 15) / 16));
     P.ep = ep;
     const int gy = (s.C_out + CB * 32 - 1) / (CB * 32);

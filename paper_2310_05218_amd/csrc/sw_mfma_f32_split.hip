@@ -54,7 +54,7 @@ constexpr int win_waves(int PH) { return PH == 4 ? 1 : 4 - PH; }
 constexpr int max_cells(int PH) { return PH == 1 ? 528 : PH == 2 ? 400 : 112; }
 // cells of a window lane's items: its byte offsets wait in LDS for the rolled loop that computes them
 constexpr int lane_items(int PH) { return (2 * max_cells(PH) + 64 * win_waves(PH) - 1) / (64 * win_waves(PH)); }
-constexpr int lds_bytes(int PH) { return (PH + 1) * kFilterStage + 2 * 96 * max_cells(PH) + 64 + 256 * win_waves(PH) * lane_items(PH); }
+constexpr int lds_bytes(int PH) { return (PH + 1) * kFilterStage + 2 * 96 * max_cells(PH) + 256 * win_waves(PH) * lane_items(PH); }
 
 struct SplitParams {
     Epilogue ep;
@@ -80,16 +80,13 @@ __global__ __launch_bounds__(64 * (mul_waves(PH) + PH + win_waves(PH)), mul_wave
     constexpr int CELLS = max_cells(PH);
     constexpr int OCT = CELLS * 16, PLANE = 2 * OCT, WSTAGE = 3 * PLANE;
     constexpr int WIN0 = (PH + 1) * kFilterStage;
-    constexpr int FLAG0 = WIN0 + 2 * WSTAGE;
+    constexpr int TABLE0 = WIN0 + 2 * WSTAGE;
     extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
-    int* flag = reinterpret_cast<int*>(smem + FLAG0);
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int my_tiles = (P.tiles - (int)blockIdx.x + (int)gridDim.x - 1) / (int)gridDim.x;
     const int T = my_tiles * P.chunks;                  // chunks of all of this workgroup's tiles, one barrier each
     const int HW = P.H * P.W;
-    if (tid == 0) *flag = 0;
-    __syncthreads();
 
     // the splitting wavefronts first: a matrix instruction needs an issue slot every 32 cycles only
     if (wave >= CW) __builtin_amdgcn_s_setprio(3);
@@ -97,12 +94,11 @@ __global__ __launch_bounds__(64 * (mul_waves(PH) + PH + win_waves(PH)), mul_wave
         // ------------------------------------------------------------------------------------------ windows
         constexpr int NW = win_waves(PH), IT = lane_items(PH);
         const int q0 = (wave - CW - PH) * 64 + lane;
-        unsigned* table = reinterpret_cast<unsigned*>(smem + FLAG0 + 64) + (wave - CW - PH) * 64 * IT + lane;
+        unsigned* table = reinterpret_cast<unsigned*>(smem + TABLE0) + (wave - CW - PH) * 64 * IT + lane;
         const int items = 2 * P.WC;
         const __amdgpu_buffer_rsrc_t xr = __builtin_amdgcn_make_buffer_rsrc(const_cast<float*>(x), 0, P.x_bytes, 0x00020000);
         unsigned base[IT];
         float raw0[IT][8], raw1[IT][8];                 // two chunks in flight
-        unsigned tiny = ~0u;
         auto locate = [&](int t) __attribute__((always_inline)) {
             const int pt = t - fast_div(t, P.by_px_tiles) * P.px_tiles;
             const int ig = fast_div(pt, P.by_tiles_y), ty = pt - ig * P.tiles_y;
@@ -127,19 +123,9 @@ __global__ __launch_bounds__(64 * (mul_waves(PH) + PH + win_waves(PH)), mul_wave
 #pragma unroll
             for (int it = 0; it < IT; ++it) {
                 if (64 * NW * it >= items) break;
-                const int q = q0 + 64 * NW * it;
-                // channels beyond the last one (in the last chunk) are zeros; the chunk's first octet always has one
-                const int lim = P.C_in - ci0 - (q >= P.WC ? 8 : 0);
-                if (ci0 + 16 <= P.C_in) {
 #pragma unroll
-                    for (int j = 0; j < 8; ++j)
-                        raw[it][j] = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(xr, base[it] + (unsigned)((ci0 + j) * HW * 4), 0, 0));
-                } else {
-#pragma unroll
-                    for (int j = 0; j < 8; ++j)
-                        raw[it][j] = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(
-                                                                   xr, j < lim ? base[it] + (unsigned)((ci0 + j) * HW * 4) : kBeyond, 0, 0));
-                }
+                for (int j = 0; j < 8; ++j)
+                    raw[it][j] = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(xr, base[it] + (unsigned)((ci0 + j) * HW * 4), 0, 0));
             }
         };
         // loads the next chunk, if there is one, and steps on
@@ -151,13 +137,21 @@ __global__ __launch_bounds__(64 * (mul_waves(PH) + PH + win_waves(PH)), mul_wave
             ++issued;
             if (++c == P.chunks) { c = 0; t += gridDim.x; }
         };
+        int cc = 0;                                     // the next chunk to convert
         auto convert = [&](int i, float (&raw)[IT][8]) __attribute__((always_inline)) {
             unsigned char* sw = smem + WIN0 + (i & 1) * WSTAGE;
+            const int beyond = P.C_in - 16 * cc;
+            if (++cc == P.chunks) cc = 0;
 #pragma unroll
             for (int it = 0; it < IT; ++it) {
                 if (64 * NW * it >= items) break;
                 const int q = q0 + 64 * NW * it;
-                const Split8 s = split_f32(raw[it], tiny);
+                if (beyond < 16) {
+#pragma unroll
+                    for (int j = 0; j < 8; ++j)
+                        if (j >= beyond - (q >= P.WC ? 8 : 0)) raw[it][j] = 0.f;
+                }
+                const Split8 s = split_f32(raw[it]);
                 if (q < items) {
                     unsigned char* d = sw + (q >= P.WC ? OCT + (q - P.WC) * 16 : q * 16);
                     *reinterpret_cast<bf16x8*>(d) = s.h;
@@ -165,7 +159,6 @@ __global__ __launch_bounds__(64 * (mul_waves(PH) + PH + win_waves(PH)), mul_wave
                     *reinterpret_cast<bf16x8*>(d + 2 * PLANE) = s.l;
                 }
             }
-            if (tiny < kTinyBits) *flag = 1;
         };
         load_next(raw0);
         load_next(raw1);
@@ -194,7 +187,6 @@ __global__ __launch_bounds__(64 * (mul_waves(PH) + PH + win_waves(PH)), mul_wave
         const __amdgpu_buffer_rsrc_t wr = __builtin_amdgcn_make_buffer_rsrc(const_cast<float*>(w), 0, P.w_bytes, 0x00020000);
         constexpr bool kAhead = PH == 4;
         floatx4 raw0[18], raw1[kAhead ? 18 : 1];
-        unsigned tiny = ~0u;
         // pieces first .. last - 1 of the 18 of this lane's run of chunk i
         auto load = [&](int i, auto& raw, int first, int last) __attribute__((always_inline)) {
             const int k = i / P.chunks, c = i - k * P.chunks;
@@ -224,13 +216,12 @@ __global__ __launch_bounds__(64 * (mul_waves(PH) + PH + win_waves(PH)), mul_wave
                     float v[8];
 #pragma unroll
                     for (int j = 0; j < 8; ++j) v[j] = raw[(kTaps * j + tap) / 4][(kTaps * j + tap) % 4];
-                    const Split8 s = split_f32(v, tiny);
+                    const Split8 s = split_f32(v);
                     *reinterpret_cast<bf16x8*>(sf + tap * 3072) = s.h;
                     *reinterpret_cast<bf16x8*>(sf + tap * 3072 + 1024) = s.m;
                     *reinterpret_cast<bf16x8*>(sf + tap * 3072 + 2048) = s.l;
                 }
-                if (tiny < kTinyBits) *flag = 1;
-                // the next chunk's loads: 64 lanes 288 bytes apart take 64 ticks a load to issue; in one piece they made every
+                    // the next chunk's loads: 64 lanes 288 bytes apart take 64 ticks a load to issue; in one piece they made every
                 // third period of a small tile twice as long
                 if constexpr (kAhead) load(i + PH, next, 18 * ph / PH, 18 * (ph + 1) / PH);
             }
@@ -368,25 +359,23 @@ __global__ __launch_bounds__(64 * (mul_waves(PH) + PH + win_waves(PH)), mul_wave
         }
 
         // ---- store: register v of a lane is output channel 8 (v / 4) + 4 kk + v % 4, pixel lj
-        const bool again = *flag != 0;                  // (not volatile: that would be a flat load, and wait for the stores)
 #pragma unroll
         for (int b = 0; b < PB; ++b) {
             const int p = (kShared ? 0 : 32 * (CW * b + wave)) + lj;
-            if (p >= valid_px) continue;
             const int im = fast_div(p, P.by_thwo), rem = p - im * thwo;
             const int ol = fast_div(rem, P.by_Wo), ow = rem - ol * P.Wo;
-            float* yp = y + ((int64_t)(n0 + im) * P.C_out + co0) * HoWo + (row0 + ol) * P.Wo + ow;
-            if (__builtin_expect(again || split_suspect(acc[b]), 0)) {
-#pragma unroll 1
-                for (int v = 0; v < 16; ++v) {
-                    const int co = 8 * (v >> 2) + 4 * kk + (v & 3);
-                    if (co0 + co < P.C_out)
-                        yp[(int64_t)co * HoWo] = apply_epilogue(conv_output_f32(x, w, P.C_in, P.H, P.W, P.R, P.S, P.stride, P.pad, P.dil, n0 + im,
-                                                                                co0 + co, row0 + ol, ow), co0 + co, P.ep);
-                }
-                continue;
+            float* yp = y + ((int64_t)(n0 + im) * P.C_out + co0 + 4 * kk) * HoWo + (row0 + ol) * P.Wo + ow;
+            const bool beyond = p < valid_px && split_overflow(acc[b]);
+            split_unscale(acc[b]);
+            if (p < valid_px) store_block(acc[b], yp, HoWo, co0 + 4 * kk, P.C_out, co0 + 32 <= P.C_out, P.ep);
+            if (__builtin_expect(__ballot(beyond) != 0, 0)) {
+                const int per = P.C_in * kTaps;
+                const __amdgpu_buffer_rsrc_t xr = __builtin_amdgcn_make_buffer_rsrc(const_cast<float*>(x), 0, P.x_bytes, 0x00020000);
+                const splitx16 again = multiply_f32<8>(w, per, co0 + lj, P.C_out, kk,
+                                                    ConvInputs(xr, P.C_in, P.H, P.W, P.R, P.S, P.stride, P.pad, P.dil, n0 + im, row0 + ol, ow,
+                                                               kk * ((per + 1) >> 1)));
+                if (beyond) store_outputs(again, yp, HoWo, co0 + 4 * kk, P.C_out, P.ep);
             }
-            store_block(acc[b], yp + (int64_t)(4 * kk) * HoWo, HoWo, co0 + 4 * kk, P.C_out, co0 + 32 <= P.C_out, P.ep);
         }
     }
 }
@@ -404,7 +393,8 @@ SplitPlan search_split(const Conv2dShape& s)
     SplitPlan best;
     if (s.R * s.S != kTaps) return best;
     const int64_t x_bytes = (int64_t)s.N * s.C_in * s.H * s.W * 4, w_bytes = (int64_t)s.C_out * s.C_in * kTaps * 4;
-    if (x_bytes >= (1LL << 31) || w_bytes >= (1LL << 31)) return best;
+    // (the last chunk's channels that do not exist are read and cleared: their offsets stay below 2^31 as well)
+    if (x_bytes + 60LL * s.H * s.W >= (1LL << 31) || w_bytes >= (1LL << 31)) return best;
     const int64_t IW = (int64_t)(s.Wo - 1) * s.stride + (int64_t)(s.S - 1) * s.dil + 1;
     if (IW > 528) return best;
     const int chunks = (s.C_in + 15) / 16, co_blocks = (s.C_out + 31) / 32;

@@ -41,7 +41,6 @@ struct StemParams {
     int N, C_in, C_out, H, W, Ho, Wo, R, S, stride, pad;
     int TH, tiles_y, tiles, cgroups;   // rows per tile, row tiles per image, tiles, groups of 64 output channels
     int rows, extra, pitch, plane;     // window rows of all channels, those of them that hold zeros, bytes per row, bytes per part
-    int flag_off;
     int groups, items;                 // items per row, items per tile
     unsigned x_bytes, w_bytes;
     FastDiv by_tiles_y, by_groups, by_cin, by_Wo;
@@ -61,7 +60,6 @@ __global__ __launch_bounds__(512, 2) void mfma_f32_stem_kernel(const float* __re
                                                                float* __restrict__ y, const StemParams P)
 {
     extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
-    int* flag = reinterpret_cast<int*>(smem + P.flag_off);
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int lj = lane & 31, kk = lane >> 5;
@@ -73,10 +71,8 @@ __global__ __launch_bounds__(512, 2) void mfma_f32_stem_kernel(const float* __re
     const int co0 = 64 * cg + 32 * cb;
     const int HW = P.H * P.W, HoWo = P.Ho * P.Wo;
     const __amdgpu_buffer_rsrc_t xr = __builtin_amdgcn_make_buffer_rsrc(const_cast<float*>(x), 0, P.x_bytes, 0x00020000);
-    unsigned tiny = ~0u;
 
     // ---- filters: split by all threads into LDS, operands to registers
-    if (tid == 0) *flag = 0;
     const int RC = P.R * P.C_in;
     // (as they lie in memory first: gathered straight from there, 64 output channels per load, they took 8 k ticks)
     constexpr int kStaged = 64 * 2 * STEPS * 3 * 16;
@@ -138,7 +134,7 @@ __global__ __launch_bounds__(512, 2) void mfma_f32_stem_kernel(const float* __re
             float v[8];
 #pragma unroll
             for (int j = 0; j < 8; ++j) v[j] = (unsigned)(gc + j) < (unsigned)P.W ? __uint_as_float(raw[it][j >> 2][j & 3]) : 0.f;
-            const Split8 s = split_f32(v, tiny);
+            const Split8 s = split_f32(v);
             if (i < P.items) {
                 unsigned char* d = d0 + (e * P.C_in + ci) * P.pitch + 16 * k;
                 *reinterpret_cast<bf16x8*>(d) = s.h;
@@ -147,7 +143,6 @@ __global__ __launch_bounds__(512, 2) void mfma_f32_stem_kernel(const float* __re
             }
             __builtin_amdgcn_sched_barrier(0);
         }
-        if (tiny < kTinyBits) *flag = 1;
     };
     load(blockIdx.x);
 
@@ -166,7 +161,7 @@ __global__ __launch_bounds__(512, 2) void mfma_f32_stem_kernel(const float* __re
         float v[8];
 #pragma unroll
         for (int j = 0; j < 8; ++j) v[j] = in && j < P.S ? wp[j] : 0.f;
-        const Split8 s = split_f32(v, tiny);
+        const Split8 s = split_f32(v);
         bf16x8* d = reinterpret_cast<bf16x8*>(smem) + 3 * 64 * q + co;
         d[0] = s.h;
         d[64] = s.m;
@@ -198,7 +193,6 @@ __global__ __launch_bounds__(512, 2) void mfma_f32_stem_kernel(const float* __re
         const int n = fast_div(t, P.by_tiles_y), ty = t - n * P.tiles_y;
         const int row0 = ty * P.TH;
         const int valid_px = min(P.TH, P.Ho - row0) * P.Wo;
-        const bool again = *flag != 0;
         const unsigned char* win = smem + 3 * buf * P.plane + kk * P.pitch;
 #pragma unroll 1
         for (int b = first; 32 * b < valid_px; b += every) {
@@ -233,19 +227,15 @@ __global__ __launch_bounds__(512, 2) void mfma_f32_stem_kernel(const float* __re
             }
             acc += low;
             // register v of a lane is output channel 8 (v / 4) + 4 kk + v % 4, pixel lj
-            if (p < valid_px) {
-                float* yp = y + ((int64_t)n * P.C_out + co0 + 4 * kk) * HoWo + (int64_t)row0 * P.Wo + p;
-                if (__builtin_expect(again || split_suspect(acc), 0)) {
-#pragma unroll 1
-                    for (int v = 0; v < 16; ++v) {
-                        const int c = 8 * (v >> 2) + (v & 3), co = co0 + 4 * kk + c;
-                        if (co < P.C_out)
-                            yp[(int64_t)c * HoWo] = apply_epilogue(conv_output_f32(x, w, P.C_in, P.H, P.W, P.R, P.S, P.stride, P.pad, 1, n, co,
-                                                                                   row0 + ol, ow), co, P.ep);
-                    }
-                } else {
-                    store_block(acc, yp, HoWo, co0 + 4 * kk, P.C_out, co0 + 32 <= P.C_out, P.ep);
-                }
+            float* yp = y + ((int64_t)n * P.C_out + co0 + 4 * kk) * HoWo + (int64_t)row0 * P.Wo + p;
+            const bool beyond = p < valid_px && split_overflow(acc);
+            split_unscale(acc);
+            if (p < valid_px) store_block(acc, yp, HoWo, co0 + 4 * kk, P.C_out, co0 + 32 <= P.C_out, P.ep);
+            if (__builtin_expect(__ballot(beyond) != 0, 0)) {
+                const splitx16 again = multiply_f32<8>(w, RC * P.S, co0 + lj, P.C_out, kk,
+                                                    ConvInputs(xr, P.C_in, P.H, P.W, P.R, P.S, P.stride, P.pad, 1, n, row0 + ol, ow,
+                                                               kk * ((RC * P.S + 1) >> 1)));
+                if (beyond) store_outputs(again, yp, HoWo, co0 + 4 * kk, P.C_out, P.ep);
             }
         }
         if (more) store_window(buf ^ 1);
@@ -278,7 +268,7 @@ StemPlan search_stem(const Conv2dShape& s)
         const int64_t IH = (int64_t)s.stride * (TH - 1) + s.R, extra = 2 * STEPS - RC, rows = IH * s.C_in + extra;
         const int64_t items = IH * s.C_in * groups, pitch = 16 * groups, plane = rows * pitch;
         if (items > 512 * kMaxItems) continue;
-        const int64_t lds = std::max<int64_t>(6 * plane, 64 * 6 * 16 * STEPS + 256 * RC * s.S) + 16;
+        const int64_t lds = std::max<int64_t>(6 * plane, 64 * 6 * 16 * STEPS + 256 * RC * s.S);
         const int64_t tiles = (int64_t)s.N * tiles_y;
         if (lds > kMaxLds || tiles * tiles_y >= (1LL << 32)) continue;
         const int cgroups = (s.C_out + 63) / 64;
@@ -297,7 +287,7 @@ StemPlan search_stem(const Conv2dShape& s)
         P.N = s.N; P.C_in = s.C_in; P.C_out = s.C_out; P.H = s.H; P.W = s.W; P.Ho = s.Ho; P.Wo = s.Wo;
         P.R = s.R; P.S = s.S; P.stride = s.stride; P.pad = s.pad;
         P.TH = TH; P.tiles_y = tiles_y; P.tiles = (int)tiles; P.cgroups = cgroups;
-        P.rows = (int)rows; P.extra = (int)extra; P.flag_off = (int)lds - 16; P.pitch = (int)pitch; P.plane = (int)plane;
+        P.rows = (int)rows; P.extra = (int)extra; P.pitch = (int)pitch; P.plane = (int)plane;
         P.groups = (int)groups; P.items = (int)items;
         P.x_bytes = (unsigned)x_bytes; P.w_bytes = (unsigned)w_bytes;
         P.by_tiles_y = make_fastdiv(tiles_y); P.by_groups = make_fastdiv((int)groups);

@@ -213,3 +213,121 @@ def test_split_pointwise_special_values(torch, sw, value, where):
         _same_but_finite(y, ref.astype(np.float32) if not np.isfinite(value) else ref, f"{value} in {where}")
         ok = np.isfinite(ref)
         assert np.all(np.abs(y[ok] - ref[ok]) <= 2e-5 * np.abs(ref[ok]))
+
+
+# One launch of every variant of the split kernels, most of them with several tiles per workgroup:
+# N, C_in, C_out, H, W, R, stride, pad, kernel
+LAUNCHES = [
+    (12, 48, 96, 56, 56, 3, 1, 1, "mfma_f32_split_kernel<11,1,4>"),     # 504 tiles
+    (129, 48, 512, 8, 8, 3, 1, 1, "mfma_f32_split_kernel<12,5,8>"),     # 416 tiles of five images, the last of four
+    (130, 48, 512, 6, 6, 3, 1, 1, "mfma_f32_split_kernel<21,3,6>"),     # 704 tiles of three images, the last of one
+    (201, 64, 64, 3, 3, 3, 1, 1, "mfma_f32_split_kernel<41,2,3>"),      # 202 tiles of two images, one per workgroup
+    (40, 3, 64, 56, 56, 7, 2, 3, "mfma_f32_stem_kernel<11,"),
+    (64, 5, 48, 56, 56, 3, 2, 1, "mfma_f32_stem_kernel<8,"),
+    (64, 2, 96, 56, 56, 5, 2, 2, "mfma_f32_stem_kernel<5,"),
+    (32, 64, 64, 56, 56, 1, 1, 0, "mfma_f32_pointwise_kernel<2,4>"),
+    (32, 128, 128, 28, 28, 1, 1, 0, "mfma_f32_pointwise_kernel<1,4>"),
+    (40, 64, 128, 33, 34, 1, 1, 0, "mfma_f32_pointwise_kernel<2,2>"),
+    (2, 136, 40, 9, 10, 1, 1, 0, "mfma_f32_pointwise_kernel<1,2>"),
+]
+launches = pytest.mark.parametrize("case", LAUNCHES, ids=lambda c: "x".join(map(str, c[:8])))
+
+
+@launches
+def test_several_images_and_tiles(torch, sw, oracle, case):
+    N, Ci, Co, H, W, R, st, pad, kernel = case
+    x = inputs.normal_f32((N, Ci, H, W), 6700 + Ci)
+    w = inputs.normal_f32((Co, Ci, R, R), 6800 + Co, (2.0 / (Ci * R * R)) ** 0.5)
+    y_ref, d = oracle.conv2d(x, w, st, pad)
+    buf, out, front, n, guard = guarded_empty(torch, y_ref.shape, torch.float32)
+    sw.sw_conv2d(torch.from_numpy(x).cuda(), torch.from_numpy(w).cuda(), st, pad, out=out)
+    assert sw.sw_last_kernel().startswith(kernel), sw.sw_last_kernel()
+    assert_f32_parity(out.cpu().numpy(), y_ref, d, str(case))
+    assert_guards_intact(buf, front, n, guard)
+
+
+@launches
+def test_one_small_value_changes_nothing(torch, sw, case):
+    """A weight or an input far too small to show in any result (denormal, or just above) in the first filter and in the last
+    image: every output has the bits it has with a zero in its place.  (An output computed any other way would not.)"""
+    N, Ci, Co, H, W, R, st, pad, kernel = case
+    g = torch.Generator(device="cuda").manual_seed(41)
+    x = torch.randn(N, Ci, H, W, generator=g, device="cuda")
+    w = torch.randn(Co, Ci, R, R, generator=g, device="cuda")
+    w[0, Ci - 1, 0, 0] = 0.0
+    x[N - 1, Ci - 1, H // 2, W // 2] = 0.0
+    clean = sw.sw_conv2d(x, w, st, pad)
+    assert sw.sw_last_kernel().startswith(kernel), sw.sw_last_kernel()
+    for small in (1e-38, -3e-32, 1e-42):
+        w[0, Ci - 1, 0, 0] = small
+        assert torch.equal(sw.sw_conv2d(x, w, st, pad), clean), f"weight {small}"
+        w[0, Ci - 1, 0, 0] = 0.0
+        x[N - 1, Ci - 1, H // 2, W // 2] = small
+        assert torch.equal(sw.sw_conv2d(x, w, st, pad), clean), f"input {small}"
+        x[N - 1, Ci - 1, H // 2, W // 2] = 0.0
+
+
+@launches
+def test_powers_of_two_pass_through(torch, sw, case):
+    """Inputs times 2^-142 (denormal: the last bits of the smallest fp32 values) under weights times 2^100, and the other way
+    round: the same bits as without the factors, because a factor of 2 changes no rounding."""
+    N, Ci, Co, H, W, R, st, pad, kernel = case
+    g = torch.Generator(device="cuda").manual_seed(42)
+    a = torch.randint(-1000, 1001, (N, Ci, H, W), generator=g, device="cuda").float() / 128     # whole multiples of 2^-7
+    b = torch.randn(Co, Ci, R, R, generator=g, device="cuda").clamp_(-6, 6)
+    plain = sw.sw_conv2d(a, b, st, pad)
+    assert sw.sw_last_kernel().startswith(kernel), sw.sw_last_kernel()
+    small = (a.double() * 2.0 ** -142).float()
+    assert torch.equal((small.double() * 2.0 ** 142).float(), a)
+    y = sw.sw_conv2d(small, b * 2.0 ** 100, st, pad)
+    assert torch.equal(y * 2.0 ** 42, plain)
+    a, b = a.clamp_(-6, 6) / 8, (torch.randint(-1000, 1001, b.shape, generator=g, device="cuda").float() / 128)
+    plain = sw.sw_conv2d(a, b, st, pad)
+    y = sw.sw_conv2d(a * 2.0 ** 100, (b.double() * 2.0 ** -142).float(), st, pad)
+    assert torch.equal(y * 2.0 ** 42, plain)
+
+
+@pytest.mark.parametrize("value", [np.inf, -np.inf, np.nan, 3.4028234e38, 1e32], ids=str)
+@launches
+def test_one_special_value(torch, sw, case, value):
+    """One operand that the scaled sums do not hold, in the last image or in one filter: what it reaches has the value fp32
+    arithmetic gives, everything else the bits it has without it.  Positive operands: no other infinity or NaN can arise."""
+    N, Ci, Co, H, W, R, st, pad, kernel = case
+    g = torch.Generator(device="cuda").manual_seed(43)
+    x = torch.rand(N, Ci, H, W, generator=g, device="cuda") * 0.1 + 0.1
+    w = torch.rand(Co, Ci, R, R, generator=g, device="cuda") * 0.001 + 0.001
+    clean = sw.sw_conv2d(x, w, st, pad)
+    assert sw.sw_last_kernel().startswith(kernel), sw.sw_last_kernel()
+
+    def check(xv, wv, reached, images, channels, what):
+        y = sw.sw_conv2d(xv, wv, st, pad)
+        ref = torch.nn.functional.conv2d(xv[images].double().cpu(), wv[channels].double().cpu(), stride=st, padding=pad)
+        got = y[images][:, channels].cpu()
+        with np.errstate(all="ignore"):
+            _same_but_finite(got.numpy(), ref.float().numpy() if not np.isfinite(value) else ref.numpy(), what)
+        ok = torch.isfinite(ref)
+        # plain multiply-adds one after the other: a rounding of 2^-24 of a partial sum each, all terms positive
+        assert torch.all((got.double() - ref).abs()[ok] <= Ci * R * R * 2.0 ** -24 * ref.abs()[ok]), what
+        assert torch.equal(y[~reached], clean[~reached]), f"{what}: outputs that it does not reach"
+
+    i, j = H // 2, W // 2
+    xv = x.clone()
+    xv[N - 1, Ci - 1, i, j] = value
+    reached = torch.zeros_like(clean, dtype=torch.bool)
+    for r in range(R):
+        for s in range(R):
+            p, q = i + pad - r, j + pad - s
+            if p % st == 0 and q % st == 0 and 0 <= p // st < clean.shape[2] and 0 <= q // st < clean.shape[3]:
+                reached[N - 1, :, p // st, q // st] = True
+    # (a window's cells beyond a filter's last tap meet zero weights: outputs beside the reached ones are computed again too)
+    if kernel.startswith("mfma_f32_stem"):
+        reached[N - 1] = True
+    check(xv, w, reached, slice(N - 1, N), slice(0, Co), f"{value} in x")
+    wv = w.clone()
+    wv[Co // 2, Ci - 1, R // 2, R // 2] = value
+    reached = torch.zeros_like(clean, dtype=torch.bool)
+    reached[:, Co // 2] = True
+    # (a lane's sixteen output channels are computed again together)
+    block = Co // 2 // 32 * 32
+    reached[:, block:block + 32] = True
+    check(x, wv, reached, slice(0, min(N, 2)), slice(Co // 2, Co // 2 + 1), f"{value} in w")
