@@ -109,7 +109,8 @@ int sw_pool2d(const float* x, float* y, int N, int C, int H, int W, int R, int S
  * (2 to 7, rows of at most 8 taps, R * C_in <= 22) and 1x1 at stride 1 without padding
  * (C_in % 16 == 0 or >= 128, see the source for small launches) take every fp32 operand
  * as a sum of three bf16 values on the bf16 matrix instructions: six of nine products,
- * fp32 sums, errors against 64-bit sums below those of the fp32 instructions.  Outputs that
+ * fp32 sums; what is left out of a product is up to 2^-24 of it, errors of sums of N(0,1)
+ * data against 64-bit sums are below those of the fp32 instructions.  Outputs that
  * meet an infinity, a NaN, an operand from about 2^104 up or a sum from 2^80 up are computed
  * on the fp32 instructions instead: the same results at up to ten times a launch's time
  * where all outputs do.  3x3 and 5x5 at stride 1 with C_in % 16 == 0,

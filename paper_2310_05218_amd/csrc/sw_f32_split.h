@@ -1,13 +1,18 @@
 // fp32 operands for the bf16 matrix instructions: every fp32 value is the sum of three bf16 values
 //     v = h + m + l,   h = bf16(v), m = bf16(v - h), l = v - h - m      (rounded to nearest even; the sum is exact),
 // and a product is taken as   lh + hl + mm + mh + hm + hh,   six products of eight-bit significands that are exact in the
-// fp32 accumulators.  What is left out (ml, lm, ll) is at most 2^-26 of the product, below the rounding of one fp32 addition.
+// fp32 accumulators.  What is left out (ml, lm, ll) is up to 2^-24.0 of the product, as much as an fp32 rounding (both operands
+// 1 + 2^-8 - 2^-17; over random pairs 2^-27.5 in the mean square, above 2^-26 for 2.7 % of them).  A sum of a single product is off by
+// up to 1.0e-7 of it where an fp32 instruction gives 6e-8 (1.5e-7 in 1 x 1 layers, whose six products share an accumulator), and where
+// many equal operands give the left-out parts one sign they are still 2^-24 of the result.
 //
-// Why: v_mfma_f32_32x32x16_bf16 performs 16 times the multiply-adds of v_mfma_f32_32x32x2_f32 in half its time per K step of
-// 16 (32 cycles against 8 x 64), so six of them still take 0.375 of the fp32 instruction's time; and an accumulator is rounded
+// Why: v_mfma_f32_32x32x16_bf16 performs 8 times the multiply-adds of v_mfma_f32_32x32x2_f32 in half its time (per K step of
+// 16: 32 cycles against 8 x 64), so six of them still take 0.375 of the fp32 instruction's time; and an accumulator is rounded
 // 6 / 16 instead of 1 / 2 times per product.  Against 64-bit sums of N(0,1) data (rel: 2-norm of the error over 2-norm of the
 // result), fp32 instruction -> six bf16 ones: 144 products 2.15e-7 -> 1.74e-7, 576: 4.34e-7 -> 3.61e-7, 2304: 8.60e-7 -> 7.42e-7,
 // 4608: 1.21e-6 -> 1.07e-6; all products positive, 576: 3.71e-7 -> 2.78e-7; magnitudes spread over 2^40, 576: 3.27e-7 -> 3.21e-7.
+// In the layers (the kernels of before -> now): 3 x 3 over 512 channels, N(0,1) 5.8e-7 -> 2.2e-7, all operands 1/3 1.2e-5 -> 5.7e-8;
+// 1 x 1 over 256, N(0,1) 2.9e-7 -> 2.4e-7, operands within 2e-7 of 1 + 2^-8 - 2^-17 8.6e-8 -> 1.3e-7; 7 x 7 over 3, N(0,1) 2.1e-7 -> 6.9e-8.
 //
 // Range.  A value is split after a factor of 2^24, and a sum of products leaves with a factor of 2^-48 (split_unscale).  Scaled so,
 // every part of every fp32 value, denormal ones included, is a normal bf16 value or zero (the last bit of the smallest value is

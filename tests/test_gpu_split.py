@@ -331,3 +331,19 @@ def test_one_special_value(torch, sw, case, value):
     block = Co // 2 // 32 * 32
     reached[:, block:block + 32] = True
     check(x, wv, reached, slice(0, min(N, 2)), slice(Co // 2, Co // 2 + 1), f"{value} in w")
+
+
+@launches
+def test_left_out_products(torch, sw, case):
+    """Operands of 1 + 2^-8 - 2^-17 throughout: of a product, what the six bf16 products leave out is 2^-24.01, its largest, and
+    has one sign (2^-24 of the result).  The parts are powers of two, their sums whole multiples of 2^-17: what else is rounded is the
+    result (2^-24)."""
+    N, Ci, Co, H, W, R, st, pad, kernel = case
+    v = 1.0 + 2.0 ** -8 - 2.0 ** -17
+    x = torch.full((N, Ci, H, W), v, device="cuda")
+    w = torch.full((Co, Ci, R, R), v, device="cuda")
+    y = sw.sw_conv2d(x, w, st, pad).double().cpu()
+    assert sw.sw_last_kernel().startswith(kernel), sw.sw_last_kernel()
+    taps = torch.nn.functional.conv2d(torch.ones(1, Ci, H, W, dtype=torch.float64), torch.ones(1, Ci, R, R, dtype=torch.float64), stride=st, padding=pad)
+    ref = taps * (v * v)
+    assert torch.all((y - ref).abs() <= 2.0 ** -23 * ref)
