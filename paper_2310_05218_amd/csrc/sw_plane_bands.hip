@@ -154,9 +154,10 @@ BandPlan plan_bands(const void* x, int64_t planes, int planes_per_x, int n_filte
     QH = (QHall + bands - 1) / bands;
     bands = (QHall + QH - 1) / QH;
     if (planes * bands * bands >= (1LL << 31)) return a;
-    a.ok = true;
     a.groups = planes * bands;
     a.threads = (int64_t)QH * s.Wo <= 128 ? 128 : 256;
+    if (a.groups * a.threads >= (1LL << 32)) return a;      // (work items of a launch)
+    a.ok = true;
     BandParams& P = a.P;
     P.H = s.H; P.W = s.W; P.R = s.R; P.S = s.S; P.stride = s.stride; P.pad = s.pad; P.Ho = s.Ho; P.Wo = s.Wo;
     P.n_filters = n_filters; P.planes_per_x = planes_per_x;

@@ -1,0 +1,26 @@
+"""The launch plans of kernels that a shape selects, asked on the host (a plan touches no device): limits of a launch."""
+import ctypes
+
+from paper_2310_05218_amd import binding
+
+
+class Shape(ctypes.Structure):
+    _fields_ = [(n, ctypes.c_int) for n in ("N", "C_in", "C_out", "H", "W", "R", "S", "stride", "pad", "Ho", "Wo", "dil")]
+
+
+def shape(N, C_in, C_out, H, W, R, S, stride, pad):
+    return Shape(N, C_in, C_out, H, W, R, S, stride, pad, (H + 2 * pad - R) // stride + 1, (W + 2 * pad - S) // stride + 1, 1)
+
+
+def bands(planes, planes_per_x, s, bf16=False):
+    f = getattr(binding.lib(), "_ZN6swconv21plane_bands_supportedEPKvliiRKNS_11Conv2dShapeEb")
+    f.restype, f.argtypes = ctypes.c_bool, [ctypes.c_void_p, ctypes.c_long, ctypes.c_int, ctypes.c_int, ctypes.POINTER(Shape), ctypes.c_bool]
+    return f(4096, planes, planes_per_x, planes_per_x, ctypes.byref(s), bf16)
+
+
+def test_bands_stay_below_the_work_items_of_a_launch():
+    """One workgroup of at least 128 threads per plane: 2^25 planes would be 2^32 work items, one more than a launch has."""
+    s = shape(32767, 1, 1024, 70, 64, 64, 64, 2, 0)          # four outputs a plane, 64 x 64 taps
+    assert bands(32767 * 1024, 1024, s)
+    s.N = 32768
+    assert not bands(32768 * 1024, 1024, s)
