@@ -12,6 +12,8 @@
 // Measured (us per launch): fp32 5x5 stride 2 on 8 x 144 x 75 x 75 38.5 (one thread per output) -> 10.2, 3.2 TB/s; 7x7 on
 // 8 x 488 x 47 x 42 41.8 (tile kernel) -> 28.3; bf16 5x5 stride 2 on 8 x 144 x 75 x 75 35.9 -> 9.5.  Bound by the memory round
 // trip in front of each workgroup's only barrier, and by LDS reads for the larger filters (18 per 49 multiply-adds at 7x7).
+#include <algorithm>
+
 #include "swconv_internal.h"
 
 namespace swconv {
@@ -199,9 +201,34 @@ hipError_t launch_any(const void* x, const float* w, void* y, const BandPlan& a,
 
 }  // namespace
 
+// Where bands are no slower than one thread per output.  us, one thread per output / bands:
+// - Taps unrolled: a workgroup per plane needs enough to do.  131072 planes under 3x3, 81 outputs each, 59.6 / 74.5, 121 outputs 86.3 /
+//   74.9; 5x5, 49 outputs 66.9 / 84.2, 81 outputs 109 / 85.5; 7x7 stride 2, 25 outputs 109 / 131, 36 outputs 133 / 133.  With few planes
+//   bands were never slower (256 planes under 3x3, 25 outputs each, 3.93 / 3.98; 4096 under 5x5, 49 outputs each, 6.7 / 5.8).
+// - Taps in loops: bands pay for the framed plane and for whole groups of four output rows, one thread per output for the taps that
+//   meet the plane (`met`: at most R / stride rows of taps meet an input row).  The lines fit 845 timed shapes; six lie on the wrong
+//   side by more than 6 %, at most 17 %.  113 x 113, 512 planes: 2x2 stride 4 5.0 / 8.4, 3x3 stride 4 7.1 / 8.7, stride 3 10.0 / 8.7,
+//   7x7 stride 8 16.1 / 10.5, 256 planes: 9x9 stride 4 25.0 / 11.7, 51x51 stride 3 602 / 461; 6x6 stride 9 on 225 x 84 23.4 / 27.8; 33x33 on 12 x 5, mostly over the padding,
+//   44 / 83; 21x21 stride 7 on 23 x 230, one output row, 63 / 119; 2x2 on 8 planes of 118 x 279 3.5 / 4.1.
+bool plane_bands_worthwhile(int64_t planes, const Conv2dShape& s, bool bf16)
+{
+    const int taps = s.R * s.S;
+    const int64_t work = (int64_t)s.Ho * s.Wo * taps;
+    if (bf16 && work < 2000) return false;      // (3x3 stride 2 on 19 x 19: 3.5 us against 3.8; 7x7 on 10 x 10: 8.0 against 11.9)
+    if (plane_bands_unrolled(s)) return bf16 || planes <= (s.R == 3 ? 512 : 4096) || work >= (s.R == 3 ? 1000 : 1600);
+    const auto met = [&](int n, int k, int n_out) { return std::min((double)n_out * k, n * std::min((double)n_out, (double)k / s.stride)); };
+    const double real = met(s.H, s.R, s.Ho) * met(s.W, s.S, s.Wo);
+    const double frame = ((double)(s.Ho - 1) * s.stride + s.R) * ((double)(s.Wo - 1) * s.stride + s.S);
+    const bool few = planes <= 512;
+    if ((few ? 4 : 3) * real < (double)((s.Ho + 3) / 4 * 4) * s.Wo * taps) return false;
+    if (few && taps >= (bf16 ? 25 : 12) && real >= frame) return true;
+    if (taps < 25) return (double)planes * real >= 1e6 && real >= frame + 1000;
+    return real >= (bf16 ? frame : frame / 2) + 2000;
+}
+
 bool plane_bands_supported(const void* x, int64_t planes, int planes_per_x, int n_filters, const Conv2dShape& s, bool bf16)
 {
-    return plan_bands(x, planes, planes_per_x, n_filters, s, bf16 ? 2 : 4).ok;
+    return plane_bands_worthwhile(planes, s, bf16) && plan_bands(x, planes, planes_per_x, n_filters, s, bf16 ? 2 : 4).ok;
 }
 
 hipError_t launch_plane_bands(const void* x, const float* w, void* y, int64_t planes, int planes_per_x, int n_filters, const Conv2dShape& s,

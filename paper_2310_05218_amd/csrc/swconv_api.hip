@@ -79,13 +79,16 @@ int run_plane(const float* x, const float* w, float* y, int64_t planes, int plan
         // 8 x 488 x 47 x 42 7x7 41.8 -> 28.3, one image 200 x 62 x 62 3x3 13.4 -> 4.6); the tile keeps the other extents.
         if (!whole && plane_bands_unrolled(s) && plane_bands_supported(x, planes, planes_per_x, n_filters, s, false))
             return launch_status(launch_plane_bands(x, w, y, planes, planes_per_x, n_filters, s, false, st, ep));
-        if (sliding_plane_supported(s.H, s.W, s.R, s.S, s.stride, s.pad) &&
+        // (where a plane is too little for a workgroup of bands, it is for a tile: 131072 planes of 5 x 5 under 3x3 266 us on tiles, 73 on
+        // bands, 22 with one thread per output)
+        const bool little = plane_bands_unrolled(s) && !plane_bands_worthwhile(planes, s, false);
+        if (!little && sliding_plane_supported(s.H, s.W, s.R, s.S, s.stride, s.pad) &&
             sliding_plane_worthwhile(planes, s.Ho, s.Wo, s.R, s.S))
             return launch_status(launch_sliding_plane(x, w, y, planes, planes_per_x, n_filters, s.H, s.W, s.R, s.S,
                                                       s.pad, s.Ho, s.Wo, st, ep));
     }
     // strides above 1 the rows kernel does not take, few or short planes: bands too, their taps in loops where not unrolled (us:
-    // 8 x 144 x 75 x 75 5x5 stride 2 38.5 -> 10.2 in place of one thread per output)
+    // 8 x 144 x 75 x 75 5x5 stride 2 38.5 -> 10.2 in place of one thread per output; plane_bands_worthwhile)
     if (!force_direct() && plane_bands_supported(x, planes, planes_per_x, n_filters, s, false))
         return launch_status(launch_plane_bands(x, w, y, planes, planes_per_x, n_filters, s, false, st, ep));
     return launch_status(launch_direct_conv2d_f32(x, w, y, s, depthwise, st, &ep));
@@ -444,9 +447,8 @@ int sw_conv2d_depthwise_bf16(const uint16_t* x, const float* w, uint16_t* y, int
     hipStream_t st = static_cast<hipStream_t>(hip_stream);
     if (!force_direct() && sliding_plane_bf16_supported(x, y, H, W, R, S, stride, pad, s.Ho, s.Wo))
         return launch_status(launch_sliding_plane_bf16(x, w, y, (int64_t)N * C, C, H, W, R, pad, s.Ho, s.Wo, st));
-    // bands of output rows, but one thread per output on planes with little to do (3x3 stride 2 on 19 x 19: 3.5 us against 3.8;
-    // 7x7 on 10 x 10: 11.9 against 8.0)
-    if (!force_direct() && (int64_t)s.Ho * s.Wo * R * S >= 2000 && plane_bands_supported(x, (int64_t)N * C, 1, C, s, true))
+    // bands of output rows, but one thread per output on planes with little to do (plane_bands_worthwhile)
+    if (!force_direct() && plane_bands_supported(x, (int64_t)N * C, 1, C, s, true))
         return launch_status(launch_plane_bands(x, w, y, (int64_t)N * C, 1, C, s, true, st));
     return launch_status(launch_direct_depthwise_bf16(x, w, y, s, st));
 }

@@ -222,6 +222,7 @@ int        jit_launch_plane(const float* x, const float* w, float* y, int64_t pl
 // ---- one filter per plane, any width, stride and extent, fp32 or bf16 planes: bands of output rows through LDS
 // (extents and strides whose taps are unrolled)
 inline bool plane_bands_unrolled(const Conv2dShape& s) { return s.dil == 1 && s.R == s.S && (s.R == 3 || s.R == 5 || s.R == 7) && s.stride <= 2; }
+bool       plane_bands_worthwhile(int64_t planes, const Conv2dShape& s, bool bf16);
 bool       plane_bands_supported(const void* x, int64_t planes, int planes_per_x, int n_filters, const Conv2dShape& s, bool bf16);
 hipError_t launch_plane_bands(const void* x, const float* w, void* y, int64_t planes, int planes_per_x, int n_filters,
                               const Conv2dShape& s, bool bf16, hipStream_t st, const Epilogue& ep = Epilogue{nullptr, 0});

@@ -89,3 +89,28 @@ def test_one_input_channel_many_filters(torch, sw, oracle):
     y = sw.sw_conv2d(torch.from_numpy(x).cuda(), torch.from_numpy(w).cuda(), 1, 2)
     assert sw.sw_last_kernel().startswith("plane_bands_kernel<5,1"), sw.sw_last_kernel()
     assert_f32_parity(y.cpu().numpy(), *oracle.conv2d(x, w, 1, 2), "one input channel")
+
+
+@pytest.mark.parametrize("case", [
+    # N, filters, H, W, R, S, stride, pad, kernel: one input channel, on both sides of what bands are worth
+    (8, 64, 5, 5, 3, 3, 1, 1, "plane_bands_kernel<3,1"), (27, 19, 5, 5, 3, 3, 1, 1, "direct_conv2d_kernel"),          # 512, 513 planes
+    (64, 64, 7, 7, 5, 5, 1, 2, "plane_bands_kernel<5,1"), (241, 17, 7, 7, 5, 5, 1, 2, "direct_conv2d_kernel"),        # 4096, 4097
+    (100, 64, 11, 11, 3, 3, 1, 1, "plane_bands_kernel<3,1"), (100, 64, 7, 9, 3, 3, 2, 1, "direct_conv2d_kernel"),
+    (100, 64, 13, 13, 7, 7, 2, 3, "plane_bands_kernel<7,2"), (100, 64, 9, 9, 7, 7, 2, 3, "direct_conv2d_kernel"),
+    (4, 16, 33, 33, 3, 3, 4, 1, "direct_conv2d_kernel"), (4, 16, 33, 33, 9, 9, 4, 4, "plane_bands_kernel<0,0"),       # taps in loops
+], ids=lambda c: "x".join(map(str, c[:8])))
+def test_many_small_planes(torch, sw, oracle, case):
+    N, K, H, W, R, S, st, pad, kernel = case
+    x = inputs.normal_f32((N, 1, H, W), 6700 + H)
+    w = inputs.normal_f32((K, 1, R, S), 6800 + R, 1.0 / R)
+    b = inputs.normal_f32((K,), 6900, 0.5)
+    xd, wd = torch.from_numpy(x).cuda(), torch.from_numpy(w).cuda()
+    y_ref, d = oracle.conv2d(x, w, st, pad)
+    buf, out, front, n, guard = guarded_empty(torch, y_ref.shape, torch.float32)
+    sw.sw_conv2d(xd, wd, st, pad, out=out)
+    assert sw.sw_last_kernel().startswith(kernel), sw.sw_last_kernel()
+    assert_f32_parity(out.cpu().numpy(), y_ref, d, str(case))
+    assert_guards_intact(buf, front, n, guard)
+    y = sw.sw_conv2d_bias_relu(xd, wd, torch.from_numpy(b).cuda(), st, pad, True)
+    yr, dr = oracle.conv2d_bias_relu(x, w, b, st, pad, True)
+    assert_f32_parity(y.cpu().numpy(), yr, np.maximum(dr, 1e-30), f"{case} bias, rectifier")

@@ -1,5 +1,8 @@
-"""The launch plans of kernels that a shape selects, asked on the host (a plan touches no device): limits of a launch."""
+"""The launch plans of kernels that a shape selects, asked on the host (a plan touches no device): limits of a launch, and which
+shapes the one-filter-per-plane bands take."""
 import ctypes
+
+import pytest
 
 from paper_2310_05218_amd import binding
 
@@ -24,3 +27,15 @@ def test_bands_stay_below_the_work_items_of_a_launch():
     assert bands(32767 * 1024, 1024, s)
     s.N = 32768
     assert not bands(32768 * 1024, 1024, s)
+
+
+@pytest.mark.parametrize("planes,size,R,stride,takes", [
+    (512, 5, 3, 1, True), (513, 5, 3, 1, False),              # few planes whatever they hold; many that hold little
+    (131072, 10, 3, 1, False), (131072, 11, 3, 1, True),      # 100 and 121 outputs of nine taps
+    (4096, 7, 5, 1, True), (4097, 7, 5, 1, False), (131072, 8, 5, 1, True),
+    (131072, 10, 7, 2, False), (131072, 11, 7, 2, True),      # 25 and 36 outputs of 49 taps
+    (512, 113, 2, 4, False), (512, 113, 3, 4, False), (512, 113, 9, 4, True), (512, 113, 51, 3, True),     # taps in loops
+    (2574, 12, 33, 9, False),                                 # mostly over the padding
+])
+def test_bands_take_what_they_are_faster_at(planes, size, R, stride, takes):
+    assert bands(planes, planes, shape(1, 1, planes, size, size, R, R, stride, R // 2)) == takes
