@@ -259,6 +259,7 @@ StemPlan search_stem(const Conv2dShape& s)
     const int64_t w_bytes = (int64_t)s.C_out * RC * s.S * 4;
     if (s.C_in < 2 || s.C_in > 7 || s.S > 8 || RC > 22 || s.stride % 2 != 0 || s.dil != 1 || x_bytes >= (1LL << 31) || w_bytes >= (1LL << 31)) return best;
     const int STEPS = RC <= 10 ? 5 : RC <= 16 ? 8 : 11;
+    if ((s.C_out + 63) / 64 > 65535) return best;            // (second dimension of a launch)
     const int64_t cols = (int64_t)s.stride * (s.Wo - 1) + 8, groups = (cols + 7) / 8;
     if (groups > 512) return best;
     for (int tiles_y = 1; tiles_y <= s.Ho; ++tiles_y) {

@@ -39,3 +39,14 @@ def test_bands_stay_below_the_work_items_of_a_launch():
 ])
 def test_bands_take_what_they_are_faster_at(planes, size, R, stride, takes):
     assert bands(planes, planes, shape(1, 1, planes, size, size, R, R, stride, R // 2)) == takes
+
+
+def split_supported(name, s):
+    f = getattr(binding.lib(), f"_ZN6swconv{19 + len(name)}mfma_f32_{name}_supportedERKNS_11Conv2dShapeE")
+    f.restype, f.argtypes = ctypes.c_bool, [ctypes.POINTER(Shape)]
+    return f(ctypes.byref(s))
+
+
+def test_few_channels_kernel_stays_below_a_launch_s_second_dimension():
+    assert split_supported("stem", shape(1, 3, 64 * 65535, 9, 9, 3, 3, 2, 1))
+    assert not split_supported("stem", shape(1, 3, 64 * 65535 + 1, 9, 9, 3, 3, 2, 1))
