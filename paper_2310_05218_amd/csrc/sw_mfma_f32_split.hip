@@ -444,7 +444,11 @@ SplitPlan search_split(const Conv2dShape& s)
         }
     };
     for (int NI = 2; NI <= s.N && (int64_t)NI * s.Ho * s.Wo <= 512; ++NI) consider(NI, 1);
-    for (int ty = 1; ty <= s.Ho; ++ty) consider(1, ty);
+    for (int TH = std::min(s.Ho, 512 / s.Wo), last = 0; TH >= 1; --TH) {        // (tiles of at most 512 pixels, however tall the image)
+        const int tiles_y = (s.Ho + TH - 1) / TH;
+        if (tiles_y != last) consider(1, tiles_y);
+        last = tiles_y;
+    }
     return best;
 }
 

@@ -262,9 +262,11 @@ StemPlan search_stem(const Conv2dShape& s)
     if ((s.C_out + 63) / 64 > 65535) return best;            // (second dimension of a launch)
     const int64_t cols = (int64_t)s.stride * (s.Wo - 1) + 8, groups = (cols + 7) / 8;
     if (groups > 512) return best;
-    for (int tiles_y = 1; tiles_y <= s.Ho; ++tiles_y) {
-        const int TH = (s.Ho + tiles_y - 1) / tiles_y;
-        if ((s.Ho + TH - 1) / TH != tiles_y) continue;
+    const int64_t most = (512 * kMaxItems / (s.C_in * groups) - s.R) / s.stride + 1;     // rows of a tile whose window the items hold
+    for (int rows_max = (int)std::min<int64_t>(s.Ho, most), last = 0; rows_max >= 1; --rows_max) {
+        const int tiles_y = (s.Ho + rows_max - 1) / rows_max, TH = (s.Ho + tiles_y - 1) / tiles_y;
+        if (tiles_y == last) continue;
+        last = tiles_y;
         // window rows of a tile: those of its output rows, and rows of zeros for the pairs of the last steps beyond the filter
         const int64_t IH = (int64_t)s.stride * (TH - 1) + s.R, extra = 2 * STEPS - RC, rows = IH * s.C_in + extra;
         const int64_t items = IH * s.C_in * groups, pitch = 16 * groups, plane = rows * pitch;

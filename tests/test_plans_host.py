@@ -1,6 +1,7 @@
 """The launch plans of kernels that a shape selects, asked on the host (a plan touches no device): limits of a launch, and which
 shapes the one-filter-per-plane bands take."""
 import ctypes
+import time
 
 import pytest
 
@@ -50,3 +51,13 @@ def split_supported(name, s):
 def test_few_channels_kernel_stays_below_a_launch_s_second_dimension():
     assert split_supported("stem", shape(1, 3, 64 * 65535, 9, 9, 3, 3, 2, 1))
     assert not split_supported("stem", shape(1, 3, 64 * 65535 + 1, 9, 9, 3, 3, 2, 1))
+
+
+@pytest.mark.parametrize("name,s", [("split", (1, 33, 8, 15_000_000, 1, 9, 1, 1, 4)), ("stem", (1, 3, 8, 40_000_000, 1, 7, 7, 2, 3))])
+def test_plans_of_tall_images_take_no_longer(name, s):
+    """The search goes over the tiles that can be, not over all row counts of the image (65 and 85 ms here)."""
+    s = shape(*s)
+    binding.lib()
+    start = time.perf_counter()
+    split_supported(name, s)
+    assert time.perf_counter() - start < 0.01
