@@ -259,6 +259,15 @@ StemPlan search_stem(const Conv2dShape& s)
     const int64_t w_bytes = (int64_t)s.C_out * RC * s.S * 4;
     if (s.C_in < 2 || s.C_in > 7 || s.S > 8 || RC > 22 || s.stride % 2 != 0 || s.dil != 1 || x_bytes >= (1LL << 31) || w_bytes >= (1LL << 31)) return best;
     const int STEPS = RC <= 10 ? 5 : RC <= 16 ? 8 : 11;
+    // Short filter rows leave most of the K index empty: the kernels on fp32 matrix instructions have R S products of 2, 4 or 8 channels
+    // against 6 STEPS steps of sixteen here.  From 0.6 of them up (two channels, which those kernels hold without a rest: 0.7) this one
+    // is no slower (us, theirs / this one: 1 x 1 over 2 channels, 32 images of 224 x 224, 24.2 / 37.1, 2 x 2 over 3 35.9 / 33.2 but 16 of
+    // 112 x 112 9.1 / 10.0, over 7 59.1 / 52.0, 3 x 3 over 2 9.3 / 10.3, over 3 52.3 / 33.0).  At strides from 4 up they bring in whole windows
+    // of mostly unused columns, unless there is next to nothing to do (2 x 2 stride 8 over 4, 20 of 132 x 18, 11.3 / 6.7; 1 x 5 stride 4 over
+    // 2, 34 of 9 x 116 6.3 / 7.4).  Two of 840 timed shapes are slower by more than 10 %.
+    const double products = (double)s.R * s.S * (s.C_in == 2 ? 2 : s.C_in <= 4 ? 4 : 8) / (6 * STEPS);
+    if (products < (s.C_in == 2 ? 0.7 : 0.6) &&
+        !(s.stride >= 4 && products >= 0.25 && (int64_t)s.Ho * s.Wo >= 40 && std::min(s.Ho, s.Wo) >= 2)) return best;
     if ((s.C_out + 63) / 64 > 65535) return best;            // (second dimension of a launch)
     const int64_t cols = (int64_t)s.stride * (s.Wo - 1) + 8, groups = (cols + 7) / 8;
     if (groups > 512) return best;

@@ -61,3 +61,12 @@ def test_plans_of_tall_images_take_no_longer(name, s):
     start = time.perf_counter()
     split_supported(name, s)
     assert time.perf_counter() - start < 0.01
+
+
+@pytest.mark.parametrize("C,R,S,stride,size,takes", [
+    (3, 7, 7, 2, 224, True), (3, 3, 3, 2, 224, True), (7, 2, 2, 2, 224, True),
+    (2, 1, 1, 2, 224, False), (3, 2, 2, 2, 224, False), (2, 3, 3, 2, 224, False), (2, 5, 4, 2, 224, True),     # 0.07, 0.53, 0.6, 1.33
+    (2, 2, 2, 4, 50, True), (2, 2, 2, 4, 20, False), (4, 1, 1, 4, 50, False),                                 # strides from 4 up
+])
+def test_few_channels_kernel_takes_what_it_is_faster_at(C, R, S, stride, size, takes):
+    assert split_supported("stem", shape(8, C, 64, size, size, R, S, stride, 0)) == takes
