@@ -496,11 +496,23 @@ PwPlan plan_pointwise(const Conv2dShape& s, const float* x, const float* w, cons
     }
     if (a.ok) a.lds = (size_t)a.CB * 32 * (s.C_in + 4) * sizeof(float);
     // Split operands where their filters fit LDS, but not where the last, half empty step of 16 channels is a large part of few
-    // (8 -> 32 at 256 x 256, 5 images: 15.4 us against 25.1; 72 -> 248 at 66 x 65, 7 images: 20.7 against 21.8), nor for
-    // launches of a few short tiles, where the splitting before the first product shows (32 -> 64 at 28 x 28, 2 images: 5.4
-    // against 5.7; 16 -> 7, 270 pixels: 3.9 against 4.8).
+    // (8 -> 32 at 256 x 256, 5 images: 15.4 us against 25.1; 72 -> 248 at 66 x 65, 7 images: 20.7 against 21.8), and from `least`
+    // channels up: few channels leave little to multiply per value split and stored, and <2,4> has half the wavefronts per SIMD of the
+    // fp32 kernel, which shows where there are more tiles than those.  us, fp32 instructions / split:
+    //   fewer than 256 wavefronts: 64 -> 24, 1560 pixels 6.7 / 7.8, 152 -> 25, 858 pixels 9.8 / 10.8, 200 -> 256 at 14 x 14 12.4 / 11.9
+    //   fewer than 700: 200 -> 16, 40000 pixels 12.1 / 12.6, 384 -> 384 at 14 x 14, 32 images 29.7 / 28.4
+    //   <2,4>: 64 -> 64 at 56 x 56, 32 images 19.9 / 14.9, 64 images 0.88 to 0.93 of the fp32 kernel's rate, 96 channels 1.03 to 1.07
+    //   <2,4>, 16 -> 64 at 56 x 56, 32 images 12.5 / 10.9, -> 32 12.4 / 13.9 (a block of channels that is not whole is stored value by value)
+    //   <2,2>: 64 channels, 1124 wavefronts 1.13, 4488 wavefronts 0.95, 80 channels 1.05;  <1,4>: 32 -> 256 at 28 x 28, 16 images 9.8 / 8.1,
+    //   32 -> 187 at 84 x 3, 63 images 9.7 / 10.9, 48 channels 1.12
+    //   <1,2>: 64 -> 61, 24534 pixels 8.2 / 9.4, 80 channels 1.00 to 1.04
     const size_t steps = (s.C_in + 15) / 16, split_lds = steps * 96 * (a.CB * 32 + 1);
-    a.split = a.ok && split_lds <= kPwLdsSplit && (s.C_in % 16 == 0 || s.C_in >= 128) && (s.C_in >= 64 || units(a.CB, a.QB) >= 700);
+    const int64_t waves = a.ok ? units(a.CB, a.QB) : 0;
+    int least = waves < 256 ? 192 : waves < 700 ? 320 : 80;
+    const bool whole = s.C_out % (32 * a.CB) == 0;
+    if (waves >= 700 && a.CB * a.QB == 8) least = waves > 1024 ? 96 : whole ? 16 : 32;
+    if (waves >= 700 && a.CB * a.QB == 4) least = waves > 2560 ? 80 : whole && a.QB == 4 ? 16 : 48;
+    a.split = a.ok && split_lds <= kPwLdsSplit && (s.C_in % 16 == 0 || s.C_in >= 128) && s.C_in >= least;
     if (a.split) a.lds = split_lds;
     return a;
 }
