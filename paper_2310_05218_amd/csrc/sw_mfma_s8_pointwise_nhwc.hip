@@ -169,9 +169,9 @@ PwS8Plan plan_pw_s8(const int8_t* x, const int8_t* w, const int8_t* y, const Con
     // a last channel group that is half empty, over many channels: its filters' way into LDS is most of a small launch
     // (640 -> 160 at 25 x 25, 6 images: 7.1 us in the window kernel, 7.6 here)
     if (s.C_in > 256 && s.C_out % 64 != 0 && s.C_out % 64 <= 32) return a;
-    // ... nor over channels in whole groups of 128, which the window kernel steps through without a rest (us, window kernel / this one:
-    // 128 -> 208, 3196 pixels 5.4 / 5.9, 128 -> 528, 312 pixels 5.0 / 5.5, 640 -> 432, 1056 pixels 7.2 / 8.0; 256 and 512 channels: no slower)
-    if (s.C_in % 128 == 0 && (s.C_in < 256 || s.C_in > 512) && s.C_out > 64 && s.C_out % 64 != 0) return a;
+    // ... nor over 128 channels, all of which the window kernel holds as well, in launches that CB = 4 does not fill (us, window kernel /
+    // this one: 128 -> 208, 3136 pixels 5.4 / 5.8, 25088 pixels 10.8 / 10.1, 128 -> 528, 312 pixels 5.0 / 5.5, 25088 pixels 19.0 / 16.8)
+    if (s.C_in == 128 && s.C_out > 64 && s.C_out % 64 != 0 && (px + 127) / 128 * ((s.C_out + 127) / 128) < 192) return a;
     const int pitch = s.C_in + 16;
     for (int CB : {4, 2}) {
         const int64_t groups = (s.C_out + 32 * CB - 1) / (32 * CB);
