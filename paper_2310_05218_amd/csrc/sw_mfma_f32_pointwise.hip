@@ -219,7 +219,7 @@ __global__ __launch_bounds__(256, 2) void mfma_f32_pointwise_kernel(const float*
 // of K = 16 take 0.375 of the fp32 instruction's time).  A K step is 16 channels, 8 kk + j for element j of lane half kk: a lane
 // splits the eight values it loaded for one of its pixels, between the matrix instructions of the pixel before.  The filters
 // (zeros up to the next 16 channels) are split into LDS once, before the first tile: [step][h, m, l][lane half][output channel]
-// of 16 bytes.  Both kernels report one name: block and pixel counts are chosen the same way for both.
+// of 16 bytes.  Block and pixel counts are chosen as for the kernel above.
 // Measured (us per launch, fp32 matrix instructions -> split): 32 x 256 x 56 x 56 -> 64 48.6 -> 37.2, 64 -> 256 53.5 -> 47.1,
 // 256 -> 256 at 28 x 28 44.5 -> 33, 512 -> 512 at 14 x 14 42.5 -> 37, 24 x 136 x 58 x 58 -> 16 26.0 -> 20.5; error against
 // 64 bits 2.9e-7 -> 2.4e-7.  128 MB are 23 us at the rate of a large copy; the products are 13 us, one wavefront per SIMD.
@@ -543,7 +543,7 @@ hipError_t launch_pw(const float* x, const float* w, float* y, const Conv2dShape
     const int cap = (256 * per_cu + gy - 1) / gy;
     if (gx > cap) gx = cap;
     if (a.split) {
-        SW_NOTED_LAUNCH(note_kernel("mfma_f32_pointwise_kernel", CB, QB), (mfma_f32_pointwise_split_kernel<CB, QB, NB>),
+        SW_NOTED_LAUNCH(note_kernel("mfma_f32_pointwise_split_kernel", CB, QB), (mfma_f32_pointwise_split_kernel<CB, QB, NB>),
                         dim3((unsigned)gx, (unsigned)gy), dim3(256), a.lds, st, x, w, y, P);
         return hipGetLastError();
     }

@@ -31,11 +31,11 @@ CASES = [
     (120, 16, 128, 15, 14, "mfma_f32_pointwise_kernel<2,2>"),
     (3, 16, 7, 9, 10, "mfma_f32_pointwise_kernel<1,2>"),
     # more input channels than two channel blocks' filters fit beside: one block per wavefront
-    (4, 600, 512, 40, 40, "mfma_f32_pointwise_kernel<1,4>"),
-    (32, 512, 512, 14, 14, "mfma_f32_pointwise_kernel<1,4>"),
+    (4, 600, 512, 40, 40, "mfma_f32_pointwise_split_kernel<1,4>"),
+    (32, 512, 512, 14, 14, "mfma_f32_pointwise_split_kernel<1,4>"),
     # one full-size image of a bottleneck layer
-    (1, 256, 64, 56, 56, "mfma_f32_pointwise_kernel<1,2>"),
-    (8, 256, 64, 56, 56, "mfma_f32_pointwise_kernel<1,2>"),
+    (1, 256, 64, 56, 56, "mfma_f32_pointwise_split_kernel<1,2>"),
+    (8, 256, 64, 56, 56, "mfma_f32_pointwise_split_kernel<1,2>"),
 ]
 
 
@@ -63,7 +63,7 @@ def test_pointwise_bias_relu(oracle, case):
     b = inputs.normal_f32((Co,), inputs.seed_for(7, 7))
     y_ref, d = oracle.conv2d_bias_relu(x, w, b, 1, 0, relu)
     y = sw.sw_conv2d_bias_relu(dev(x), dev(w), dev(b), 1, 0, relu)
-    assert sw.sw_last_kernel().startswith("mfma_f32_pointwise_kernel")
+    assert sw.sw_last_kernel().startswith("mfma_f32_pointwise_split_kernel" if Ci == 64 else "mfma_f32_pointwise_kernel")
     assert_f32_parity(y.cpu().numpy(), y_ref, d, f"pointwise bias/relu {case}")
 
 
@@ -81,5 +81,5 @@ def test_pointwise_fallbacks(oracle, case):
     xv = xd[shift:shift + x.size].view(x.shape)       # shift = 1: four bytes off the 16-byte grid
     xv.copy_(dev(x))
     y = sw.sw_conv2d(xv, dev(w), stride, pad)
-    assert not sw.sw_last_kernel().startswith("mfma_f32_pointwise_kernel")
+    assert not sw.sw_last_kernel().startswith("mfma_f32_pointwise")
     assert_f32_parity(y.cpu().numpy(), y_ref, d, f"1 x 1 outside the pointwise kernel {case}")

@@ -28,7 +28,8 @@ CASES = [
     (3, 53, 77, 23, 41, 3, 3, 2, 1, 1, "mfma_f32_split_kernel<21,1,1>"),           # five of sixteen channels in the last chunk, stride 2
     (1, 57, 33, 12, 12, 3, 3, 1, 0, 1, "mfma_f32_split_kernel<41,1,3>"),           # nine of sixteen: the second octet holds one channel
     (45, 48, 40, 7, 7, 3, 3, 1, 1, 1, "mfma_f32_split_kernel<41,1,4>"),            # row tiles of small images, the last one short
-    (4, 48, 64, 6, 6, 3, 3, 1, 1, 1, "mfma_f32_split_kernel<"),            # several whole images per tile where the planner takes them
+    (4, 48, 64, 6, 6, 3, 3, 1, 1, 1, "mfma_f32_split_kernel<41,1,2>"),             # row tiles of small images
+    (65, 48, 128, 6, 6, 3, 3, 1, 1, 1, "mfma_f32_split_kernel<21,2,6>"),           # two whole images per tile, the last one single
     (12, 48, 64, 56, 56, 3, 3, 1, 1, 1, "mfma_f32_split_kernel<12,1,6>"),          # large windows
     (12, 48, 96, 56, 56, 3, 3, 1, 1, 1, "mfma_f32_split_kernel<11,1,4>"),          # more tiles than workgroups
     (1, 48, 40, 30, 31, 3, 3, 1, 2, 2, "mfma_f32_split_kernel<21,1,1>"),           # dilation 2
@@ -170,14 +171,18 @@ def test_few_channels_kernel_special_values(torch, sw, value, where):
         assert np.all(np.abs(y[ok] - ref[ok]) <= 2e-5 * np.abs(ref[ok]))
 
 
-# N, C_in, C_out, H, W: 1 x 1 layers whose operands are split, one per (channel blocks, pixels per lane) and remainder
-POINTWISE_CASES = [(2, 64, 100, 28, 28), (32, 48, 64, 56, 56), (32, 152, 40, 30, 32), (30, 64, 128, 33, 34), (1, 136, 7, 9, 10),
-                   (8, 256, 64, 40, 40), (3, 384, 33, 12, 12), (40, 512, 512, 8, 8)]
+# N, C_in, C_out, H, W: 1 x 1 layers, one per (channel blocks, pixels per lane) and remainder
+POINTWISE_CASES = [(2, 64, 100, 28, 28, "mfma_f32_pointwise_kernel<1,2>"), (2, 200, 100, 28, 28, "mfma_f32_pointwise_split_kernel<1,2>"),
+                   (32, 48, 64, 56, 56, "mfma_f32_pointwise_split_kernel<2,4>"), (16, 32, 256, 28, 28, "mfma_f32_pointwise_split_kernel<1,4>"),
+                   (32, 152, 40, 30, 32, "mfma_f32_pointwise_split_kernel<1,2>"), (30, 64, 128, 33, 34, "mfma_f32_pointwise_split_kernel<2,2>"),
+                   (1, 136, 7, 9, 10, "mfma_f32_pointwise_kernel<1,2>"), (1, 200, 7, 9, 10, "mfma_f32_pointwise_split_kernel<1,2>"),
+                   (8, 256, 64, 40, 40, "mfma_f32_pointwise_kernel<1,2>"), (3, 384, 33, 12, 12, "mfma_f32_pointwise_split_kernel<1,2>"),
+                   (40, 512, 512, 8, 8, "mfma_f32_pointwise_split_kernel<1,2>")]
 
 
-@pytest.mark.parametrize("case", POINTWISE_CASES, ids=lambda c: "x".join(map(str, c)))
+@pytest.mark.parametrize("case", POINTWISE_CASES, ids=lambda c: "x".join(map(str, c[:5])))
 def test_split_pointwise(torch, sw, oracle, case):
-    N, Ci, Co, H, W = case
+    N, Ci, Co, H, W, kernel = case
     x = inputs.normal_f32((N, Ci, H, W), 5700 + Ci)
     w = inputs.normal_f32((Co, Ci, 1, 1), 5800 + Co, (2.0 / Ci) ** 0.5)
     b = inputs.normal_f32((Co,), 5900, 0.5)
@@ -185,7 +190,7 @@ def test_split_pointwise(torch, sw, oracle, case):
     y_ref, d = oracle.conv2d(x, w, 1, 0)
     buf, out, front, n, guard = guarded_empty(torch, y_ref.shape, torch.float32)
     sw.sw_conv2d(xd, wd, 1, 0, out=out)
-    assert sw.sw_last_kernel().startswith("mfma_f32_pointwise_kernel"), sw.sw_last_kernel()
+    assert sw.sw_last_kernel() == kernel
     assert_f32_parity(out.cpu().numpy(), y_ref, d, str(case))
     assert_guards_intact(buf, front, n, guard)
     y = sw.sw_conv2d_bias_relu(xd, wd, torch.from_numpy(b).cuda(), 1, 0, True)
@@ -197,8 +202,8 @@ def test_split_pointwise(torch, sw, oracle, case):
 @pytest.mark.parametrize("where", ["x", "w"])
 def test_split_pointwise_special_values(torch, sw, value, where):
     rng = np.random.default_rng(9)
-    x = rng.uniform(0.5, 1.0, (1, 136, 9, 10)).astype(np.float32)
-    w = rng.uniform(0.001, 0.002, (40, 136, 1, 1)).astype(np.float32)
+    x = rng.uniform(0.5, 1.0, (1, 200, 9, 10)).astype(np.float32)
+    w = rng.uniform(0.001, 0.002, (40, 200, 1, 1)).astype(np.float32)
     if value < 1e-30:
         (x if where == "x" else w)[:] = 0.0
         (w if where == "x" else x)[:] *= np.float32(2.0 ** 100)
@@ -207,7 +212,7 @@ def test_split_pointwise_special_values(torch, sw, value, where):
         x *= 0.125
     (x if where == "x" else w).flat[7777 if where == "x" else 700] = value
     y = sw.sw_conv2d(torch.from_numpy(x).cuda(), torch.from_numpy(w).cuda(), 1, 0).cpu().numpy()
-    assert sw.sw_last_kernel().startswith("mfma_f32_pointwise_kernel")
+    assert sw.sw_last_kernel().startswith("mfma_f32_pointwise_split_kernel")
     ref = torch.nn.functional.conv2d(torch.from_numpy(x).double(), torch.from_numpy(w).double()).numpy()
     with np.errstate(all="ignore"):
         _same_but_finite(y, ref.astype(np.float32) if not np.isfinite(value) else ref, f"{value} in {where}")
@@ -225,10 +230,10 @@ LAUNCHES = [
     (40, 3, 64, 56, 56, 7, 2, 3, "mfma_f32_stem_kernel<11,"),
     (64, 5, 48, 56, 56, 3, 2, 1, "mfma_f32_stem_kernel<8,"),
     (64, 2, 96, 56, 56, 5, 2, 2, "mfma_f32_stem_kernel<5,"),
-    (32, 64, 64, 56, 56, 1, 1, 0, "mfma_f32_pointwise_kernel<2,4>"),
-    (32, 128, 128, 28, 28, 1, 1, 0, "mfma_f32_pointwise_kernel<1,4>"),
-    (40, 64, 128, 33, 34, 1, 1, 0, "mfma_f32_pointwise_kernel<2,2>"),
-    (2, 136, 40, 9, 10, 1, 1, 0, "mfma_f32_pointwise_kernel<1,2>"),
+    (32, 64, 64, 56, 56, 1, 1, 0, "mfma_f32_pointwise_split_kernel<2,4>"),
+    (32, 128, 128, 28, 28, 1, 1, 0, "mfma_f32_pointwise_split_kernel<1,4>"),
+    (40, 64, 128, 33, 34, 1, 1, 0, "mfma_f32_pointwise_split_kernel<2,2>"),
+    (2, 200, 40, 9, 10, 1, 1, 0, "mfma_f32_pointwise_split_kernel<1,2>"),
 ]
 launches = pytest.mark.parametrize("case", LAUNCHES, ids=lambda c: "x".join(map(str, c[:8])))
 
