@@ -494,7 +494,8 @@ PwPlan plan_pointwise(const Conv2dShape& s, const float* x, const float* w, cons
         a.ok = true;
         if (units(v[0], v[1]) >= 700) break;
     }
-    if (a.ok) a.lds = (size_t)a.CB * 32 * (s.C_in + 4) * sizeof(float);
+    if (!a.ok) return a;                // (odd planes, filters beyond LDS)
+    a.lds = (size_t)a.CB * 32 * (s.C_in + 4) * sizeof(float);
     // Split operands where their filters fit LDS, but not where the last, half empty step of 16 channels is a large part of few
     // (8 -> 32 at 256 x 256, 5 images: 15.4 us against 25.1; 72 -> 248 at 66 x 65, 7 images: 20.7 against 21.8), and from `least`
     // channels up: few channels leave little to multiply per value split and stored, and <2,4> has half the wavefronts per SIMD of the
@@ -507,12 +508,12 @@ PwPlan plan_pointwise(const Conv2dShape& s, const float* x, const float* w, cons
     //   32 -> 187 at 84 x 3, 63 images 9.7 / 10.9, 48 channels 1.12
     //   <1,2>: 64 -> 61, 24534 pixels 8.2 / 9.4, 80 channels 1.00 to 1.04
     const size_t steps = (s.C_in + 15) / 16, split_lds = steps * 96 * (a.CB * 32 + 1);
-    const int64_t waves = a.ok ? units(a.CB, a.QB) : 0;
+    const int64_t waves = units(a.CB, a.QB);
     int least = waves < 256 ? 192 : waves < 700 ? 320 : 80;
     const bool whole = s.C_out % (32 * a.CB) == 0;
     if (waves >= 700 && a.CB * a.QB == 8) least = waves > 1024 ? 96 : whole ? 16 : 32;
     if (waves >= 700 && a.CB * a.QB == 4) least = waves > 2560 ? 80 : whole && a.QB == 4 ? 16 : 48;
-    a.split = a.ok && split_lds <= kPwLdsSplit && (s.C_in % 16 == 0 || s.C_in >= 128) && s.C_in >= least;
+    a.split = split_lds <= kPwLdsSplit && (s.C_in % 16 == 0 || s.C_in >= 128) && s.C_in >= least;
     if (a.split) a.lds = split_lds;
     return a;
 }

@@ -70,3 +70,17 @@ def test_plans_of_tall_images_take_no_longer(name, s):
 ])
 def test_few_channels_kernel_takes_what_it_is_faster_at(C, R, S, stride, size, takes):
     assert split_supported("stem", shape(8, C, 64, size, size, R, S, stride, 0)) == takes
+
+
+def pointwise_supported(N, C_in, C_out, H, W, x=4096, w=4096, y=4096):
+    f = getattr(binding.lib(), "_ZN6swconv28mfma_f32_pointwise_supportedERKNS_11Conv2dShapeEPKfS4_S4_")
+    f.restype, f.argtypes = ctypes.c_bool, [ctypes.POINTER(Shape)] + [ctypes.c_void_p] * 3
+    return f(ctypes.byref(shape(N, C_in, C_out, H, W, 1, 1, 1, 0)), x, w, y)
+
+
+def test_pointwise_plan_refuses_what_no_variant_takes():
+    """Odd planes, pointers off the 8-byte loads and filters beyond LDS leave no variant (and no divisor for what follows)."""
+    assert pointwise_supported(32, 64, 256, 56, 56)
+    assert not pointwise_supported(32, 512, 512, 7, 7)
+    assert not pointwise_supported(1, 64, 64, 8, 8, x=4100) and not pointwise_supported(1, 64, 64, 8, 8, y=4100)
+    assert not pointwise_supported(1, 2048, 64, 8, 8)
