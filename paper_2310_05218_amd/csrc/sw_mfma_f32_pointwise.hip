@@ -23,6 +23,8 @@
 // Measured on 32 x 256 x 56 x 56 -> 64 (784 tiles of 128 pixels, one per wavefront): filters in LDS 3.5 us after the
 // start, 33.8 us in the loop (65536 cycles of matrix instructions at the 1.94 GHz the chip holds under them: the loop
 // runs at the rate of the matrix pipe), 3.8 us of stores; 46 us per launch, where the window kernels take 71.
+#include <algorithm>
+
 #include "sw_f32_split.h"
 #include "swconv_internal.h"
 
@@ -498,21 +500,26 @@ PwPlan plan_pointwise(const Conv2dShape& s, const float* x, const float* w, cons
     a.lds = (size_t)a.CB * 32 * (s.C_in + 4) * sizeof(float);
     // Split operands where their filters fit LDS, but not where the last, half empty step of 16 channels is a large part of few
     // (8 -> 32 at 256 x 256, 5 images: 15.4 us against 25.1; 72 -> 248 at 66 x 65, 7 images: 20.7 against 21.8), and from `least`
-    // channels up: few channels leave little to multiply per value split and stored, and <2,4> has half the wavefronts per SIMD of the
-    // fp32 kernel, which shows where there are more tiles than those.  us, fp32 instructions / split:
+    // channels up: few channels leave little to multiply per value split and stored.  Where <2,4> has more tiles than the 1024
+    // wavefronts that run at once it needs twice the rounds of the fp32 kernel, which has 2048; from two rounds of that up it makes
+    // up for them.  A block of channels that is not whole is stored value by value.  us, fp32 instructions / split:
     //   fewer than 256 wavefronts: 64 -> 24, 1560 pixels 6.7 / 7.8, 152 -> 25, 858 pixels 9.8 / 10.8, 200 -> 256 at 14 x 14 12.4 / 11.9
     //   fewer than 700: 200 -> 16, 40000 pixels 12.1 / 12.6, 384 -> 384 at 14 x 14, 32 images 29.7 / 28.4
-    //   <2,4>: 64 -> 64 at 56 x 56, 32 images 19.9 / 14.9, 64 images 0.88 to 0.93 of the fp32 kernel's rate, 96 channels 1.03 to 1.07
-    //   <2,4>, 16 -> 64 at 56 x 56, 32 images 12.5 / 10.9, -> 32 12.4 / 13.9 (a block of channels that is not whole is stored value by value)
-    //   <2,2>: 64 channels, 1124 wavefronts 1.13, 4488 wavefronts 0.95, 80 channels 1.05;  <1,4>: 32 -> 256 at 28 x 28, 16 images 9.8 / 8.1,
-    //   32 -> 187 at 84 x 3, 63 images 9.7 / 10.9, 48 channels 1.12
-    //   <1,2>: 64 -> 61, 24534 pixels 8.2 / 9.4, 80 channels 1.00 to 1.04
+    //   <2,4>, up to 1024: 16 -> 64 at 56 x 56, 32 images 12.7 / 10.9, -> 24 9.1 / 10.5, 32 -> 24 11.1 / 11.0, 64 -> 64 19.9 / 14.9
+    //   <2,4>, up to 2048: 48 to 80 channels 0.97 to 1.27 of the fp32 kernel's time, 96 channels 0.92 to 1.06
+    //   <2,4>, beyond: 64 -> 256 at 56 x 56, 32 images 51.6 / 45.2, whole blocks of 32 channels 0.81 to 1.08, others 1.00 to 1.07, of
+    //   48 0.73 to 1.00
+    //   <2,2>: 32 channels up to 1536 wavefronts 0.86 to 1.08, 48 up to 2560 0.87 to 1.08, 64 up to 3584 0.85 to 1.11, beyond 0.95 to 1.17
+    //   and 80 channels 0.80 to 1.03
+    //   <1,4>: 32 -> 256 at 28 x 28, 16 images 9.8 / 8.1, 32 -> 187 at 84 x 3, 63 images 9.7 / 10.9, 48 channels 1.12
+    //   <1,2>: 64 -> 61, 24534 pixels 8.2 / 9.4, 80 channels 0.99 to 1.05
     const size_t steps = (s.C_in + 15) / 16, split_lds = steps * 96 * (a.CB * 32 + 1);
     const int64_t waves = units(a.CB, a.QB);
     int least = waves < 256 ? 192 : waves < 700 ? 320 : 80;
     const bool whole = s.C_out % (32 * a.CB) == 0;
-    if (waves >= 700 && a.CB * a.QB == 8) least = waves > 1024 ? 96 : whole ? 16 : 32;
-    if (waves >= 700 && a.CB * a.QB == 4) least = waves > 2560 ? 80 : whole && a.QB == 4 ? 16 : 48;
+    if (waves >= 700 && a.CB * a.QB == 8) least = waves > 2048 ? (whole ? 32 : 48) : waves > 1024 ? 96 : whole ? 16 : 32;
+    if (waves >= 700 && a.CB == 1 && a.QB == 4) least = waves > 2560 ? 80 : whole ? 16 : 48;
+    if (waves >= 700 && a.CB == 2 && a.QB == 2) least = (int)std::min<int64_t>(80, 32 + 16 * (std::max<int64_t>(0, waves - 512) / 1024));
     a.split = split_lds <= kPwLdsSplit && (s.C_in % 16 == 0 || s.C_in >= 128) && s.C_in >= least;
     if (a.split) a.lds = split_lds;
     return a;

@@ -22,7 +22,7 @@ CASES = [
     # several tiles per wavefront (more than 2048 tiles): 1, 3 and 6 channel groups
     (5, 8, 32, 256, 256, "mfma_f32_pointwise_kernel<2,4>"),
     (5, 24, 40, 256, 256, "mfma_f32_pointwise_kernel<2,4>"),
-    (3, 48, 64, 300, 300, "mfma_f32_pointwise_kernel<2,4>"),
+    (3, 48, 64, 300, 300, "mfma_f32_pointwise_split_kernel<2,4>"),
     # few tiles: the smallest variant; 4 and 5 channel groups, partial channel blocks
     (2, 32, 100, 28, 28, "mfma_f32_pointwise_kernel<1,2>"),
     (2, 40, 64, 14, 14, "mfma_f32_pointwise_kernel<1,2>"),

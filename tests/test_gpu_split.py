@@ -177,7 +177,9 @@ POINTWISE_CASES = [(2, 64, 100, 28, 28, "mfma_f32_pointwise_kernel<1,2>"), (2, 2
                    (32, 152, 40, 30, 32, "mfma_f32_pointwise_split_kernel<1,2>"), (30, 64, 128, 33, 34, "mfma_f32_pointwise_split_kernel<2,2>"),
                    (1, 136, 7, 9, 10, "mfma_f32_pointwise_kernel<1,2>"), (1, 200, 7, 9, 10, "mfma_f32_pointwise_split_kernel<1,2>"),
                    (8, 256, 64, 40, 40, "mfma_f32_pointwise_kernel<1,2>"), (3, 384, 33, 12, 12, "mfma_f32_pointwise_split_kernel<1,2>"),
-                   (40, 512, 512, 8, 8, "mfma_f32_pointwise_split_kernel<1,2>")]
+                   (40, 512, 512, 8, 8, "mfma_f32_pointwise_split_kernel<1,2>"),
+                   # more tiles of <2,4> than run at once, and more than two rounds of them
+                   (16, 64, 192, 56, 56, "mfma_f32_pointwise_kernel<2,4>"), (22, 64, 256, 56, 56, "mfma_f32_pointwise_split_kernel<2,4>")]
 
 
 @pytest.mark.parametrize("case", POINTWISE_CASES, ids=lambda c: "x".join(map(str, c[:5])))
