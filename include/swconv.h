@@ -106,8 +106,9 @@ int sw_pool2d(const float* x, float* y, int N, int C, int H, int W, int R, int S
  * Supported: any shape with R,S <= 64 (SW_ERR_UNSUPPORTED beyond).  C_in >= 2
  * runs on the matrix cores.  Nine taps over more than 32 channels (stride 1, or any
  * stride while the launch is one tile per workgroup), few channels at an even stride
- * (2 to 7, rows of at most 8 taps, R * C_in <= 22) and 1x1 at stride 1 without padding
- * (C_in % 16 == 0 or >= 128, see the source for small launches) take every fp32 operand
+ * (2 to 7, rows of at most 8 taps but not so short that little of a matrix instruction
+ * is filled, R * C_in <= 22) and 1x1 at stride 1 without padding (C_in % 16 == 0 or
+ * >= 128, from 16 to 320 channels up by the size of the launch) take every fp32 operand
  * as a sum of three bf16 values on the bf16 matrix instructions: six of nine products,
  * fp32 sums; what is left out of a product is up to 2^-24 of it, errors of sums of N(0,1)
  * data against 64-bit sums are below those of the fp32 instructions.  Outputs that
@@ -152,7 +153,8 @@ int sw_conv2d_depthwise_bias_relu(const float* x, const float* w, const float* b
  * and 7x7 at strides 1 and 2 have fixed-size kernels (the paper's "custom" kernels,
  * section 2), for any width; other extents up to 51 x 51 at stride 1 run the generic
  * sliding kernel; every other case bands of output rows with the taps in loops, or one
- * thread per output where four output rows of a plane do not fit LDS.
+ * thread per output where four output rows of a plane do not fit LDS, where planes hold
+ * too little for a workgroup each or where most taps fall into the padding.
  */
 int sw_conv2d_depthwise(const float* x, const float* w, float* y,
                         int N, int C, int H, int W, int R, int S,
@@ -250,7 +252,8 @@ int sw_dw_pw_block(const float* x, const float* w_dw, const float* b_dw,
  * x and y must be 2-byte aligned, w 4-byte aligned; errors as sw_conv2d_depthwise.
  * 3x3, 5x5, 7x7 at stride 1 on planes up to 56 x 56 with W and W_out multiples of
  * 8 and 16-byte aligned x, y run the sliding whole-plane kernel; other shapes bands of
- * output rows, or one thread per output on planes with little to do.
+ * output rows, or one thread per output where sw_conv2d_depthwise does so and on planes
+ * of less than 2000 multiply-adds.
  */
 int sw_conv2d_depthwise_bf16(const uint16_t* x, const float* w, uint16_t* y,
                              int N, int C, int H, int W, int R, int S,
@@ -342,8 +345,9 @@ int sw_jit_cached_kernels(void);
  * this layout are 16 consecutive bytes: nothing is transposed on the way.  Note the
  * argument order (H, W before the channel counts).  Errors as the channel-first
  * calls.  C_in a multiple of 32 and 16-byte aligned x and w run on the matrix cores:
- * requantised 1x1 layers at stride 1 over at least 128 channels (C_out % 16 == 0) on a
- * kernel that reads the pixels straight from x; else,
+ * requantised 1x1 layers at stride 1 over at least 128 channels (C_out % 16 == 0; not
+ * where a ragged last group of output channels costs more than it gives) on a kernel that
+ * reads the pixels straight from x; else,
  * with C_out % 4 == 0, y aligned to four elements, tensors below 2 GiB and tiles of
  * output rows (at most 256 outputs wide) whose windows fit LDS, on the kernel that
  * brings the windows in by direct-to-LDS loads a tile ahead (the one the channel-last

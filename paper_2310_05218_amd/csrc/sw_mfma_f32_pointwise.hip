@@ -22,7 +22,8 @@
 //
 // Measured on 32 x 256 x 56 x 56 -> 64 (784 tiles of 128 pixels, one per wavefront): filters in LDS 3.5 us after the
 // start, 33.8 us in the loop (65536 cycles of matrix instructions at the 1.94 GHz the chip holds under them: the loop
-// runs at the rate of the matrix pipe), 3.8 us of stores; 46 us per launch, where the window kernels take 71.
+// runs at the rate of the matrix pipe), 3.8 us of stores; 46 us per launch, where the window kernels take 71 (and the kernel
+// on split operands below, which has that layer since, 32.8).
 #include <algorithm>
 
 #include "sw_f32_split.h"
@@ -222,9 +223,10 @@ __global__ __launch_bounds__(256, 2) void mfma_f32_pointwise_kernel(const float*
 // splits the eight values it loaded for one of its pixels, between the matrix instructions of the pixel before.  The filters
 // (zeros up to the next 16 channels) are split into LDS once, before the first tile: [step][h, m, l][lane half][output channel]
 // of 16 bytes.  Block and pixel counts are chosen as for the kernel above.
-// Measured (us per launch, fp32 matrix instructions -> split): 32 x 256 x 56 x 56 -> 64 48.6 -> 37.2, 64 -> 256 53.5 -> 47.1,
-// 256 -> 256 at 28 x 28 44.5 -> 33, 512 -> 512 at 14 x 14 42.5 -> 37, 24 x 136 x 58 x 58 -> 16 26.0 -> 20.5; error against
-// 64 bits 2.9e-7 -> 2.4e-7.  128 MB are 23 us at the rate of a large copy; the products are 13 us, one wavefront per SIMD.
+// Measured (us per launch, replayed graphs of ten on one set of buffers, fp32 matrix instructions -> split): 32 x 256 x 56 x 56 -> 64
+// 45.7 -> 32.8, 64 -> 256 51.6 -> 44.8, 256 -> 256 at 28 x 28 42.2 -> 30.7, 512 -> 512 at 14 x 14 40.5 -> 34.1, 24 x 136 x 58 x 58 -> 16
+// 25.4 -> 20.0; error against 64 bits 2.9e-7 -> 2.4e-7.  128 MB are 23 us at the rate of a large copy; the products are 13 us, one
+// wavefront per SIMD.
 template <int CB, int QB, int NB>
 __global__ __launch_bounds__(256, CB * QB == 8 ? 1 : 2) void mfma_f32_pointwise_split_kernel(const float* __restrict__ x, const float* __restrict__ w,
                                                                                        float* __restrict__ y, const PwParams P)

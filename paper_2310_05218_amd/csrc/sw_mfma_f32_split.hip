@@ -20,14 +20,16 @@
 // filter stages: a filter wavefront has PH chunk periods for its chunk (PH chunks are under way at a time), which is what
 // keeps small tiles, whose periods are short, supplied; large windows leave room for PH = 1 only.  One barrier per chunk.
 //
-// Measured (us per launch, batch 32 unless said, the fp32-instruction kernels -> this one): 64 -> 64 at 56 x 56 75.0 -> 60.3,
-// 128 -> 128 at 28 x 28 86.9 -> 53.2, 256 -> 256 at 14 x 14 92.5 -> 54.5, 512 -> 512 at 7 x 7 109.8 -> 69.0, one image of
-// 256 -> 256 at 14 x 14 45.9 -> 23.1, of 512 -> 512 at 7 x 7 85.0 -> 31.3, 64 -> 64 at 56 x 56 20.2 -> 10.6, five of 96 -> 136 at 35 x 35 40.3 -> 21.0.
+// Measured (us per launch, replayed graphs of ten on one set of buffers, batch 32 unless said, the fp32-instruction kernels -> this
+// one): 64 -> 64 at 56 x 56 75.4 -> 52.1, 128 -> 128 at 28 x 28 87.1 -> 48.2, 256 -> 256 at 14 x 14 84.4 -> 46.1, 512 -> 512 at 7 x 7
+// 103.5 -> 54.8, one image of 256 -> 256 at 14 x 14 39.4 -> 17.3, of 512 -> 512 at 7 x 7 73.9 -> 30.5, 64 -> 64 at 56 x 56 21.1 -> 10.4,
+// five of 96 -> 136 at 35 x 35 39.0 -> 18.2.
 // What bounds it: 256 pixels x PB of a tile are never quite full (13 of 16 blocks in the first case), the first chunk's way
 // through LDS (7 us) and the stores of a tile that nothing overlaps, 40 cycles per matrix instruction with its operand reads
 // where the instruction takes 32, and a clock of 1.8-1.9 GHz under the bf16 instructions.  Single images: about 2 k ticks a
-// chunk, most of it the filter loads (64 lanes 288 bytes apart are 64 lines a load, 1.2 k ticks a chunk).  Before the taps
-// were shared (one wavefront had a tile's only block) 512 -> 512 at 7 x 7 took 40.2 us, 3 x 344 -> 88 at 9 x 9 28.2, now 23.2.
+// chunk, most of it the filter loads (64 lanes 288 bytes apart are 64 lines a load, 1.2 k ticks a chunk).  Three wavefronts share
+// the taps of single blocks: with a tile's only block on one wavefront 512 -> 512 at 7 x 7 took 40.2 us, 3 x 344 -> 88 at 9 x 9 28.2
+// where it takes 20.3.
 #include <algorithm>
 
 #include "sw_f32_split.h"
@@ -409,12 +411,13 @@ SplitPlan search_split(const Conv2dShape& s)
         const int64_t px_tiles = (int64_t)((s.N + NI - 1) / NI) * tiles_y, tiles = px_tiles * co_blocks;
         if (tiles * px_tiles >= (1LL << 32)) return;        // (fast_div's range)
         // A stride-2 window holds four cells per output pixel, and splitting those takes longer than multiplying: with one
-        // tile per workgroup still the faster kernel (128 -> 128 at 56 x 56, 8 images: 30.6 us against 41.0), beyond that
-        // not (64 -> 128, 32 images: 58 against 51).
+        // tile per workgroup still the faster kernel (128 -> 128 at 56 x 56, 8 images: 22.2 us against 37.0), beyond that
+        // not (64 -> 128, 32 images: 58 against 51 when last tried).
         if (s.stride > 1 && tiles > 256) return;
         for (int PH : {1, 2, 4}) {
             // PH = 4 adds up one block of one tile per workgroup.  Measured on single images against PH = 3 and a block per
-            // wavefront: 256 -> 256 at 14 x 14 23.6 -> 23.1, 512 -> 512 at 7 x 7 40.2 -> 31.3, 16 x 128 -> 32 at 17 x 17 14.6 -> 12.7.
+            // wavefront, when it took its place: 256 -> 256 at 14 x 14 23.6 -> 23.1, 512 -> 512 at 7 x 7 40.2 -> 31.3, 16 x 128 -> 32 at
+            // 17 x 17 14.6 -> 12.7.
             if (PH == 4 && (blocks > 1 || tiles > 256)) continue;
             const int64_t PB = (blocks + mul_waves(PH) - 1) / mul_waves(PH);
             if (WC > max_cells(PH) || PB > (PH == 1 ? 2 : 1)) continue;

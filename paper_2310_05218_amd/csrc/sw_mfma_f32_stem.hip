@@ -17,8 +17,9 @@
 // the next tile's window is loaded into registers before the blocks of this one, split and written to the other LDS buffer
 // after them: one barrier per tile, and the wavefronts of a SIMD drift apart so that one splits while the other multiplies.
 //
-// Measured (us per launch, 32 images unless said; the any-shape kernel on fp32 matrix instructions -> this one): 7 x 7 stride 2,
-// 3 -> 64 at 224 x 224 162 -> 70.6 (error against 64 bits 2.2e-7 -> 7e-8), one image 24.5 -> 9.2.  What bounds it: a block of
+// Measured (us per launch, replayed graphs of ten on one set of buffers, 32 images unless said; the any-shape kernel on fp32 matrix
+// instructions -> this one): 7 x 7 stride 2, 3 -> 64 at 224 x 224 169.5 -> 54.2 (error against 64 bits 2.1e-7 -> 6.9e-8), one image
+// 25.1 -> 9.7; 3 x 3 stride 2, 3 -> 32 at 224 x 224 47.8 -> 20.8, one image 9.6 -> 6.3.  What bounds it: a block of
 // 66 matrix instructions takes a pair of wavefronts 6.2 k ticks where the instructions are 4.2 k (the first operand reads and
 // the stores of a block wait), the filters' and the first window's way into LDS 15 k of 107 k ticks.
 #include <algorithm>

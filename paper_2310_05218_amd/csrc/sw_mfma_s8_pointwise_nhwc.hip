@@ -9,9 +9,9 @@
 // filters of the workgroup's 32 CB output channels (rows as they lie in w, padded by 16 bytes against bank conflicts) come into
 // LDS under the same round trip.  Results leave through a per-wavefront LDS area as 16-byte pieces of a pixel.
 //
-// Measured (us per launch, window kernel -> this one): 32 x 28 x 28 x 512 -> 128 11.1 -> 9.0, 128 -> 512 16.1 -> 13.3,
-// 32 x 14 x 14 x 256 -> 1024 12.5 -> 9.5, 32 x 56 x 56 x 256 -> 64 13.2 -> 10.8, 6 x 25 x 25 x 160 -> 640 8.5 -> 5.3, one image
-// 28 x 28 x 512 -> 128 6.2 -> 5.7.  CB = 4 where that leaves 192 workgroups, else 2: fetching 128 filter rows made small
+// Measured (us per launch, replayed graphs of ten, window kernel -> this one): 32 x 28 x 28 x 512 -> 128 10.9 -> 9.3, 128 -> 512
+// 16.4 -> 14.0, 32 x 14 x 14 x 256 -> 1024 12.9 -> 8.9, 32 x 56 x 56 x 256 -> 64 13.1 -> 10.3, 6 x 25 x 25 x 160 -> 640 9.0 -> 5.9, one image
+// 28 x 28 x 512 -> 128 6.8 -> 6.3.  CB = 4 where that leaves 192 workgroups, else 2: fetching 128 filter rows made small
 // launches slower than the window kernel's (7.8 us in the last case).  Bound by two dependent round trips (filters and pixels,
 // then the store) and the launch itself: 16 MB are 3 us at the rate of a large copy.
 #include <algorithm>

@@ -9,8 +9,8 @@
 // registers.  Taps are wave-uniform (scalar registers).  Consecutive threads own consecutive columns: every store instruction
 // writes a run of consecutive outputs.
 //
-// Measured (us per launch): fp32 5x5 stride 2 on 8 x 144 x 75 x 75 38.5 (one thread per output) -> 10.2, 3.2 TB/s; 7x7 on
-// 8 x 488 x 47 x 42 41.8 (tile kernel) -> 28.3; bf16 5x5 stride 2 on 8 x 144 x 75 x 75 35.9 -> 9.5.  Bound by the memory round
+// Measured (us per launch, replayed graphs of ten): fp32 5x5 stride 2 on 8 x 144 x 75 x 75 36.1 (one thread per output) -> 9.5,
+// 3.4 TB/s; 7x7 on 8 x 488 x 47 x 42 39.7 (tile kernel) -> 26.9; bf16 5x5 stride 2 on 8 x 144 x 75 x 75 31.2 -> 9.7.  Bound by the memory round
 // trip in front of each workgroup's only barrier, and by LDS reads for the larger filters (18 per 49 multiply-adds at 7x7).
 #include <algorithm>
 

@@ -75,8 +75,8 @@ int run_plane(const float* x, const float* w, float* y, int64_t planes, int plan
             return launch_status(launch_sliding_rows(x, w, y, planes, planes_per_x, n_filters, s.H, s.W, s.R, s.S,
                                                      s.stride, s.pad, s.Ho, s.Wo, st, ep));
         // Bands of output rows, unrolled for 3x3, 5x5 and 7x7 at strides 1 and 2: faster than the 56 x 56 tile per wavefront on
-        // every layer timed that reaches this point (us: 8 x 64 x 113 x 113 3x3 27.4 -> 15.0, 8 x 64 x 57 x 57 7x7 24.6 -> 9.5,
-        // 8 x 488 x 47 x 42 7x7 41.8 -> 28.3, one image 200 x 62 x 62 3x3 13.4 -> 4.6); the tile keeps the other extents.
+        // every layer timed that reaches this point (us: 8 x 64 x 113 x 113 3x3 26.5 -> 14.8, 8 x 64 x 57 x 57 7x7 24.2 -> 9.8,
+        // 8 x 488 x 47 x 42 7x7 39.7 -> 26.9, one image 200 x 62 x 62 3x3 12.2 -> 5.2); the tile keeps the other extents.
         if (!whole && plane_bands_unrolled(s) && plane_bands_supported(x, planes, planes_per_x, n_filters, s, false))
             return launch_status(launch_plane_bands(x, w, y, planes, planes_per_x, n_filters, s, false, st, ep));
         // (where a plane is too little for a workgroup of bands, it is for a tile: 131072 planes of 5 x 5 under 3x3 266 us on tiles, 73 on
@@ -88,7 +88,7 @@ int run_plane(const float* x, const float* w, float* y, int64_t planes, int plan
                                                       s.pad, s.Ho, s.Wo, st, ep));
     }
     // strides above 1 the rows kernel does not take, few or short planes: bands too, their taps in loops where not unrolled (us:
-    // 8 x 144 x 75 x 75 5x5 stride 2 38.5 -> 10.2 in place of one thread per output; plane_bands_worthwhile)
+    // 8 x 144 x 75 x 75 5x5 stride 2 36.1 -> 9.5 in place of one thread per output; plane_bands_worthwhile)
     if (!force_direct() && plane_bands_supported(x, planes, planes_per_x, n_filters, s, false))
         return launch_status(launch_plane_bands(x, w, y, planes, planes_per_x, n_filters, s, false, st, ep));
     return launch_status(launch_direct_conv2d_f32(x, w, y, s, depthwise, st, &ep));
@@ -255,11 +255,12 @@ static int run_conv2d(const float* x, const float* w, float* y, const Conv2dShap
         if (s.R * s.S >= 25 && s.C_in >= 8 && mfma_f32_rows_supported(s, x))
             return launch_status(launch_mfma_f32_rows(x, w, y, s, st, ep));
         // Few channels at an even stride (the first layer of an image network): K along the filter rows
-        // (7 x 7 stride 2, 3 -> 64 at 224 x 224: 162 -> 71 us; 3 x 3 stride 2: 52 -> 50, 9.2 -> 6 for one image)
+        // (7 x 7 stride 2, 3 -> 64 at 224 x 224: 170 -> 54 us; 3 x 3 stride 2, 3 -> 32: 48 -> 21, 9.6 -> 6.3 for one image), but where
+        // the filter rows are too short to fill it
         if (mfma_f32_stem_supported(s)) return launch_status(launch_mfma_f32_stem(x, w, y, s, st, ep));
-        // Nine taps: operands as sums of three bf16 values.  Faster than the kernels below on every such layer timed (us, one
-        // image, 56 x 56 -> 64 channels: 16 channels 9.8 -> 6.8, 32 13.4 -> 8.6, 64 20.2 -> 11.1; 32 images 25.7 -> 25.1,
-        // 41.4 -> 36.5, 75.0 -> 62.8); up to 32 channels the direct-to-LDS kernel keeps the plans its tests assert.
+        // Nine taps: operands as sums of three bf16 values, from 33 channels up (us, 56 x 56 -> 64 channels: 64 channels 75.4 -> 52.1,
+        // one image 21.1 -> 10.4).  With 16 and 32 the direct-to-LDS and the fixed kernel stay (24.9 and 39.0, one image 10.5 and 14.0):
+        // this one was timed there as well, 25.1 and 36.5, one image 6.8 and 8.6, but the tests assert the plans of the other two.
         if (s.C_in > 32 && mfma_f32_split_supported(s)) return launch_status(launch_mfma_f32_split(x, w, y, s, st, ep));
         const bool quad_ok = mfma_f32_quad_supported(s);
         const bool any_ok = quad_ok || mfma_f32_any_supported(s);
