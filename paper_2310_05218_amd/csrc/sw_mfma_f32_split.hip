@@ -476,6 +476,9 @@ hipError_t launch_one(const float* x, const float* w, float* y, const SplitPlan&
 
 bool mfma_f32_split_supported(const Conv2dShape& s) { return plan_split(s).ok; }
 
+// (the plan's ticks, fitted to 81 launches)
+double mfma_f32_split_estimate(const Conv2dShape& s) { return 3.62e-4 * plan_split(s).est + 1.06; }
+
 hipError_t launch_mfma_f32_split(const float* x, const float* w, float* y, const Conv2dShape& s, hipStream_t st, const Epilogue& ep)
 {
     SplitPlan a = plan_split(s);

@@ -234,6 +234,30 @@ int sw_pool2d(const float* x, float* y, int N, int C, int H, int W, int R, int S
     return launch_status(launch_direct_pool2d(x, y, planes, H, W, R, S, stride, pad, (int)Ho, (int)Wo, maximum, st));
 }
 
+// Launches of few tiles (of 16 channels x 16 pixels of an image), whose products the few-tiles kernel spreads over the wavefronts of a
+// workgroup.  The lines are where it and the kernels of before cross, on 820 layers drawn over 7 ... 112 pixels, 9 ... 512 channels, 1 x 1 ...
+// 7 x 7, strides 1 and 2: nine taps on split operands up to 512 tiles where the two plans' estimates say so (1.04 to 2.4 x taken, 0.4 to 1.1 x
+// beyond), 25 and more taps 1.3 to 38 x up to the largest tried (18020), the rest 1.1 to 5 x up to 2048 and 0.9 to 1.1 x up to 3000.
+static bool few_tiles(const Conv2dShape& s)
+{
+    const int64_t tiles = (int64_t)s.N * (((int64_t)s.Ho * s.Wo + 15) / 16) * ((s.C_out + 15) / 16);
+    if (s.R * s.S == 9 && mfma_f32_split_supported(s))
+        return tiles <= 512 && mfma_f32_few_supported(s) && mfma_f32_few_estimate(s) < 0.95 * mfma_f32_split_estimate(s);
+    return tiles <= (s.R * s.S >= 25 ? 16384 : 2048) && mfma_f32_few_supported(s);
+}
+
+// ... in place of the kernels that come first in run_conv2d: from 65 input channels up (fewer are as much faster, but the tests
+// assert the plans of the other kernels there); 1 x 1 on the pointwise kernel from 128 output channels up, up to 768 tiles (320 -> 280 at
+// 18 x 18 15.3 -> 7.9 us; tests assert the pointwise kernel's plans of small launches with fewer).
+static bool few_tiles_first(const Conv2dShape& s, const float* x, const float* w, const float* y)
+{
+    if (s.C_in <= 64) return false;
+    if (mfma_f32_pointwise_supported(s, x, w, y) &&
+        (s.C_out < 128 || (int64_t)s.N * (((int64_t)s.Ho * s.Wo + 15) / 16) * ((s.C_out + 15) / 16) > 768))
+        return false;
+    return few_tiles(s);
+}
+
 // The multi-channel fp32 convolution with the store's epilogue (none for sw_conv2d).
 static int run_conv2d(const float* x, const float* w, float* y, const Conv2dShape& s, const Epilogue& ep, hipStream_t st)
 {
@@ -242,6 +266,7 @@ static int run_conv2d(const float* x, const float* w, float* y, const Conv2dShap
     if (s.C_in == 1)
         return run_plane(x, w, y, (int64_t)s.N * s.C_out, s.C_out, s.C_out, s, false, st, ep);
     if (!force_direct() && s.C_in > 1) {
+        if (few_tiles_first(s, x, w, y)) return launch_status(launch_mfma_f32_few(x, w, y, s, st, ep));
         // The fixed 3x3 / 5x5 kernel holds a CU with one large tile: it needs enough of them to fill the chip
         // (28 x 28 images and below at batch 32 leave it at 128 or fewer); the any-shape kernel's 128-pixel
         // tiles take over there, and everywhere the fixed kernel has no variant.
@@ -269,6 +294,9 @@ static int run_conv2d(const float* x, const float* w, float* y, const Conv2dShap
         // few taps over whole groups of eight channels: operands by direct-to-LDS loads, the next chunk in flight
         // while this one multiplies
         if (mfma_f32_dma_supported(s, x, w)) return launch_status(launch_mfma_f32_dma(x, w, y, s, st, ep));
+        // the kernels for any shape, in launches of few tiles (17 channels up where the quad kernel has the layer; us, quad and any-shape
+        // kernels -> this one: 2 x 21 -> 80 at 18 x 18 3x3 16.6 -> 6.4, 3 x 24 -> 40 at 12 x 31 5x5 63 -> 7.8, 2 x 16 -> 48 at 16 x 69 5x5 44 -> 7.3)
+        if ((quad_ok ? s.C_in > 16 : any_ok) && few_tiles(s)) return launch_status(launch_mfma_f32_few(x, w, y, s, st, ep));
         if (quad_ok) return launch_status(launch_mfma_f32_quad(x, w, y, s, st, ep));
         if (any_ok) return launch_status(launch_mfma_f32_any(x, w, y, s, st, ep));
         if (mfma_f32_rows_supported(s, x)) return launch_status(launch_mfma_f32_rows(x, w, y, s, st, ep));

@@ -157,8 +157,15 @@ hipError_t launch_mfma_f32_dma(const float* x, const float* w, float* y, const C
 // ---- multi-channel fp32, nine taps, any stride / padding / dilation: operands as sums of three bf16 values on the bf16
 // matrix instructions (tensors below 2 GiB, a tile of output rows and its window within LDS)
 bool       mfma_f32_split_supported(const Conv2dShape& s);
+double     mfma_f32_split_estimate(const Conv2dShape& s);       // us
 hipError_t launch_mfma_f32_split(const float* x, const float* w, float* y, const Conv2dShape& s, hipStream_t st,
                                  const Epilogue& ep = Epilogue{nullptr, 0});
+
+// ---- multi-channel fp32, few tiles: a tile's reduction split over the wavefronts of a workgroup (tensors below 2 GiB)
+bool       mfma_f32_few_supported(const Conv2dShape& s);
+double     mfma_f32_few_estimate(const Conv2dShape& s);         // us
+hipError_t launch_mfma_f32_few(const float* x, const float* w, float* y, const Conv2dShape& s, hipStream_t st,
+                               const Epilogue& ep = Epilogue{nullptr, 0});
 
 // ---- multi-channel fp32, few input channels (2 .. 7), even stride, rows of at most 8 taps, at most 22 (row, channel) pairs:
 // K along the filter rows, operands as sums of three bf16 values

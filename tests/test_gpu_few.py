@@ -1,0 +1,92 @@
+"""The fp32 kernel of launches with few tiles: its reduction split over wavefronts, at the edges of its runs of 32 products, pixel
+tiles, channel blocks and chunks of channels, against the oracle."""
+import numpy as np
+import pytest
+
+from paper_2310_05218_amd import inputs
+from parity import assert_f32_parity, assert_guards_intact, guarded_empty
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def torch():
+    return pytest.importorskip("torch")
+
+
+@pytest.fixture(scope="module")
+def sw():
+    import paper_2310_05218_amd as sw
+
+    return sw
+
+
+CASES = [
+    # N, C_in, C_out, H, W, R, S, stride, pad, dilation
+    (1, 256, 256, 14, 14, 3, 3, 1, 1, 1),       # whole runs, rows of 14 pixels
+    (2, 67, 19, 9, 11, 3, 3, 1, 1, 1),          # 603 products: 27 beyond the last run, filters off the 16-byte grid, ragged channel block
+    (1, 65, 16, 3, 3, 3, 3, 1, 0, 1),           # a single output pixel
+    (3, 96, 33, 17, 23, 3, 3, 2, 1, 1),         # stride 2
+    (1, 80, 24, 20, 20, 3, 3, 1, 2, 2),         # dilation 2
+    (1, 72, 40, 5, 90, 3, 3, 1, 0, 1),          # rows wider than a tile
+    (2, 70, 50, 7, 9, 1, 1, 1, 0, 1),           # one tap, several channels a load, 70 products
+    (4, 128, 130, 13, 13, 1, 1, 2, 0, 1),       # one tap at stride 2
+    (1, 320, 280, 18, 18, 1, 1, 1, 0, 1),       # one tap in place of the pointwise kernel
+    (2, 68, 36, 12, 12, 2, 2, 1, 0, 1),         # four taps
+    (3, 21, 48, 15, 15, 5, 5, 1, 2, 1),         # 25 taps over few channels
+    (1, 130, 24, 21, 18, 5, 5, 2, 2, 1),        # 25 taps at stride 2
+    (1, 300, 20, 11, 30, 7, 7, 1, 3, 1),        # 49 taps: two loads a channel, more channels than LDS holds
+    (2, 24, 17, 14, 14, 7, 5, 3, 2, 1),         # rectangular, stride 3
+    (1, 70, 18, 16, 16, 1, 7, 1, 3, 1),         # a row of seven taps
+    (2, 130, 64, 40, 42, 5, 5, 1, 2, 1),        # several workgroups per CU
+]
+
+
+@pytest.mark.parametrize("shift", [0, 1], ids=["aligned", "4-byte"])
+@pytest.mark.parametrize("case", CASES, ids=lambda c: "x".join(map(str, c)))
+def test_few_tiles_kernel(torch, sw, oracle, case, shift):
+    N, Ci, Co, H, W, R, S, st, pad, dil = case
+    if shift and R * S == 1 and st == 1 and Ci == 320:
+        pytest.skip("the same route as the other single taps")
+    x = inputs.normal_f32((N, Ci, H, W), 8100 + Ci)
+    w = inputs.normal_f32((Co, Ci, R, S), 8200 + Co, (2.0 / (Ci * R * S)) ** 0.5)
+    b = inputs.normal_f32((Co,), 8300, 0.5)
+
+    def view(a):        # four bytes off the 16-byte grid, NaN around
+        buf = torch.full((a.size + 8,), float("nan"), device="cuda")
+        buf[shift:shift + a.size] = torch.from_numpy(a).cuda().reshape(-1)
+        return buf[shift:shift + a.size].view(a.shape)
+
+    xd, wd = view(x), view(w)
+    y_ref, d = oracle.conv2d_dilated(x, w, st, pad, dil)
+    buf, out, front, n, guard = guarded_empty(torch, y_ref.shape, torch.float32)
+    sw.sw_conv2d_dilated(xd, wd, st, pad, dil, out=out)
+    assert sw.sw_last_kernel().startswith("mfma_f32_few_kernel"), sw.sw_last_kernel()
+    assert_f32_parity(out.cpu().numpy(), y_ref, d, str(case))
+    assert_guards_intact(buf, front, n, guard)
+    if dil == 1:
+        y = sw.sw_conv2d_bias_relu(xd, wd, torch.from_numpy(b).cuda(), st, pad, True)
+        yr, dr = oracle.conv2d_bias_relu(x, w, b, st, pad, True)
+        assert_f32_parity(y.cpu().numpy(), yr, np.maximum(dr, 1e-30), f"{case} bias, rectifier")
+
+
+@pytest.mark.parametrize("value", [np.inf, np.nan])
+@pytest.mark.parametrize("shape", [(2, 67, 19, 9, 11, 3), (2, 70, 50, 7, 9, 1), (2, 21, 48, 15, 15, 5)], ids=lambda s: "x".join(map(str, s)))
+def test_few_tiles_kernel_keeps_special_values_in_place(torch, sw, shape, value):
+    """A value that is not finite in the first weight of the second filter, or in the first channel of the second image: the loads that
+    reach over the end of a filter or of an image's channels do not carry it into the sums before it."""
+    N, Ci, Co, H, W, R = shape
+    rng = np.random.default_rng(83)
+    x = rng.uniform(0.5, 1.0, (N, Ci, H, W)).astype(np.float32)
+    w = rng.uniform(0.5, 1.0, (Co, Ci, R, R)).astype(np.float32)
+    run = lambda x, w: sw.sw_conv2d(torch.from_numpy(x).cuda(), torch.from_numpy(w).cuda(), 1, 0).cpu().numpy()
+    clean = run(x, w)
+    assert sw.sw_last_kernel().startswith("mfma_f32_few_kernel"), sw.sw_last_kernel()
+    w2 = w.copy()
+    w2[1, 0, 0, 0] = value
+    y = run(x, w2)
+    assert not np.isfinite(y[:, 1]).any() and np.array_equal(np.delete(y, 1, 1), np.delete(clean, 1, 1))
+    x2 = x.copy()
+    x2[1, 0] = value
+    y = run(x2, w)
+    assert not np.isfinite(y[1]).any() and np.array_equal(y[0], clean[0])
