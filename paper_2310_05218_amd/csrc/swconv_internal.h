@@ -284,6 +284,10 @@ hipError_t launch_conv2d_s8_packed(const int8_t* x, const int8_t* wp, int32_t* y
 bool       mfma_s8_band_supported(const int8_t* x, const int8_t* w, const Conv2dShape& s, bool raw_filters);
 hipError_t launch_mfma_s8_band(const int8_t* x, const int8_t* w, int32_t* y, int8_t* y8, const Requant* rq,
                                const Conv2dShape& s, bool raw_filters, hipStream_t st);
+// ---- int8 channel-first, one or nine taps over whole groups of 16 channels: window and filters byte-transposed on their way to the
+// matrix instructions, a tile's reduction split over wavefronts; rq == nullptr: int32 out (y), else int8 out (y8) (w 4-byte aligned)
+bool       mfma_s8_tiles_supported(const int8_t* w, bool requant, const Conv2dShape& s);
+hipError_t launch_mfma_s8_tiles(const int8_t* x, const int8_t* w, int32_t* y, int8_t* y8, const Requant* rq, const Conv2dShape& s, hipStream_t st);
 bool       mfma_s8_any_supported(const Conv2dShape& s);   // any extent, stride and channel count
 hipError_t launch_mfma_s8_any(const int8_t* x, const int8_t* w, int32_t* y, const Conv2dShape& s, hipStream_t st);
 
