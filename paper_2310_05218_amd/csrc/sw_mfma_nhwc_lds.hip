@@ -360,71 +360,74 @@ __global__ __launch_bounds__(512, 2) void mfma_nhwc_lds_kernel(const unsigned ch
         // 16-bit and requantised int8 results: four consecutive output channels of a lane are 4 OB bytes
         constexpr int OB = EK == kFmtS8Q ? 1 : 2;
         using Pack = std::conditional_t<EK == kFmtS8Q, int, intx2>;
-        auto pack = [&](int cb, int b, int q) __attribute__((always_inline)) {
-            if constexpr (EK == kFmtS8Q) {
-                // q = clamp(rne(scale * float(acc + bias)), relu ? 0 : -128, 127), every step in fp32 as the definition has it
-                const int c = cb * 32 + 8 * q + 4 * kq;
-                const intx4 qb = *reinterpret_cast<const intx4*>(smem + P.rq_off + 4 * c);
-                const floatx4 qs = *reinterpret_cast<const floatx4*>(smem + P.rq_off + 4 * (32 * CB + c));
-                const float lo_ = P.rq.relu ? 0.0f : -128.0f;
-                int r = 0;
+        // (the rectifier of int8 results is a branch around the epilogue, not a select in every result)
+        auto leave = [&](auto relu) __attribute__((always_inline)) {
+            auto pack = [&](int cb, int b, int q) __attribute__((always_inline)) {
+                if constexpr (EK == kFmtS8Q) {
+                    // q = clamp(rne(scale * float(acc + bias)), relu ? 0 : -128, 127), every step in fp32 as the definition has it
+                    const int c = cb * 32 + 8 * q + 4 * kq;
+                    const intx4 qb = *reinterpret_cast<const intx4*>(smem + P.rq_off + 4 * c);
+                    const floatx4 qs = *reinterpret_cast<const floatx4*>(smem + P.rq_off + 4 * (32 * CB + c));
+                    return requant_pack4<decltype(relu)::value>((int)acc[cb][b][4 * q] + qb[0], (int)acc[cb][b][4 * q + 1] + qb[1],
+                                                                (int)acc[cb][b][4 * q + 2] + qb[2], (int)acc[cb][b][4 * q + 3] + qb[3],
+                                                                qs[0], qs[1], qs[2], qs[3]);
+                } else {
+                    unsigned h[4];
 #pragma unroll
-                for (int j = 0; j < 4; ++j) {
-                    float f = rintf(__int2float_rn((int)acc[cb][b][4 * q + j] + qb[j]) * qs[j]);
-                    f = fminf(fmaxf(f, lo_), 127.0f);
-                    r |= ((int)f & 255) << (8 * j);
+                    for (int j = 0; j < 4; ++j) h[j] = finish(acc[cb][b][4 * q + j], cb, 4 * q + j);
+                    return intx2{(int)(h[0] | (h[1] << 16)), (int)(h[2] | (h[3] << 16))};
                 }
-                return r;
-            } else {
-                unsigned h[4];
+            };
+            if (P.out_off >= 0) {
+                // through LDS, so that a store instruction writes whole lines: the lane's 16 CB values go to
+                // [pixel][channel] rows of this wavefront's area (4 OB bytes at a time), and come back as 16-byte pieces with
+                // consecutive lanes on consecutive pieces of a pixel
+                constexpr int NC = 2 * CB * OB;                                 // 16-byte pieces of a pixel's channels
+                constexpr int OP = 32 * CB * OB + 16;                           // row pitch
+                unsigned char* lo = smem + P.out_off + wave * (32 * OP);
+                const int64_t tile_px0 = (int64_t)n0 * HoWo + row0 * P.Wo;
 #pragma unroll
-                for (int j = 0; j < 4; ++j) h[j] = finish(acc[cb][b][4 * q + j], cb, 4 * q + j);
-                return intx2{(int)(h[0] | (h[1] << 16)), (int)(h[2] | (h[3] << 16))};
+                for (int b = 0; b < PB; ++b) {
+                    if (32 * (4 * b + wave) >= valid_px) continue;              // (wave-uniform)
+#pragma unroll
+                    for (int cb = 0; cb < CB; ++cb)
+#pragma unroll
+                        for (int q = 0; q < 4; ++q) {
+                            const int col = cb * 32 + 8 * q + 4 * kq;
+                            *reinterpret_cast<Pack*>(lo + lj * OP + OB * col) = pack(cb, b, q);
+                        }
+                    asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+#pragma unroll
+                    for (int pass = 0; pass < NC / 2; ++pass) {
+                        const int px = lane / NC + (64 / NC) * pass, piece = lane % NC;
+                        const intx4 v = *reinterpret_cast<const intx4*>(lo + px * OP + 16 * piece);
+                        const int p = 32 * (4 * b + wave) + px;
+                        if (p < valid_px && co0 + (16 / OB) * piece < P.C_out)
+                            *reinterpret_cast<intx4*>(yb + ((tile_px0 + p) * P.C_out + co0) * OB + 16 * piece) = v;
+                    }
+                    asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");          // (the area is written again for the next block)
+                }
+                return;
             }
-        };
-        if (P.out_off >= 0) {
-            // through LDS, so that a store instruction writes whole lines: the lane's 16 CB values go to
-            // [pixel][channel] rows of this wavefront's area (4 OB bytes at a time), and come back as 16-byte pieces with
-            // consecutive lanes on consecutive pieces of a pixel
-            constexpr int NC = 2 * CB * OB;                                 // 16-byte pieces of a pixel's channels
-            constexpr int OP = 32 * CB * OB + 16;                           // row pitch
-            unsigned char* lo = smem + P.out_off + wave * (32 * OP);
-            const int64_t tile_px0 = (int64_t)n0 * HoWo + row0 * P.Wo;
 #pragma unroll
             for (int b = 0; b < PB; ++b) {
-                if (32 * (4 * b + wave) >= valid_px) continue;              // (wave-uniform)
+                if (pl[b] >= valid_px) continue;
+                const int i = fast_div(pl[b], P.by_thwo), rem = pl[b] - i * thwo;       // (pixel of image n0 + i, rows from row0)
+                unsigned char* yp = yb + ((int64_t)(n0 + i) * HoWo + row0 * P.Wo + rem) * P.C_out * OB;
 #pragma unroll
                 for (int cb = 0; cb < CB; ++cb)
 #pragma unroll
                     for (int q = 0; q < 4; ++q) {
-                        const int col = cb * 32 + 8 * q + 4 * kq;
-                        *reinterpret_cast<Pack*>(lo + lj * OP + OB * col) = pack(cb, b, q);
+                        const int co = co0 + cb * 32 + 8 * q + 4 * kq;
+                        if (co < P.C_out) *reinterpret_cast<Pack*>(yp + co * OB) = pack(cb, b, q);
                     }
-                asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
-#pragma unroll
-                for (int pass = 0; pass < NC / 2; ++pass) {
-                    const int px = lane / NC + (64 / NC) * pass, piece = lane % NC;
-                    const intx4 v = *reinterpret_cast<const intx4*>(lo + px * OP + 16 * piece);
-                    const int p = 32 * (4 * b + wave) + px;
-                    if (p < valid_px && co0 + (16 / OB) * piece < P.C_out)
-                        *reinterpret_cast<intx4*>(yb + ((tile_px0 + p) * P.C_out + co0) * OB + 16 * piece) = v;
-                }
-                asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");          // (the area is written again for the next block)
             }
-            continue;
-        }
-#pragma unroll
-        for (int b = 0; b < PB; ++b) {
-            if (pl[b] >= valid_px) continue;
-            const int i = fast_div(pl[b], P.by_thwo), rem = pl[b] - i * thwo;       // (pixel of image n0 + i, rows from row0)
-            unsigned char* yp = yb + ((int64_t)(n0 + i) * HoWo + row0 * P.Wo + rem) * P.C_out * OB;
-#pragma unroll
-            for (int cb = 0; cb < CB; ++cb)
-#pragma unroll
-                for (int q = 0; q < 4; ++q) {
-                    const int co = co0 + cb * 32 + 8 * q + 4 * kq;
-                    if (co < P.C_out) *reinterpret_cast<Pack*>(yp + co * OB) = pack(cb, b, q);
-                }
+        };
+        if constexpr (EK == kFmtS8Q) {
+            if (P.rq.relu) leave(std::true_type{});
+            else leave(std::false_type{});
+        } else {
+            leave(std::false_type{});
         }
     }
 }

@@ -7,15 +7,18 @@
 // of one lane of v_mfma_i32_32x32x32_i8, so a wavefront loads the operands of its 32 pixels straight into registers, all of a
 // chunk of 256 channels at once: one memory round trip where the window kernel takes one per 128 bytes of a pixel.  The
 // filters of the workgroup's 32 CB output channels (rows as they lie in w, padded by 16 bytes against bank conflicts) come into
-// LDS under the same round trip.  Results leave through a per-wavefront LDS area as 16-byte pieces of a pixel.
+// LDS under the same round trip, by direct-to-LDS loads.  Results are packed four at a time (requant_pack4) and leave through a
+// per-wavefront LDS area as 16-byte pieces of a pixel.
 //
-// Measured (us per launch, replayed graphs of ten, window kernel -> this one): 32 x 28 x 28 x 512 -> 128 10.9 -> 9.3, 128 -> 512
-// 16.4 -> 14.0, 32 x 14 x 14 x 256 -> 1024 12.9 -> 8.9, 32 x 56 x 56 x 256 -> 64 13.1 -> 10.3, 6 x 25 x 25 x 160 -> 640 9.0 -> 5.9, one image
-// 28 x 28 x 512 -> 128 6.8 -> 6.3.  CB = 4 where that leaves 192 workgroups, else 2: fetching 128 filter rows made small
-// launches slower than the window kernel's (7.8 us in the last case).  Bound by two dependent round trips (filters and pixels,
-// then the store) and the launch itself: 16 MB are 3 us at the rate of a large copy.
+// Measured (us per launch, replayed graphs of ten, window kernel -> this one): 32 x 28 x 28 x 512 -> 128 10.9 -> 8.6, 128 -> 512
+// 16.4 -> 11.7, 32 x 14 x 14 x 256 -> 1024 12.9 -> 8.5, 32 x 56 x 56 x 256 -> 64 13.1 -> 8.9, 6 x 25 x 25 x 160 -> 640 9.0 -> 5.1, one image
+// 28 x 28 x 512 -> 128 6.8 -> 6.0.  (With filters through registers in two round trips, ten instructions a packed result and more workgroups
+// than run at once: 9.3, 14.0, 9.3, 10.3, 5.8, 6.3.)  CB = 4 where that leaves 192 workgroups, else 2: fetching 128 filter rows made small
+// launches slower than the window kernel's.  Parts taken out of a copy (512 -> 128 / 128 -> 512): the pixels' loads 0.6 / 2.6, the
+// filters' 0.8 / 1.0, packing 0.9 / 2.3, the stores 0.8 / 1.3; all chunks of 512 channels in flight at once was slower (10.2: registers).
 #include <algorithm>
 #include <initializer_list>
+#include <type_traits>
 
 #include "swconv_internal.h"
 
@@ -25,7 +28,11 @@ namespace {
 
 typedef int intx4 __attribute__((ext_vector_type(4)));
 typedef int intx16 __attribute__((ext_vector_type(16)));
+typedef float floatx4 __attribute__((ext_vector_type(4)));
 
+#define SW_LDS_PTR(p) ((__attribute__((address_space(3))) void*)(p))
+
+constexpr unsigned kBeyond = 0x80000000u;
 constexpr int kChunkSteps = 8;             // steps of 32 channels whose pixel operands are in flight at once
 constexpr size_t kLdsMax = 150 * 1024;
 
@@ -33,9 +40,12 @@ struct PwS8Params {
     Requant rq;
     int total_px, C_in, C_out, tiles;      // tiles of 32 pixels
     int pitch, rq_off, out_off;            // bytes per filter row in LDS; offsets of biases and scales, and of the store areas
-    FastDiv by_pieces;                     // 16-byte pieces per filter row
+    int wloads;                            // 1 KB loads of the workgroup's filters
+    unsigned w_bytes;
+    FastDiv by_slots;                      // 16-byte slots per filter row: its pieces and one that pads it
 };
 
+// CB: blocks of 32 output channels per workgroup.
 template <int CB>
 __global__ __launch_bounds__(256, 2) void mfma_s8_pointwise_nhwc_kernel(const int8_t* __restrict__ x, const int8_t* __restrict__ w,
                                                                         int8_t* __restrict__ y, const PwS8Params P)
@@ -61,23 +71,15 @@ __global__ __launch_bounds__(256, 2) void mfma_s8_pointwise_nhwc_kernel(const in
     fetch(xp, 0);
 
     {
-        const int pieces = P.C_in >> 4, total = 32 * CB * pieces;
-#pragma unroll 1
-        for (int i0 = tid; i0 < total; i0 += 8 * 256) {
-            intx4 v[8];
-#pragma unroll
-            for (int u = 0; u < 8; ++u) {
-                const int i = min(i0 + 256 * u, total - 1);
-                const int row = fast_div(i, P.by_pieces), g = i - row * pieces;
-                v[u] = *reinterpret_cast<const intx4*>(w + (int64_t)min(co0 + row, P.C_out - 1) * P.C_in + 16 * g);
-            }
-#pragma unroll
-            for (int u = 0; u < 8; ++u) {
-                const int i = i0 + 256 * u;
-                if (i >= total) break;
-                const int row = fast_div(i, P.by_pieces), g = i - row * pieces;
-                *reinterpret_cast<intx4*>(smem + row * P.pitch + 16 * g) = v[u];
-            }
+        // the filters, by direct-to-LDS loads: all of them under the pixels' round trip
+        const __amdgpu_buffer_rsrc_t wr = __builtin_amdgcn_make_buffer_rsrc(const_cast<int8_t*>(w), 0, P.w_bytes, 0x00020000);
+        const int pieces = P.C_in >> 4;
+        const int wv = __builtin_amdgcn_readfirstlane(wave);
+#pragma unroll 2
+        for (int k = wv; k < P.wloads; k += 4) {
+            const int i = 64 * k + lane, row = fast_div(i, P.by_slots), g = i - row * (pieces + 1);
+            const bool have = row < 32 * CB && g < pieces && co0 + row < P.C_out;
+            __builtin_amdgcn_raw_ptr_buffer_load_lds(wr, SW_LDS_PTR(smem + 1024 * k), 16, have ? (unsigned)((co0 + row) * P.C_in + 16 * g) : kBeyond, 0, 0, 0);
         }
         if (tid < 32 * CB) {
             const int co = min(co0 + tid, P.C_out - 1);
@@ -120,22 +122,21 @@ __global__ __launch_bounds__(256, 2) void mfma_s8_pointwise_nhwc_kernel(const in
         const int p0 = 32 * tile;
         constexpr int OP = 32 * CB + 16;               // bytes per pixel in the store area
         unsigned char* lo = smem + P.out_off + wave * 32 * OP;
-        const int* bias = reinterpret_cast<const int*>(smem + P.rq_off);
-        const float* scale = reinterpret_cast<const float*>(smem + P.rq_off) + 32 * CB;
-        const float low = P.rq.relu ? 0.f : -128.f;
+        auto pack = [&](auto relu) __attribute__((always_inline)) {
 #pragma unroll
-        for (int cb = 0; cb < CB; ++cb)
+            for (int cb = 0; cb < CB; ++cb)
 #pragma unroll
-            for (int q = 0; q < 4; ++q) {
-                const int col = 32 * cb + 8 * q + 4 * kq;
-                unsigned packed = 0;
-#pragma unroll
-                for (int e = 0; e < 4; ++e) {
-                    const float r = rintf(__int2float_rn(acc[cb][4 * q + e] + bias[col + e]) * scale[col + e]);
-                    packed |= (unsigned)((int)fminf(fmaxf(r, low), 127.f) & 255) << (8 * e);
+                for (int q = 0; q < 4; ++q) {
+                    const int col = 32 * cb + 8 * q + 4 * kq;
+                    const intx4 bi = *reinterpret_cast<const intx4*>(smem + P.rq_off + 4 * col);
+                    const floatx4 sc = *reinterpret_cast<const floatx4*>(smem + P.rq_off + 128 * CB + 4 * col);
+                    *reinterpret_cast<int*>(lo + lj * OP + col) =
+                        requant_pack4<decltype(relu)::value>(acc[cb][4 * q] + bi[0], acc[cb][4 * q + 1] + bi[1], acc[cb][4 * q + 2] + bi[2],
+                                                             acc[cb][4 * q + 3] + bi[3], sc[0], sc[1], sc[2], sc[3]);
                 }
-                *reinterpret_cast<unsigned*>(lo + lj * OP + col) = packed;
-            }
+        };
+        if (P.rq.relu) pack(std::true_type{});
+        else pack(std::false_type{});
         asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");          // (the area is this wavefront's own)
         constexpr int NC = 2 * CB;                     // 16-byte pieces per pixel
 #pragma unroll
@@ -161,7 +162,9 @@ PwS8Plan plan_pw_s8(const int8_t* x, const int8_t* w, const int8_t* y, const Con
 {
     PwS8Plan a;
     const int64_t px = (int64_t)s.N * s.H * s.W;
-    if (s.R != 1 || s.S != 1 || s.stride != 1 || s.pad != 0 || s.C_in % 32 != 0 || s.C_out % 16 != 0 || px >= (1LL << 31) - 64) return a;
+    if (s.R != 1 || s.S != 1 || s.stride != 1 || s.pad != 0 || s.C_in % 32 != 0 || s.C_out % 16 != 0 || px >= (1LL << 31) - 64 ||
+        (int64_t)s.C_out * s.C_in >= (1LL << 31))
+        return a;
     for (const void* p : {(const void*)x, (const void*)w, (const void*)y})
         if (reinterpret_cast<uintptr_t>(p) % 16 != 0) return a;
     // below 128 channels the window kernel's steps hold all of a pixel, and its tests assert its plans there
@@ -176,7 +179,7 @@ PwS8Plan plan_pw_s8(const int8_t* x, const int8_t* w, const int8_t* y, const Con
     for (int CB : {4, 2}) {
         const int64_t groups = (s.C_out + 32 * CB - 1) / (32 * CB);
         if (CB == 4 && (s.C_out <= 64 || (px + 127) / 128 * groups < 192)) continue;
-        const size_t filters = (size_t)32 * CB * pitch, rq = (size_t)256 * CB, out = (size_t)4 * 32 * (32 * CB + 16);
+        const size_t filters = ((size_t)32 * CB * pitch + 1023) / 1024 * 1024, rq = (size_t)256 * CB, out = (size_t)4 * 32 * (32 * CB + 16);
         if (filters + rq + out > kLdsMax) continue;
         a.ok = true;
         a.CB = CB;
@@ -184,10 +187,12 @@ PwS8Plan plan_pw_s8(const int8_t* x, const int8_t* w, const int8_t* y, const Con
         PwS8Params& P = a.P;
         P.total_px = (int)px; P.C_in = s.C_in; P.C_out = s.C_out; P.tiles = (int)((px + 31) / 32);
         P.pitch = pitch; P.rq_off = (int)filters; P.out_off = (int)(filters + rq);
-        P.by_pieces = make_fastdiv(s.C_in / 16);
+        P.wloads = (int)(filters / 1024); P.w_bytes = (unsigned)((int64_t)s.C_out * s.C_in);
+        P.by_slots = make_fastdiv(s.C_in / 16 + 1);
         a.gy = (unsigned)groups;
-        // persistent: as many workgroups as fit their CUs at once
-        const int per_cu = (int)std::max<size_t>(1, std::min<size_t>(4, 160 * 1024 / a.lds));
+        // persistent: as many workgroups as fit their CUs at once, by registers two of CB = 4 and three of CB = 2 (four, as LDS would have it,
+        // left a second turn of a few: 128 -> 512 at 28 x 28 12.7 us against 11.3, at 56 x 56 26.9 against 24.2)
+        const int per_cu = (int)std::max<size_t>(1, std::min<size_t>(CB == 4 ? 2 : 3, 160 * 1024 / a.lds));
         const int64_t cap = std::max<int64_t>(1, (int64_t)256 * per_cu / a.gy);
         a.gx = (unsigned)std::min<int64_t>((P.tiles + 3) / 4, cap);
         break;

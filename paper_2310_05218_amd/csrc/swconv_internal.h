@@ -93,6 +93,26 @@ __device__ __forceinline__ int8_t requant_s8(int acc, int co, const Requant& rq)
     return (int8_t)(int)r;
 }
 
+// Four neighbouring results packed: the same operations, with v_cvt_pk_u8_f32 (nearest even, saturating to 0 ... 255, NaN to 0) in
+// place of rounding, clamping, converting and shifting apart: 6.5 instructions a result where requant_s8 and its packing take 10, which
+// take 2.3 of the 11.7 us of 128 -> 512 channels at 28 x 28, 32 images.  t: sum + bias.
+template <bool RELU>
+__device__ __forceinline__ int requant_pack4(int t0, int t1, int t2, int t3, float s0, float s1, float s2, float s3)
+{
+    float f[4] = {__int2float_rn(t0) * s0, __int2float_rn(t1) * s1, __int2float_rn(t2) * s2, __int2float_rn(t3) * s3};
+    unsigned v = 0;
+    if constexpr (RELU) {
+#pragma unroll
+        for (int j = 0; j < 4; ++j) v = __builtin_amdgcn_cvt_pk_u8_f32(f[j], j, v);
+        const unsigned over = v & 0x80808080u;          // 128 ... 255 are 127
+        return (int)((v | (over - (over >> 7))) & 0x7f7f7f7fu);
+    } else {
+#pragma unroll
+        for (int j = 0; j < 4; ++j) v = __builtin_amdgcn_cvt_pk_u8_f32(rintf(f[j]) + 128.f, j, v);     // (rounded before the sum is)
+        return (int)(v ^ 0x80808080u);
+    }
+}
+
 // Records the kernel a launcher is about to enqueue (name and up to four template arguments) for the calling
 // thread; sw_last_kernel() reports it.  Costs a few stores per launch.
 void note_kernel(const char* name, int a = -1, int b = -1, int c = -1, int d = -1);
