@@ -1,4 +1,4 @@
-"""Thin ctypes binding of libswconv.so: argument marshalling only.
+"""Thin binding of libswconv.so: argument marshalling only, by ctypes and, for the plain calls, by a native module.
 
 PyTorch supplies device memory and the current HIP stream; every step of the computation runs in
 the library's kernels.  The functions carry the names of the C entry points they call.  If the
@@ -127,6 +127,10 @@ def sw_conv2d_s8_nhwc(x, w, stride: int = 1, pad: int = 0, bias=None, scale=None
     """Channel-last int8 convolution: x [N,H,W,C_in] int8, w [C_out,R,S,C_in] int8 -> y [N,H_out,W_out,C_out]
     int32 (exact sums), or int8 when `scale` ([C_out] fp32, with optional int32 `bias`) is given:
     clamp(rne(scale * float(acc + bias)), 0 if relu else -128, 127)."""
+    if out is None and stream is None:
+        y = _native(_S8_NHWC, x, w, bias, scale, stride, pad, 1, relu)
+        if y is not None:
+            return _done(y, "sw_conv2d_s8_nhwc" if scale is None else "sw_conv2d_s8_nhwc_requant")
     import torch
 
     N, H, W, C_in = x.shape
@@ -157,6 +161,14 @@ def sw_conv2d_nhwc(x, w, stride: int = 1, pad: int = 0, dilation: int = 1, bias=
     """Channel-last convolution: x [N,H,W,C_in], w [C_out,R,S,C_in] -> y [N,H_out,W_out,C_out] = act(conv + bias[co]);
     fp32 tensors, or 16-bit tensors (torch.bfloat16 / torch.float16: fp32 accumulation, one rounding of the result);
     bias [C_out] fp32."""
+    if out is None and stream is None:
+        y = _native(_NHWC, x, w, bias, None, stride, pad, dilation, relu)
+        if y is not None:
+            if y.__class__ is not int:
+                return y
+            import torch
+
+            return _done(y, {torch.bfloat16: "sw_conv2d_bf16_nhwc", torch.float16: "sw_conv2d_f16_nhwc"}.get(x.dtype, "sw_conv2d_nhwc"))
     import torch
 
     N, H, W, C_in = x.shape
@@ -198,6 +210,10 @@ def sw_conv2d_f16_nhwc(x, w, stride: int = 1, pad: int = 0, dilation: int = 1, b
 def sw_conv2d_s8_requant(x, w, bias, scale, stride: int = 1, pad: int = 0, relu: bool = False, out=None, stream=None):
     """x [N,C_in,H,W] int8, w [C_out,C_in,R,S] int8, bias [C_out] int32 or None, scale [C_out] fp32 ->
     y [N,C_out,H_out,W_out] int8 = clamp(rne(scale * float(acc + bias)), 0 if relu else -128, 127)."""
+    if out is None and stream is None:
+        y = _native(_S8_REQUANT, x, w, bias, scale, stride, pad, relu)
+        if y is not None:
+            return _done(y, "sw_conv2d_s8_requant")
     import torch
 
     N, C_in, H, W = x.shape
@@ -263,6 +279,42 @@ def _bind_current_stream():
     return _current_stream
 
 
+# operations of the native short way (csrc/binding/sw_binding.cpp), in its order
+(_CONV1D, _POOL1D, _POOL2D, _CONV2D, _BIAS_RELU, _DILATED, _DEPTHWISE, _DEPTHWISE_BIAS_RELU, _DEPTHWISE_BF16, _S8, _S8_REQUANT, _S8_NHWC,
+ _NHWC) = range(13)
+_NATIVE_ENTRIES = ("sw_conv1d", "sw_pool1d", "sw_pool2d", "sw_conv2d", "sw_conv2d_bias_relu", "sw_conv2d_dilated", "sw_conv2d_depthwise",
+                   "sw_conv2d_depthwise_bias_relu", "sw_conv2d_depthwise_bf16", "sw_conv2d_s8", "sw_conv2d_s8_requant", "sw_conv2d_s8_nhwc",
+                   "sw_conv2d_s8_nhwc_requant", "sw_conv2d_nhwc", "sw_conv2d_bf16_nhwc", "sw_conv2d_f16_nhwc")
+
+
+def _bind_native(*args):
+    """The first call through `_native`: binds it to the library's entry points (torch has to be imported before the module is)."""
+    global _native
+    import torch  # noqa: F401
+
+    L = lib()
+    try:
+        from . import _swnative
+    except ImportError:         # not built: every call goes the long way
+        _native = lambda *args: None
+    else:
+        _swnative.bind(tuple(ctypes.cast(getattr(L, n), ctypes.c_void_p).value for n in _NATIVE_ENTRIES))
+        _native = _swnative.run
+    return _native(*args)
+
+
+# (op, x, w, bias, scale, integers ...) -> the output tensor, a status code, or None for a call that goes the long way: through the
+# checks in Python, which take it or raise.  7.1 us a call that way, of which the launch itself is 1.6.
+_native = _bind_native
+
+
+def _done(y, what):
+    """The output of a native call, or its status raised."""
+    if y.__class__ is int:
+        raise SwError(y, what)
+    return y
+
+
 def _stream(stream):
     if stream is not None:
         return stream.cuda_stream
@@ -298,6 +350,10 @@ def _out_shape(what, *dims):
 
 def sw_conv1d(x, w, stride: int = 1, pad: int = 0, out=None, stream=None):
     """x [rows, len] fp32, w [k] fp32 -> y [rows, len_out] fp32 (device tensors)."""
+    if out is None and stream is None:
+        y = _native(_CONV1D, x, w, None, None, stride, pad)
+        if y is not None:
+            return _done(y, "sw_conv1d")
     import torch
 
     rows, length = x.shape
@@ -313,6 +369,10 @@ def sw_conv1d(x, w, stride: int = 1, pad: int = 0, out=None, stream=None):
 
 def sw_pool1d(x, window: int, stride: int = 1, mode: int = SW_POOL_AVG, out=None, stream=None):
     """x [rows, len] fp32 -> y [rows, len_out] fp32; mode SW_POOL_AVG or SW_POOL_MAX."""
+    if out is None and stream is None:
+        y = _native(_POOL1D, x, None, None, None, window, stride, mode)
+        if y is not None:
+            return _done(y, "sw_pool1d")
     import torch
 
     rows, length = x.shape
@@ -327,6 +387,10 @@ def sw_pool1d(x, window: int, stride: int = 1, mode: int = SW_POOL_AVG, out=None
 
 def sw_pool2d(x, R: int, S: int, stride: int = 1, pad: int = 0, mode: int = SW_POOL_AVG, out=None, stream=None):
     """x [N,C,H,W] fp32 -> y [N,C,H_out,W_out] fp32; mode SW_POOL_AVG (divisor R*S) or SW_POOL_MAX."""
+    if out is None and stream is None:
+        y = _native(_POOL2D, x, None, None, None, R, S, stride, pad, mode)
+        if y is not None:
+            return _done(y, "sw_pool2d")
     import torch
 
     N, C, H, W = x.shape
@@ -341,6 +405,10 @@ def sw_pool2d(x, R: int, S: int, stride: int = 1, pad: int = 0, mode: int = SW_P
 
 def sw_conv2d(x, w, stride: int = 1, pad: int = 0, out=None, stream=None):
     """x [N,C_in,H,W] fp32, w [C_out,C_in,R,S] fp32 -> y [N,C_out,H_out,W_out] fp32."""
+    if out is None and stream is None:
+        y = _native(_CONV2D, x, w, None, None, stride, pad)
+        if y is not None:
+            return _done(y, "sw_conv2d")
     import torch
 
     N, C_in, H, W = x.shape
@@ -359,6 +427,10 @@ def sw_conv2d(x, w, stride: int = 1, pad: int = 0, out=None, stream=None):
 
 def sw_conv2d_bias_relu(x, w, bias, stride: int = 1, pad: int = 0, relu: bool = False, out=None, stream=None):
     """x [N,C_in,H,W] fp32, w [C_out,C_in,R,S] fp32, bias [C_out] fp32 or None -> y = act(conv + bias)."""
+    if out is None and stream is None:
+        y = _native(_BIAS_RELU, x, w, bias, None, stride, pad, relu)
+        if y is not None:
+            return _done(y, "sw_conv2d_bias_relu")
     import torch
 
     N, C_in, H, W = x.shape
@@ -380,6 +452,10 @@ def sw_conv2d_bias_relu(x, w, bias, stride: int = 1, pad: int = 0, relu: bool = 
 
 def sw_conv2d_depthwise_bias_relu(x, w, bias, stride: int = 1, pad: int = 0, relu: bool = False, out=None, stream=None):
     """x [N,C,H,W] fp32, w [C,1,R,S] fp32, bias [C] fp32 or None -> y = act(depthwise conv + bias)."""
+    if out is None and stream is None:
+        y = _native(_DEPTHWISE_BIAS_RELU, x, w, bias, None, stride, pad, relu)
+        if y is not None:
+            return _done(y, "sw_conv2d_depthwise_bias_relu")
     import torch
 
     N, C, H, W = x.shape
@@ -423,6 +499,10 @@ def sw_dw_pw_block(x, w_dw, b_dw, w_pw, b_pw, relu_dw: bool = True, relu_pw: boo
 
 def sw_conv2d_dilated(x, w, stride: int = 1, pad: int = 0, dilation: int = 1, out=None, stream=None):
     """x [N,C_in,H,W] fp32, w [C_out,C_in,R,S] fp32, taps `dilation` positions apart -> y fp32."""
+    if out is None and stream is None:
+        y = _native(_DILATED, x, w, None, None, stride, pad, dilation)
+        if y is not None:
+            return _done(y, "sw_conv2d_dilated")
     import torch
 
     N, C_in, H, W = x.shape
@@ -462,6 +542,10 @@ def sw_conv2d_depthwise_dilated(x, w, stride: int = 1, pad: int = 0, dilation: i
 
 def sw_conv2d_depthwise(x, w, stride: int = 1, pad: int = 0, out=None, stream=None):
     """x [N,C,H,W] fp32, w [C,1,R,S] fp32 -> y [N,C,H_out,W_out] fp32."""
+    if out is None and stream is None:
+        y = _native(_DEPTHWISE, x, w, None, None, stride, pad)
+        if y is not None:
+            return _done(y, "sw_conv2d_depthwise")
     import torch
 
     N, C, H, W = x.shape
@@ -480,6 +564,10 @@ def sw_conv2d_depthwise(x, w, stride: int = 1, pad: int = 0, out=None, stream=No
 
 def sw_conv2d_depthwise_bf16(x, w, stride: int = 1, pad: int = 0, out=None, stream=None):
     """x [N,C,H,W] bfloat16, w [C,1,R,S] fp32 -> y [N,C,H_out,W_out] bfloat16 (fp32 accumulation, one rounding)."""
+    if out is None and stream is None:
+        y = _native(_DEPTHWISE_BF16, x, w, None, None, stride, pad)
+        if y is not None:
+            return _done(y, "sw_conv2d_depthwise_bf16")
     import torch
 
     N, C, H, W = x.shape
@@ -559,6 +647,10 @@ def sw_jit_cached_kernels() -> int:
 
 def sw_conv2d_s8(x, w, stride: int = 1, pad: int = 0, out=None, stream=None):
     """x [N,C_in,H,W] int8, w [C_out,C_in,R,S] int8 -> y [N,C_out,H_out,W_out] int32 (exact sums)."""
+    if out is None and stream is None:
+        y = _native(_S8, x, w, None, None, stride, pad)
+        if y is not None:
+            return _done(y, "sw_conv2d_s8")
     import torch
 
     N, C_in, H, W = x.shape

@@ -9,6 +9,7 @@ import sys
 PKG = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(PKG, "csrc")
 LIB = os.path.join(PKG, "libswconv.so")
+BINDING = os.path.join(PKG, "_swnative.so")
 
 HIPCC_FLAGS = [
     "-O3", "-std=c++17", "--offload-arch=gfx950", "-fPIC",
@@ -20,6 +21,29 @@ HIPCC_FLAGS = [
 
 def sources():
     return sorted(glob.glob(os.path.join(CSRC, "*.hip")))
+
+
+def build_binding(verbose: bool = False) -> str:
+    """Compile the native part of the Python binding (host code against torch's headers) into ``_swnative.so``."""
+    import sysconfig
+
+    import torch
+    from torch.utils import cpp_extension
+
+    rocm = os.environ.get("ROCM_PATH", "/opt/rocm")
+    cmd = [os.environ.get("CXX", "g++"), "-O2", "-std=c++17", "-fPIC", "-shared", "-D__HIP_PLATFORM_AMD__=1", "-DUSE_ROCM=1",
+           f"-D_GLIBCXX_USE_CXX11_ABI={int(torch.compiled_with_cxx11_abi())}"]
+    for d in [*cpp_extension.include_paths(), os.path.join(rocm, "include"), sysconfig.get_paths()["include"]]:
+        cmd += ["-isystem", d]
+    # (torch is imported before the module is: its libraries are found where it loaded them)
+    cmd += [os.path.join(CSRC, "binding", "sw_binding.cpp"), "-o", BINDING]
+    for d in cpp_extension.library_paths():
+        cmd += ["-L", d]
+    cmd += ["-lc10", "-lc10_hip", "-ltorch_cpu", "-ltorch", "-ltorch_python"]
+    if verbose:
+        print(" ".join(cmd), flush=True)
+    subprocess.run(cmd, check=True)
+    return BINDING
 
 
 def build(verbose: bool = False, jobs: int = 8) -> str:
@@ -51,7 +75,9 @@ def build(verbose: bool = False, jobs: int = 8) -> str:
             return obj
 
         with concurrent.futures.ThreadPoolExecutor(max_workers=max(1, jobs)) as pool:
+            binding = pool.submit(build_binding, verbose)
             objs = list(pool.map(compile_one, sources()))
+            binding.result()
         cmd = [hipcc, "--offload-arch=gfx950", "-fPIC", "-shared", "-o", LIB, *objs, "-lhiprtc"]
         if verbose:
             print(" ".join(cmd), flush=True)
