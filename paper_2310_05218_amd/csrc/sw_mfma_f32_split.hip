@@ -21,12 +21,15 @@
 // keeps small tiles, whose periods are short, supplied; large windows leave room for PH = 1 only.  One barrier per chunk.
 //
 // Measured (us per launch, replayed graphs of ten on one set of buffers, batch 32 unless said, the fp32-instruction kernels -> this
-// one): 64 -> 64 at 56 x 56 75.4 -> 52.1, 128 -> 128 at 28 x 28 87.1 -> 48.2, 256 -> 256 at 14 x 14 84.4 -> 46.1, 512 -> 512 at 7 x 7
+// one): 64 -> 64 at 56 x 56 75.4 -> 49.6, 128 -> 128 at 28 x 28 87.1 -> 45.5, 256 -> 256 at 14 x 14 84.4 -> 46.1, 512 -> 512 at 7 x 7
 // 103.5 -> 54.8, one image of 256 -> 256 at 14 x 14 39.4 -> 17.3, of 512 -> 512 at 7 x 7 73.9 -> 30.5, 64 -> 64 at 56 x 56 21.1 -> 10.4,
 // five of 96 -> 136 at 35 x 35 39.0 -> 18.2.
 // What bounds it: 256 pixels x PB of a tile are never quite full (13 of 16 blocks in the first case), the first chunk's way
-// through LDS (7 us) and the stores of a tile that nothing overlaps, 40 cycles per matrix instruction with its operand reads
-// where the instruction takes 32, and a clock of 1.8-1.9 GHz under the bf16 instructions.  Single images: about 2 k ticks a
+// through LDS (7 us) and the stores of a tile that nothing overlaps, and a clock of 1.8-1.9 GHz under the bf16 instructions.  With
+// parts left out, the first case takes 14 us for launch, barriers and window loads, 34 with the matrix instructions of three blocks
+// per SIMD besides (30 cycles each: their chains cost nothing), 36 with their operand reads, 44 with the stores and the thirteenth
+// block, 50 with the splitting.  (The thirteenth block in quarters over four SIMDs, on 16 x 16 x 32 instructions, gained nothing over
+// leaving out the dead ones: each quarter reads as much of LDS as the block.)  Single images: about 2 k ticks a
 // chunk, most of it the filter loads (64 lanes 288 bytes apart are 64 lines a load, 1.2 k ticks a chunk).  Three wavefronts share
 // the taps of single blocks: with a tile's only block on one wavefront 512 -> 512 at 7 x 7 took 40.2 us, 3 x 344 -> 88 at 9 x 9 28.2
 // where it takes 20.3.
@@ -285,50 +288,45 @@ __global__ __launch_bounds__(64 * (mul_waves(PH) + PH + win_waves(PH)), mul_wave
             if (nlive == 0) continue;
             const unsigned char* sf = smem + (i % (PH + 1)) * kFilterStage + kk * 512 + lj * 16;
             const unsigned char* sw = smem + WIN0 + (i & 1) * WSTAGE;
+            auto split_at = [](const unsigned char* p, int plane) __attribute__((always_inline)) {
+                return Split8{*reinterpret_cast<const bf16x8*>(p), *reinterpret_cast<const bf16x8*>(p + plane), *reinterpret_cast<const bf16x8*>(p + 2 * plane)};
+            };
+            auto filters = [&](int tap) __attribute__((always_inline)) { return split_at(sf + tap * 3072, 1024); };
+            auto pixels = [&](int tap, int b) __attribute__((always_inline)) { return split_at(sw + (pix[b] + P.tap_off[tap]), PLANE); };
             struct Ops {
-                Split8 a, b[PB];
+                Split8 a, b;
             };
             auto fetch = [&](Ops& o, int tap) __attribute__((always_inline)) {
-                o.a.h = *reinterpret_cast<const bf16x8*>(sf + tap * 3072);
-                o.a.m = *reinterpret_cast<const bf16x8*>(sf + tap * 3072 + 1024);
-                o.a.l = *reinterpret_cast<const bf16x8*>(sf + tap * 3072 + 2048);
-                const int to = P.tap_off[tap];
-#pragma unroll
-                for (int b = 0; b < PB; ++b) {
-                    const unsigned char* p = sw + (pix[b] + to);
-                    o.b[b].h = *reinterpret_cast<const bf16x8*>(p);
-                    o.b[b].m = *reinterpret_cast<const bf16x8*>(p + PLANE);
-                    o.b[b].l = *reinterpret_cast<const bf16x8*>(p + 2 * PLANE);
-                }
+                o.a = filters(tap);
+                o.b = pixels(tap, 0);
             };
-            auto mul = [&](const Ops& o) __attribute__((always_inline)) {
-                // product by product over the blocks, in ascending order of magnitude
-#pragma unroll
-                for (int b = 0; b < PB; ++b) low[b] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(o.a.l, o.b[b].h, low[b], 0, 0, 0);
-#pragma unroll
-                for (int b = 0; b < PB; ++b) low[b] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(o.a.h, o.b[b].l, low[b], 0, 0, 0);
-#pragma unroll
-                for (int b = 0; b < PB; ++b) low[b] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(o.a.m, o.b[b].m, low[b], 0, 0, 0);
-#pragma unroll
-                for (int b = 0; b < PB; ++b) low[b] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(o.a.m, o.b[b].h, low[b], 0, 0, 0);
-#pragma unroll
-                for (int b = 0; b < PB; ++b) low[b] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(o.a.h, o.b[b].m, low[b], 0, 0, 0);
-#pragma unroll
-                for (int b = 0; b < PB; ++b) acc[b] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(o.a.h, o.b[b].h, acc[b], 0, 0, 0);
+            auto mul = [&](const Split8& f, const Split8& v, int b) __attribute__((always_inline)) {
+                // in ascending order of magnitude
+                low[b] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(f.l, v.h, low[b], 0, 0, 0);
+                low[b] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(f.h, v.l, low[b], 0, 0, 0);
+                low[b] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(f.m, v.m, low[b], 0, 0, 0);
+                low[b] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(f.m, v.h, low[b], 0, 0, 0);
+                low[b] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(f.h, v.m, low[b], 0, 0, 0);
+                acc[b] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(f.h, v.h, acc[b], 0, 0, 0);
             };
             if constexpr (kShared) {
                 Ops o[3];
 #pragma unroll
                 for (int j = 0; j < 3; ++j) fetch(o[j], 3 * wave + j);
 #pragma unroll
-                for (int j = 0; j < 3; ++j) mul(o[j]);
+                for (int j = 0; j < 3; ++j) mul(o[j].a, o[j].b, 0);
             } else if constexpr (PB == 2) {
-                // (registers for one set of operands: the other wavefront of the SIMD covers the reads)
+                // (registers for one set of operands: the other wavefront of the SIMD covers the reads.)  A wavefront whose second
+                // block lies beyond the tile -- three of eight where a tile has 13 blocks of 16 -- leaves its products out: they took the
+                // SIMD's other wavefront a sixth of its matrix time (64 -> 64 at 56 x 56, batch 12 of 48 -> 64, 22 of 88 -> 24 at
+                // 47 x 54 with dilation 2: 52.9 -> 50.2, 21.1 -> 17.8, 33.1 -> 26.9 us).  The test is on the tile's size only, the same for
+                // all lanes; a lone block in a copy of the loop took 54 registers more than there are.
+                const bool two = nlive == 2;
 #pragma unroll
                 for (int tap = 0; tap < kTaps; ++tap) {
-                    Ops o;
-                    fetch(o, tap);
-                    mul(o);
+                    const Split8 f = filters(tap);
+                    mul(f, pixels(tap, 0), 0);
+                    if (two) mul(f, pixels(tap, 1), 1);
                 }
             } else {
                 Ops o[2];
@@ -337,7 +335,7 @@ __global__ __launch_bounds__(64 * (mul_waves(PH) + PH + win_waves(PH)), mul_wave
                 for (int tap = 0; tap < kTaps; ++tap) {
                     if (tap + 1 < kTaps) fetch(o[(tap + 1) & 1], tap + 1);
                     __builtin_amdgcn_sched_barrier(0);
-                    mul(o[tap & 1]);
+                    mul(o[tap & 1].a, o[tap & 1].b, 0);
                     __builtin_amdgcn_sched_barrier(0);
                 }
             }

@@ -94,6 +94,24 @@ def test_split_kernel_special_values(torch, sw, value, where):
         assert np.max(np.abs(y[..., keep] - clean[..., keep]) / clean[..., keep]) <= 2e-5
 
 
+@pytest.mark.parametrize("case", [
+    (22, 88, 24, 47, 54, 2, "mfma_f32_split_kernel<12,1,5>"),       # 9 blocks: one wavefront has two; the last tile's two rows leave wavefronts without any
+    (24, 64, 64, 33, 40, 1, "mfma_f32_split_kernel<12,1,9>"),       # 12 blocks; 8 in the last tile, one each
+    (32, 96, 96, 28, 28, 1, "mfma_f32_split_kernel<12,1,14>"),      # 13 blocks, the last of 8 pixels
+], ids=lambda c: "x".join(map(str, c[:6])))
+def test_tiles_of_uneven_blocks(torch, sw, oracle, case):
+    """Tiles whose wavefronts multiply two pixel blocks, one or none."""
+    N, Ci, Co, H, W, dil, kernel = case
+    x = inputs.normal_f32((N, Ci, H, W), 5150 + Ci)
+    w = inputs.normal_f32((Co, Ci, 3, 3), 5250 + Co, (2.0 / (Ci * 9)) ** 0.5)
+    y_ref, d = oracle.conv2d_dilated(x, w, 1, dil, dil)
+    buf, out, front, n, guard = guarded_empty(torch, y_ref.shape, torch.float32)
+    sw.sw_conv2d_dilated(torch.from_numpy(x).cuda(), torch.from_numpy(w).cuda(), 1, dil, dil, out=out)
+    assert sw.sw_last_kernel() == kernel, sw.sw_last_kernel()
+    assert_f32_parity(out.cpu().numpy(), y_ref, d, str(case))
+    assert_guards_intact(buf, front, n, guard)
+
+
 @pytest.mark.parametrize("exponent", [-100, -110, -120, -126])
 def test_split_kernel_small_values(torch, sw, oracle, exponent):
     """Inputs whose low parts would leave the bf16 range, under weights that lift the products back: the fp32 bar holds."""
