@@ -12,10 +12,17 @@
 // (choice of accumulator row).  Strips overlap by one lane on each inner side, because the edge lanes
 // have no neighbour to take the halo from; at the image border the shifted-in value is the padding
 // itself (zero for sums, minus infinity for the maximum, which padding must never win).
-// All row loads of a band are issued before the first use, so a band costs one memory round trip: this
-// is the kernel for planes that are too few or too ragged for the 56 x 56 tile kernel.
+// All row loads of a band are issued before the first use, so a band costs one memory round trip.
+//
+// Measured (us per launch, replayed graphs of ten; before -> with loads that no branch guards): one image of 256 x 256 under 3x3
+// 5.1 -> 3.75, seven of 423 x 480 under 5x5 7.6 -> 5.5, depthwise 5x5 on 14 x 184 x 18 x 84 19.1 -> 9.5, at stride 2 on 32 x 300 x 400
+// 11.0 -> 5.1.  With a branch around every row's load the compiler copied the rows from register to register at each join (133 to
+// 216 registers for 24 to 68 in use, three waves per SIMD or two); an address clamped into the image and a select take none.
+// Bound by bytes where the planes fill the chip (3x3 pooling at stride 2 on 32 x 64 x 112 x 112: 20.3, 6.3 TB/s), by one memory round
+// trip and the launch where they do not.
 #include "swconv_internal.h"
 
+#include <algorithm>
 #include <cmath>
 
 namespace swconv {
@@ -23,7 +30,8 @@ namespace swconv {
 namespace {
 
 typedef float floatx4 __attribute__((ext_vector_type(4)));
-typedef float floatx2 __attribute__((ext_vector_type(2)));
+typedef float floatx4u __attribute__((ext_vector_type(4), aligned(4)));
+typedef float floatx2u __attribute__((ext_vector_type(2), aligned(4)));
 
 constexpr int kStripIn = 256;             // input columns per wavefront
 constexpr int kStripFirst = 252;          // input columns whose lanes have both neighbours, first strip
@@ -50,17 +58,25 @@ __device__ __forceinline__ float from_right(float v)
         return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), 0x130, 0xF, 0xF, true));
 }
 
+// A wavefront's place among strips, bands and planes, without the integer divide sequence (64-bit as they were, the four divisions took
+// a third of a microsecond of a launch: 5.12 -> 4.75 us for one image of 256 x 256) where the numbers are in fast_div's range.
+struct RowsPlace {
+    FastDiv by_strips, by_bands, by_planes_per_x, by_filters;
+    int wide;                       // a number beyond fast_div's range: the integer divide sequence
+    __device__ __forceinline__ int div(int n, FastDiv f) const { return wide ? (int)((uint32_t)n / f.d) : fast_div(n, f); }
+};
+
 // PADC: padding (compile time).  ST: stride, 1 or 2.  OP: weighted sum, average or maximum.
 // SEGL: lanes per work item.  64: the wavefront walks strips of a wide plane.  8, 16 or 32: planes narrower
 // than 4 * SEGL columns, one (plane, band) item per group of SEGL lanes; the lanes of a group beyond the
 // plane's width hold padding, which is exactly what the neighbouring group's edge lane must shift in.
-template <int R, int S, int PADC, int TR, int ST, int OP, int SEGL>
+// ANY: rows that begin at any 4-byte address and end inside a lane's four columns.
+template <int R, int S, int PADC, int TR, int ST, int OP, int SEGL, bool ANY>
 __global__ __launch_bounds__(256) void sliding_rows_kernel(const float* __restrict__ x,
                                                            const float* __restrict__ w,
-                                                           float* __restrict__ y, int planes_per_x,
-                                                           int n_filters, int H, int W, int Ho, int Wo,
-                                                           int strips, int bands, int64_t waves, int64_t items,
-                                                           int y_vec_ok, const Epilogue ep)
+                                                           float* __restrict__ y, int planes, int H, int W, int Ho, int Wo,
+                                                           int strips, int bands, int waves, int items,
+                                                           const RowsPlace place, const Epilogue ep)
 {
     constexpr int NOUT = 4 / ST;                                   // outputs per lane and output row
     constexpr int LEFT = PADC;
@@ -69,46 +85,62 @@ __global__ __launch_bounds__(256) void sliding_rows_kernel(const float* __restri
     static_assert(LEFT <= 4 && RIGHT <= 4, "halo wider than one neighbour lane");
     const float FILL = OP == ROWS_MAX ? -INFINITY : 0.f;
     const int lane = threadIdx.x & 63;
-    const int64_t wv = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6);
+    const int wv = blockIdx.x * 4 + __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
     if (wv >= waves) return;
     int c0, col, band, plane;
     bool live = true;
     if constexpr (SEGL == 64) {
-        const int strip = (int)(wv % strips);
-        const int64_t t = wv / strips;
-        band = (int)(t % bands);
-        plane = (int)(t / bands);
-        c0 = strip * kStripStep;                      // first input column of the strip
+        const int t = place.div(wv, place.by_strips);
+        plane = place.div(t, place.by_bands);
+        band = t - plane * bands;
+        c0 = (wv - t * strips) * kStripStep;          // first input column of the strip
         col = c0 + 4 * lane;                          // this lane's input columns
     } else {
         // the last wavefront may hold fewer than 64 / SEGL items: its idle groups load and store nothing
-        const int64_t item = wv * (64 / SEGL) + lane / SEGL;
+        const int item = wv * (64 / SEGL) + lane / SEGL;
         live = item < items;
-        const int64_t it = live ? item : 0;
-        band = (int)(it % bands);
-        plane = (int)(it / bands);
+        const int it = live ? item : 0;
+        plane = place.div(it, place.by_bands);
+        band = it - plane * bands;
         c0 = 0;
         col = 4 * (lane % SEGL);
     }
     const int ocol = col / ST;                        // the lane's first output column
     const int i0 = band * TR;                         // first output row of the band
-    const float* xp = x + (int64_t)(plane / planes_per_x) * H * W;
+    const float* xp = x + (int64_t)(OP == ROWS_CONV ? place.div(plane, place.by_planes_per_x) : plane) * H * W;
     float* yp = y + (int64_t)plane * Ho * Wo;
+    const int filter = OP == ROWS_CONV ? plane - place.div(plane, place.by_filters) * (int)place.by_filters.d : 0;
 
     float wr[R * S];
     if constexpr (OP == ROWS_CONV) {
-        const float* wf = w + (int64_t)(plane % n_filters) * R * S;
+        const float* wf = w + (int64_t)filter * R * S;
 #pragma unroll
         for (int k = 0; k < R * S; ++k) wr[k] = wf[k];
     }
 
-    // every input row of the band, one aligned 16-byte load each (padding outside the image)
+    // Every input row of the band, one 16-byte load each, without a branch: rows and columns outside the image load what lies nearest
+    // inside and are replaced by padding.  ANY: the lane whose columns run over the end of its row loads the row's last four and moves
+    // them down, so that no load leaves the tensor.
+    const int lcol = min(col, W - 4);
     floatx4 in[NIN];
 #pragma unroll
     for (int e = 0; e < NIN; ++e) {
+        const float* p = xp + (int64_t)min(max(ST * i0 - PADC + e, 0), H - 1) * W + lcol;
+        if constexpr (ANY) in[e] = *reinterpret_cast<const floatx4u*>(p);
+        else in[e] = *reinterpret_cast<const floatx4*>(p);
+    }
+    const int over = ANY && col < W ? col - lcol : 0;
+    const bool one = over & 1, two = over & 2;
+#pragma unroll
+    for (int e = 0; e < NIN; ++e) {
+        floatx4 v = in[e];
+        if constexpr (ANY) {
+            v = floatx4{one ? v.y : v.x, one ? v.z : v.y, one ? v.w : v.z, one ? FILL : v.w};
+            v = floatx4{two ? v.z : v.x, two ? v.w : v.y, two ? FILL : v.z, two ? FILL : v.w};
+        }
         const int gr = ST * i0 - PADC + e;
-        in[e] = floatx4{FILL, FILL, FILL, FILL};
-        if (gr >= 0 && gr < H && col < W && live) in[e] = *reinterpret_cast<const floatx4*>(xp + (int64_t)gr * W + col);
+        const bool inside = gr >= 0 && gr < H && col < W;
+        in[e] = floatx4{inside ? v.x : FILL, inside ? v.y : FILL, inside ? v.z : FILL, inside ? v.w : FILL};
     }
 
     float acc[TR][NOUT];
@@ -150,7 +182,7 @@ __global__ __launch_bounds__(256) void sliding_rows_kernel(const float* __restri
     constexpr float kScale = 1.0f / (float)(R * S);
     // convolution only: per-channel bias and rectifier of the fused-epilogue entry point (both off otherwise)
     const bool with_ep = OP == ROWS_CONV && (ep.bias != nullptr || ep.relu != 0);
-    const float ep_bias = (OP == ROWS_CONV && ep.bias) ? ep.bias[plane % n_filters] : 0.f;
+    const float ep_bias = (OP == ROWS_CONV && ep.bias) ? ep.bias[filter] : 0.f;
 #pragma unroll
     for (int orow = 0; orow < TR; ++orow) {
         const int oi = i0 + orow;
@@ -167,13 +199,13 @@ __global__ __launch_bounds__(256) void sliding_rows_kernel(const float* __restri
             }
         }
         float* dst = yp + (int64_t)oi * Wo + ocol;
-        if (y_vec_ok && ocol + NOUT - 1 < Wo) {
+        if (ocol + NOUT - 1 < Wo) {
             // (streaming stores: the output is not read again by this kernel)
             if constexpr (NOUT == 4)
-                __builtin_nontemporal_store(floatx4{acc[orow][0], acc[orow][1], acc[orow][2], acc[orow][3]},
-                                            reinterpret_cast<floatx4*>(dst));
+                __builtin_nontemporal_store(floatx4u{acc[orow][0], acc[orow][1], acc[orow][2], acc[orow][3]},
+                                            reinterpret_cast<floatx4u*>(dst));
             else
-                __builtin_nontemporal_store(floatx2{acc[orow][0], acc[orow][1]}, reinterpret_cast<floatx2*>(dst));
+                __builtin_nontemporal_store(floatx2u{acc[orow][0], acc[orow][1]}, reinterpret_cast<floatx2u*>(dst));
         } else {
 #pragma unroll
             for (int p = 0; p < NOUT; ++p)
@@ -182,12 +214,10 @@ __global__ __launch_bounds__(256) void sliding_rows_kernel(const float* __restri
     }
 }
 
-template <int R, int S, int PADC, int ST, int OP, int SEGL>
+template <int R, int S, int PADC, int ST, int OP, int SEGL, bool ANY>
 hipError_t launch_rows_seg(const float* x, const float* w, float* y, int64_t planes, int planes_per_x, int n_filters,
                            int H, int W, int Ho, int Wo, hipStream_t st, const Epilogue& ep)
 {
-    constexpr int NOUT = 4 / ST;
-    const int y_vec_ok = reinterpret_cast<uintptr_t>(y) % (4 * NOUT) == 0 && Wo % NOUT == 0;
     int strips = 1;
     if (SEGL == 64 && W > kStripIn) {
         // input columns whose lanes produce an output
@@ -204,25 +234,28 @@ hipError_t launch_rows_seg(const float* x, const float* w, float* y, int64_t pla
     const int64_t items = planes * strips * bands;
     const int64_t waves = (items + PER_WAVE - 1) / PER_WAVE;
     const int64_t blocks = (waves + 3) / 4;
-    if (blocks > 2147483647LL) return hipErrorInvalidValue;
+    if (4 * blocks > 2147483647LL || planes > 2147483647LL) return hipErrorInvalidValue;       // (an item has at least one of 2^31 outputs)
+    const int64_t most = std::max<int64_t>({strips, bands, planes_per_x, n_filters});
+    const RowsPlace place{make_fastdiv(strips), make_fastdiv(bands), make_fastdiv(planes_per_x), make_fastdiv(n_filters),
+                          PER_WAVE * waves * most >= (1LL << 32) || planes * most >= (1LL << 32)};
     dim3 grid((unsigned)blocks), block(256);
     if (small)
-        SW_NOTED_LAUNCH(note_kernel("sliding_rows_kernel", (int)(R), (int)(S), (int)(PADC), (int)(TR_SMALL)), (sliding_rows_kernel<R, S, PADC, TR_SMALL, ST, OP, SEGL>), grid, block, 0, st, x, w, y,
-                           planes_per_x, n_filters, H, W, Ho, Wo, strips, bands, waves, items, y_vec_ok, ep);
+        SW_NOTED_LAUNCH(note_kernel("sliding_rows_kernel", (int)(R), (int)(S), (int)(PADC), (int)(TR_SMALL)), (sliding_rows_kernel<R, S, PADC, TR_SMALL, ST, OP, SEGL, ANY>), grid, block, 0, st, x, w, y,
+                           (int)planes, H, W, Ho, Wo, strips, bands, (int)waves, (int)items, place, ep);
     else
-        SW_NOTED_LAUNCH(note_kernel("sliding_rows_kernel", (int)(R), (int)(S), (int)(PADC), (int)(TR_BIG)), (sliding_rows_kernel<R, S, PADC, TR_BIG, ST, OP, SEGL>), grid, block, 0, st, x, w, y,
-                           planes_per_x, n_filters, H, W, Ho, Wo, strips, bands, waves, items, y_vec_ok, ep);
+        SW_NOTED_LAUNCH(note_kernel("sliding_rows_kernel", (int)(R), (int)(S), (int)(PADC), (int)(TR_BIG)), (sliding_rows_kernel<R, S, PADC, TR_BIG, ST, OP, SEGL, ANY>), grid, block, 0, st, x, w, y,
+                           (int)planes, H, W, Ho, Wo, strips, bands, (int)waves, (int)items, place, ep);
     return hipGetLastError();
 }
 
 // Narrow planes share a wavefront: the group must be at least one lane wider than the plane (W / 4 lanes), so
 // that the lane between two planes holds padding.
-template <int R, int S, int PADC, int ST, int OP>
+template <int R, int S, int PADC, int ST, int OP, bool ANY = false>
 hipError_t launch_rows(const float* x, const float* w, float* y, int64_t planes, int planes_per_x, int n_filters,
                        int H, int W, int Ho, int Wo, hipStream_t st, const Epilogue& ep)
 {
     const int lanes = W / 4 + 1;
-#define SW_SEG(L) return launch_rows_seg<R, S, PADC, ST, OP, L>(x, w, y, planes, planes_per_x, n_filters, H, W, Ho, Wo, st, ep)
+#define SW_SEG(L) return launch_rows_seg<R, S, PADC, ST, OP, L, ANY>(x, w, y, planes, planes_per_x, n_filters, H, W, Ho, Wo, st, ep)
     if (lanes <= 8) SW_SEG(8);
     if (lanes <= 16) SW_SEG(16);
     if (lanes <= 32) SW_SEG(32);
@@ -268,12 +301,16 @@ hipError_t launch_sliding_rows(const float* x, const float* w, float* y, int64_t
     return hipErrorInvalidValue;
 }
 
-// Pooling windows with a register-only kernel: 2x2 and 3x3, stride 1 or 2, padding up to half the window.
+// Pooling windows with a register-only kernel: 2x2 and 3x3, stride 1 or 2, padding up to half the window, rows of any width.  Against one
+// thread per output (us, 3x3 at stride 2 unless said): 27 x 64 x 109 x 79 31.1 -> 13.5 (5.5 TB/s), 8 x 64 x 113 x 250 28.9 -> 13.0,
+// 2 x 64 x 93 x 122 5.0 -> 3.6, 16 x 256 x 7 x 7 3.6 -> 3.2, at stride 1 on 16 x 192 x 14 x 14 6.0 -> 4.1.  Rows of four to six columns off the
+// grid stay with the latter: a lane group is eight lanes, and they fill two (64 x 512 x 6 x 6 under 2x2 4.1 against 4.5, x 5 x 5 4.6
+// against 4.8).
 bool pool_rows_supported(const float* x, int W, int R, int S, int stride, int pad)
 {
     if ((stride != 1 && stride != 2) || R != S || (R != 2 && R != 3) || pad < 0 || pad > (R == 3 ? 1 : 0)) return false;
     if (R == 2 && stride == 1) return false;       // (no compiled variant; the direct kernel takes it)
-    return W % 4 == 0 && reinterpret_cast<uintptr_t>(x) % 16 == 0;
+    return W >= 7 || (W % 4 == 0 && reinterpret_cast<uintptr_t>(x) % 16 == 0);
 }
 
 hipError_t launch_pool_rows(const float* x, float* y, int64_t planes, int H, int W, int R, int stride, int pad,
@@ -281,8 +318,10 @@ hipError_t launch_pool_rows(const float* x, float* y, int64_t planes, int H, int
 {
 #define SW_POOL(RC, PC, SC)                                                                                    \
     if (R == RC && pad == PC && stride == SC) {                                                                \
-        if (maximum) return launch_rows<RC, RC, PC, SC, ROWS_MAX>(x, nullptr, y, planes, 1, 1, H, W, Ho, Wo, st, Epilogue{nullptr, 0}); \
-        return launch_rows<RC, RC, PC, SC, ROWS_AVG>(x, nullptr, y, planes, 1, 1, H, W, Ho, Wo, st, Epilogue{nullptr, 0}); \
+        const bool any = W % 4 != 0 || reinterpret_cast<uintptr_t>(x) % 16 != 0;                                \
+        auto f = maximum ? any ? launch_rows<RC, RC, PC, SC, ROWS_MAX, true> : launch_rows<RC, RC, PC, SC, ROWS_MAX> \
+                         : any ? launch_rows<RC, RC, PC, SC, ROWS_AVG, true> : launch_rows<RC, RC, PC, SC, ROWS_AVG>; \
+        return f(x, nullptr, y, planes, 1, 1, H, W, Ho, Wo, st, Epilogue{nullptr, 0});                          \
     }
     SW_POOL(2, 0, 2) SW_POOL(3, 0, 1) SW_POOL(3, 1, 1) SW_POOL(3, 0, 2) SW_POOL(3, 1, 2)
 #undef SW_POOL
