@@ -60,17 +60,27 @@ int run_plane(const float* x, const float* w, float* y, int64_t planes, int plan
             return launch_status(launch_sliding_plane(x, w, y, planes, planes_per_x, n_filters, s.H, s.W, s.R, s.S,
                                                       s.pad, s.Ho, s.Wo, st, ep, s.dil));
     } else if (!force_direct()) {
-        // planes up to 20 x 20, and larger ragged ones (width not a multiple of 4) that the register-only and
+        const bool rows = sliding_rows_supported(x, s.H, s.W, s.R, s.S, s.stride, s.pad);
+        // The rows kernel first where it has a variant: at stride 2 always, at stride 1 from 12 columns on (narrower planes leave five of a
+        // group's eight lanes idle: 64 x 512 x 4 x 4 under 7x7 12.7 us against 7.9, 8 x 64 x 8 x 8 under 5x5 4.8 against 4.0).  us, the kernel of
+        // small planes -> rows: 32 x 512 x 16 x 16 under 3x3 12.9 -> 7.1, 5x5 14.8 -> 10.7, 7x7 21.9 -> 16.1, 7x7 at stride 2 15.4 -> 9.6;
+        // 32 x 256 x 28 x 28 under 5x5 22.2 -> 13.4, 7x7 39.3 -> 16.1; 13 x 560 x 12 x 20 under 3x3 7.7 -> 5.1.  Up to 512 planes under 5x5 and
+        // 7x7 at stride 1 stay (5.4 -> 5.0 at 1024 planes of 16 x 16 under 7x7, 4.7 -> 4.8 at 80): a launch's latency either way, if not for the
+        // larger planes (4 x 96 x 24 x 24 under 5x5 6.1 against 4.2).
+        const bool rows_first = rows && (s.stride == 2 || (s.W >= 12 && (s.R == 3 || planes > 512)));
+        // planes up to 20 x 20, larger filters' planes and larger ragged ones (width not a multiple of 4) that the register-only and
         // whole-plane kernels do not take: a run of planes per workgroup
-        if ((s.H * s.W <= 400 || s.W % 4 != 0 || s.R * s.S >= 25) &&
+        if (!rows_first && (s.H * s.W <= 400 || s.W % 4 != 0 || s.R * s.S >= 25) &&
             small_planes_supported(planes, planes_per_x, s.H, s.W, s.R, s.S, s.stride, s.Ho, s.Wo))
             return launch_status(launch_small_planes(x, w, y, planes, n_filters, s.H, s.W, s.R, s.S, s.stride, s.pad,
                                                      s.Ho, s.Wo, st, ep));
-        const bool rows = sliding_rows_supported(x, s.H, s.W, s.R, s.S, s.stride, s.pad);
-        // the whole-plane kernel spends a 56 x 56 tile per plane: planes up to 32 wide leave most of its lanes
-        // idle and go to the rows kernel (lane groups) when that has a variant
+        // The whole-plane kernel spends a 56 x 56 tile per plane: less than that leaves lanes idle, and up to 1024 planes do not fill the
+        // chip with it; both go to the rows kernel when that has a variant.  us, tile -> rows: 8 x 256 x 48 x 40 under 3x3 12.7 -> 7.2, 7x7
+        // 19.5 -> 12.6; 32 x 256 x 48 x 48 5x5 36.0 -> 29.2, 7x7 48.3 -> 43.0; 32 x 256 x 56 x 40 5x5 35.5 -> 31.3; 8 x 64 x 56 x 56 3x3 5.7 -> 4.6,
+        // 7x7 9.5 -> 6.5; 16 x 64 x 56 x 56 5x5 8.5 -> 7.1.  It keeps more full planes: 32 x 64 x 56 x 56 under 3x3 10.5 against 11.1, under 5x5
+        // 12.4 against 12.6, 128 x 64 under 7x7 49.9 against 54.7.
         const bool whole = s.stride == 1 && sliding_plane_whole(x, y, s.H, s.W, s.R, s.S, s.pad, s.Ho, s.Wo) &&
-                           planes >= 512 && !(rows && s.W <= 32);
+                           planes >= 512 && !(rows && (s.H < 56 || s.W < 56 || planes <= 1024));
         if (!whole && rows)
             return launch_status(launch_sliding_rows(x, w, y, planes, planes_per_x, n_filters, s.H, s.W, s.R, s.S,
                                                      s.stride, s.pad, s.Ho, s.Wo, st, ep));

@@ -70,3 +70,28 @@ def test_filters_at_the_edges_of_bands(torch, sw, oracle, case):
         assert sw.sw_last_kernel().startswith("sliding_rows_kernel"), sw.sw_last_kernel()
         assert_f32_parity(out.cpu().numpy(), y_ref, d, f"{case} {K}")
         assert_guards_intact(buf, front, n, guard)
+
+
+@pytest.mark.parametrize("case", [
+    # N, C, H, W, R, stride, pad, kernel: on both sides of the lines between the rows kernel, small planes and whole planes
+    (2, 35, 9, 8, 3, 1, 1, "small_planes_kernel<3,3,1>"), (2, 35, 9, 12, 3, 1, 1, "sliding_rows_kernel<3,3,1,"),
+    (8, 64, 11, 12, 5, 1, 2, "small_planes_kernel<5,5,1>"), (27, 19, 11, 12, 5, 1, 2, "sliding_rows_kernel<5,5,2,"),        # 512, 513 planes
+    (27, 19, 14, 28, 7, 1, 3, "sliding_rows_kernel<7,7,3,"), (2, 50, 4, 4, 3, 2, 1, "sliding_rows_kernel<3,3,1,"),
+    (3, 41, 13, 16, 5, 2, 2, "sliding_rows_kernel<5,5,2,"), (3, 41, 8, 8, 7, 2, 3, "sliding_rows_kernel<7,7,3,"),
+    (16, 64, 56, 56, 3, 1, 1, "sliding_rows_kernel<3,3,1,"), (25, 41, 56, 56, 3, 1, 1, "sliding_plane_full_kernel<3,3,1,0>"),        # 1024, 1025
+    (25, 41, 55, 56, 5, 1, 2, "sliding_rows_kernel<5,5,2,"),
+], ids=lambda c: "x".join(map(str, c[:7])))
+def test_depthwise_routes(torch, sw, oracle, case):
+    N, C, H, W, R, stride, pad, kernel = case
+    x, w = inputs.normal_f32((N, C, H, W), 6400 + W), inputs.normal_f32((C, 1, R, R), 6500 + R)
+    b = inputs.normal_f32((C,), 6600, 0.5)
+    y_ref, d = oracle.conv2d_depthwise(x, w, stride, pad)
+    xd, wd, bd = (torch.from_numpy(a).cuda() for a in (x, w, b))
+    buf, out, front, n, guard = guarded_empty(torch, y_ref.shape, torch.float32)
+    sw.sw_conv2d_depthwise(xd, wd, stride, pad, out=out)
+    assert sw.sw_last_kernel().startswith(kernel), sw.sw_last_kernel()
+    assert_f32_parity(out.cpu().numpy(), y_ref, d, str(case))
+    assert_guards_intact(buf, front, n, guard)
+    y = sw.sw_conv2d_depthwise_bias_relu(xd, wd, bd, stride, pad, True)
+    z = torch.clamp(out + bd.view(1, -1, 1, 1), min=0)      # (one rounding on the same sum either way)
+    assert torch.equal(y, z)
