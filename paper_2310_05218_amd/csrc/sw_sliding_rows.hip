@@ -248,13 +248,13 @@ hipError_t launch_rows_seg(const float* x, const float* w, float* y, int64_t pla
     return hipGetLastError();
 }
 
-// Narrow planes share a wavefront: the group must be at least one lane wider than the plane (W / 4 lanes), so
-// that the lane between two planes holds padding.
+// Narrow planes share a wavefront: between two planes must lie as many columns of padding as the next one's first lane shifts in, PADC
+// (rows of whole groups leave at least a lane of them).
 template <int R, int S, int PADC, int ST, int OP, bool ANY = false>
 hipError_t launch_rows(const float* x, const float* w, float* y, int64_t planes, int planes_per_x, int n_filters,
                        int H, int W, int Ho, int Wo, hipStream_t st, const Epilogue& ep)
 {
-    const int lanes = W / 4 + 1;
+    const int lanes = std::max(W / 4 + 1, (W + PADC + 3) / 4);
 #define SW_SEG(L) return launch_rows_seg<R, S, PADC, ST, OP, L, ANY>(x, w, y, planes, planes_per_x, n_filters, H, W, Ho, Wo, st, ep)
     if (lanes <= 8) SW_SEG(8);
     if (lanes <= 16) SW_SEG(16);
@@ -262,6 +262,9 @@ hipError_t launch_rows(const float* x, const float* w, float* y, int64_t planes,
     SW_SEG(64);
 #undef SW_SEG
 }
+
+// rows of whole 16-byte groups on the 16-byte grid
+bool whole_quads(const float* x, int W) { return W % 4 == 0 && reinterpret_cast<uintptr_t>(x) % 16 == 0; }
 
 }  // namespace
 
@@ -272,7 +275,7 @@ bool sliding_rows_supported(const float* x, int H, int W, int R, int S, int stri
     // (padding beyond (R-1)/2 would need more than the compiled halo widths; 7x7 reaches at most four columns into
     // the right neighbour, which rules out the smallest paddings)
     if (R == 7 && pad < (stride == 1 ? 2 : 1)) return false;
-    return W % 4 == 0 && reinterpret_cast<uintptr_t>(x) % 16 == 0;
+    return W >= 4;
 }
 
 hipError_t launch_sliding_rows(const float* x, const float* w, float* y, int64_t planes, int planes_per_x,
@@ -280,23 +283,13 @@ hipError_t launch_sliding_rows(const float* x, const float* w, float* y, int64_t
                                hipStream_t st, const Epilogue& ep)
 {
     (void)S;
-#define SW_ROWS(RC, PC)                                                                                        \
-    if (R == RC && pad == PC) {                                                                                \
-        if (stride == 1)                                                                                       \
-            return launch_rows<RC, RC, PC, 1, ROWS_CONV>(x, w, y, planes, planes_per_x, n_filters, H, W, Ho, Wo, st, ep); \
-        return launch_rows<RC, RC, PC, 2, ROWS_CONV>(x, w, y, planes, planes_per_x, n_filters, H, W, Ho, Wo, st, ep);     \
-    }
-    SW_ROWS(3, 0) SW_ROWS(3, 1) SW_ROWS(5, 0) SW_ROWS(5, 1) SW_ROWS(5, 2)
-    if (R == 7 && pad == 3) {
-        if (stride == 1) return launch_rows<7, 7, 3, 1, ROWS_CONV>(x, w, y, planes, planes_per_x, n_filters, H, W, Ho, Wo, st, ep);
-        return launch_rows<7, 7, 3, 2, ROWS_CONV>(x, w, y, planes, planes_per_x, n_filters, H, W, Ho, Wo, st, ep);
-    }
-    if (R == 7 && pad == 2) {
-        if (stride == 1) return launch_rows<7, 7, 2, 1, ROWS_CONV>(x, w, y, planes, planes_per_x, n_filters, H, W, Ho, Wo, st, ep);
-        return launch_rows<7, 7, 2, 2, ROWS_CONV>(x, w, y, planes, planes_per_x, n_filters, H, W, Ho, Wo, st, ep);
-    }
-    if (R == 7 && pad == 1 && stride == 2)
-        return launch_rows<7, 7, 1, 2, ROWS_CONV>(x, w, y, planes, planes_per_x, n_filters, H, W, Ho, Wo, st, ep);
+    const bool any = !whole_quads(x, W);
+#define SW_ROWS(RC, PC, SC)                                                                                              \
+    if (R == RC && pad == PC && stride == SC)                                                                            \
+        return (any ? launch_rows<RC, RC, PC, SC, ROWS_CONV, true> : launch_rows<RC, RC, PC, SC, ROWS_CONV>)(x, w, y, planes, \
+               planes_per_x, n_filters, H, W, Ho, Wo, st, ep);
+    SW_ROWS(3, 0, 1) SW_ROWS(3, 1, 1) SW_ROWS(5, 0, 1) SW_ROWS(5, 1, 1) SW_ROWS(5, 2, 1) SW_ROWS(7, 2, 1) SW_ROWS(7, 3, 1)
+    SW_ROWS(3, 0, 2) SW_ROWS(3, 1, 2) SW_ROWS(5, 0, 2) SW_ROWS(5, 1, 2) SW_ROWS(5, 2, 2) SW_ROWS(7, 1, 2) SW_ROWS(7, 2, 2) SW_ROWS(7, 3, 2)
 #undef SW_ROWS
     return hipErrorInvalidValue;
 }
@@ -310,7 +303,7 @@ bool pool_rows_supported(const float* x, int W, int R, int S, int stride, int pa
 {
     if ((stride != 1 && stride != 2) || R != S || (R != 2 && R != 3) || pad < 0 || pad > (R == 3 ? 1 : 0)) return false;
     if (R == 2 && stride == 1) return false;       // (no compiled variant; the direct kernel takes it)
-    return W >= 7 || (W % 4 == 0 && reinterpret_cast<uintptr_t>(x) % 16 == 0);
+    return W >= 7 || whole_quads(x, W);
 }
 
 hipError_t launch_pool_rows(const float* x, float* y, int64_t planes, int H, int W, int R, int stride, int pad,
@@ -318,7 +311,7 @@ hipError_t launch_pool_rows(const float* x, float* y, int64_t planes, int H, int
 {
 #define SW_POOL(RC, PC, SC)                                                                                    \
     if (R == RC && pad == PC && stride == SC) {                                                                \
-        const bool any = W % 4 != 0 || reinterpret_cast<uintptr_t>(x) % 16 != 0;                                \
+        const bool any = !whole_quads(x, W);                                \
         auto f = maximum ? any ? launch_rows<RC, RC, PC, SC, ROWS_MAX, true> : launch_rows<RC, RC, PC, SC, ROWS_MAX> \
                          : any ? launch_rows<RC, RC, PC, SC, ROWS_AVG, true> : launch_rows<RC, RC, PC, SC, ROWS_AVG>; \
         return f(x, nullptr, y, planes, 1, 1, H, W, Ho, Wo, st, Epilogue{nullptr, 0});                          \

@@ -95,3 +95,21 @@ def test_depthwise_routes(torch, sw, oracle, case):
     y = sw.sw_conv2d_depthwise_bias_relu(xd, wd, bd, stride, pad, True)
     z = torch.clamp(out + bd.view(1, -1, 1, 1), min=0)      # (one rounding on the same sum either way)
     assert torch.equal(y, z)
+
+
+@pytest.mark.parametrize("shift", [0, 1], ids=["aligned", "4-byte"])
+@pytest.mark.parametrize("W,filt", [
+    (W, f) for W in (9, 13, 29, 30, 31, 32, 61, 62, 63, 125, 126, 127, 129, 254, 257)
+    for f in ((3, 1, 0), (3, 1, 1), (3, 2, 1), (5, 1, 2), (5, 2, 1), (7, 1, 3), (7, 2, 3), (7, 2, 1)) if W < 200 or f[0] < 7
+], ids=lambda v: "x".join(map(str, v)) if isinstance(v, tuple) else str(v))
+def test_depthwise_any_width(torch, sw, oracle, W, filt, shift):
+    """Rows off the 16-byte grid: lane groups whose last columns are the next plane's padding, strips, the tensor's last row."""
+    R, stride, pad = filt
+    N, C, H = 2, 520, 3 if W > 200 else 7
+    x, w = inputs.normal_f32((N, C, H, W), 6700 + W), inputs.normal_f32((C, 1, R, R), 6800 + R)
+    y_ref, d = oracle.conv2d_depthwise(x, w, stride, pad)
+    buf, out, front, n, guard = guarded_empty(torch, y_ref.shape, torch.float32)
+    sw.sw_conv2d_depthwise(within_nan(torch, x, shift), torch.from_numpy(w).cuda(), stride, pad, out=out)
+    assert sw.sw_last_kernel().startswith(f"sliding_rows_kernel<{R},{R},{pad},"), sw.sw_last_kernel()
+    assert_f32_parity(out.cpu().numpy(), y_ref, d, f"{W} {filt}")
+    assert_guards_intact(buf, front, n, guard)
