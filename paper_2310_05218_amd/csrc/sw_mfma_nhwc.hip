@@ -21,6 +21,10 @@
 // B = filters: a lane of the result holds one output channel for 16 pixels, so a store instruction writes runs of
 // 32 consecutive channels, the fastest axis of the output.  LDS pitches: a pixel takes CB + 16 bytes, an output
 // channel's filters R*S*CB + 16 (+ what makes that 16 modulo 128).
+#include <algorithm>
+#include <cmath>
+#include <type_traits>
+
 #include "swconv_internal.h"
 
 namespace swconv {
@@ -288,6 +292,179 @@ __global__ __launch_bounds__(256) void direct_nhwc_kernel(const void* __restrict
     }
 }
 
+// Up to four input channels (the first layer of a network): 2 to 8 bytes a pixel are no K step of a matrix instruction.  The filters,
+// turned to [tap][channel][output channel], and the input rows under a band of output rows go to LDS as fp32, padding as zeros; a thread
+// owns eight consecutive output channels of PX consecutive pixels of a row, so that two 16-byte reads of filters feed 8 PX multiply-adds
+// and a wavefront stores whole runs of channels.  The sums run in the order of the one-thread-per-output kernel, to the same bits; that one
+// leaves taps in the padding out, which only an infinite or NaN filter value can tell from a product with zero: then the taps are tested.
+//
+// Measured (us, replayed graphs of ten, 3x3 at stride 2 on three channels, against one thread per output):
+// half, 4 x 210 x 198 to 64 channels 74.7 -> 10.3, 4 x 152 x 108 31.1 -> 8.4, 32 x 224 x 224 649 -> 45 (31 TFLOP/s), 7x7 on 8 x 224 x 224
+// 901 -> 62; fp32 4 x 152 x 108 33.6 -> 7.7.  Bound by the round trip in front of the barrier and, of small launches, a thread's chain of
+// LDS reads and multiply-adds; of large ones by those.
+struct FewNhwcParams {
+    Epilogue ep;
+    int H, W, C_out, R, S, stride, pad, dil, Ho, Wo, TH, bands, IH, pitch;      // pitch: floats of a framed input row
+    int octets, slots, groups;          // of output channels, threads with the same octet, groups of four pixels per output row
+    FastDiv by_pitch, by_octets, by_groups, by_bands, by_K;
+};
+
+template <int EK, int CI, int PX>
+__global__ __launch_bounds__(256) void few_channels_nhwc_kernel(const void* __restrict__ xv, const void* __restrict__ wv, void* __restrict__ yv,
+                                                                const FewNhwcParams P)
+{
+    extern __shared__ __attribute__((aligned(16))) float few_lds[];
+    const int tid = threadIdx.x, taps = P.R * P.S, K = taps * CI;
+    const int wp = P.C_out + 4;                     // (consecutive taps four banks apart: they arrive together)
+    float* ws = few_lds;                            // [K][wp]
+    float* xs = few_lds + K * wp;                   // [IH][pitch]
+    const int n = fast_div(blockIdx.x, P.by_bands), o0 = (blockIdx.x - n * P.bands) * P.TH;
+    auto value = [](const void* p, int64_t i) __attribute__((always_inline)) {
+        if constexpr (EK != kElemF32) return widen16<EK>(static_cast<const unsigned short*>(p)[i]);
+        else return static_cast<const float*>(p)[i];
+    };
+    const int slot = fast_div(tid, P.by_octets), co = 8 * (tid - slot * P.octets);
+    float bias[8] = {};
+    if (P.ep.bias && slot < P.slots) {
+#pragma unroll
+        for (int c = 0; c < 8; ++c) bias[c] = P.ep.bias[co + c];
+    }
+    // four input values and four filter values in flight per thread
+    const int64_t first = (int64_t)n * P.H * P.W * CI;
+    const int cells = P.IH * P.pitch, rowlen = P.W * CI, filters = K * P.C_out;
+    bool beyond = false;
+    for (int base = tid; base < max(cells, filters); base += 4 * 256) {
+        float v[4], f[4];
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+            const int i = base + 256 * u, r = fast_div(i, P.by_pitch), e = i - r * P.pitch - P.pad * CI, h = o0 * P.stride - P.pad + r;
+            v[u] = i < cells && h >= 0 && h < P.H && e >= 0 && e < rowlen ? value(xv, first + (int64_t)h * rowlen + e) : 0.f;
+            f[u] = i < filters ? value(wv, i) : 0.f;
+        }
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+            const int i = base + 256 * u;
+            if (i < cells) xs[i] = v[u];
+            if (i < filters) {
+                const int c = fast_div(i, P.by_K);
+                ws[(i - c * K) * wp + c] = f[u];
+                beyond |= !(fabsf(f[u]) < INFINITY);
+            }
+        }
+    }
+    const bool strict = __syncthreads_or(beyond) != 0;
+    if (slot >= P.slots) return;
+    const int items = min(P.TH, P.Ho - o0) * P.groups;
+    for (int it = slot; it < items; it += P.slots) {
+        const int tr = fast_div(it, P.by_groups), j0 = PX * (it - tr * P.groups), oi = o0 + tr;
+        float acc[PX][8] = {};
+        int at[PX];
+#pragma unroll
+        for (int j = 0; j < PX; ++j) at[j] = tr * P.stride * P.pitch + min(j0 + j, P.Wo - 1) * P.stride * CI;
+        auto sum = [&](auto tested) __attribute__((always_inline)) {
+            int k = 0;
+#pragma unroll 1
+            for (int r = 0; r < P.R; ++r)
+#pragma unroll 1
+                for (int q = 0; q < P.S; ++q) {
+                    const float* xp = xs + r * P.dil * P.pitch + q * P.dil * CI;
+                    bool in[PX];
+                    if constexpr (tested.value) {
+                        const int h = oi * P.stride + r * P.dil - P.pad;
+#pragma unroll
+                        for (int j = 0; j < PX; ++j) {
+                            const int v = (j0 + j) * P.stride + q * P.dil - P.pad;
+                            in[j] = h >= 0 && h < P.H && v >= 0 && v < P.W;
+                        }
+                    }
+#pragma unroll
+                    for (int ci = 0; ci < CI; ++ci, ++k) {
+                        const floatx4 a = *reinterpret_cast<const floatx4*>(ws + k * wp + co), b = *reinterpret_cast<const floatx4*>(ws + k * wp + co + 4);
+                        const float f[8] = {a.x, a.y, a.z, a.w, b.x, b.y, b.z, b.w};
+#pragma unroll
+                        for (int j = 0; j < PX; ++j) {
+                            const float v = xp[at[j] + ci];
+#pragma unroll
+                            for (int c = 0; c < 8; ++c) {
+                                const float s = fmaf(v, f[c], acc[j][c]);
+                                if constexpr (tested.value) acc[j][c] = in[j] ? s : acc[j][c];
+                                else acc[j][c] = s;
+                            }
+                        }
+                    }
+                }
+        };
+        if (strict) sum(std::true_type{});
+        else sum(std::false_type{});
+#pragma unroll
+        for (int j = 0; j < PX; ++j) {
+            if (j0 + j >= P.Wo) break;
+            const int64_t o = (((int64_t)n * P.Ho + oi) * P.Wo + j0 + j) * P.C_out + co;
+            float t[8];
+#pragma unroll
+            for (int c = 0; c < 8; ++c) {
+                t[c] = acc[j][c];
+                if (P.ep.bias) t[c] += bias[c];
+                if (P.ep.relu) t[c] = fmaxf(t[c], 0.f);
+            }
+            if constexpr (EK != kElemF32) {
+                intx4 v;
+#pragma unroll
+                for (int c = 0; c < 4; ++c) v[c] = (int)(round16<EK>(t[2 * c]) | (unsigned)round16<EK>(t[2 * c + 1]) << 16);
+                *reinterpret_cast<intx4*>(static_cast<unsigned short*>(yv) + o) = v;
+            } else {
+                *reinterpret_cast<floatx4*>(static_cast<float*>(yv) + o) = floatx4{t[0], t[1], t[2], t[3]};
+                *reinterpret_cast<floatx4*>(static_cast<float*>(yv) + o + 4) = floatx4{t[4], t[5], t[6], t[7]};
+            }
+        }
+    }
+}
+
+struct FewNhwcPlan {
+    FewNhwcParams P;
+    unsigned grid;
+    size_t lds;
+    int PX;
+    bool ok;
+};
+
+FewNhwcPlan plan_few_nhwc(const Conv2dShape& s, const void* y)
+{
+    FewNhwcPlan a{};
+    FewNhwcParams& P = a.P;
+    if (s.C_in > 4 || s.C_out % 8 != 0 || s.C_out > 256 || reinterpret_cast<uintptr_t>(y) % 16 != 0) return a;
+    const int64_t pitch = ((int64_t)(s.Wo - 1) * s.stride + (int64_t)(s.S - 1) * s.dil + 1) * s.C_in;
+    // (a launch of less is over sooner with one thread per output: 8 x 8 pixels, one channel to eight, 1x1 3.0 us against 3.8)
+    if ((double)s.N * s.Ho * s.Wo * s.C_out * s.R * s.S * s.C_in < 2e5) return a;
+    const int64_t filters = (int64_t)s.R * s.S * s.C_in * (s.C_out + 4), span = (int64_t)(s.R - 1) * s.dil + 1;
+    constexpr int64_t kFloats = 16 * 1024;          // 64 KB: two workgroups per CU
+    if (filters + span * pitch > kFloats) return a;
+    P.octets = s.C_out / 8;
+    P.slots = 256 / P.octets;
+    // four pixels a thread for long sums (7x7 on three channels 28.3 us against 36.5 with one, 8 images 62 against 78) and where a row is
+    // more than three turns of the workgroup at one (105 x 99 outputs of 64 channels 10.3 against 12.0), one otherwise (76 x 54 8.4 against
+    // 9.2, 32 x 32 of one image 5.4 against 7.9: half the latency of a thread's chain)
+    a.PX = s.R * s.S * s.C_in >= 64 || s.Wo > 3 * P.slots ? 4 : 1;
+    P.groups = (s.Wo + a.PX - 1) / a.PX;
+    // rows enough that every thread has an item, but not so many that the launch leaves CUs without a workgroup
+    int TH = std::max(1, std::min(s.Ho, P.slots / P.groups));
+    while (TH > 1 && (filters + ((TH - 1) * (int64_t)s.stride + span) * pitch > kFloats || (int64_t)s.N * ((s.Ho + TH - 1) / TH) < 512)) --TH;
+    P.TH = TH;
+    P.bands = (s.Ho + TH - 1) / TH;
+    P.IH = (int)((TH - 1) * (int64_t)s.stride + span);
+    P.pitch = (int)pitch;
+    const int64_t grid = (int64_t)s.N * P.bands;
+    if (grid * P.bands >= (1LL << 32) || grid > 2147483647LL) return a;         // (fast_div's range)
+    P.H = s.H; P.W = s.W; P.C_out = s.C_out; P.R = s.R; P.S = s.S; P.stride = s.stride; P.pad = s.pad; P.dil = s.dil;
+    P.Ho = s.Ho; P.Wo = s.Wo;
+    P.by_pitch = make_fastdiv(P.pitch); P.by_octets = make_fastdiv(P.octets); P.by_groups = make_fastdiv(P.groups);
+    P.by_bands = make_fastdiv(P.bands); P.by_K = make_fastdiv(s.R * s.S * s.C_in);
+    a.grid = (unsigned)grid;
+    a.lds = (size_t)(filters + P.IH * pitch) * 4;
+    a.ok = true;
+    return a;
+}
+
 struct NhwcFPlan {
     NhwcFParams P;
     size_t lds;
@@ -386,6 +563,28 @@ hipError_t launch_mfma_nhwc(const void* x, const void* w, void* y, const Conv2dS
     if (ek == kElemBF16) SW_NHWC(kElemBF16);
     SW_NHWC(kElemF32);
 #undef SW_NHWC
+}
+
+bool few_channels_nhwc_supported(const void* y, const Conv2dShape& s) { return plan_few_nhwc(s, y).ok; }
+
+hipError_t launch_few_channels_nhwc(const void* x, const void* w, void* y, const Conv2dShape& s, int ek, const Epilogue& ep, hipStream_t st)
+{
+    FewNhwcPlan a = plan_few_nhwc(s, y);
+    if (!a.ok) return hipErrorInvalidValue;
+    a.P.ep = ep;
+#define SW_FEW2(E, C, X)                                                                                                   \
+    if (ek == E && s.C_in == C && a.PX == X) {                                                                             \
+        SW_NOTED_LAUNCH(note_kernel("few_channels_nhwc_kernel", (int)(E), (int)(C), (int)(X)), (few_channels_nhwc_kernel<E, C, X>), dim3(a.grid), dim3(256), \
+                        a.lds, st, x, w, y, a.P);                                                                          \
+        return hipGetLastError();                                                                                          \
+    }
+#define SW_FEW(E, C) SW_FEW2(E, C, 1) SW_FEW2(E, C, 4)
+    SW_FEW(kElemF32, 1) SW_FEW(kElemF32, 2) SW_FEW(kElemF32, 3) SW_FEW(kElemF32, 4)
+    SW_FEW(kElemBF16, 1) SW_FEW(kElemBF16, 2) SW_FEW(kElemBF16, 3) SW_FEW(kElemBF16, 4)
+    SW_FEW(kElemF16, 1) SW_FEW(kElemF16, 2) SW_FEW(kElemF16, 3) SW_FEW(kElemF16, 4)
+#undef SW_FEW
+#undef SW_FEW2
+    return hipErrorInvalidValue;
 }
 
 hipError_t launch_direct_nhwc(const void* x, const void* w, void* y, const Conv2dShape& s, int ek, const Epilogue& ep,

@@ -387,6 +387,7 @@ static int run_nhwc(const void* x, const void* w, const float* bias, void* y, in
     if (!force_direct() && esz == 2 && mfma_bf16_nhwc_direct_supported(x, w, y, s))
         return launch_status(launch_mfma_bf16_nhwc_direct(x, w, y, s, ek == kElemF16, ep, st));
     if (!force_direct() && mfma_nhwc_supported(x, w, s, ek)) return launch_status(launch_mfma_nhwc(x, w, y, s, ek, ep, st));
+    if (!force_direct() && few_channels_nhwc_supported(y, s)) return launch_status(launch_few_channels_nhwc(x, w, y, s, ek, ep, st));
     return launch_status(launch_direct_nhwc(x, w, y, s, ek, ep, st));
 }
 

@@ -215,6 +215,8 @@ hipError_t launch_mfma_s8_nhwc_lds(const int8_t* x, const int8_t* w, void* y, co
 // aligned tensors)
 bool       mfma_s8_pointwise_nhwc_supported(const int8_t* x, const int8_t* w, const int8_t* y, const Conv2dShape& s);
 hipError_t launch_mfma_s8_pointwise_nhwc(const int8_t* x, const int8_t* w, int8_t* y, const Requant& rq, const Conv2dShape& s, hipStream_t st);
+bool few_channels_nhwc_supported(const void* y, const Conv2dShape& s);
+hipError_t launch_few_channels_nhwc(const void* x, const void* w, void* y, const Conv2dShape& s, int ek, const Epilogue& ep, hipStream_t st);
 hipError_t launch_direct_nhwc(const void* x, const void* w, void* y, const Conv2dShape& s, int ek, const Epilogue& ep,
                               hipStream_t st);
 
