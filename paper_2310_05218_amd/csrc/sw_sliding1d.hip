@@ -17,15 +17,18 @@ namespace swconv {
 namespace {
 
 typedef float floatx4 __attribute__((ext_vector_type(4)));
+typedef float floatx4u __attribute__((ext_vector_type(4), aligned(4)));
 
-// Inputs are read once and outputs written once: both bypass the caches' retention (nontemporal).
-__device__ __forceinline__ floatx4 stream_load4(const float* p) { return __builtin_nontemporal_load(reinterpret_cast<const floatx4*>(p)); }
+// Inputs are read once and outputs written once: both bypass the caches' retention (nontemporal).  Input rows may begin at any 4-byte
+// address (rows of a length that is no multiple of four came in by 4-byte loads, a round trip each: 128 x 65535 under 9
+// taps 17.6 us, 10.8 now; 33 x 51229 under a maximum of 22 8.1, 6.0).
+__device__ __forceinline__ floatx4 stream_load4(const float* p) { return __builtin_nontemporal_load(reinterpret_cast<const floatx4u*>(p)); }
 __device__ __forceinline__ void stream_store4(float* p, floatx4 v) { __builtin_nontemporal_store(v, reinterpret_cast<floatx4*>(p)); }
 
 constexpr int kThreads = 256;
 constexpr int kSub = kThreads * 4;      // outputs per pass over the workgroup
 constexpr int kPasses = 4;
-constexpr int kTile = kSub * kPasses;   // outputs per workgroup
+constexpr int kTile = kSub * kPasses;   // outputs per workgroup (fewer passes where the launch would leave CUs idle)
 constexpr int kMaxK = 64;
 constexpr int kMaxBlocks = 256 * 32;     // workgroups per launch; beyond that a workgroup walks over several tiles
 constexpr int kLdsIn = kTile + kMaxK + 16;  // tile + halo + alignment offset + read-ahead, multiple of 4
@@ -82,11 +85,12 @@ __device__ __forceinline__ void slide4(const float* __restrict__ src, const floa
 // Both passes of a lane over the staged tile, for one register offset SH.
 template <int OP, int KC, int SH>
 __device__ __forceinline__ void tile_outputs(const float* __restrict__ s_in, const float* __restrict__ w, int k,
-                                             float* __restrict__ yrow, int o0, int o_end, int tid)
+                                             float* __restrict__ yrow, int o0, int o_end, int tid, int passes)
 {
     const float inv_k = 1.0f / (float)k;
 #pragma unroll
     for (int pass = 0; pass < kPasses; ++pass) {
+        if (pass >= passes) break;
         const int q = pass * kSub + 4 * tid;           // first of this lane's four outputs, tile-relative
         const int o = o0 + q;                          // ... and row-relative (may be < 0 in the first tile)
         if (o + 3 < 0 || o >= o_end) continue;
@@ -120,7 +124,7 @@ struct Tile1D {
 };
 
 __device__ __forceinline__ Tile1D tile_geometry(const float* x, float* y, int tile_id, int tiles_per_row,
-                                                int len, int len_out, int k, int pad)
+                                                int len, int len_out, int k, int pad, int tile_len)
 {
     Tile1D g;
     const int row = tile_id / tiles_per_row;          // (tile counts are checked to fit 31 bits on the host)
@@ -128,16 +132,16 @@ __device__ __forceinline__ Tile1D tile_geometry(const float* x, float* y, int ti
     g.xr = x + (int64_t)row * len;
     g.yrow = y + (int64_t)row * len_out;
     // Outputs are grouped so that every group of four starts on a 16-byte boundary in memory: with `a` the
-    // misalignment (in floats) of the row's first output, the tile owns outputs o0 .. o0 + kTile - 1 with
-    // o0 = tile * kTile - a.
+    // misalignment (in floats) of the row's first output, the tile owns outputs o0 .. o0 + tile_len - 1 with
+    // o0 = tile * tile_len - a.
     const int a = (int)((reinterpret_cast<uintptr_t>(g.yrow) >> 2) & 3);
-    g.o0 = tile * kTile - a;
+    g.o0 = tile * tile_len - a;
     // LDS element e holds input position t0 + e; t0 is a multiple of 4 so that 16-byte global loads stay
     // aligned.  Output o0 + q reads inputs from position o0 + q - pad, i.e. LDS element q + sh.
     const int lead = (a + pad + 3) & ~3;
     g.sh = lead - a - pad;
-    g.t0 = tile * kTile - lead;
-    g.o_end = min(g.o0 + kTile, len_out);
+    g.t0 = tile * tile_len - lead;
+    g.o_end = min(g.o0 + tile_len, len_out);
     g.n_in4 = ((g.o_end - g.o0) + k - 1 + g.sh + 3) >> 2;
     return g;
 }
@@ -169,51 +173,40 @@ __global__ __launch_bounds__(kThreads) void sliding_1d_kernel(const float* __res
                                                               const float* __restrict__ w,
                                                               float* __restrict__ y, int len,
                                                               int len_out, int k_rt, int pad,
-                                                              int tiles_per_row, int tiles, int x_vec_ok)
+                                                              int tiles_per_row, int tiles, int passes)
 {
     __shared__ __attribute__((aligned(16))) float s_in[kLdsIn];
 
     const int k = KC > 0 ? KC : k_rt;
     const int tid = threadIdx.x;
     int tile_id = blockIdx.x;
-    Tile1D g = tile_geometry(x, y, tile_id, tiles_per_row, len, len_out, k, pad);
+    Tile1D g = tile_geometry(x, y, tile_id, tiles_per_row, len, len_out, k, pad, kSub * passes);
 
     floatx4 pre[kPre];
-    if (x_vec_ok) {
+#pragma unroll
+    for (int i = 0; i < kPre; ++i)
+        if (tid + i * kThreads < g.n_in4) pre[i] = load_group(g.xr, g.t0 + 4 * (tid + i * kThreads), len);
+    while (true) {
 #pragma unroll
         for (int i = 0; i < kPre; ++i)
-            if (tid + i * kThreads < g.n_in4) pre[i] = load_group(g.xr, g.t0 + 4 * (tid + i * kThreads), len);
-    }
-    while (true) {
-        if (x_vec_ok) {
-#pragma unroll
-            for (int i = 0; i < kPre; ++i)
-                if (tid + i * kThreads < g.n_in4) *reinterpret_cast<floatx4*>(s_in + 4 * (tid + i * kThreads)) = pre[i];
-        } else {
-            for (int e = tid; e < 4 * g.n_in4; e += kThreads) {
-                const int t = g.t0 + e;
-                s_in[e] = (t >= 0 && t < len) ? g.xr[t] : 0.f;
-            }
-        }
+            if (tid + i * kThreads < g.n_in4) *reinterpret_cast<floatx4*>(s_in + 4 * (tid + i * kThreads)) = pre[i];
         lds_barrier();
 
         const int next_id = tile_id + (int)gridDim.x;
         const bool more = next_id < tiles;
         Tile1D gn = g;
         if (more) {
-            gn = tile_geometry(x, y, next_id, tiles_per_row, len, len_out, k, pad);
-            if (x_vec_ok) {
+            gn = tile_geometry(x, y, next_id, tiles_per_row, len, len_out, k, pad, kSub * passes);
 #pragma unroll
-                for (int i = 0; i < kPre; ++i)
-                    if (tid + i * kThreads < gn.n_in4) pre[i] = load_group(gn.xr, gn.t0 + 4 * (tid + i * kThreads), len);
-            }
+            for (int i = 0; i < kPre; ++i)
+                if (tid + i * kThreads < gn.n_in4) pre[i] = load_group(gn.xr, gn.t0 + 4 * (tid + i * kThreads), len);
         }
 
         switch (g.sh) {
-            case 0: tile_outputs<OP, KC, 0>(s_in, w, k, g.yrow, g.o0, g.o_end, tid); break;
-            case 1: tile_outputs<OP, KC, 1>(s_in, w, k, g.yrow, g.o0, g.o_end, tid); break;
-            case 2: tile_outputs<OP, KC, 2>(s_in, w, k, g.yrow, g.o0, g.o_end, tid); break;
-            default: tile_outputs<OP, KC, 3>(s_in, w, k, g.yrow, g.o0, g.o_end, tid); break;
+            case 0: tile_outputs<OP, KC, 0>(s_in, w, k, g.yrow, g.o0, g.o_end, tid, passes); break;
+            case 1: tile_outputs<OP, KC, 1>(s_in, w, k, g.yrow, g.o0, g.o_end, tid, passes); break;
+            case 2: tile_outputs<OP, KC, 2>(s_in, w, k, g.yrow, g.o0, g.o_end, tid, passes); break;
+            default: tile_outputs<OP, KC, 3>(s_in, w, k, g.yrow, g.o0, g.o_end, tid, passes); break;
         }
         if (!more) break;
         lds_barrier();      // every lane is done reading this tile before the next one is written
@@ -226,17 +219,20 @@ template <int OP>
 hipError_t launch_op(const float* x, const float* w, float* y, int64_t rows, int len, int len_out, int k,
                      int pad, hipStream_t st)
 {
-    // up to three outputs of misalignment per row are absorbed by the first tile
-    const int tiles_per_row = (len_out + 3 + kTile - 1) / kTile;
+    // Four passes over a tile where that gives two workgroups per CU, else shorter tiles (us, 22 taps: 4 x 36032 6.1 -> 4.2,
+    // 2 x 131072 6.1 -> 4.3; 9 taps 16 x 8192 4.1 -> 3.6; at 1024 four-pass tiles, 64 x 65536, the passes make no difference).
+    // (Up to three outputs of misalignment per row are absorbed by the first tile.)
+    int passes = kPasses;
+    while (passes > 1 && rows * ((len_out + 3LL + kSub * passes - 1) / (kSub * passes)) < 512) passes /= 2;
+    const int tiles_per_row = (int)((len_out + 3LL + kSub * passes - 1) / (kSub * passes));
     const int64_t tiles = rows * tiles_per_row;
     // enough workgroups to fill the chip several times over in flight, each walking over >= 1 tiles
     const int64_t blocks = tiles < kMaxBlocks ? tiles : kMaxBlocks;
-    const int x_vec_ok = (reinterpret_cast<uintptr_t>(x) % 16 == 0) && (len % 4 == 0 || rows == 1);
     dim3 grid((unsigned)blocks), block(kThreads);
 #define SW_CASE(KC)                                                                                      \
     case KC:                                                                                             \
         SW_NOTED_LAUNCH(note_kernel("sliding_1d_kernel", (int)(OP), (int)(KC)), (sliding_1d_kernel<OP, KC>), grid, block, 0, st, x, w, y, len, len_out, k,    \
-                           pad, tiles_per_row, (int)tiles, x_vec_ok);                                    \
+                           pad, tiles_per_row, (int)tiles, passes);                                    \
         break;
     switch (k) {
         SW_CASE(2) SW_CASE(3) SW_CASE(4) SW_CASE(5) SW_CASE(6) SW_CASE(7) SW_CASE(8) SW_CASE(9)
@@ -244,7 +240,7 @@ hipError_t launch_op(const float* x, const float* w, float* y, int64_t rows, int
         SW_CASE(25) SW_CASE(32) SW_CASE(33) SW_CASE(49) SW_CASE(64)
         default:
             SW_NOTED_LAUNCH(note_kernel("sliding_1d_kernel", (int)(OP), (int)(0)), (sliding_1d_kernel<OP, 0>), grid, block, 0, st, x, w, y, len, len_out, k, pad,
-                               tiles_per_row, (int)tiles, x_vec_ok);
+                               tiles_per_row, (int)tiles, passes);
     }
 #undef SW_CASE
     return hipGetLastError();
