@@ -39,13 +39,14 @@ struct Entries {
 Entries g_entry;
 constexpr int kEntries = sizeof(Entries) / sizeof(void*);
 bool g_bound = false;
+bool g_host = false;        // bound to entry points that work on host memory, without a stream
 
 // a contiguous tensor on the GPU of that type and number of dimensions, or null
 const at::Tensor* tensor(PyObject* o, at::ScalarType type, int dims)
 {
     if (!THPVariable_CheckExact(o)) return nullptr;
     const at::Tensor& t = THPVariable_Unpack(o);
-    return t.is_cuda() && t.scalar_type() == type && t.dim() == dims && t.is_contiguous() ? &t : nullptr;
+    return (g_host ? t.is_cpu() : t.is_cuda()) && t.scalar_type() == type && t.dim() == dims && t.is_contiguous() ? &t : nullptr;
 }
 
 // an exact Python integer within int
@@ -81,24 +82,41 @@ bool fits(const at::Tensor& t)
     return true;
 }
 
+// without the interpreter's lock, which is taken back however the scope ends
+class Unlocked {
+    PyThreadState* const state_ = PyEval_SaveThread();
+
+public:
+    Unlocked() = default;
+    Unlocked(const Unlocked&) = delete;
+    ~Unlocked() { PyEval_RestoreThread(state_); }
+};
+
+// f(output, stream): the entry point on addresses that were taken before (one that there is not, of a transformed tensor, raises as it is)
 template <class F>
 PyObject* call(const at::Tensor& x, at::IntArrayRef shape, at::ScalarType type, F&& f)
 {
     for (int64_t d : shape)
         if (d <= 0) return nullptr;
     at::Tensor y = at::empty(shape, x.options().dtype(type));
-    if (!y.is_cuda()) return nullptr;
+    if (g_host ? !y.is_cpu() : !y.is_cuda()) return nullptr;
     void* const out = y.mutable_data_ptr();
-    void* const stream = c10::hip::getCurrentHIPStream().stream();
+    void* const stream = g_host ? nullptr : static_cast<void*>(c10::hip::getCurrentHIPStream().stream());
     int rc;
-    Py_BEGIN_ALLOW_THREADS
-    rc = f(out, stream);
-    Py_END_ALLOW_THREADS
+    {
+        const Unlocked unlocked;
+        rc = f(out, stream);
+    }
     return rc == SW_OK ? THPVariable_Wrap(std::move(y)) : PyLong_FromLong(rc);
 }
 
-template <class T>
-const T* ptr(const at::Tensor* t) { return t ? static_cast<const T*>(t->const_data_ptr()) : nullptr; }
+// the address of a tensor's memory, whatever an entry point takes it for
+struct Address {
+    const void* p;
+    Address(const at::Tensor* t) : p(t ? t->const_data_ptr() : nullptr) {}
+    template <class T>
+    operator const T*() const { return static_cast<const T*>(p); }
+};
 
 // null: not taken
 PyObject* run_op(int op, PyObject* const* a, Py_ssize_t n)
@@ -120,22 +138,25 @@ PyObject* run_op(int op, PyObject* const* a, Py_ssize_t n)
         if (!x || !w || !ints(2) || !fits(*w)) return nullptr;
         const int64_t rows = x->size(0), len = x->size(1);
         const int k = (int)w->size(0);
+        const Address xa(x), wa(w);
         return call(*x, {rows, extent(len, k, i[0], i[1], 1)}, f32,
-                    [&](void* y, void* st) { return g_entry.conv1d(ptr<float>(x), ptr<float>(w), (float*)y, rows, len, k, i[0], i[1], st); });
+                    [&](void* y, void* st) { return g_entry.conv1d(xa, wa, (float*)y, rows, len, k, i[0], i[1], st); });
     }
     if (op == kPool1d) {
         const at::Tensor* x = tensor(px, f32, 2);
         if (!x || !ints(3)) return nullptr;
         const int64_t rows = x->size(0), len = x->size(1);
+        const Address xa(x);
         return call(*x, {rows, extent(len, i[0], i[1], 0, 1)}, f32,
-                    [&](void* y, void* st) { return g_entry.pool1d(ptr<float>(x), (float*)y, rows, len, i[0], i[1], i[2], st); });
+                    [&](void* y, void* st) { return g_entry.pool1d(xa, (float*)y, rows, len, i[0], i[1], i[2], st); });
     }
     if (op == kPool2d) {
         const at::Tensor* x = tensor(px, f32, 4);
         if (!x || !ints(5) || !fits(*x)) return nullptr;
         const auto d = x->sizes();
+        const Address xa(x);
         return call(*x, {d[0], d[1], extent(d[2], i[0], i[2], i[3], 1), extent(d[3], i[1], i[2], i[3], 1)}, f32, [&](void* y, void* st) {
-            return g_entry.pool2d(ptr<float>(x), (float*)y, (int)d[0], (int)d[1], (int)d[2], (int)d[3], i[0], i[1], i[2], i[3], i[4], st);
+            return g_entry.pool2d(xa, (float*)y, (int)d[0], (int)d[1], (int)d[2], (int)d[3], i[0], i[1], i[2], i[3], i[4], st);
         });
     }
     if (op == kConv2d || op == kBiasRelu || op == kDilated || op == kS8 || op == kS8Requant) {
@@ -155,13 +176,14 @@ PyObject* run_op(int op, PyObject* const* a, Py_ssize_t n)
             if (pb != Py_None && (!(b = tensor(pb, q ? s32 : f32, 1)) || b->size(0) != K)) return nullptr;
             if (q && (!(sc = tensor(ps, f32, 1)) || sc->size(0) != K)) return nullptr;
         }
+        const Address xa(x), wa(w), ba(b), sa(sc);
         return call(*x, {N, K, extent(H, R, i[0], i[1], dil), extent(W, S, i[0], i[1], dil)}, op == kS8 ? s32 : op == kS8Requant ? s8 : f32, [&](void* y, void* st) {
             switch (op) {
-            case kConv2d: return g_entry.conv2d(ptr<float>(x), ptr<float>(w), (float*)y, N, C, K, H, W, R, S, i[0], i[1], st);
-            case kBiasRelu: return g_entry.bias_relu(ptr<float>(x), ptr<float>(w), ptr<float>(b), (float*)y, N, C, K, H, W, R, S, i[0], i[1], relu, st);
-            case kDilated: return g_entry.dilated(ptr<float>(x), ptr<float>(w), (float*)y, N, C, K, H, W, R, S, i[0], i[1], dil, st);
-            case kS8: return g_entry.s8(ptr<int8_t>(x), ptr<int8_t>(w), (int32_t*)y, N, C, K, H, W, R, S, i[0], i[1], st);
-            default: return g_entry.s8_requant(ptr<int8_t>(x), ptr<int8_t>(w), ptr<int32_t>(b), ptr<float>(sc), (int8_t*)y, N, C, K, H, W, R, S, i[0], i[1], relu, st);
+            case kConv2d: return g_entry.conv2d(xa, wa, (float*)y, N, C, K, H, W, R, S, i[0], i[1], st);
+            case kBiasRelu: return g_entry.bias_relu(xa, wa, ba, (float*)y, N, C, K, H, W, R, S, i[0], i[1], relu, st);
+            case kDilated: return g_entry.dilated(xa, wa, (float*)y, N, C, K, H, W, R, S, i[0], i[1], dil, st);
+            case kS8: return g_entry.s8(xa, wa, (int32_t*)y, N, C, K, H, W, R, S, i[0], i[1], st);
+            default: return g_entry.s8_requant(xa, wa, ba, sa, (int8_t*)y, N, C, K, H, W, R, S, i[0], i[1], relu, st);
             }
         });
     }
@@ -178,11 +200,12 @@ PyObject* run_op(int op, PyObject* const* a, Py_ssize_t n)
             if (ni < 3 || !flag(a[6], &relu)) return nullptr;
             if (pb != Py_None && (!(b = tensor(pb, f32, 1)) || b->size(0) != C)) return nullptr;
         }
+        const Address xa(x), wa(w), ba(b);
         return call(*x, {N, C, extent(H, R, i[0], i[1], 1), extent(W, S, i[0], i[1], 1)}, type, [&](void* y, void* st) {
             switch (op) {
-            case kDepthwise: return g_entry.depthwise(ptr<float>(x), ptr<float>(w), (float*)y, N, C, H, W, R, S, i[0], i[1], st);
-            case kDepthwiseBiasRelu: return g_entry.depthwise_bias_relu(ptr<float>(x), ptr<float>(w), ptr<float>(b), (float*)y, N, C, H, W, R, S, i[0], i[1], relu, st);
-            default: return g_entry.depthwise_bf16(ptr<unsigned short>(x), ptr<float>(w), (unsigned short*)y, N, C, H, W, R, S, i[0], i[1], st);
+            case kDepthwise: return g_entry.depthwise(xa, wa, (float*)y, N, C, H, W, R, S, i[0], i[1], st);
+            case kDepthwiseBiasRelu: return g_entry.depthwise_bias_relu(xa, wa, ba, (float*)y, N, C, H, W, R, S, i[0], i[1], relu, st);
+            default: return g_entry.depthwise_bf16(xa, wa, (unsigned short*)y, N, C, H, W, R, S, i[0], i[1], st);
             }
         });
     }
@@ -201,14 +224,15 @@ PyObject* run_op(int op, PyObject* const* a, Py_ssize_t n)
         const bool q = op == kS8Nhwc && ps != Py_None;
         if (q && (!(sc = tensor(ps, f32, 1)) || sc->size(0) != K)) return nullptr;
         if ((q || op == kNhwc) && pb != Py_None && (!(b = tensor(pb, q ? s32 : f32, 1)) || b->size(0) != K)) return nullptr;
+        const Address xa(x), wa(w), ba(b), sa(sc);
         const auto out = op == kNhwc ? type : q ? s8 : s32;
         return call(*x, {N, extent(H, R, i[0], i[1], i[2]), extent(W, S, i[0], i[1], i[2]), K}, out, [&](void* y, void* st) {
             if (op == kS8Nhwc)
-                return q ? g_entry.s8_nhwc_requant(ptr<int8_t>(x), ptr<int8_t>(w), ptr<int32_t>(b), ptr<float>(sc), (int8_t*)y, N, H, W, C, K, R, S, i[0], i[1], relu, st)
-                         : g_entry.s8_nhwc(ptr<int8_t>(x), ptr<int8_t>(w), (int32_t*)y, N, H, W, C, K, R, S, i[0], i[1], st);
-            if (type == f32) return g_entry.nhwc(ptr<float>(x), ptr<float>(w), ptr<float>(b), (float*)y, N, H, W, C, K, R, S, i[0], i[1], i[2], relu, st);
-            if (type == bf16) return g_entry.bf16_nhwc(x->const_data_ptr(), w->const_data_ptr(), ptr<float>(b), y, N, H, W, C, K, R, S, i[0], i[1], i[2], relu, st);
-            return g_entry.f16_nhwc(x->const_data_ptr(), w->const_data_ptr(), ptr<float>(b), y, N, H, W, C, K, R, S, i[0], i[1], i[2], relu, st);
+                return q ? g_entry.s8_nhwc_requant(xa, wa, ba, sa, (int8_t*)y, N, H, W, C, K, R, S, i[0], i[1], relu, st)
+                         : g_entry.s8_nhwc(xa, wa, (int32_t*)y, N, H, W, C, K, R, S, i[0], i[1], st);
+            if (type == f32) return g_entry.nhwc(xa, wa, ba, (float*)y, N, H, W, C, K, R, S, i[0], i[1], i[2], relu, st);
+            if (type == bf16) return g_entry.bf16_nhwc(xa, wa, ba, y, N, H, W, C, K, R, S, i[0], i[1], i[2], relu, st);
+            return g_entry.f16_nhwc(xa, wa, ba, y, N, H, W, C, K, R, S, i[0], i[1], i[2], relu, st);
         });
     }
     return nullptr;
@@ -228,9 +252,12 @@ PyObject* run(PyObject*, PyObject* const* a, Py_ssize_t n)
     Py_RETURN_NONE;
 }
 
-// bind(addresses of the entry points in the order of Entries)
-PyObject* bind(PyObject*, PyObject* addresses)
+// bind(addresses of the entry points in the order of Entries, host = False); host: entry points for tensors in host memory, as tests have them
+PyObject* bind(PyObject*, PyObject* args)
 {
+    PyObject* addresses;
+    int host = 0;
+    if (!PyArg_ParseTuple(args, "O|p", &addresses, &host)) return nullptr;
     if (!PyTuple_CheckExact(addresses) || PyTuple_GET_SIZE(addresses) != kEntries) {
         PyErr_SetString(PyExc_ValueError, "one address per entry point");
         return nullptr;
@@ -245,13 +272,14 @@ PyObject* bind(PyObject*, PyObject* addresses)
     }
     static_assert(sizeof p == sizeof g_entry, "entries are addresses");
     std::memcpy(&g_entry, p, sizeof g_entry);
+    g_host = host != 0;
     g_bound = true;
     Py_RETURN_NONE;
 }
 
 PyMethodDef kMethods[] = {
     {"run", reinterpret_cast<PyCFunction>(reinterpret_cast<void (*)()>(run)), METH_FASTCALL, nullptr},
-    {"bind", bind, METH_O, nullptr},
+    {"bind", bind, METH_VARARGS, nullptr},
     {nullptr, nullptr, 0, nullptr},
 };
 PyModuleDef kModule = {PyModuleDef_HEAD_INIT, "_swnative", nullptr, -1, kMethods, nullptr, nullptr, nullptr, nullptr};

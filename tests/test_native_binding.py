@@ -77,6 +77,16 @@ def test_on_the_gpu(monkeypatch):
 
 
 @pytest.mark.gpu
+def test_transformed_tensors_raise():
+    """A tensor without memory of its own is no argument of a kernel: what torch says of it, and the next call is an ordinary one."""
+    x, w = torch.randn(2, 8, 12, 14, device="cuda"), torch.randn(16, 8, 3, 3, device="cuda")
+    for _ in range(2):
+        with pytest.raises(RuntimeError, match="storage"):
+            torch.vmap(lambda a: sw.sw_conv2d(a, w, 1, 1))(x[None])
+    assert sw.sw_conv2d(x, w, 1, 1).shape == (2, 16, 12, 14)
+
+
+@pytest.mark.gpu
 def test_current_stream_and_threads():
     """The call goes to the current stream of its thread; several threads call at once."""
     import threading
