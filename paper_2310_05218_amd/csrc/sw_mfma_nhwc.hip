@@ -437,7 +437,7 @@ FewNhwcPlan plan_few_nhwc(const Conv2dShape& s, const void* y)
     // (a launch of less is over sooner with one thread per output: 8 x 8 pixels, one channel to eight, 1x1 3.0 us against 3.8)
     if ((double)s.N * s.Ho * s.Wo * s.C_out * s.R * s.S * s.C_in < 2e5) return a;
     const int64_t filters = (int64_t)s.R * s.S * s.C_in * (s.C_out + 4), span = (int64_t)(s.R - 1) * s.dil + 1;
-    constexpr int64_t kFloats = 16 * 1024;          // 64 KB: two workgroups per CU
+    constexpr int64_t kFloats = 16 * 1024;          // 64 KB beside the 256 bytes of __syncthreads_or: two workgroups per CU
     if (filters + span * pitch > kFloats) return a;
     P.octets = s.C_out / 8;
     P.slots = 256 / P.octets;
@@ -572,8 +572,12 @@ hipError_t launch_few_channels_nhwc(const void* x, const void* w, void* y, const
     FewNhwcPlan a = plan_few_nhwc(s, y);
     if (!a.ok) return hipErrorInvalidValue;
     a.P.ep = ep;
+    // (with the kernel's own 256 bytes a plan may come to more than the 64 KB that a launch has unasked)
 #define SW_FEW2(E, C, X)                                                                                                   \
     if (ek == E && s.C_in == C && a.PX == X) {                                                                             \
+        static const hipError_t attr = hipFuncSetAttribute(reinterpret_cast<const void*>(few_channels_nhwc_kernel<E, C, X>),  \
+                                                           hipFuncAttributeMaxDynamicSharedMemorySize, 64 * 1024);         \
+        if (attr != hipSuccess) return attr;                                                                               \
         SW_NOTED_LAUNCH(note_kernel("few_channels_nhwc_kernel", (int)(E), (int)(C), (int)(X)), (few_channels_nhwc_kernel<E, C, X>), dim3(a.grid), dim3(256), \
                         a.lds, st, x, w, y, a.P);                                                                          \
         return hipGetLastError();                                                                                          \

@@ -80,3 +80,15 @@ def test_few_channels_special_values(torch, sw, value, where):
     y, z = both(torch, lambda out: sw.sw_conv2d_nhwc(xd, wd, 2, 1, out=out), (2, 17, 21, 64), torch.float32)
     assert torch.equal(y.isnan(), z.isnan()) and torch.equal(torch.nan_to_num(y), torch.nan_to_num(z))
     assert not bool(torch.isfinite(y).all()) and bool(torch.isfinite(y).any())
+
+
+@pytest.mark.parametrize("W,takes", [(16372, True), (16373, False)])
+@pytest.mark.parametrize("ek", [0, 1, 2], ids=["f32", "bf16", "f16"])
+def test_few_channels_fill_the_lds(torch, sw, oracle, ek, W, takes):
+    """Filters (a row of eight floats and four to pad it) and an input row to the last float of 64 KB, and one more: one thread per output."""
+    dtype = (torch.float32, torch.bfloat16, torch.float16)[ek]
+    x = torch.from_numpy(inputs.normal_f32((1, 2, W, 1), 7600)).cuda().to(dtype)
+    w = torch.from_numpy(inputs.normal_f32((8, 1, 1, 1), 7700)).cuda().to(dtype)
+    y = (sw.sw_conv2d_nhwc, sw.sw_conv2d_bf16_nhwc, sw.sw_conv2d_f16_nhwc)[ek](x, w)
+    assert sw.sw_last_kernel() == (f"few_channels_nhwc_kernel<{ek},1,4>" if takes else f"direct_nhwc_kernel<{ek}>")
+    assert torch.equal(y, (x.float() * w.float().view(8)).to(dtype))       # (a sum of one product is that product, rounded once)
