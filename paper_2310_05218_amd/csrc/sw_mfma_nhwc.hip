@@ -420,6 +420,24 @@ __global__ __launch_bounds__(256) void few_channels_nhwc_kernel(const void* __re
     }
 }
 
+// us of a launch with filters and rows in LDS, and of one with a thread per output, fitted to 11151 drawn layers of both (1 to 32 images, 1 to 2000
+// rows and columns, 1 to 121 taps, strides 1 to 16, 8 to 256 output channels; both within 18 and 19 % of what was measured, 2-norm).  The
+// first pays for a workgroup's filters a thousand at a time and for a thread's chain of products, however few outputs share them.
+double few_nhwc_us(const FewNhwcParams& P, int PX, int64_t K, int64_t grid, size_t lds)
+{
+    const double fill = (double)std::max<int64_t>((int64_t)P.IH * P.pitch, K * P.C_out);
+    const double chain = (double)K * ((P.TH * P.groups + P.slots - 1) / P.slots);
+    const double at_once = 256.0 * std::max<int64_t>(1, std::min<int64_t>(160 * 1024 / (int64_t)(lds + 256), PX == 4 ? 4 : 8));
+    return 3.2 + std::ceil(grid / at_once) * (0.76 * std::ceil(fill / 1024) + (PX == 4 ? 0.084 : 0.033) * chain) +
+           std::ceil(grid / 256.0) * (1.3e-5 * fill + (PX == 4 ? 0.044 : 0.0115) * chain + 0.42);
+}
+double one_per_output_nhwc_us(const Conv2dShape& s)
+{
+    // (taps outside the image cost a test)
+    const double taps = (double)std::min(s.R, (s.H + s.dil - 1) / s.dil) * std::min(s.S, (s.W + s.dil - 1) / s.dil), K = taps * s.C_in;
+    return 2.7 + 0.072 * K + 0.059 * s.R * s.S + 0.88e-6 * ((double)s.N * s.Ho * s.Wo * s.C_out) * (K + 1.8);
+}
+
 struct FewNhwcPlan {
     FewNhwcParams P;
     unsigned grid;
@@ -434,8 +452,6 @@ FewNhwcPlan plan_few_nhwc(const Conv2dShape& s, const void* y)
     FewNhwcParams& P = a.P;
     if (s.C_in > 4 || s.C_out % 8 != 0 || s.C_out > 256 || reinterpret_cast<uintptr_t>(y) % 16 != 0) return a;
     const int64_t pitch = ((int64_t)(s.Wo - 1) * s.stride + (int64_t)(s.S - 1) * s.dil + 1) * s.C_in;
-    // (a launch of less is over sooner with one thread per output: 8 x 8 pixels, one channel to eight, 1x1 3.0 us against 3.8)
-    if ((double)s.N * s.Ho * s.Wo * s.C_out * s.R * s.S * s.C_in < 2e5) return a;
     const int64_t filters = (int64_t)s.R * s.S * s.C_in * (s.C_out + 4), span = (int64_t)(s.R - 1) * s.dil + 1;
     constexpr int64_t kFloats = 16 * 1024;          // 64 KB beside the 256 bytes of __syncthreads_or: two workgroups per CU
     if (filters + span * pitch > kFloats) return a;
@@ -461,7 +477,11 @@ FewNhwcPlan plan_few_nhwc(const Conv2dShape& s, const void* y)
     P.by_bands = make_fastdiv(P.bands); P.by_K = make_fastdiv(s.R * s.S * s.C_in);
     a.grid = (unsigned)grid;
     a.lds = (size_t)(filters + P.IH * pitch) * 4;
-    a.ok = true;
+    // Where it is faster, and in launches of 32 workgroups up (with fewer the estimates are worth little).  us, one thread per output
+    // against this kernel: 2 x 4 x 1436 x 1 -> 120 under 5x5 at stride 2 7.4 and 51.2, 5 x 8 x 46 x 4 -> 248 under 3x3 at stride 4 6.2 and 15.0,
+    // 30 x 17 x 20 x 4 -> 104 under 3x8 at stride 16 15.0 and 22.8; of the drawn layers those that stay took 1.32 x as long
+    // here, those that come 0.32 x.
+    a.ok = grid >= 32 && few_nhwc_us(P, a.PX, (int64_t)s.R * s.S * s.C_in, grid, a.lds) < 0.9 * one_per_output_nhwc_us(s);
     return a;
 }
 

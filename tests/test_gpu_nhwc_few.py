@@ -23,10 +23,10 @@ def sw():
 
 CASES = [
     # N, H, W, C_in, C_out, R, S, stride, pad, dilation, pixels per thread
-    (2, 37, 41, 3, 64, 3, 3, 2, 1, 1, 1), (1, 30, 199, 3, 64, 3, 3, 2, 1, 1, 4),        # rows of one turn, of more than three
-    (1, 33, 35, 3, 40, 7, 7, 2, 3, 1, 4), (2, 29, 27, 1, 48, 5, 5, 1, 2, 1, 1),         # long sums; octets that do not divide the workgroup
-    (1, 40, 41, 4, 8, 3, 3, 1, 1, 1, 1), (1, 26, 29, 2, 72, 3, 3, 1, 3, 2, 1),          # one octet; dilation and wide padding
-    (3, 9, 250, 3, 256, 3, 3, 1, 0, 1, 4), (1, 50, 3, 3, 256, 2, 5, 1, 2, 1, 1),        # 32 octets; columns of padding only
+    (3, 37, 41, 3, 64, 3, 3, 2, 1, 1, 1), (3, 30, 199, 3, 64, 3, 3, 2, 1, 1, 4),        # rows of one turn, of more than three
+    (10, 33, 35, 3, 40, 7, 7, 2, 3, 1, 4), (2, 29, 27, 1, 48, 5, 5, 1, 2, 1, 1),         # long sums; octets that do not divide the workgroup
+    (2, 40, 41, 4, 8, 3, 3, 1, 1, 1, 1), (3, 26, 29, 2, 72, 3, 3, 1, 3, 2, 1),          # one octet; dilation and wide padding
+    (5, 9, 250, 3, 256, 3, 3, 1, 0, 1, 4), (16, 50, 3, 3, 256, 2, 5, 1, 2, 1, 1),        # 32 octets; columns of padding only
 ]
 
 
@@ -74,10 +74,12 @@ def test_few_channels(torch, sw, oracle, ek, case):
 @pytest.mark.parametrize("where", ["x", "w"])
 def test_few_channels_special_values(torch, sw, value, where):
     """Taps in the padding are left out: an infinite filter value reaches no output over padding alone."""
-    x, w = inputs.normal_f32((2, 33, 41, 3), 7400), inputs.normal_f32((64, 3, 3, 3), 7500)
+    x, w = inputs.normal_f32((4, 33, 41, 3), 7400), inputs.normal_f32((64, 3, 3, 3), 7500)
     (x if where == "x" else w).flat[700] = value
     xd, wd = torch.from_numpy(x).cuda(), torch.from_numpy(w).cuda()
-    y, z = both(torch, lambda out: sw.sw_conv2d_nhwc(xd, wd, 2, 1, out=out), (2, 17, 21, 64), torch.float32)
+    names = []
+    y, z = both(torch, lambda out: (sw.sw_conv2d_nhwc(xd, wd, 2, 1, out=out), names.append(sw.sw_last_kernel())), (4, 17, 21, 64), torch.float32)
+    assert names == ["few_channels_nhwc_kernel<0,3,1>", "direct_nhwc_kernel<0>"], names
     assert torch.equal(y.isnan(), z.isnan()) and torch.equal(torch.nan_to_num(y), torch.nan_to_num(z))
     assert not bool(torch.isfinite(y).all()) and bool(torch.isfinite(y).any())
 
@@ -87,7 +89,7 @@ def test_few_channels_special_values(torch, sw, value, where):
 def test_few_channels_fill_the_lds(torch, sw, oracle, ek, W, takes):
     """Filters (a row of eight floats and four to pad it) and an input row to the last float of 64 KB, and one more: one thread per output."""
     dtype = (torch.float32, torch.bfloat16, torch.float16)[ek]
-    x = torch.from_numpy(inputs.normal_f32((1, 2, W, 1), 7600)).cuda().to(dtype)
+    x = torch.from_numpy(inputs.normal_f32((32, 2, W, 1), 7600)).cuda().to(dtype)
     w = torch.from_numpy(inputs.normal_f32((8, 1, 1, 1), 7700)).cuda().to(dtype)
     y = (sw.sw_conv2d_nhwc, sw.sw_conv2d_bf16_nhwc, sw.sw_conv2d_f16_nhwc)[ek](x, w)
     assert sw.sw_last_kernel() == (f"few_channels_nhwc_kernel<{ek},1,4>" if takes else f"direct_nhwc_kernel<{ek}>")

@@ -84,3 +84,15 @@ def test_pointwise_plan_refuses_what_no_variant_takes():
     assert not pointwise_supported(32, 512, 512, 7, 7)
     assert not pointwise_supported(1, 64, 64, 8, 8, x=4100) and not pointwise_supported(1, 64, 64, 8, 8, y=4100)
     assert not pointwise_supported(1, 2048, 64, 8, 8)
+
+
+@pytest.mark.parametrize("N,H,W,C,K,R,S,stride,pad,takes", [
+    (32, 224, 224, 3, 64, 3, 3, 2, 1, True), (1, 224, 224, 3, 64, 7, 7, 2, 3, True), (1, 224, 224, 3, 96, 4, 4, 4, 0, True),
+    (2, 4, 1436, 1, 120, 5, 5, 2, 1, False), (1, 1, 2158, 1, 152, 5, 5, 1, 2, False),      # one long row: 7.4 us and 51.2, 5.3 and 161.6
+    (2, 52, 81, 2, 192, 3, 3, 4, 1, False), (21, 4, 399, 4, 216, 1, 1, 8, 0, False),       # few outputs a workgroup: 5.6 and 8.9, 4.1 and 7.3
+    (17, 19, 28, 3, 40, 5, 5, 8, 2, False), (30, 17, 20, 4, 104, 3, 8, 16, 0, False),      # ... and many filters: 15.0 and 22.8
+])
+def test_few_channels_channel_last_kernel_takes_what_it_is_faster_at(N, H, W, C, K, R, S, stride, pad, takes):
+    f = getattr(binding.lib(), "_ZN6swconv27few_channels_nhwc_supportedEPKvRKNS_11Conv2dShapeE")
+    f.restype, f.argtypes = ctypes.c_bool, [ctypes.c_void_p, ctypes.POINTER(Shape)]
+    assert f(4096, ctypes.byref(shape(N, C, K, H, W, R, S, stride, pad))) == takes
