@@ -278,6 +278,33 @@ bool sliding_rows_supported(const float* x, int H, int W, int R, int S, int stri
     return W >= 4;
 }
 
+// Of the planes that a workgroup of the small-planes kernel could take a run of, those that the rows kernel is faster at.  A lane group of the
+// rows kernel is eight lanes: planes of up to eight columns leave five or six idle at stride 1, of up to 15 still four, which costs where a
+// launch fills the chip; and the smallest launches are over sooner in the other kernel.  us, small planes -> rows: 32 x 512 x 16 x 16 under 3x3
+// 12.9 -> 7.1, 5x5 14.8 -> 10.7, 7x7 21.9 -> 16.1, 7x7 at stride 2 15.4 -> 9.6; 32 x 256 x 28 x 28 under 5x5 22.2 -> 13.4, 7x7 39.3 -> 16.1; off
+// the 16-byte grid 32 x 512 x 14 x 14 under 3x3 13.0 -> 9.9, 5x5 14.2 -> 12.5, 5x5 at stride 2 9.7 -> 7.4; 16 x 200 x 27 x 27 under 5x5 11.7 -> 7.9,
+// 7x7 at stride 2 13.1 -> 5.5.  The other way 64 x 512 x 4 x 4 under 7x7 7.9 -> 12.7, 32 x 512 x 7 x 7 8.7 -> 10.6; tall planes 19 x 800 x 78 x 4 under
+// 5x5 at stride 2 11.1 -> 16.9, 54 x 522 x 64 x 4 under 3x3 at stride 2 10.4 -> 14.2, 13 x 369 x 95 x 9 under 5x5 11.8 -> 16.2, 56 x 754 x 17 x 9 under
+// 7x7 40.7 -> 52.5; small ones 4 x 381 x 9 x 11 under 5x5 4.4 -> 6.0.  Over 12338 drawn planes the rows kernel takes 0.76 of the time
+// where it is taken, and as long as the other (1.00) where it is not.
+bool rows_before_small_planes(int64_t planes, const Conv2dShape& s, bool off_grid)
+{
+    const int64_t lines = planes * s.Ho;
+    // (up to 512 planes off the grid and under 5x5 and 7x7 at stride 1 stay, and up to 1024 off the grid under 7x7: a launch's latency either way)
+    const bool wide_filter = s.stride == 1 && s.R > 3;
+    if (planes <= (off_grid && wide_filter && s.R == 7 ? 1024 : off_grid || wide_filter ? 512 : 0)) return false;
+    if (s.stride == 2) {
+        if (s.W >= 9) return true;
+        if (off_grid && s.W < 7) return false;
+        return s.W == 4 ? lines <= (s.R == 3 ? 131072 : 65536) : s.R != 5 || lines <= 131072;
+    }
+    if (s.W >= 16) return true;
+    if (s.W < 9) return false;
+    if (s.R == 3) return (s.W >= 11 || lines > 5000) && (s.W >= 14 || lines <= 300000);
+    if (s.R == 5) return lines > (s.pad == 2 ? 5600 : 12000) && (s.W >= 12 || lines <= 32768 || (s.W > 9 && (s.pad == 2 || lines <= 65536)));
+    return lines > 7000 && (s.W > 9 || lines <= 32768);
+}
+
 hipError_t launch_sliding_rows(const float* x, const float* w, float* y, int64_t planes, int planes_per_x,
                                int n_filters, int H, int W, int R, int S, int stride, int pad, int Ho, int Wo,
                                hipStream_t st, const Epilogue& ep)

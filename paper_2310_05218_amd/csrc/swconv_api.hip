@@ -65,16 +65,8 @@ int run_plane(const float* x, const float* w, float* y, int64_t planes, int plan
         // planes up to 20 x 20, larger filters' planes and larger ragged ones (width not a multiple of 4): a run of planes per workgroup ...
         const bool small = (s.H * s.W <= 400 || s.W % 4 != 0 || s.R * s.S >= 25) &&
                            small_planes_supported(planes, planes_per_x, s.H, s.W, s.R, s.S, s.stride, s.Ho, s.Wo);
-        // ... but the rows kernel first where it has a variant: at stride 2, and at stride 1 from nine columns on (narrower planes leave five
-        // or six of a group's eight lanes idle: 64 x 512 x 4 x 4 under 7x7 12.7 us against 7.9, 32 x 512 x 7 x 7 10.6 against 8.7).  us, small
-        // planes -> rows: 32 x 512 x 16 x 16 under 3x3 12.9 -> 7.1, 5x5 14.8 -> 10.7, 7x7 21.9 -> 16.1, 7x7 at stride 2 15.4 -> 9.6;
-        // 32 x 256 x 28 x 28 under 5x5 22.2 -> 13.4, 7x7 39.3 -> 16.1; off the 16-byte grid 32 x 512 x 14 x 14 under 3x3 13.0 -> 9.9, 5x5
-        // 14.2 -> 12.5, 5x5 at stride 2 9.7 -> 7.4; 16 x 200 x 27 x 27 under 5x5 11.7 -> 7.9, 7x7 at stride 2 13.1 -> 5.5.  Up to 512 planes off
-        // the grid and under 5x5 and 7x7 at stride 1 stay, and up to 1024 off the grid under 7x7: a launch's latency either way, and mixed
-        // (16 x 16 under 7x7 5.4 -> 5.0 at 1024 planes, 4.7 -> 4.8 at 80; 14 x 14 5.0 -> 5.2 at 1024; 24 x 24 under 5x5 6.1 -> 4.2 at 384).
-        const bool wide_filter = s.stride == 1 && s.R > 3;
-        const int64_t few = off_grid && wide_filter && s.R == 7 ? 1024 : off_grid || wide_filter ? 512 : 0;
-        if (small && any_rows && planes > few && (s.stride == 2 ? !off_grid || s.W >= 7 : s.W >= 9))
+        // ... but the rows kernel first where it has a variant and is faster
+        if (small && any_rows && rows_before_small_planes(planes, s, off_grid))
             return launch_status(launch_sliding_rows(x, w, y, planes, planes_per_x, n_filters, s.H, s.W, s.R, s.S,
                                                      s.stride, s.pad, s.Ho, s.Wo, st, ep));
         if (small)

@@ -96,3 +96,15 @@ def test_few_channels_channel_last_kernel_takes_what_it_is_faster_at(N, H, W, C,
     f = getattr(binding.lib(), "_ZN6swconv27few_channels_nhwc_supportedEPKvRKNS_11Conv2dShapeE")
     f.restype, f.argtypes = ctypes.c_bool, [ctypes.c_void_p, ctypes.POINTER(Shape)]
     assert f(4096, ctypes.byref(shape(N, C, K, H, W, R, S, stride, pad))) == takes
+
+
+@pytest.mark.parametrize("planes,H,W,R,stride,pad,off,takes", [
+    (16384, 14, 14, 3, 1, 1, True, True), (8192, 28, 28, 5, 1, 2, False, True), (16384, 16, 16, 7, 1, 3, False, True), (16384, 16, 16, 7, 2, 3, False, True),
+    (15200, 78, 4, 5, 2, 2, False, False), (28188, 64, 4, 3, 2, 0, False, False), (19800, 120, 4, 7, 2, 3, False, False),      # tall and narrow: 11.1 us and
+    (4797, 95, 9, 5, 1, 0, True, False), (42224, 17, 9, 7, 1, 3, True, False), (32940, 45, 11, 3, 1, 1, True, False),          # 16.9, 10.4 and 14.2, ...
+    (1524, 9, 11, 5, 1, 0, True, False), (800, 5, 9, 3, 1, 0, True, False),                                                    # small: 4.4 and 6.0
+])
+def test_rows_kernel_takes_the_planes_that_it_is_faster_at(planes, H, W, R, stride, pad, off, takes):
+    f = getattr(binding.lib(), "_ZN6swconv24rows_before_small_planesElRKNS_11Conv2dShapeEb")
+    f.restype, f.argtypes = ctypes.c_bool, [ctypes.c_long, ctypes.POINTER(Shape), ctypes.c_bool]
+    assert f(planes, ctypes.byref(shape(1, 1, 1, H, W, R, R, stride, pad)), off) == takes
