@@ -90,9 +90,9 @@ int sw_pool1d(const float* x, float* y, int64_t rows, int64_t len,
  * x: [N,C,H,W];  y: [N,C,H_out,W_out], extents by sw_out_dim.
  * Supported: R,S <= 64 and 2*pad <= min(R,S) (so that no window lies wholly in
  * the padding), else SW_ERR_UNSUPPORTED; mode as in sw_pool1d.  2x2 stride 2 and
- * 3x3 stride 1 or 2 run in the register-only kernel (rows of fewer than seven columns
- * when W % 4 == 0 and x is 16-byte aligned), every other case in the one-thread-per-output
- * kernel or, for global pooling and large windows, a wavefront's.
+ * 3x3 stride 1 or 2 run in the register-only kernel (rows of up to seven columns mostly
+ * only when W % 4 == 0 and x is 16-byte aligned), every other case in the
+ * one-thread-per-output kernel or, for global pooling and large windows, a wavefront's.
  * The maximum is bit-exact; NaN inputs are outside the contract.
  */
 int sw_pool2d(const float* x, float* y, int N, int C, int H, int W, int R, int S,

@@ -329,12 +329,14 @@ hipError_t launch_sliding_rows(const float* x, const float* w, float* y, int64_t
 // thread per output (us, 3x3 at stride 2 unless said): 27 x 64 x 109 x 79 31.1 -> 13.5 (5.5 TB/s), 8 x 64 x 113 x 250 28.9 -> 13.0,
 // 2 x 64 x 93 x 122 5.0 -> 3.6, 16 x 256 x 7 x 7 3.6 -> 3.2, at stride 1 on 16 x 192 x 14 x 14 6.0 -> 4.1.  Rows of four to six columns off the
 // grid stay with the latter: a lane group is eight lanes, and they fill two (64 x 512 x 6 x 6 under 2x2 4.1 against 4.5, x 5 x 5 4.6
-// against 4.8).
-bool pool_rows_supported(const float* x, int W, int R, int S, int stride, int pad)
+// against 4.8); of seven under 2x2 (0.9 to 1.0 x the time from 2^18 outputs up, the same below) and, up to 65536 outputs, under
+// 3x3 at stride 1 (3.5 us against 3.7).
+bool pool_rows_supported(const float* x, int64_t planes, int W, int R, int S, int stride, int pad, int Ho, int Wo)
 {
     if ((stride != 1 && stride != 2) || R != S || (R != 2 && R != 3) || pad < 0 || pad > (R == 3 ? 1 : 0)) return false;
     if (R == 2 && stride == 1) return false;       // (no compiled variant; the direct kernel takes it)
-    return W >= 7 || whole_quads(x, W);
+    if (whole_quads(x, W)) return true;
+    return W > 7 || (W == 7 && R == 3 && (stride == 2 || planes * Ho * Wo >= 65536));
 }
 
 hipError_t launch_pool_rows(const float* x, float* y, int64_t planes, int H, int W, int R, int stride, int pad,

@@ -237,7 +237,7 @@ int sw_pool2d(const float* x, float* y, int N, int C, int H, int W, int R, int S
     const bool maximum = mode == SW_POOL_MAX;
     if (!force_direct() && global_pool_supported(H, W, R, S, pad))
         return launch_status(launch_global_pool(x, y, planes, H * W, maximum, st));
-    if (!force_direct() && pool_rows_supported(x, W, R, S, stride, pad))
+    if (!force_direct() && pool_rows_supported(x, planes, W, R, S, stride, pad, (int)Ho, (int)Wo))
         return launch_status(launch_pool_rows(x, y, planes, H, W, R, stride, pad, (int)Ho, (int)Wo, maximum, st));
     return launch_status(launch_direct_pool2d(x, y, planes, H, W, R, S, stride, pad, (int)Ho, (int)Wo, maximum, st));
 }

@@ -162,7 +162,7 @@ bool       rows_before_small_planes(int64_t planes, const Conv2dShape& s, bool o
 hipError_t launch_sliding_rows(const float* x, const float* w, float* y, int64_t planes, int planes_per_x,
                                int n_filters, int H, int W, int R, int S, int stride, int pad, int Ho, int Wo,
                                hipStream_t st, const Epilogue& ep = Epilogue{nullptr, 0});
-bool       pool_rows_supported(const float* x, int W, int R, int S, int stride, int pad);
+bool       pool_rows_supported(const float* x, int64_t planes, int W, int R, int S, int stride, int pad, int Ho, int Wo);
 hipError_t launch_pool_rows(const float* x, float* y, int64_t planes, int H, int W, int R, int stride, int pad,
                             int Ho, int Wo, bool maximum, hipStream_t st);
 hipError_t launch_sliding_plane(const float* x, const float* w, float* y, int64_t planes,

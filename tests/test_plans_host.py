@@ -108,3 +108,14 @@ def test_rows_kernel_takes_the_planes_that_it_is_faster_at(planes, H, W, R, stri
     f = getattr(binding.lib(), "_ZN6swconv24rows_before_small_planesElRKNS_11Conv2dShapeEb")
     f.restype, f.argtypes = ctypes.c_bool, [ctypes.c_long, ctypes.POINTER(Shape), ctypes.c_bool]
     assert f(planes, ctypes.byref(shape(1, 1, 1, H, W, R, R, stride, pad)), off) == takes
+
+
+@pytest.mark.parametrize("planes,H,W,R,stride,pad,x,takes", [
+    (16384, 28, 7, 2, 2, 0, 4096, False), (60, 28, 8, 2, 2, 0, 4100, True), (60, 28, 8, 2, 2, 0, 4096, True),       # seven columns under 2x2
+    (168, 7, 7, 3, 1, 0, 4096, False), (2621, 7, 7, 3, 1, 0, 4096, False), (2622, 7, 7, 3, 1, 0, 4096, True),       # ... and 3x3, 25 outputs a plane
+    (168, 7, 7, 3, 2, 1, 4096, True), (60, 28, 6, 3, 2, 1, 4096, False), (60, 28, 4, 3, 2, 1, 4096, True), (60, 28, 4, 3, 2, 1, 4100, False),
+])
+def test_pooling_rows_take_what_they_are_faster_at(planes, H, W, R, stride, pad, x, takes):
+    f = getattr(binding.lib(), "_ZN6swconv19pool_rows_supportedEPKfliiiiiii")
+    f.restype, f.argtypes = ctypes.c_bool, [ctypes.c_void_p, ctypes.c_long] + [ctypes.c_int] * 7
+    assert f(x, planes, W, R, R, stride, pad, (H + 2 * pad - R) // stride + 1, (W + 2 * pad - R) // stride + 1) == takes
