@@ -296,13 +296,11 @@ FewPlan search_few(const Conv2dShape& s)
         for (int KW = waves; KW >= 1; KW /= 2)
             for (int CW = 1; CW * KW <= waves; CW *= 2) {
                 const int PW = waves / KW / CW;
-                // columns of a tile: equal parts of an output row
-                int last = 0;
-                for (int nx = std::max(1, (s.Wo + 16 * PW - 1) / (16 * PW)), tried = 0; nx <= s.Wo && tried < 12; ++nx) {
-                    const int TW = (s.Wo + nx - 1) / nx;
-                    if (TW == last || TW > 16 * PW || TW < std::min(s.Wo, 4)) continue;     // (narrow tiles: scattered loads and stores)
-                    last = TW;
-                    ++tried;
+                // columns of a tile: equal parts of an output row, the twelve widest (TW - 1 columns or fewer from as many parts up)
+                int TW = 0;
+                for (int64_t nx = std::max(1, (s.Wo + 16 * PW - 1) / (16 * PW)), tried = 0; tried < 12 && TW != 1; nx = ((int64_t)s.Wo + TW - 2) / std::max(TW - 1, 1), ++tried) {
+                    TW = (int)((s.Wo + nx - 1) / nx);
+                    if (TW < std::min(s.Wo, 4)) break;                                      // (narrow tiles: scattered loads and stores)
                     consider(waves, KW, CW, PW, TW);
                 }
             }

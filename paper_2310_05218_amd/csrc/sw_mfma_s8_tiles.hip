@@ -261,12 +261,11 @@ S8TilesPlan search_s8_tiles(const Conv2dShape& s, bool requant)
         for (int CW = 1; CW * KW <= 8; CW *= 2)
             for (int PB : {1, 2, 4}) {
                 const int px = 16 * PB * (8 / KW / CW);
-                int last = 0;
-                for (int nx = std::max(1, (s.Wo + px - 1) / px), tried = 0; nx <= s.Wo && tried < 12; ++nx) {
-                    const int TW = (s.Wo + nx - 1) / nx;
-                    if (TW == last || TW < std::min(s.Wo, 4)) continue;
-                    last = TW;
-                    ++tried;
+                // columns of a tile: equal parts of an output row, the twelve widest (TW - 1 columns or fewer from as many parts up)
+                int TW = 0;
+                for (int64_t nx = std::max(1, (s.Wo + px - 1) / px), tried = 0; tried < 12 && TW != 1; nx = ((int64_t)s.Wo + TW - 2) / std::max(TW - 1, 1), ++tried) {
+                    TW = (int)((s.Wo + nx - 1) / nx);
+                    if (TW < std::min(s.Wo, 4)) break;
                     consider(KW, CW, PB, TW);
                 }
             }

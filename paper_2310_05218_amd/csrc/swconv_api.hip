@@ -549,10 +549,10 @@ int sw_jit_cached_kernels(void) { return jit_cached_kernels(); }
 // (32 x 256 -> 256 at 12 x 12 17.9 -> 16.8, 8 x 64 -> 128 at 100 x 100, 40000 tiles, 33.8 and 33.2).
 static bool s8_tiles_first(const int8_t* w, const Conv2dShape& s, bool requant)
 {
-    if (!mfma_s8_tiles_supported(w, requant, s)) return false;
-    if (requant ? mfma_s8_requant_supported(s) : mfma_s8_supported(s))
-        return (int64_t)s.N * (((int64_t)s.Ho * s.Wo + 15) / 16) * ((s.C_out + 15) / 16) <= 8192;
-    return requant || s.R * s.S > 1 || s.C_in > 32;
+    const bool by_rows = requant ? mfma_s8_requant_supported(s) : mfma_s8_supported(s);
+    if (by_rows ? (int64_t)s.N * (((int64_t)s.Ho * s.Wo + 15) / 16) * ((s.C_out + 15) / 16) > 8192 : !requant && s.R * s.S == 1 && s.C_in <= 32)
+        return false;
+    return mfma_s8_tiles_supported(w, requant, s);       // (the search comes last)
 }
 
 int sw_conv2d_s8(const int8_t* x, const int8_t* w, int32_t* y, int N, int C_in, int C_out, int H, int W,

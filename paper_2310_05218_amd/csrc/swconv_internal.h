@@ -6,6 +6,9 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include <memory>
+#include <new>
+
 namespace swconv {
 
 enum Op1D { OP_CONV = 0, OP_AVG = 1, OP_MAX = 2 };
@@ -25,8 +28,10 @@ struct Conv2dShape {
     int dil = 1;      // input positions between neighbouring taps (the any-shape fp32, run-time-extent tile and direct kernels take > 1)
 };
 
-// A launch plan found by a search over tilings costs host time that a small layer cannot hide behind its own run time.
-// Each host thread keeps the plans of the shapes it saw last.  A plan may depend on the shape and on the low four address
+// A launch plan found by a search over tilings costs host time that a small layer cannot hide behind its own run time (3 to 12 us).
+// Each host thread keeps the plans of the shapes it saw last, up to 512 of a kernel: a network has some dozens, and with 16 entries 24 shapes
+// in turn were searched for anew each time (int8 3x3 at 56 x 56 12.3 us a call, 1.5 now).  The entries are made with the first plan and given back when the
+// thread ends; without memory for them every plan is searched for.  A plan may depend on the shape and on the low four address
 // bits of up to three buffers, on nothing else.
 template <class Plan>
 struct PlanCache {
@@ -36,9 +41,13 @@ struct PlanCache {
         unsigned align = 0;
         Plan plan;
     };
-    static constexpr int kEntries = 16;
-    Entry e[kEntries];
-    int next = 0;
+    struct Set {
+        static constexpr int kWays = 4;
+        Entry e[kWays];
+        int next = 0;
+    };
+    static constexpr unsigned kSets = 128;
+    std::unique_ptr<Set[]> sets;
     static unsigned low_bits(const void* a, const void* b, const void* c)
     {
         return (unsigned)(reinterpret_cast<uintptr_t>(a) & 15) | (unsigned)(reinterpret_cast<uintptr_t>(b) & 15) << 4 |
@@ -49,13 +58,23 @@ struct PlanCache {
         return a.N == b.N && a.C_in == b.C_in && a.C_out == b.C_out && a.H == b.H && a.W == b.W && a.R == b.R && a.S == b.S &&
                a.stride == b.stride && a.pad == b.pad && a.Ho == b.Ho && a.Wo == b.Wo && a.dil == b.dil;
     }
-    template <class Search>
-    const Plan& get(const Conv2dShape& s, unsigned align, Search&& search)
+    // (a multiplicative hash: its high bits depend on every field)
+    static unsigned place(const Conv2dShape& s, unsigned align)
     {
-        for (int i = 0; i < kEntries; ++i)
-            if (e[i].used && e[i].align == align && same(e[i].s, s)) return e[i].plan;
-        Entry& n = e[next];
-        next = (next + 1) % kEntries;
+        uint64_t h = align;
+        for (int f : {s.N, s.C_in, s.C_out, s.H, s.W, s.R, s.S, s.stride, s.pad, s.dil}) h = (h ^ (uint64_t)(unsigned)f) * 0x9e3779b97f4a7c15ULL, h ^= h >> 32;
+        return (unsigned)(h >> 8) % kSets;
+    }
+    template <class Search>
+    Plan get(const Conv2dShape& s, unsigned align, Search&& search)
+    {
+        if (!sets) sets.reset(new (std::nothrow) Set[kSets]);
+        if (!sets) return search();
+        Set& t = sets[place(s, align)];
+        for (const Entry& e : t.e)
+            if (e.used && e.align == align && same(e.s, s)) return e.plan;
+        Entry& n = t.e[t.next];
+        t.next = (t.next + 1) % Set::kWays;
         n.used = true; n.s = s; n.align = align; n.plan = search();
         return n.plan;
     }

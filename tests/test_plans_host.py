@@ -119,3 +119,40 @@ def test_pooling_rows_take_what_they_are_faster_at(planes, H, W, R, stride, pad,
     f = getattr(binding.lib(), "_ZN6swconv19pool_rows_supportedEPKfliiiiiii")
     f.restype, f.argtypes = ctypes.c_bool, [ctypes.c_void_p, ctypes.c_long] + [ctypes.c_int] * 7
     assert f(x, planes, W, R, R, stride, pad, (H + 2 * pad - R) // stride + 1, (W + 2 * pad - R) // stride + 1) == takes
+
+
+def s8_tiles_supported(s):
+    f = getattr(binding.lib(), "_ZN6swconv23mfma_s8_tiles_supportedEPKabRKNS_11Conv2dShapeE")
+    f.restype, f.argtypes = ctypes.c_bool, [ctypes.c_void_p, ctypes.c_bool, ctypes.POINTER(Shape)]
+    return f(4096, True, ctypes.byref(s))
+
+
+@pytest.mark.parametrize("supported,shapes", [
+    (s8_tiles_supported, [(4, 64, 16 * n, 56, 56, 3, 3, 1, 1) for n in range(1, 101)]),
+    (lambda s: split_supported("few", s), [(1, 40, 16 * n, 97, 101, 5, 5, 1, 2) for n in range(1, 101)]),
+], ids=["s8_tiles", "few"])
+def test_plans_of_a_network_s_layers_are_found_once(supported, shapes):
+    """A hundred shapes in turn: none is searched for again (7 to 12 us a shape when they are, of which the call from here is 1)."""
+    shapes = [shape(*s) for s in shapes]
+
+    def once():
+        start = time.perf_counter()
+        took = [supported(s) for s in shapes]
+        assert all(took)
+        return time.perf_counter() - start
+
+    first = once()
+    assert min(once() for _ in range(20)) < first / 2.5
+
+
+@pytest.mark.parametrize("supported,s", [
+    (s8_tiles_supported, (1, 16, 1, 1, 100_000_000, 1, 1, 1, 0)), (s8_tiles_supported, (1, 16, 1, 1, 60_000_000, 1, 9, 1, 4)),
+    (lambda s: split_supported("few", s), (1, 2, 1, 1, 100_000_000, 1, 7, 1, 3)),
+], ids=["s8_tiles", "s8_tiles-9", "few"])
+def test_plans_of_wide_images_take_no_longer(supported, s):
+    """The search goes over the tile widths that there are, not over all numbers of parts of a row."""
+    s = shape(*s)
+    binding.lib()
+    start = time.perf_counter()
+    supported(s)
+    assert time.perf_counter() - start < 0.01
