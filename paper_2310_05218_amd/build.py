@@ -46,6 +46,17 @@ def build_binding(verbose: bool = False) -> str:
     return BINDING
 
 
+def _build_binding_if_possible(verbose: bool):
+    """The binding is optional (without it every call goes through ctypes) and needs torch's headers and a host compiler: where they are
+    missing the library is built all the same, and no module of an older build stays beside it."""
+    try:
+        build_binding(verbose)
+    except (ImportError, OSError, subprocess.CalledProcessError) as e:
+        if os.path.exists(BINDING):
+            os.remove(BINDING)
+        print(f"native binding not built, calls go through ctypes: {e}", file=sys.stderr, flush=True)
+
+
 def build(verbose: bool = False, jobs: int = 8) -> str:
     """Compile every kernel and the C ABI into ``libswconv.so``; always recompiles.  The translation units
     are compiled side by side into ``_build/`` at the repository root (not tracked), then linked."""
@@ -75,7 +86,7 @@ def build(verbose: bool = False, jobs: int = 8) -> str:
             return obj
 
         with concurrent.futures.ThreadPoolExecutor(max_workers=max(1, jobs)) as pool:
-            binding = pool.submit(build_binding, verbose)
+            binding = pool.submit(_build_binding_if_possible, verbose)
             objs = list(pool.map(compile_one, sources()))
             binding.result()
         cmd = [hipcc, "--offload-arch=gfx950", "-fPIC", "-shared", "-o", LIB, *objs, "-lhiprtc"]
