@@ -360,17 +360,19 @@ __global__ __launch_bounds__(512, 2) void mfma_nhwc_lds_kernel(const unsigned ch
         // 16-bit and requantised int8 results: four consecutive output channels of a lane are 4 OB bytes
         constexpr int OB = EK == kFmtS8Q ? 1 : 2;
         using Pack = std::conditional_t<EK == kFmtS8Q, int, intx2>;
-        // (the rectifier of int8 results is a branch around the epilogue, not a select in every result)
-        auto leave = [&](auto relu) __attribute__((always_inline)) {
+        // (int8: a copy with the rectifier and one without, one of which runs, in place of a select in every result)
+#pragma unroll
+        for (int relu = 0; relu < (EK == kFmtS8Q ? 2 : 1); ++relu) {
+            if (EK == kFmtS8Q && relu != (P.rq.relu != 0)) continue;
             auto pack = [&](int cb, int b, int q) __attribute__((always_inline)) {
                 if constexpr (EK == kFmtS8Q) {
                     // q = clamp(rne(scale * float(acc + bias)), relu ? 0 : -128, 127), every step in fp32 as the definition has it
                     const int c = cb * 32 + 8 * q + 4 * kq;
                     const intx4 qb = *reinterpret_cast<const intx4*>(smem + P.rq_off + 4 * c);
                     const floatx4 qs = *reinterpret_cast<const floatx4*>(smem + P.rq_off + 4 * (32 * CB + c));
-                    return requant_pack4<decltype(relu)::value>((int)acc[cb][b][4 * q] + qb[0], (int)acc[cb][b][4 * q + 1] + qb[1],
-                                                                (int)acc[cb][b][4 * q + 2] + qb[2], (int)acc[cb][b][4 * q + 3] + qb[3],
-                                                                qs[0], qs[1], qs[2], qs[3]);
+                    const int t0 = (int)acc[cb][b][4 * q] + qb[0], t1 = (int)acc[cb][b][4 * q + 1] + qb[1];
+                    const int t2 = (int)acc[cb][b][4 * q + 2] + qb[2], t3 = (int)acc[cb][b][4 * q + 3] + qb[3];
+                    return relu ? requant_pack4<true>(t0, t1, t2, t3, qs[0], qs[1], qs[2], qs[3]) : requant_pack4<false>(t0, t1, t2, t3, qs[0], qs[1], qs[2], qs[3]);
                 } else {
                     unsigned h[4];
 #pragma unroll
@@ -407,7 +409,7 @@ __global__ __launch_bounds__(512, 2) void mfma_nhwc_lds_kernel(const unsigned ch
                     }
                     asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");          // (the area is written again for the next block)
                 }
-                return;
+                continue;
             }
 #pragma unroll
             for (int b = 0; b < PB; ++b) {
@@ -422,12 +424,6 @@ __global__ __launch_bounds__(512, 2) void mfma_nhwc_lds_kernel(const unsigned ch
                         if (co < P.C_out) *reinterpret_cast<Pack*>(yp + co * OB) = pack(cb, b, q);
                     }
             }
-        };
-        if constexpr (EK == kFmtS8Q) {
-            if (P.rq.relu) leave(std::true_type{});
-            else leave(std::false_type{});
-        } else {
-            leave(std::false_type{});
         }
     }
 }
