@@ -319,7 +319,7 @@ hipError_t launch_one(const float* x, const float* w, float* y, const FewPlan& a
     static const hipError_t attr = hipFuncSetAttribute(reinterpret_cast<const void*>(mfma_f32_few_kernel<WAVES>),
                                                        hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024);
     if (attr != hipSuccess) return attr;
-    SW_NOTED_LAUNCH(note_kernel("mfma_f32_few_kernel", WAVES, a.P.KW, a.P.CW, a.P.TW), (mfma_f32_few_kernel<WAVES>),
+    SW_NOTED_LAUNCH(note_kernel("mfma_f32_few_kernel", WAVES, a.P.KW, a.P.PW, a.P.chunks), (mfma_f32_few_kernel<WAVES>),
                     dim3((unsigned)a.grid), dim3(64 * WAVES), a.lds, st, x, w, y, a.P);
     return hipGetLastError();
 }

@@ -35,7 +35,7 @@ CASES = [
     (2, 68, 36, 12, 12, 2, 2, 1, 0, 1),         # four taps
     (3, 21, 48, 15, 15, 5, 5, 1, 2, 1),         # 25 taps over few channels
     (1, 130, 24, 21, 18, 5, 5, 2, 2, 1),        # 25 taps at stride 2
-    (1, 300, 20, 11, 30, 7, 7, 1, 3, 1),        # 49 taps: two loads a channel, more channels than LDS holds
+    (1, 300, 20, 11, 30, 7, 7, 1, 3, 1),        # 49 taps: two loads a channel, all channels in 138 KB
     (2, 24, 17, 14, 14, 7, 5, 3, 2, 1),         # rectangular, stride 3
     (1, 70, 18, 16, 16, 1, 7, 1, 3, 1),         # a row of seven taps
     (2, 130, 64, 40, 42, 5, 5, 1, 2, 1),        # several workgroups per CU
@@ -68,6 +68,29 @@ def test_few_tiles_kernel(torch, sw, oracle, case, shift):
         y = sw.sw_conv2d_bias_relu(xd, wd, torch.from_numpy(b).cuda(), st, pad, True)
         yr, dr = oracle.conv2d_bias_relu(x, w, b, st, pad, True)
         assert_f32_parity(y.cpu().numpy(), yr, np.maximum(dr, 1e-30), f"{case} bias, rectifier")
+
+
+@pytest.mark.parametrize("case,plan", [
+    # wavefronts, those that share a tile's products, tiles of 16 pixels, chunks of channels
+    ((1, 256, 64, 14, 14, 7, 7, 2, 3, 1), "8,8,1,2"), ((6, 302, 9, 14, 4, 5, 5, 2, 2, 1), "8,8,1,2"),       # whole runs to the end of the last chunk; 30 products over
+    ((7, 283, 5, 29, 34, 7, 7, 1, 3, 1), "8,4,2,2"), ((5, 259, 36, 17, 59, 5, 5, 1, 2, 1), "8,2,4,3"), ((7, 176, 48, 35, 35, 5, 5, 1, 2, 1), "8,1,8,2"),
+    ((5, 69, 97, 13, 57, 2, 2, 1, 1, 1), "4,1,1,1"), ((4, 82, 76, 22, 59, 2, 2, 1, 1, 1), "4,1,2,1"), ((8, 74, 48, 20, 31, 2, 2, 1, 1, 1), "4,2,2,1"),
+    ((3, 80, 12, 28, 60, 2, 2, 1, 1, 1), "4,4,1,1"), ((5, 76, 100, 32, 21, 2, 2, 1, 1, 1), "8,1,1,1"), ((5, 83, 174, 9, 45, 2, 2, 1, 1, 1), "8,1,2,1"),
+    ((9, 85, 20, 40, 40, 2, 2, 1, 1, 1), "8,1,4,1"), ((7, 94, 141, 35, 12, 2, 2, 1, 1, 1), "8,1,8,1"), ((4, 67, 96, 38, 13, 2, 2, 1, 1, 1), "8,2,2,1"),
+    ((9, 199, 108, 12, 16, 2, 2, 1, 1, 1), "8,2,4,1"),
+], ids=lambda v: "x".join(map(str, v)) if isinstance(v, tuple) else v)
+def test_few_tiles_plans(torch, sw, oracle, case, plan):
+    """Every form of a plan: tiles whose products one wavefront adds up, several pixel tiles and channel tiles a workgroup, a window that
+    comes in chunks of channels, the last of which ends in a partial run."""
+    N, Ci, Co, H, W, R, S, st, pad, dil = case
+    x = inputs.normal_f32((N, Ci, H, W), 8400 + Ci)
+    w = inputs.normal_f32((Co, Ci, R, S), 8500 + Co, (2.0 / (Ci * R * S)) ** 0.5)
+    y_ref, d = oracle.conv2d_dilated(x, w, st, pad, dil)
+    buf, out, front, n, guard = guarded_empty(torch, y_ref.shape, torch.float32)
+    sw.sw_conv2d_dilated(torch.from_numpy(x).cuda(), torch.from_numpy(w).cuda(), st, pad, dil, out=out)
+    assert sw.sw_last_kernel() == f"mfma_f32_few_kernel<{plan}>"
+    assert_f32_parity(out.cpu().numpy(), y_ref, d, str(case))
+    assert_guards_intact(buf, front, n, guard)
 
 
 @pytest.mark.parametrize("value", [np.inf, np.nan])

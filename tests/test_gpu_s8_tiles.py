@@ -62,6 +62,40 @@ def test_s8_tiles(oracle, case, shift):
         assert_guards_intact(buf, front, n, guard)
 
 
+@pytest.mark.parametrize("case,plan", [
+    # taps, wavefronts that share a tile's units, tiles of 16 channels, tiles of 16 pixels per wavefront; ragged channels, tiles partly beyond
+    ((7, 16, 151, 17, 53, 3, 3, 1, 1), "9,1,8,4"), ((5, 16, 153, 38, 34, 3, 3, 1, 1), "9,1,4,4"), ((9, 80, 68, 26, 26, 3, 3, 1, 1), "9,2,4,4"),
+    ((9, 80, 24, 39, 43, 3, 3, 1, 1), "9,2,2,4"), ((5, 160, 18, 37, 48, 3, 3, 1, 1), "9,4,2,4"), ((8, 272, 5, 35, 31, 3, 3, 1, 1), "9,8,1,4"),
+    ((8, 16, 110, 32, 17, 3, 3, 1, 1), "9,1,8,2"), ((8, 80, 21, 33, 34, 3, 3, 1, 1), "9,2,2,2"), ((2, 144, 17, 34, 60, 3, 3, 1, 1), "9,4,2,2"),
+    ((5, 304, 5, 34, 29, 3, 3, 1, 1), "9,8,1,2"), ((4, 48, 158, 29, 55, 1, 1, 1, 0), "1,1,8,4"), ((9, 48, 134, 34, 26, 1, 1, 1, 0), "1,1,4,4"),
+    ((6, 96, 132, 31, 59, 1, 1, 1, 0), "1,1,2,4"), ((6, 48, 165, 38, 46, 1, 1, 2, 0), "1,1,8,2"), ((8, 48, 186, 7, 35, 1, 1, 1, 0), "1,1,4,2"),
+    ((8, 224, 17, 33, 20, 1, 1, 1, 0), "1,4,2,2"), ((6, 272, 7, 30, 23, 1, 1, 1, 0), "1,8,1,2"),
+], ids=lambda v: "x".join(map(str, v)) if isinstance(v, tuple) else v)
+def test_s8_tiles_plans(oracle, case, plan):
+    """Several pixel tiles a wavefront, with and without other wavefronts on the same tiles' units, under one and nine taps."""
+    torch = pytest.importorskip("torch")
+    import paper_2310_05218_amd as sw
+
+    N, Ci, Co, H, W, R, S, st, pad = case
+    x, w = inputs.uniform_s8((N, Ci, H, W), 9600 + Ci), inputs.uniform_s8((Co, Ci, R, S), 9700 + Co)
+    xd, wd = torch.from_numpy(x).cuda(), torch.from_numpy(w).cuda()
+    y_ref = oracle.conv2d_s8(x, w, st, pad)
+    buf, out, front, n, guard = guarded_empty(torch, y_ref.shape, torch.int32)
+    sw.sw_conv2d_s8(xd, wd, st, pad, out=out)
+    assert sw.sw_last_kernel() == f"mfma_s8_tiles_kernel<{plan}>"
+    assert np.array_equal(out.cpu().numpy(), y_ref)
+    assert_guards_intact(buf, front, n, guard)
+    rng = np.random.default_rng(9800)
+    bias = rng.integers(-20000, 20000, Co).astype(np.int32)
+    scale = (rng.uniform(0.5, 2.0, Co) * 40.0 / ((Ci * R * S) ** 0.5 * 5461.0)).astype(np.float32)
+    q_ref = oracle.conv2d_s8_requant(x, w, bias, scale, st, pad, False)
+    buf, out, front, n, guard = guarded_empty(torch, q_ref.shape, torch.int8, fill=77)
+    sw.sw_conv2d_s8_requant(xd, wd, torch.from_numpy(bias).cuda(), torch.from_numpy(scale).cuda(), st, pad, False, out=out)
+    assert sw.sw_last_kernel() == f"mfma_s8_tiles_kernel<{plan}>"
+    assert np.array_equal(out.cpu().numpy(), q_ref)
+    assert_guards_intact(buf, front, n, guard)
+
+
 @pytest.mark.parametrize("case,takes", [((8, 32, 64, 14, 14, 1, 0), False), ((8, 48, 64, 14, 14, 1, 0), True), ((2, 40, 64, 14, 14, 3, 1), False),
                                         ((1, 64, 64, 9, 3, 3, 1), False)], ids=str)
 def test_s8_tiles_leaves_the_rest(oracle, case, takes):
