@@ -246,12 +246,20 @@ int sw_pool2d(const float* x, float* y, int N, int C, int H, int W, int R, int S
 // workgroup.  The lines are where it and the kernels of before cross, on 820 layers drawn over 7 ... 112 pixels, 9 ... 512 channels, 1 x 1 ...
 // 7 x 7, strides 1 and 2: nine taps on split operands up to 512 tiles where the two plans' estimates say so (1.04 to 2.4 x taken, 0.4 to 1.1 x
 // beyond), 25 and more taps 1.3 to 38 x up to the largest tried (18020), the rest 1.1 to 5 x up to 2048 and 0.9 to 1.1 x up to 3000.
+// 25 and more taps over two to six channels are short sums, which the any-shape kernel is as fast at once its launch is filled: 13 x 2 -> 51 at
+// 157 x 31 under 5x5 12.9 us there against 27.1 (13468 tiles), 2 x 2 -> 24 at 198 x 329 under 6x6 24.2 against 31.1; of 5904 drawn layers of
+// 3000 to 16384 tiles those below the lines are 2.0 x as fast here, those beyond 1.0.
 static bool few_tiles(const Conv2dShape& s)
 {
     const int64_t tiles = (int64_t)s.N * (((int64_t)s.Ho * s.Wo + 15) / 16) * ((s.C_out + 15) / 16);
     if (s.R * s.S == 9 && mfma_f32_split_supported(s))
         return tiles <= 512 && mfma_f32_few_supported(s) && mfma_f32_few_estimate(s) < 0.95 * mfma_f32_split_estimate(s);
-    return tiles <= (s.R * s.S >= 25 ? 16384 : 2048) && mfma_f32_few_supported(s);
+    int64_t most = s.R * s.S >= 25 ? 16384 : 2048;
+    if (s.R * s.S >= 25 && s.C_in <= 6) {
+        if (s.C_out > 32) most = s.C_in == 2 ? 3000 : 6000;
+        else if (s.C_out > 16 && s.C_in == 2) most = 6000;
+    }
+    return tiles <= most && mfma_f32_few_supported(s);
 }
 
 // ... in place of the kernels that come first in run_conv2d: from 65 input channels up (fewer are as much faster, but the tests

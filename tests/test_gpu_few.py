@@ -113,3 +113,18 @@ def test_few_tiles_kernel_keeps_special_values_in_place(torch, sw, shape, value)
     x2[1, 0] = value
     y = run(x2, w)
     assert not np.isfinite(y[1]).any() and np.array_equal(y[0], clean[0])
+
+
+@pytest.mark.parametrize("case,takes", [
+    ((1, 2, 40, 90, 100, 5, 5, 1, 2), True), ((9, 2, 51, 60, 31, 5, 5, 1, 2), False), ((3, 5, 34, 60, 71, 5, 5, 1, 0), True), ((8, 5, 34, 70, 71, 7, 7, 1, 3), False),
+    ((2, 2, 24, 91, 171, 6, 6, 1, 0), True), ((2, 2, 24, 198, 329, 6, 6, 1, 0), False), ((2, 2, 16, 198, 229, 6, 6, 1, 0), True), ((8, 9, 34, 70, 71, 7, 7, 1, 3), True),
+], ids=lambda v: "x".join(map(str, v)) if isinstance(v, tuple) else str(v))
+def test_large_filters_over_few_channels(torch, sw, oracle, case, takes):
+    """Short sums in launches that fill the chip: the any-shape kernel, with the same result."""
+    N, Ci, Co, H, W, R, S, st, pad = case
+    x = inputs.normal_f32((N, Ci, H, W), 8600 + Ci)
+    w = inputs.normal_f32((Co, Ci, R, S), 8700 + Co, (2.0 / (Ci * R * S)) ** 0.5)
+    y_ref, d = oracle.conv2d(x, w, st, pad)
+    y = sw.sw_conv2d(torch.from_numpy(x).cuda(), torch.from_numpy(w).cuda(), st, pad)
+    assert sw.sw_last_kernel().startswith("mfma_f32_few_kernel" if takes else "mfma_f32_any_kernel"), sw.sw_last_kernel()
+    assert_f32_parity(y.cpu().numpy(), y_ref, d, str(case))
