@@ -553,13 +553,15 @@ int sw_jit_cached_kernels(void) { return jit_cached_kernels(); }
 
 // One or nine taps on the kernel that turns its operands in registers, where the band kernel has no plan.  Against the any-shape kernel it was
 // faster on 368 of 370 drawn layers and on all larger ones tried (1.1 to 12 x), but for single taps over at most 32 channels whose sums
-// leave as int32 (one unit of channels: 32 -> 64 at 56 x 56, 32 images, 9.6 us against 11.8); against the 32-row kernel (mfma_s8_kernel) up to 8192 tiles
+// leave as int32 (one unit of channels: 32 -> 64 at 56 x 56, 32 images, 9.6 us against 11.8), and over at most 64 into more than 32 from 8192
+// tiles up on planes of whole dwords (51 drawn layers 0.62 to 1.3 x: 29 x 48 -> 36 at 80 x 104 17.8 us against 28.6); against the 32-row kernel (mfma_s8_kernel) up to 8192 tiles
 // (32 x 256 -> 256 at 12 x 12 17.9 -> 16.8, 8 x 64 -> 128 at 100 x 100, 40000 tiles, 33.8 and 33.2).
 static bool s8_tiles_first(const int8_t* w, const Conv2dShape& s, bool requant)
 {
     const bool by_rows = requant ? mfma_s8_requant_supported(s) : mfma_s8_supported(s);
-    if (by_rows ? (int64_t)s.N * (((int64_t)s.Ho * s.Wo + 15) / 16) * ((s.C_out + 15) / 16) > 8192 : !requant && s.R * s.S == 1 && s.C_in <= 32)
-        return false;
+    const bool filled = (int64_t)s.N * (((int64_t)s.Ho * s.Wo + 15) / 16) * ((s.C_out + 15) / 16) > 8192;
+    const bool short_sums = !requant && s.R * s.S == 1 && (s.C_in <= 32 || (s.C_in <= 64 && s.C_out > 32 && s.W % 4 == 0 && s.stride == 1 && filled));
+    if (by_rows ? filled : short_sums) return false;
     return mfma_s8_tiles_supported(w, requant, s);       // (the search comes last)
 }
 

@@ -96,10 +96,11 @@ def test_s8_tiles_plans(oracle, case, plan):
     assert_guards_intact(buf, front, n, guard)
 
 
-@pytest.mark.parametrize("case,takes", [((8, 32, 64, 14, 14, 1, 0), False), ((8, 48, 64, 14, 14, 1, 0), True), ((2, 40, 64, 14, 14, 3, 1), False),
+@pytest.mark.parametrize("case,takes", [((8, 32, 64, 14, 14, 1, 0), False), ((8, 48, 64, 14, 14, 1, 0), True), ((21, 48, 36, 92, 80, 1, 0), False),
+                                        ((5, 48, 36, 92, 80, 1, 0), True), ((21, 48, 36, 92, 81, 1, 0), True), ((21, 80, 36, 92, 80, 1, 0), True), ((2, 40, 64, 14, 14, 3, 1), False),
                                         ((1, 64, 64, 9, 3, 3, 1), False)], ids=str)
 def test_s8_tiles_leaves_the_rest(oracle, case, takes):
-    """Few channels under one tap, channel counts off the grid, rows shorter than a quad: the kernels of before, with the same sums."""
+    """Few channels under one tap (up to 64 in launches that fill the chip, on planes of whole dwords), channel counts off the grid, rows shorter than a quad: the kernels of before, with the same sums."""
     torch = pytest.importorskip("torch")
     import paper_2310_05218_amd as sw
 
