@@ -74,7 +74,7 @@ struct RowsPlace {
 template <int R, int S, int PADC, int TR, int ST, int OP, int SEGL, bool ANY>
 __global__ __launch_bounds__(256) void sliding_rows_kernel(const float* __restrict__ x,
                                                            const float* __restrict__ w,
-                                                           float* __restrict__ y, int planes, int H, int W, int Ho, int Wo,
+                                                           float* __restrict__ y, int H, int W, int Ho, int Wo,
                                                            int strips, int bands, int waves, int items,
                                                            const RowsPlace place, const Epilogue ep)
 {
@@ -245,10 +245,10 @@ hipError_t launch_rows_seg(const float* x, const float* w, float* y, int64_t pla
     dim3 grid((unsigned)blocks), block(256);
     if (small)
         SW_NOTED_LAUNCH(note_kernel("sliding_rows_kernel", (int)(R), (int)(S), (int)(PADC), (int)(TR_SMALL)), (sliding_rows_kernel<R, S, PADC, TR_SMALL, ST, OP, SEGL, ANY>), grid, block, 0, st, x, w, y,
-                           (int)planes, H, W, Ho, Wo, strips, bands, (int)waves, (int)items, place, ep);
+                           H, W, Ho, Wo, strips, bands, (int)waves, (int)items, place, ep);
     else
         SW_NOTED_LAUNCH(note_kernel("sliding_rows_kernel", (int)(R), (int)(S), (int)(PADC), (int)(TR_BIG)), (sliding_rows_kernel<R, S, PADC, TR_BIG, ST, OP, SEGL, ANY>), grid, block, 0, st, x, w, y,
-                           (int)planes, H, W, Ho, Wo, strips, bands, (int)waves, (int)items, place, ep);
+                           H, W, Ho, Wo, strips, bands, (int)waves, (int)items, place, ep);
     return hipGetLastError();
 }
 
@@ -272,9 +272,8 @@ bool whole_quads(const float* x, int W) { return W % 4 == 0 && reinterpret_cast<
 
 }  // namespace
 
-bool sliding_rows_supported(const float* x, int H, int W, int R, int S, int stride, int pad)
+bool sliding_rows_supported(int W, int R, int S, int stride, int pad)
 {
-    (void)H;
     if ((stride != 1 && stride != 2) || R != S || (R != 3 && R != 5 && R != 7) || pad > (R - 1) / 2 || pad < 0) return false;
     // (padding beyond (R-1)/2 would need more than the compiled halo widths; 7x7 reaches at most four columns into
     // the right neighbour, which rules out the smallest paddings)

@@ -61,7 +61,7 @@ int run_plane(const float* x, const float* w, float* y, int64_t planes, int plan
                                                       s.pad, s.Ho, s.Wo, st, ep, s.dil));
     } else if (!force_direct()) {
         const bool off_grid = s.W % 4 != 0 || misaligned(x, 16);
-        const bool any_rows = sliding_rows_supported(x, s.H, s.W, s.R, s.S, s.stride, s.pad), rows = any_rows && !off_grid;
+        const bool any_rows = sliding_rows_supported(s.W, s.R, s.S, s.stride, s.pad), rows = any_rows && !off_grid;
         // planes up to 20 x 20, larger filters' planes and larger ragged ones (width not a multiple of 4): a run of planes per workgroup ...
         const bool small = (s.H * s.W <= 400 || s.W % 4 != 0 || s.R * s.S >= 25) &&
                            small_planes_supported(planes, planes_per_x, s.H, s.W, s.R, s.S, s.stride, s.Ho, s.Wo);

@@ -176,7 +176,7 @@ bool       sliding_plane_whole(const float* x, const float* y, int H, int W, int
 
 // ---- sliding rows kernel (stride 1 or 2; 3x3 / 5x5 filters, 2x2 / 3x3 pooling windows): registers only,
 // DPP wavefront shifts for the halo ---------------------------------------------------------------
-bool       sliding_rows_supported(const float* x, int H, int W, int R, int S, int stride, int pad);
+bool       sliding_rows_supported(int W, int R, int S, int stride, int pad);
 bool       rows_before_small_planes(int64_t planes, const Conv2dShape& s, bool off_grid);
 hipError_t launch_sliding_rows(const float* x, const float* w, float* y, int64_t planes, int planes_per_x,
                                int n_filters, int H, int W, int R, int S, int stride, int pad, int Ho, int Wo,
