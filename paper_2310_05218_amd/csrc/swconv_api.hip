@@ -1,5 +1,6 @@
 // C ABI of libswconv.so: host-side validation and kernel selection.  Every argument error is
-// reported before anything is enqueued; nothing here allocates or synchronises.
+// reported before anything is enqueued; nothing here allocates device memory or synchronises (the host memory of a thread's launch plans
+// is PlanCache's).
 #include "../../include/swconv.h"
 
 #include <cstdio>

@@ -30,8 +30,8 @@ struct Conv2dShape {
 
 // A launch plan found by a search over tilings costs host time that a small layer cannot hide behind its own run time (3 to 12 us).
 // Each host thread keeps the plans of the shapes it saw last, up to 512 of a kernel: a network has some dozens, and with 16 entries 24 shapes
-// in turn were searched for anew each time (int8 3x3 at 56 x 56 12.3 us a call, 1.5 now).  The entries are made with the first plan and given back when the
-// thread ends; without memory for them every plan is searched for.  A plan may depend on the shape and on the low four address
+// in turn were searched for anew each time (int8 3x3 at 56 x 56 12.3 us a call, 1.5 now).  Entries are made four at a time, as plans come, and given back when
+// the thread ends; without memory for them a plan is searched for.  A plan may depend on the shape and on the low four address
 // bits of up to three buffers, on nothing else.
 template <class Plan>
 struct PlanCache {
@@ -47,7 +47,7 @@ struct PlanCache {
         int next = 0;
     };
     static constexpr unsigned kSets = 128;
-    std::unique_ptr<Set[]> sets;
+    std::unique_ptr<Set> sets[kSets];
     static unsigned low_bits(const void* a, const void* b, const void* c)
     {
         return (unsigned)(reinterpret_cast<uintptr_t>(a) & 15) | (unsigned)(reinterpret_cast<uintptr_t>(b) & 15) << 4 |
@@ -68,9 +68,10 @@ struct PlanCache {
     template <class Search>
     Plan get(const Conv2dShape& s, unsigned align, Search&& search)
     {
-        if (!sets) sets.reset(new (std::nothrow) Set[kSets]);
-        if (!sets) return search();
-        Set& t = sets[place(s, align)];
+        std::unique_ptr<Set>& set = sets[place(s, align)];
+        if (!set) set.reset(new (std::nothrow) Set);
+        if (!set) return search();
+        Set& t = *set;
         for (const Entry& e : t.e)
             if (e.used && e.align == align && same(e.s, s)) return e.plan;
         Entry& n = t.e[t.next];
