@@ -21,9 +21,9 @@
 // keeps small tiles, whose periods are short, supplied; large windows leave room for PH = 1 only.  One barrier per chunk.
 //
 // Measured (us per launch, replayed graphs of ten on one set of buffers, batch 32 unless said, the fp32-instruction kernels -> this
-// one): 64 -> 64 at 56 x 56 75.4 -> 49.6, 128 -> 128 at 28 x 28 87.1 -> 45.5, 256 -> 256 at 14 x 14 84.4 -> 46.1, 512 -> 512 at 7 x 7
-// 103.5 -> 54.8, one image of 256 -> 256 at 14 x 14 39.4 -> 17.3, of 512 -> 512 at 7 x 7 73.9 -> 30.5, 64 -> 64 at 56 x 56 21.1 -> 10.4,
-// five of 96 -> 136 at 35 x 35 39.0 -> 18.2.
+// one): 64 -> 64 at 56 x 56 75.4 -> 49.7, 128 -> 128 at 28 x 28 87.1 -> 45.0, 256 -> 256 at 14 x 14 84.4 -> 45.3, 512 -> 512 at 7 x 7
+// 103.5 -> 54.8, one image of 64 -> 64 at 56 x 56 21.1 -> 10.2, five of 96 -> 136 at 35 x 35 39.0 -> 17.8.  (Smaller launches are the few-tiles kernel's
+// now: one image of 256 -> 256 at 14 x 14 39.4 -> 17.4 here and 10.6 there, of 512 -> 512 at 7 x 7 73.9 -> 29.8 and 16.1.)
 // What bounds it: 256 pixels x PB of a tile are never quite full (13 of 16 blocks in the first case), the first chunk's way
 // through LDS (7 us) and the stores of a tile that nothing overlaps, and a clock of 1.8-1.9 GHz under the bf16 instructions.  With
 // parts left out, the first case takes 14 us for launch, barriers and window loads, 34 with the matrix instructions of three blocks
@@ -31,8 +31,8 @@
 // block, 50 with the splitting.  (The thirteenth block in quarters over four SIMDs, on 16 x 16 x 32 instructions, gained nothing over
 // leaving out the dead ones: each quarter reads as much of LDS as the block.)  Single images: about 2 k ticks a
 // chunk, most of it the filter loads (64 lanes 288 bytes apart are 64 lines a load, 1.2 k ticks a chunk).  Three wavefronts share
-// the taps of single blocks: with a tile's only block on one wavefront 512 -> 512 at 7 x 7 took 40.2 us, 3 x 344 -> 88 at 9 x 9 28.2
-// where it takes 20.3.
+// the taps of single blocks: with a tile's only block on one wavefront 512 -> 512 at 7 x 7 took 40.2 us where it took 29.8, 3 x 344 -> 88
+// at 9 x 9 28.2 where it took 20.1.
 #include <algorithm>
 
 #include "sw_f32_split.h"
@@ -319,7 +319,7 @@ __global__ __launch_bounds__(64 * (mul_waves(PH) + PH + win_waves(PH)), mul_wave
                 // (registers for one set of operands: the other wavefront of the SIMD covers the reads.)  A wavefront whose second
                 // block lies beyond the tile -- three of eight where a tile has 13 blocks of 16 -- leaves its products out: they took the
                 // SIMD's other wavefront a sixth of its matrix time (64 -> 64 at 56 x 56, batch 12 of 48 -> 64, 22 of 88 -> 24 at
-                // 47 x 54 with dilation 2: 52.9 -> 50.2, 21.1 -> 17.8, 33.1 -> 26.9 us).  The test is on the tile's size only, the same for
+                // 47 x 54 with dilation 2: 51.6 -> 49.7, 20.9 -> 17.6, 32.4 -> 26.3 us).  The test is on the tile's size only, the same for
                 // all lanes; a lone block in a copy of the loop took 54 registers more than there are.
                 const bool two = nlive == 2;
 #pragma unroll
