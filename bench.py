@@ -71,15 +71,15 @@ MEASURED_ROOF = {"conv2d_64x64_3x3": "mfma_bf16_sixth_tflops", "conv2d_s8_128x12
 TRAFFIC_SOURCE = ("rocprofv3 --pmc FETCH_SIZE / WRITE_SIZE runs made by the builder (profiles/hbm_traffic_all_kernels.txt), "
                   "not measured by this run; null where the kernel's source has changed since")
 TRAFFIC = {
-    "depthwise_3x3": (207413237, "sw_sliding_plane.hip", "1d24ebdfa6df1cef"),
-    "depthwise_7x7": (206183315, "sw_sliding_plane.hip", "1d24ebdfa6df1cef"),
-    "conv2d_64x64_3x3": (85743000, "sw_mfma_f32_split.hip", "d114a74d38a1ab4d"),
-    "conv2d_s8_128x128_3x3": (22096535, "sw_mfma_s8_band.hip", "efae7346fdd97c23"),
-    "conv1d_k9": (33974646, "sw_sliding1d.hip", "b574d6ab8949af6c"),
-    "avgpool1d_w8": (34237947, "sw_sliding1d.hip", "b574d6ab8949af6c"),
-    "maxpool1d_w8": (34207183, "sw_sliding1d.hip", "b574d6ab8949af6c"),
-    "conv2d_1ch_3x3": (660943, "sw_sliding_rows.hip", "0e35510846c9b8a1"),
-    "conv2d_s8_128x128_3x3_packed": (21953725, "sw_mfma_s8_band.hip", "efae7346fdd97c23"),
+    "depthwise_3x3": (207415206, "sw_sliding_plane.hip", "1d24ebdfa6df1cef"),
+    "depthwise_7x7": (206284690, "sw_sliding_plane.hip", "1d24ebdfa6df1cef"),
+    "conv2d_64x64_3x3": (88003744, "sw_mfma_f32_split.hip", "4c66ec4593d18224"),
+    "conv2d_s8_128x128_3x3": (22166248, "sw_mfma_s8_band.hip", "efae7346fdd97c23"),
+    "conv1d_k9": (33929576, "sw_sliding1d.hip", "d65dbf978ea678b8"),
+    "avgpool1d_w8": (34203914, "sw_sliding1d.hip", "d65dbf978ea678b8"),
+    "maxpool1d_w8": (34177808, "sw_sliding1d.hip", "d65dbf978ea678b8"),
+    "conv2d_1ch_3x3": (615331, "sw_sliding_rows.hip", "4ac3e87e6d869b66"),
+    "conv2d_s8_128x128_3x3_packed": (22010222, "sw_mfma_s8_band.hip", "efae7346fdd97c23"),
 }
 
 
