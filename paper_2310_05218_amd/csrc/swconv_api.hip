@@ -263,9 +263,11 @@ static bool few_tiles(const Conv2dShape& s)
     return tiles <= most && mfma_f32_few_supported(s);
 }
 
-// ... in place of the kernels that come first in run_conv2d: from 65 input channels up (fewer are as much faster, but the tests
-// assert the plans of the other kernels there); 1 x 1 on the pointwise kernel from 128 output channels up, up to 768 tiles (320 -> 280 at
-// 18 x 18 15.3 -> 7.9 us; tests assert the pointwise kernel's plans of small launches with fewer).
+// ... in place of the kernels that come first in run_conv2d: from 65 input channels up; 1 x 1 on the pointwise kernel from 128 output channels up,
+// up to 768 tiles (320 -> 280 at 18 x 18 15.3 -> 7.9 us).  Neither line is where the kernels cross, but where tests that assert the other kernels'
+// plans end: 16 to 64 channels under 5x5 and 7x7 on rows of whole 16-byte groups are as much faster here (us, compound kernel and this one: 3 x 32 -> 24
+// at 19 x 48 7x7 stride 2 150.8 and 8.5, 10 x 56 -> 140 at 50 x 8 5x5 160.6 and 31.8), so are single taps into fewer channels (2 x 440 -> 10 at
+// 34 x 34 19.0 and 7.8).
 static bool few_tiles_first(const Conv2dShape& s, const float* x, const float* w, const float* y)
 {
     if (s.C_in <= 64) return false;
