@@ -18,14 +18,18 @@
 // roundings that meet in fp32 pairs and, over the wavefronts, in fp64: 1.05e-7 of the result (2-norm) where the split operands of
 // mfma_f32_split_kernel have 1.5e-7 (2304 products).
 //
-// Measured (us per launch, replayed graphs of ten; the kernel of before -> this one): one image of 256 -> 256 at 14 x 14 3x3 18.0 -> 11.0,
+// Measured (us per launch, replayed graphs of ten; the kernel of before -> this one): one image of 256 -> 256 at 14 x 14 3x3 18.0 -> 10.2,
 // of 512 -> 512 at 7 x 7 29.7 -> 15.7, 2 x 160 -> 40 at 11 x 11 13.4 -> 8.1, 1 x 1 over 5 x 152 -> 160 at 25 x 25 18.2 -> 10.1; 5 x 5: one
 // image of 264 -> 104 at 9 x 9 658 -> 18, 8 x 176 -> 80 at 14 x 14 448 -> 37, 11 x 40 -> 64 at 39 x 39 110 -> 49.
-// What bounds it (the first of these, with parts taken out of a copy): 4.7 us are the launch, the first round trip and the two barriers
-// of the reduction; the matrix instructions 2.8, the window's loads (4 bytes a lane) 1.5, the filters' 1.6 -- the last three one
-// after the other, because a workgroup has one barrier and a CU one workgroup.  Tried and not kept: sixteen wavefronts (12.8), loads by
-// wavefronts of their own in four chunks with a barrier each (11.3 to 16.1), the window through registers by 16-byte loads (11.0, and
-// 1 us more for the smallest layers), taps instead of runs (filters at 36-byte strides: 11.8).
+// What bounds it (the first of these, time stamps in cycles of 19.3 k): 4.5 k until the window's loads have left (kernel arguments and tile
+// coordinates 2 k; direct-to-LDS loads come in at 12 bytes a cycle and CU by words, 20 by 16-byte pieces, which need a wider window and gained
+// nothing), 2.5 k first filters, the table and the wait for the window, 7 k the nine runs of two wavefronts a SIMD, 2.5 k the meeting of the sums.  An
+// fp32 matrix instruction holds up the vector and LDS instructions of its SIMD: with those between them a run took 950 cycles where
+// the eight matrix instructions take 290 alone and the rest 350, so they stand in one block in front.  That, uniform loop counts and no
+// reads in branches: 1.07 x over 31 drawn layers (1.00 to 1.14), this one 11.1 -> 10.2 us, 10 x 80 -> 192 at 19 x 19 5 x 5 47.3 -> 41.5.
+// Tried and not kept: sixteen wavefronts (12.8), loads by wavefronts of their own in four chunks with a barrier each (11.3 to 16.1), the window
+// through registers by 16-byte loads (11.0, and 1 us more for the smallest layers), taps instead of runs (filters at 36-byte strides: 11.8),
+// the outputs' places computed before the products (10.7).
 #include <algorithm>
 #include <cmath>
 
@@ -50,6 +54,7 @@ struct FewParams {
     int N, C_in, C_out, H, W, Ho, Wo, stride, pad;
     int K, T, S, dil;               // products of an output, taps, filter columns
     int KW, CW, PW, lKW, lCW;       // wavefronts that share a tile's products; tiles of 16 channels; tiles of 16 pixels
+    int KWq, KWr;                   // KW runs in whole periods of T and the rest
     int TH, TW, IW, cells;          // rows and columns of a pixel tile, columns and cells of its window
     int pitch, pieces, group;       // words from a channel's window to the next's; loads per channel, or channels per load
     int CC, chunks;                 // channels in LDS at a time
@@ -66,12 +71,12 @@ __device__ __forceinline__ void wait_loads() { asm volatile("s_waitcnt vmcnt(%0)
 // barrier without the fence of __syncthreads (which would wait for the loads in flight)
 __device__ __forceinline__ void lds_barrier() { asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory"); }
 
-template <int WAVES>
-__global__ __launch_bounds__(64 * WAVES, WAVES == 4 ? 2 : 4) void mfma_f32_few_kernel(const float* __restrict__ x, const float* __restrict__ w,
+// MIN: wavefronts that run at once on a SIMD at least; RING: runs of filters under way
+template <int WAVES, int MIN, int RING>
+__global__ __launch_bounds__(64 * WAVES, MIN) void mfma_f32_few_kernel(const float* __restrict__ x, const float* __restrict__ w,
                                                                                       float* __restrict__ y, const FewParams P)
 {
     constexpr int NA = 12;                              // accumulators: short chains of roundings
-    constexpr int RING = 4;                             // runs of filters under way
     extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
     int* tab = reinterpret_cast<int*>(smem);
     const int tid = threadIdx.x, lane = tid & 63;
@@ -147,44 +152,76 @@ __global__ __launch_bounds__(64 * WAVES, WAVES == 4 ? 2 : 4) void mfma_f32_few_k
     for (int c = 0;; ++c) {
         lds_barrier();
         const int k0 = c * kc;
-        const int mine = (runs - kw + P.KW - 1) >> P.lKW;        // runs of this wavefront
-        struct Cells { int base; intx4 o[2]; };
+        const int mine = __builtin_amdgcn_readfirstlane((runs - kw + P.KW - 1) >> P.lKW);        // runs of this wavefront
+        struct Cells { intx4 o[2]; };
         struct Vals { float v[8]; };
-        int ur = kw, base = px;                                  // the next run: its place in the table, its channels' first cell
-        auto cells = [&]() __attribute__((always_inline)) {
-            while (ur >= P.T) { ur -= P.T; base += period; }
+        int ur = kw, base = 0;                                   // the next run: its place in the table, its channels' first cell
+        while (ur >= P.T) { ur -= P.T; base += period; }
+        int based = base;                                        // (of the cells that wait for it)
+        // the cells of run r of this wavefront; the place moves on while there are more (and no read past the last run leaves the window)
+        auto cells = [&](Cells& c, int r) __attribute__((always_inline)) {
             const int* q = tab + 32 * ur + 4 * g;
-            ur += P.KW;
-            return Cells{base, {*reinterpret_cast<const intx4*>(q), *reinterpret_cast<const intx4*>(q + 16)}};
+            c.o[0] = *reinterpret_cast<const intx4*>(q);
+            c.o[1] = *reinterpret_cast<const intx4*>(q + 16);
+            based = base;
+            const bool more = r + 1 < mine;
+            ur += more ? P.KWr : 0;
+            base += more ? P.KWq * period : 0;
+            const bool turn = ur >= P.T;
+            ur -= turn ? P.T : 0;
+            base += turn ? period : 0;
         };
-        auto vals = [&](const Cells& o) __attribute__((always_inline)) {
-            Vals r;
+        auto places = [&](Cells& c) __attribute__((always_inline)) {
 #pragma unroll
-            for (int j = 0; j < 8; ++j) r.v[j] = *reinterpret_cast<const float*>(smem + (o.base + o.o[j / 4][j & 3]));
-            return r;
+            for (int j = 0; j < 8; ++j) c.o[j / 4][j & 3] += px + based;
+        };
+        auto vals = [&](Vals& r, const Cells& c) __attribute__((always_inline)) {
+#pragma unroll
+            for (int j = 0; j < 8; ++j) r.v[j] = *reinterpret_cast<const float*>(smem + c.o[j / 4][j & 3]);
+        };
+        auto multiply = [&](int i, const Vals& v) __attribute__((always_inline)) {
+#pragma unroll
+            for (int j = 0; j < 8; ++j) {
+                constexpr int extra = NA - 8;
+                const int k = (i & 1) && j < extra ? 8 + j : j;
+                acc[k] = __builtin_amdgcn_mfma_f32_16x16x4f32(a[i][j / 4][j & 3], v.v[j], acc[k], 0, 0, 0);
+            }
         };
         if (mine > 0) {
-            Vals v = vals(cells());
-            Cells o = cells();                                   // (what lies past the last run is not read)
+            // Under way beside a run's matrix instructions: the next run's values, the places in LDS of those of the run after, that one's
+            // successor's from the table.  In no branch: where paths with and without reads meet, the compiler waits as if there were none.
+            Cells o[2];
+            Vals v[2];
+            cells(o[0], 0);
+            places(o[0]);
+            vals(v[0], o[0]);
+            cells(o[0], 1);
+            places(o[0]);
+            cells(o[1], 2);
+            int i0 = 0;
 #pragma unroll 1
-            for (int i0 = 0; i0 < mine; i0 += RING) {
+            for (; i0 + RING <= mine; i0 += RING) {
 #pragma unroll
                 for (int i = 0; i < RING; ++i) {
-                    if (i0 + i < mine) {
-                        Vals nv;
-                        if (i0 + i + 1 < mine) nv = vals(o);
-                        o = cells();
-#pragma unroll
-                        for (int j = 0; j < 8; ++j) {
-                            constexpr int extra = NA - 8;
-                            const int k = (i & 1) && j < extra ? 8 + j : j;
-                            acc[k] = __builtin_amdgcn_mfma_f32_16x16x4f32(a[i][j / 4][j & 3], v.v[j], acc[k], 0, 0, 0);
-                        }
-                        v = nv;
-                    }
-                    load(a[i], k0, kw + P.KW * (i0 + i + RING), runs);
+                    if (i0 + i > 0) load(a[(i + RING - 1) % RING], k0, kw + P.KW * (i0 + i + RING - 1), runs);
+                    vals(v[(i + 1) & 1], o[i & 1]);
+                    places(o[(i + 1) & 1]);
+                    cells(o[i & 1], i0 + i + 3);
+                    __builtin_amdgcn_sched_barrier(0);
+                    multiply(i, v[i & 1]);
+                    __builtin_amdgcn_sched_barrier(0);
                 }
             }
+#pragma unroll
+            for (int i = 0; i < RING - 1; ++i)
+                if (i0 + i < mine) {
+                    if (i + 1 < RING - 1) {
+                        vals(v[(i + 1) & 1], o[i & 1]);
+                        places(o[(i + 1) & 1]);
+                        cells(o[i & 1], i0 + i + 3);
+                    }
+                    multiply(i, v[i & 1]);
+                }
         }
         // the last products, less than a run
         if ((kn & 31) && kw == (runs & (P.KW - 1))) {
@@ -284,7 +321,7 @@ FewPlan search_few(const Conv2dShape& s)
         P.N = s.N; P.C_in = s.C_in; P.C_out = s.C_out; P.H = s.H; P.W = s.W; P.Ho = s.Ho; P.Wo = s.Wo;
         P.stride = s.stride; P.pad = s.pad; P.dil = s.dil;
         P.K = (int)K; P.T = T; P.S = s.S;
-        P.KW = KW; P.CW = CW; P.PW = PW; P.lKW = __builtin_ctz(KW); P.lCW = __builtin_ctz(CW);
+        P.KW = KW; P.CW = CW; P.PW = PW; P.KWq = KW / T; P.KWr = KW % T; P.lKW = __builtin_ctz(KW); P.lCW = __builtin_ctz(CW);
         P.TH = TH; P.TW = TW; P.IW = (int)IW; P.cells = cells; P.pitch = pitch; P.pieces = pieces; P.group = group;
         P.CC = CC; P.chunks = chunks; P.tab_bytes = tab_bytes;
         P.co_tiles = cot; P.tiles_x = tx; P.tiles_y = ty;
@@ -313,13 +350,13 @@ FewPlan plan_few(const Conv2dShape& s)
     return cache.get(s, 0, [&] { return search_few(s); });
 }
 
-template <int WAVES>
+template <int WAVES, int MIN, int RING>
 hipError_t launch_one(const float* x, const float* w, float* y, const FewPlan& a, hipStream_t st)
 {
-    static const hipError_t attr = hipFuncSetAttribute(reinterpret_cast<const void*>(mfma_f32_few_kernel<WAVES>),
+    static const hipError_t attr = hipFuncSetAttribute(reinterpret_cast<const void*>(mfma_f32_few_kernel<WAVES, MIN, RING>),
                                                        hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024);
     if (attr != hipSuccess) return attr;
-    SW_NOTED_LAUNCH(note_kernel("mfma_f32_few_kernel", WAVES, a.P.KW, a.P.PW, a.P.chunks), (mfma_f32_few_kernel<WAVES>),
+    SW_NOTED_LAUNCH(note_kernel("mfma_f32_few_kernel", WAVES, a.P.KW, a.P.PW, a.P.chunks), (mfma_f32_few_kernel<WAVES, MIN, RING>),
                     dim3((unsigned)a.grid), dim3(64 * WAVES), a.lds, st, x, w, y, a.P);
     return hipGetLastError();
 }
@@ -335,7 +372,9 @@ hipError_t launch_mfma_f32_few(const float* x, const float* w, float* y, const C
     FewPlan a = plan_few(s);
     if (!a.ok) return hipErrorInvalidValue;
     a.P.ep = ep;
-    return a.waves == 8 ? launch_one<8>(x, w, y, a, st) : launch_one<4>(x, w, y, a, st);
+    if (a.waves == 4) return launch_one<4, 2, 4>(x, w, y, a, st);
+    // eight wavefronts: two workgroups a CU, with half the filters under way, where there are that many and LDS has room for them
+    return a.grid > 256 && 2 * (a.lds + 512) <= 160 * 1024 ? launch_one<8, 4, 2>(x, w, y, a, st) : launch_one<8, 2, 4>(x, w, y, a, st);
 }
 
 }  // namespace swconv
