@@ -10,12 +10,16 @@
 // LDS under the same round trip, by direct-to-LDS loads.  Results are packed four at a time (requant_pack4) and leave through a
 // per-wavefront LDS area as 16-byte pieces of a pixel.
 //
-// Measured (us per launch, replayed graphs of ten, window kernel -> this one): 32 x 28 x 28 x 512 -> 128 10.9 -> 8.6, 128 -> 512
+// Measured (us per launch, replayed graphs of ten; the window kernel of the time -> first form of this one): 32 x 28 x 28 x 512 -> 128 10.9 -> 8.6, 128 -> 512
 // 16.4 -> 11.7, 32 x 14 x 14 x 256 -> 1024 12.9 -> 8.5, 32 x 56 x 56 x 256 -> 64 13.1 -> 8.9, 6 x 25 x 25 x 160 -> 640 9.0 -> 5.1, one image
-// 28 x 28 x 512 -> 128 6.8 -> 6.0.  (With filters through registers in two round trips, ten instructions a packed result and more workgroups
-// than run at once: 9.3, 14.0, 9.3, 10.3, 5.8, 6.3.)  CB = 4 where that leaves 192 workgroups, else 2: fetching 128 filter rows made small
-// launches slower than the window kernel's.  Parts taken out of a copy (512 -> 128 / 128 -> 512): the pixels' loads 0.6 / 2.6, the
-// filters' 0.8 / 1.0, packing 0.9 / 2.3, the stores 0.8 / 1.3; all chunks of 512 channels in flight at once was slower (10.2: registers).
+// 28 x 28 x 512 -> 128 6.8 -> 6.0.  CB = 4 where that leaves 192 workgroups, else 2: fetching 128 filter rows made small
+// launches slower than the window kernel's.
+// Then (time stamps, cycles, 512 -> 128 / 128 -> 512): the filters' loads took 2.7 / 1.4 k to leave (divisions for each), biases and scales came 3 k
+// later for standing behind them, every filter read was waited for by its matrix instruction, the next tile's pixels at the end of this
+// one (a register copy: 2.6 k), every scale by its results (2.8 k a tile for 64 results a lane).  Now: sums that start from the
+// biases, filters three steps ahead, pixels fetched again in place, all scales before the first result: 12.9 -> 10.5 k and 18.0 -> 13.2 k.
+// What is left: filter reads at 64 bytes a cycle and CU, 4.1 k until the first product, 1.7 k of packing a tile.  A quantised
+// bottleneck of this, a 3 x 3 and this again (32 x 28 x 28, 512 -> 128 -> 128 -> 512) 31.1 -> 26.0 us, 31 drawn ones 1.18 x, none slower.
 #include <algorithm>
 #include <initializer_list>
 #include <type_traits>
@@ -42,6 +46,7 @@ struct PwS8Params {
     int pitch, rq_off, out_off;            // bytes per filter row in LDS; offsets of biases and scales, and of the store areas
     int wloads;                            // 1 KB loads of the workgroup's filters
     unsigned w_bytes;
+    int d_row, d_piece;                    // from a lane's slot to that of its next load, 256 slots on
     FastDiv by_slots;                      // 16-byte slots per filter row: its pieces and one that pads it
 };
 
@@ -51,88 +56,138 @@ __global__ __launch_bounds__(256, 2) void mfma_s8_pointwise_nhwc_kernel(const in
                                                                         int8_t* __restrict__ y, const PwS8Params P)
 {
     extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, lj = lane & 31, kq = lane >> 5;
+    const int tid = threadIdx.x, lane = tid & 63, lj = lane & 31, kq = lane >> 5;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int co0 = blockIdx.y * (32 * CB);
     const int steps = P.C_in >> 5;
     int tile = (int)blockIdx.x * 4 + wave;
     const int nwaves = (int)gridDim.x * 4;
 
-    // (a pixel past the last one computes on the last and stores nothing)
-    auto x_of = [&](int t) __attribute__((always_inline)) {
-        const int p = min(32 * t + lj, P.total_px - 1);
-        return x + (int64_t)p * P.C_in + 16 * kq;
+    // biases and scales, on their way first: they come into LDS behind the filters' loads
+    int bias = 0;
+    float scale = 0.f;
+    if (tid < 32 * CB) {
+        const int co = min(co0 + tid, P.C_out - 1);
+        if (P.rq.bias) bias = P.rq.bias[co];
+        scale = P.rq.scale[co];
+    }
+    // a tile's pixels as a buffer: what lies beyond the last pixel, and a tile that is none, is read as zeros and without traffic
+    auto pixels = [&](int t) __attribute__((always_inline)) {
+        const int rows = t < P.tiles ? min(32, P.total_px - 32 * t) : 0;
+        return __builtin_amdgcn_make_buffer_rsrc(const_cast<int8_t*>(x) + (int64_t)min(t, P.tiles - 1) * 32 * P.C_in, 0, (unsigned)(rows * P.C_in), 0x00020000);
     };
+    const unsigned px_off = (unsigned)(lj * P.C_in + 16 * kq);
+    __amdgpu_buffer_rsrc_t xr = pixels(tile);
     intx4 b[kChunkSteps];
-    auto fetch = [&](const int8_t* src, int s0) __attribute__((always_inline)) {
-#pragma unroll
-        for (int i = 0; i < kChunkSteps; ++i) b[i] = *reinterpret_cast<const intx4*>(src + 32 * min(s0 + i, steps - 1));
+    // step s of a tile; a step beyond the last: zeros
+    auto fetch = [&](int i, __amdgpu_buffer_rsrc_t r, int s) __attribute__((always_inline)) {
+        b[i] = __builtin_bit_cast(intx4, __builtin_amdgcn_raw_buffer_load_b128(r, px_off + (s < steps ? (unsigned)(32 * s) : kBeyond), 0, 0));
     };
-    const int8_t* xp = x_of(min(tile, P.tiles - 1));
-    fetch(xp, 0);
+#pragma unroll
+    for (int i = 0; i < kChunkSteps; ++i) fetch(i, xr, i);
 
     {
-        // the filters, by direct-to-LDS loads: all of them under the pixels' round trip
+        // the filters, by direct-to-LDS loads: all of them under the pixels' round trip.  (Their rows and pieces in steps from load to load)
         const __amdgpu_buffer_rsrc_t wr = __builtin_amdgcn_make_buffer_rsrc(const_cast<int8_t*>(w), 0, P.w_bytes, 0x00020000);
-        const int pieces = P.C_in >> 4;
-        const int wv = __builtin_amdgcn_readfirstlane(wave);
+        const int pieces = P.C_in >> 4, rows = min(32 * CB, P.C_out - co0);
+        int row = fast_div(tid, P.by_slots), g = tid - row * (pieces + 1);
+        unsigned off = (unsigned)((co0 + row) * P.C_in + 16 * g);
+        const unsigned step = (unsigned)(P.d_row * P.C_in + 16 * P.d_piece), turn = (unsigned)(P.C_in - 16 * (pieces + 1));
 #pragma unroll 2
-        for (int k = wv; k < P.wloads; k += 4) {
-            const int i = 64 * k + lane, row = fast_div(i, P.by_slots), g = i - row * (pieces + 1);
-            const bool have = row < 32 * CB && g < pieces && co0 + row < P.C_out;
-            __builtin_amdgcn_raw_ptr_buffer_load_lds(wr, SW_LDS_PTR(smem + 1024 * k), 16, have ? (unsigned)((co0 + row) * P.C_in + 16 * g) : kBeyond, 0, 0, 0);
+        for (int k = wave; k < P.wloads; k += 4) {
+            __builtin_amdgcn_raw_ptr_buffer_load_lds(wr, SW_LDS_PTR(smem + 1024 * k), 16, row < rows && g < pieces ? off : kBeyond, 0, 0, 0);
+            row += P.d_row; g += P.d_piece; off += step;
+            if (g > pieces) { g -= pieces + 1; ++row; off += turn; }
         }
-        if (tid < 32 * CB) {
-            const int co = min(co0 + tid, P.C_out - 1);
-            reinterpret_cast<int*>(smem + P.rq_off)[tid] = P.rq.bias ? P.rq.bias[co] : 0;
-            reinterpret_cast<float*>(smem + P.rq_off)[32 * CB + tid] = P.rq.scale[co];
-        }
+    }
+    if (tid < 32 * CB) {
+        reinterpret_cast<int*>(smem + P.rq_off)[tid] = bias;
+        reinterpret_cast<float*>(smem + P.rq_off)[32 * CB + tid] = scale;
     }
     __syncthreads();
 
     const unsigned char* arow = smem + lj * P.pitch + 16 * kq;
+    // the filters of a step, kAhead steps ahead of it; a tile takes whole halves of a chunk, and steps beyond the last meet pixels of zeros
+    constexpr int kAhead = kChunkSteps / 2 - 1;
+    intx4 a[kAhead + 1][CB];
+    const int whole = (steps + kAhead) & ~kAhead;
+    int ahead = 0;
+    auto read = [&](int i) __attribute__((always_inline)) {
+        const unsigned char* from = arow + 32 * min(ahead, steps - 1);
+#pragma unroll
+        for (int cb = 0; cb < CB; ++cb) a[i][cb] = *reinterpret_cast<const intx4*>(from + 32 * cb * P.pitch);
+        ahead = ahead + 1 == whole ? 0 : ahead + 1;
+    };
+#pragma unroll
+    for (int i = 0; i < kAhead; ++i) read(i);
 #pragma unroll 1
     for (; tile < P.tiles; tile += nwaves) {
+        // (the sums start from the biases)
         intx16 acc[CB];
 #pragma unroll
         for (int cb = 0; cb < CB; ++cb)
 #pragma unroll
-            for (int v = 0; v < 16; ++v) acc[cb][v] = 0;
-        const bool more = tile + nwaves < P.tiles;
-        const int8_t* xn = x_of(more ? tile + nwaves : tile);
+            for (int q = 0; q < 4; ++q) {
+                const intx4 bi = *reinterpret_cast<const intx4*>(smem + P.rq_off + 4 * (32 * cb + 8 * q + 4 * kq));
+#pragma unroll
+                for (int j = 0; j < 4; ++j) acc[cb][4 * q + j] = bi[j];
+            }
+        const __amdgpu_buffer_rsrc_t xn = pixels(tile + nwaves);
 #pragma unroll 1
         for (int s0 = 0; s0 < steps; s0 += kChunkSteps) {
-            intx4 cur[kChunkSteps];
+            // The filters of the third step on between the matrix instructions of this one, in no branch: where paths with and without reads
+            // meet, the compiler waits as if there were none.  A step's pixels are fetched again, those of the next chunk or tile, as they are
+            // used: eight loads are always under way, and no register is copied.
+            const bool last = s0 + kChunkSteps >= steps;
+            auto again = [&](int i) __attribute__((always_inline)) { fetch(i, last ? xn : xr, last ? i : s0 + kChunkSteps + i); };
+            auto half = [&](int first) __attribute__((always_inline)) {
 #pragma unroll
-            for (int i = 0; i < kChunkSteps; ++i) cur[i] = b[i];
-            if (s0 + kChunkSteps < steps) fetch(xp, s0 + kChunkSteps);
-            else if (more) fetch(xn, 0);
+                for (int i = first; i < first + kChunkSteps / 2; ++i) {
+                    __builtin_amdgcn_sched_barrier(0);
+                    read((i + kAhead) & kAhead);
 #pragma unroll
-            for (int i = 0; i < kChunkSteps; ++i) {
-                if (s0 + i >= steps) break;
+                    for (int cb = 0; cb < CB; ++cb) acc[cb] = __builtin_amdgcn_mfma_i32_32x32x32_i8(a[i & kAhead][cb], b[i], acc[cb], 0, 0, 0);
 #pragma unroll
-                for (int cb = 0; cb < CB; ++cb) {
-                    const intx4 a = *reinterpret_cast<const intx4*>(arow + 32 * cb * P.pitch + 32 * (s0 + i));
-                    acc[cb] = __builtin_amdgcn_mfma_i32_32x32x32_i8(a, cur[i], acc[cb], 0, 0, 0);
+                    for (int cb = 0; cb < CB; ++cb) {
+                        __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
+                        __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);
+                    }
+                    __builtin_amdgcn_sched_barrier(0);
+                    again(i);
                 }
+            };
+            half(0);
+            if (s0 + kChunkSteps / 2 < steps) {
+                half(kChunkSteps / 2);
+            } else {
+#pragma unroll
+                for (int i = kChunkSteps / 2; i < kChunkSteps; ++i) again(i);
             }
         }
-        xp = xn;
+        xr = xn;
 
         // register v of a lane is output channel 8 (v / 4) + 4 kq + v % 4 of the block, pixel lj
         const int p0 = 32 * tile;
         constexpr int OP = 32 * CB + 16;               // bytes per pixel in the store area
         unsigned char* lo = smem + P.out_off + wave * 32 * OP;
+        // (all scales before the first result is written: the compiler lets no read of LDS pass a write to it, and sixteen waits for one
+        // scale each took most of the packing's time)
+        floatx4 scales[CB][4];
+#pragma unroll
+        for (int cb = 0; cb < CB; ++cb)
+#pragma unroll
+            for (int q = 0; q < 4; ++q)
+                scales[cb][q] = *reinterpret_cast<const floatx4*>(smem + P.rq_off + 128 * CB + 4 * (32 * cb + 8 * q + 4 * kq));
         auto pack = [&](auto relu) __attribute__((always_inline)) {
 #pragma unroll
             for (int cb = 0; cb < CB; ++cb)
 #pragma unroll
                 for (int q = 0; q < 4; ++q) {
                     const int col = 32 * cb + 8 * q + 4 * kq;
-                    const intx4 bi = *reinterpret_cast<const intx4*>(smem + P.rq_off + 4 * col);
-                    const floatx4 sc = *reinterpret_cast<const floatx4*>(smem + P.rq_off + 128 * CB + 4 * col);
+                    const floatx4& sc = scales[cb][q];
                     *reinterpret_cast<int*>(lo + lj * OP + col) =
-                        requant_pack4<decltype(relu)::value>(acc[cb][4 * q] + bi[0], acc[cb][4 * q + 1] + bi[1], acc[cb][4 * q + 2] + bi[2],
-                                                             acc[cb][4 * q + 3] + bi[3], sc[0], sc[1], sc[2], sc[3]);
+                        requant_pack4<decltype(relu)::value>(acc[cb][4 * q], acc[cb][4 * q + 1], acc[cb][4 * q + 2], acc[cb][4 * q + 3], sc[0], sc[1],
+                                                             sc[2], sc[3]);
                 }
         };
         if (P.rq.relu) pack(std::true_type{});
@@ -189,6 +244,8 @@ PwS8Plan plan_pw_s8(const int8_t* x, const int8_t* w, const int8_t* y, const Con
         P.pitch = pitch; P.rq_off = (int)filters; P.out_off = (int)(filters + rq);
         P.wloads = (int)(filters / 1024); P.w_bytes = (unsigned)((int64_t)s.C_out * s.C_in);
         P.by_slots = make_fastdiv(s.C_in / 16 + 1);
+        P.d_row = 256 / (s.C_in / 16 + 1);
+        P.d_piece = 256 % (s.C_in / 16 + 1);
         a.gy = (unsigned)groups;
         // persistent: as many workgroups as fit their CUs at once, by registers two of CB = 4 and three of CB = 2 (four, as LDS would have it,
         // left a second turn of a few: 128 -> 512 at 28 x 28 12.7 us against 11.3, at 56 x 56 26.9 against 24.2)
