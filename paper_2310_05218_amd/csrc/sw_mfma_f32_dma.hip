@@ -476,6 +476,12 @@ DmaPlan plan_dma(const Conv2dShape& s, const void* x, const void* w)
 
 bool mfma_f32_dma_supported(const Conv2dShape& s, const float* x, const float* w) { return plan_dma(s, x, w).ok; }
 
+int mfma_f32_dma_parts(const Conv2dShape& s, const float* x, const float* w)
+{
+    const DmaPlan a = plan_dma(s, x, w);
+    return a.ok ? a.KS : 0;
+}
+
 hipError_t launch_mfma_f32_dma(const float* x, const float* w, float* y, const Conv2dShape& s, hipStream_t st, const Epilogue& ep)
 {
     DmaPlan a = plan_dma(s, x, w);

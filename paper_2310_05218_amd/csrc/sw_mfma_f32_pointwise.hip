@@ -6,7 +6,7 @@
 // With one tap there is no window: per image the sum is a plain matrix product whose B operand (channels x pixels) is
 // the input tensor as it lies in memory.  The kernel therefore stages nothing of the input.  A wavefront owns 32 * QB
 // consecutive pixels (counted through all images: a plane's pixel count is a multiple of QB, so the QB pixels of a lane
-// never straddle two images) and CB blocks of 32 output channels.  Lane (lj, kk) of the 32 x 2 lane grid loads, for
+// never straddle two images; odd planes: see the loose form of the kernel on split operands) and CB blocks of 32 output channels.  Lane (lj, kk) of the 32 x 2 lane grid loads, for
 // channel c, the QB consecutive pixels QB * lj .. QB * lj + QB - 1 with ONE load of 4 * QB bytes; element q of that
 // load is its B operand for pixel block q, where block q is the pixels {QB * n + q}.  The matrix instruction does not
 // care which pixel a column stands for, and on the way out the same permutation makes a lane's QB results for an
@@ -44,6 +44,7 @@ struct PwParams {
     int C_in, C_out, HW;
     int total_px;     // N * H * W
     int tiles;        // of 32 * QB pixels
+    int plane_groups; // (loose) groups of QB pixels of a plane; total_px counts groups then
     int wpitch;       // floats between filter rows in LDS
     FastDiv by_c4;    // 16-byte groups per filter row
     FastDiv by_oct;   // (split) groups of eight channels, rounded up to whole steps
@@ -227,11 +228,14 @@ __global__ __launch_bounds__(256, 2) void mfma_f32_pointwise_kernel(const float*
 // 45.7 -> 32.8, 64 -> 256 51.6 -> 44.8, 256 -> 256 at 28 x 28 42.2 -> 30.7, 512 -> 512 at 14 x 14 40.5 -> 34.1, 24 x 136 x 58 x 58 -> 16
 // 25.4 -> 20.0; error against 64 bits 2.9e-7 -> 2.4e-7.  128 MB are 23 us at the rate of a large copy; the products are 13 us, one
 // wavefront per SIMD.
-template <int CB, int QB, int NB>
+// LOOSE: planes of any size at any 4-byte address.  A plane is taken in QB-pixel groups of its own, the last of which ends with the plane: its first
+// pixels are the group before's once more, computed alike and stored twice.  Loads and stores are of 16 bytes all the same (they need no more
+// than 4-byte alignment); the stores go through L2, because the nontemporal ones of the aligned form would write parts of lines.
+template <int CB, int QB, int NB, bool LOOSE>
 __global__ __launch_bounds__(256, CB * QB == 8 ? 1 : 2) void mfma_f32_pointwise_split_kernel(const float* __restrict__ x, const float* __restrict__ w,
                                                                                        float* __restrict__ y, const PwParams P)
 {
-    typedef float bvec __attribute__((ext_vector_type(QB)));
+    typedef float bvec __attribute__((ext_vector_type(QB), aligned(LOOSE ? 4 : 4 * QB)));
     extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
     constexpr int kRow = CB * 32 + 1;                        // 16-byte units of a (step, part, lane half): odd, spreads the writes
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, lj = lane & 31, kk = lane >> 5;
@@ -248,8 +252,16 @@ __global__ __launch_bounds__(256, CB * QB == 8 ? 1 : 2) void mfma_f32_pointwise_
         int n, pix;
     };
     auto place = [&](int tl) __attribute__((always_inline)) {
-        const int pg = tl * (32 * QB) + QB * lj;
         Place p;
+        if constexpr (LOOSE) {
+            const int g = tl * 32 + lj;
+            p.live = tl < P.tiles && g < P.total_px;            // (groups)
+            const int gc = p.live ? g : 0;
+            p.n = gc / P.plane_groups;
+            p.pix = min(QB * (gc - p.n * P.plane_groups), HW - QB);
+            return p;
+        }
+        const int pg = tl * (32 * QB) + QB * lj;
         p.live = tl < P.tiles && pg < P.total_px;
         const int pgc = p.live ? pg : 0;
         p.n = pgc / HW;
@@ -443,7 +455,8 @@ __global__ __launch_bounds__(256, CB * QB == 8 ? 1 : 2) void mfma_f32_pointwise_
                         bvec o;
 #pragma unroll
                         for (int q = 0; q < QB; ++q) o[q] = whole ? acc[cb][q][v] : apply_epilogue(acc[cb][q][v], co, P.ep);
-                        __builtin_nontemporal_store(o, reinterpret_cast<bvec*>(yp + (int64_t)co * HW));
+                        if constexpr (LOOSE) *reinterpret_cast<bvec*>(yp + (int64_t)co * HW) = o;
+                        else __builtin_nontemporal_store(o, reinterpret_cast<bvec*>(yp + (int64_t)co * HW));
                     }
                 }
             }
@@ -474,7 +487,8 @@ struct PwPlan {
     size_t lds = 0;
 };
 
-PwPlan plan_pointwise(const Conv2dShape& s, const float* x, const float* w, const float* y)
+// loose: planes of any size at any 4-byte address, on split operands alone
+PwPlan plan_pointwise(const Conv2dShape& s, const float* x, const float* w, const float* y, bool loose = false)
 {
     PwPlan a;
     const int64_t HW = (int64_t)s.H * s.W;
@@ -482,6 +496,7 @@ PwPlan plan_pointwise(const Conv2dShape& s, const float* x, const float* w, cons
     if (HW * s.N >= (1LL << 31) - (1 << 20) || HW * s.C_in >= (1LL << 31) || reinterpret_cast<uintptr_t>(w) % 16 != 0) return a;
     const auto fits = [&](int cb) { return (size_t)cb * 32 * (s.C_in + 4) * sizeof(float) <= kPwLdsMax; };
     const auto aligned = [&](int qb) {
+        if (loose) return HW >= qb && (reinterpret_cast<uintptr_t>(x) | reinterpret_cast<uintptr_t>(y)) % 4 == 0;
         return HW % qb == 0 && reinterpret_cast<uintptr_t>(x) % (4 * qb) == 0 && reinterpret_cast<uintptr_t>(y) % (4 * qb) == 0;
     };
     const auto units = [&](int cb, int qb) {
@@ -498,7 +513,7 @@ PwPlan plan_pointwise(const Conv2dShape& s, const float* x, const float* w, cons
         a.ok = true;
         if (units(v[0], v[1]) >= 700) break;
     }
-    if (!a.ok) return a;                // (odd planes, filters beyond LDS)
+    if (!a.ok) return a;                // (odd planes but for the loose form, filters beyond LDS)
     a.lds = (size_t)a.CB * 32 * (s.C_in + 4) * sizeof(float);
     // Split operands where their filters fit LDS, but not where the last, half empty step of 16 channels is a large part of few
     // (8 -> 32 at 256 x 256, 5 images: 15.4 us against 25.1; 72 -> 248 at 66 x 65, 7 images: 20.7 against 21.8), and from `least`
@@ -523,42 +538,60 @@ PwPlan plan_pointwise(const Conv2dShape& s, const float* x, const float* w, cons
     if (waves >= 700 && a.CB == 1 && a.QB == 4) least = waves > 2560 ? 80 : whole ? 16 : 48;
     if (waves >= 700 && a.CB == 2 && a.QB == 2) least = (int)std::min<int64_t>(80, 32 + 16 * (std::max<int64_t>(0, waves - 512) / 1024));
     a.split = split_lds <= kPwLdsSplit && (s.C_in % 16 == 0 || s.C_in >= 128) && s.C_in >= least;
+    if (loose) a.split = split_lds <= kPwLdsSplit && waves >= 128 && (s.C_in >= 48 || whole || a.CB * a.QB < 8 || waves <= 1024);
     if (a.split) a.lds = split_lds;
+    else if (loose) a.ok = false;
     return a;
+}
+
+template <int CB, int QB, int NB>
+PwParams pw_params(const Conv2dShape& s, const Epilogue& ep, bool loose)
+{
+    PwParams P;
+    P.C_in = s.C_in;
+    P.C_out = s.C_out;
+    P.HW = s.H * s.W;
+    P.plane_groups = (P.HW + QB - 1) / QB;
+    P.total_px = s.N * (loose ? P.plane_groups : P.HW);
+    P.tiles = loose ? (P.total_px + 31) / 32 : (P.total_px + 32 * QB - 1) / (32 * QB);
+    P.wpitch = s.C_in + 4;
+    P.by_c4 = make_fastdiv(s.C_in / 4);
+    P.by_oct = make_fastdiv(2 * ((s.C_in + 15) / 16));
+    P.ep = ep;
+    return P;
+}
+
+// persistent: at most two workgroups per CU (one when the filters take more than half of its LDS)
+dim3 pw_grid(int tiles, int groups, size_t lds)
+{
+    const int per_cu = lds <= 78 * 1024 ? 2 : 1, cap = (256 * per_cu + groups - 1) / groups;
+    return dim3((unsigned)std::min((tiles + 3) / 4, cap), (unsigned)groups);
+}
+
+template <int CB, int QB, int NB, bool LOOSE>
+hipError_t launch_split(const float* x, const float* w, float* y, const Conv2dShape& s, const PwPlan& a, hipStream_t st, const Epilogue& ep)
+{
+    static const hipError_t attr = hipFuncSetAttribute(reinterpret_cast<const void*>(mfma_f32_pointwise_split_kernel<CB, QB, NB, LOOSE>),
+                                                       hipFuncAttributeMaxDynamicSharedMemorySize, (int)kPwLdsSplit);
+    if (attr != hipSuccess) return attr;
+    const PwParams P = pw_params<CB, QB, NB>(s, ep, LOOSE);
+    SW_NOTED_LAUNCH(LOOSE ? note_kernel("mfma_f32_pointwise_split_kernel", CB, QB, 1) : note_kernel("mfma_f32_pointwise_split_kernel", CB, QB),
+                    (mfma_f32_pointwise_split_kernel<CB, QB, NB, LOOSE>), pw_grid(P.tiles, (s.C_out + CB * 32 - 1) / (CB * 32), a.lds), dim3(256), a.lds,
+                    st, x, w, y, P);
+    return hipGetLastError();
 }
 
 template <int CB, int QB, int NB>
 hipError_t launch_pw(const float* x, const float* w, float* y, const Conv2dShape& s, const PwPlan& a, hipStream_t st,
                      const Epilogue& ep)
 {
+    if (a.split) return launch_split<CB, QB, NB, false>(x, w, y, s, a, st, ep);
     static const hipError_t attr = hipFuncSetAttribute(reinterpret_cast<const void*>(mfma_f32_pointwise_kernel<CB, QB, NB>),
                                                        hipFuncAttributeMaxDynamicSharedMemorySize, (int)kPwLdsMax);
-    static const hipError_t attr_split = hipFuncSetAttribute(reinterpret_cast<const void*>(mfma_f32_pointwise_split_kernel<CB, QB, NB>),
-                                                             hipFuncAttributeMaxDynamicSharedMemorySize, (int)kPwLdsSplit);
-    if (attr != hipSuccess || attr_split != hipSuccess) return attr != hipSuccess ? attr : attr_split;
-    PwParams P;
-    P.C_in = s.C_in;
-    P.C_out = s.C_out;
-    P.HW = s.H * s.W;
-    P.total_px = s.N * P.HW;
-    P.tiles = (P.total_px + 32 * QB - 1) / (32 * QB);
-    P.wpitch = s.C_in + 4;
-    P.by_c4 = make_fastdiv(s.C_in / 4);
-    P.by_oct = make_fastdiv(2 * ((s.C_in + 15) / 16));
-    P.ep = ep;
-    const int gy = (s.C_out + CB * 32 - 1) / (CB * 32);
-    // persistent: at most two workgroups per CU (one when the filters take more than half of its LDS)
-    const int per_cu = a.lds <= 78 * 1024 ? 2 : 1;
-    int gx = (P.tiles + 3) / 4;
-    const int cap = (256 * per_cu + gy - 1) / gy;
-    if (gx > cap) gx = cap;
-    if (a.split) {
-        SW_NOTED_LAUNCH(note_kernel("mfma_f32_pointwise_split_kernel", CB, QB), (mfma_f32_pointwise_split_kernel<CB, QB, NB>),
-                        dim3((unsigned)gx, (unsigned)gy), dim3(256), a.lds, st, x, w, y, P);
-        return hipGetLastError();
-    }
-    SW_NOTED_LAUNCH(note_kernel("mfma_f32_pointwise_kernel", CB, QB), (mfma_f32_pointwise_kernel<CB, QB, NB>), dim3((unsigned)gx, (unsigned)gy),
-                    dim3(256), a.lds, st, x, w, y, P);
+    if (attr != hipSuccess) return attr;
+    const PwParams P = pw_params<CB, QB, NB>(s, ep, false);
+    SW_NOTED_LAUNCH(note_kernel("mfma_f32_pointwise_kernel", CB, QB), (mfma_f32_pointwise_kernel<CB, QB, NB>),
+                    pw_grid(P.tiles, (s.C_out + CB * 32 - 1) / (CB * 32), a.lds), dim3(256), a.lds, st, x, w, y, P);
     return hipGetLastError();
 }
 
@@ -579,6 +612,27 @@ hipError_t launch_mfma_f32_pointwise(const float* x, const float* w, float* y, c
     SW_PW(2, 4); SW_PW(1, 4); SW_PW(2, 2); SW_PW(1, 2);
 #undef SW_PW
     return hipErrorInvalidValue;
+}
+
+// Planes that the aligned form refuses.  Against the direct-to-LDS kernel, which fetches them value by value (graph of ten, us): 152 -> 488 at 21 x 21,
+// 16 images 34.7 -> 18.9; 504 -> 488 at 27 x 27, 11 images 100.6 -> 39.2; 128 -> 87 at 89 x 69, 19 images 103.7 -> 43.0; 104 -> 72 at 51 x 51, 3 images
+// 14.2 -> 9.2; 56 -> 456 at 7 x 7, 23 images 12.4 -> 8.1; over 87 drawn layers 1.50.  Left to that kernel: its sums in two or four parts
+// (small launches; 0.90 to 1.2, and one sum's error may be larger than that of parts), fewer than 128 units (0.95 to 1.05), more than one round of
+// <2,4> with fewer than 48 channels and a block of results that is not whole (40 -> 48 at 77 x 77, 23 images 26.7 / 28.2), and fewer than 32
+// channels in 16-byte groups, which are bound by the results (24 -> 248 at 63 x 63, 19 images 33.2 / 34.2; in 8-byte groups 24 -> 112 at 35 x 35, 12
+// images 13.0 / 8.3).  Even planes stay on the aligned 8-byte form, 16-byte groups are 0.81 to 1.45 of it.
+bool mfma_f32_pointwise_loose_supported(const Conv2dShape& s, const float* x, const float* w, const float* y)
+{
+    const PwPlan a = plan_pointwise(s, x, w, y, true);
+    return a.ok && (s.C_in >= 32 || (s.C_in >= 16 && a.QB == 2)) && mfma_f32_dma_parts(s, x, w) <= 1;
+}
+
+hipError_t launch_mfma_f32_pointwise_loose(const float* x, const float* w, float* y, const Conv2dShape& s, hipStream_t st, const Epilogue& ep)
+{
+    const PwPlan a = plan_pointwise(s, x, w, y, true);
+    if (!a.ok) return hipErrorInvalidValue;
+    if (a.QB == 4) return a.CB == 2 ? launch_split<2, 4, kRing, true>(x, w, y, s, a, st, ep) : launch_split<1, 4, kRing, true>(x, w, y, s, a, st, ep);
+    return a.CB == 2 ? launch_split<2, 2, kRing, true>(x, w, y, s, a, st, ep) : launch_split<1, 2, kRing, true>(x, w, y, s, a, st, ep);
 }
 
 }  // namespace swconv

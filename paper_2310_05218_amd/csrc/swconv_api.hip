@@ -296,6 +296,9 @@ static int run_conv2d(const float* x, const float* w, float* y, const Conv2dShap
         // faster than the window kernels on every such layer tried.
         if (mfma_f32_pointwise_supported(s, x, w, y))
             return launch_status(launch_mfma_f32_pointwise(x, w, y, s, st, ep));
+        // planes of an odd number of pixels and tensors that begin between 8-byte addresses
+        if (mfma_f32_pointwise_loose_supported(s, x, w, y))
+            return launch_status(launch_mfma_f32_pointwise_loose(x, w, y, s, st, ep));
         if (s.R * s.S >= 25 && s.C_in >= 8 && mfma_f32_rows_supported(s, x))
             return launch_status(launch_mfma_f32_rows(x, w, y, s, st, ep));
         // Few channels at an even stride (the first layer of an image network): K along the filter rows

@@ -192,6 +192,7 @@ hipError_t launch_sliding_plane(const float* x, const float* w, float* y, int64_
 // ---- multi-channel fp32, few taps (1x1 ... 4x4), C_in % 8 == 0, any stride / padding / dilation: both operands
 // brought into LDS by direct-to-LDS loads, two stages (16-byte aligned w, tensors below 2 GiB)
 bool       mfma_f32_dma_supported(const Conv2dShape& s, const float* x, const float* w);
+int        mfma_f32_dma_parts(const Conv2dShape& s, const float* x, const float* w);      // parts of its sums (0: not supported)
 hipError_t launch_mfma_f32_dma(const float* x, const float* w, float* y, const Conv2dShape& s, hipStream_t st,
                                const Epilogue& ep = Epilogue{nullptr, 0});
 
@@ -303,6 +304,8 @@ hipError_t launch_mfma_f32_rows(const float* x, const float* w, float* y, const 
 bool       mfma_f32_pointwise_supported(const Conv2dShape& s, const float* x, const float* w, const float* y);
 hipError_t launch_mfma_f32_pointwise(const float* x, const float* w, float* y, const Conv2dShape& s, hipStream_t st,
                                      const Epilogue& ep = Epilogue{nullptr, 0});
+bool mfma_f32_pointwise_loose_supported(const Conv2dShape& s, const float* x, const float* w, const float* y);
+hipError_t launch_mfma_f32_pointwise_loose(const float* x, const float* w, float* y, const Conv2dShape& s, hipStream_t st, const Epilogue& ep);
 bool       mfma_f32_quad_supported(const Conv2dShape& s); // the same for few taps (R * S <= 12): 16-byte operand reads
 hipError_t launch_mfma_f32_quad(const float* x, const float* w, float* y, const Conv2dShape& s, hipStream_t st,
                                 const Epilogue& ep = Epilogue{nullptr, 0});
