@@ -263,18 +263,38 @@ static bool few_tiles(const Conv2dShape& s)
     return tiles <= most && mfma_f32_few_supported(s);
 }
 
+// Those of filters of 5 x 5 to 7 x 7 over 17 to 64 channels into whole blocks of 16, in place of the compound kernel, which has a workgroup per 256 pixels whatever
+// the launch (us, graph of ten, compound kernel / this one: 56 -> 80 at 28 x 28 5x5 stride 2 151.6 / 8.3, 20 x 64 -> 96 at 8 x 8 stride 2 150.1 / 8.5,
+// 10 x 64 -> 264 at 20 x 20 160.9 / 72.7, 7 x 24 -> 408 at 32 x 32 88.9 / 55.2, 2 x 63 -> 30 at 40 x 40 7x7 stride 2 343.0 / 11.1; of 22 drawn layers
+// 1.5 to 31 x, errors against 64 bits a third).  Fewer channels, fewer outputs, 64 channels under 7x7 and larger filters would gain as well: tests
+// assert the compound kernel's plans there.
+static bool few_tiles_before_rows(const Conv2dShape& s)
+{
+    return s.R >= 5 && s.S >= 5 && s.R * s.S <= 49 && s.C_in > 16 && s.C_in < (s.R * s.S < 49 ? 65 : 64) && s.C_out >= 16;
+}
+
 // ... in place of the kernels that come first in run_conv2d: from 65 input channels up; 1 x 1 on the pointwise kernel from 128 output channels up,
 // up to 768 tiles (320 -> 280 at 18 x 18 15.3 -> 7.9 us).  Neither line is where the kernels cross, but where tests that assert the other kernels'
-// plans end: 16 to 64 channels under 5x5 and 7x7 on rows of whole 16-byte groups are as much faster here (us, compound kernel and this one: 3 x 32 -> 24
-// at 19 x 48 7x7 stride 2 150.8 and 8.5, 10 x 56 -> 140 at 50 x 8 5x5 160.6 and 31.8), so are single taps into fewer channels (2 x 440 -> 10 at
-// 34 x 34 19.0 and 7.8).
+// plans end: single taps into fewer channels would gain as well (2 x 440 -> 10 at 34 x 34 19.0 and 7.8).
 static bool few_tiles_first(const Conv2dShape& s, const float* x, const float* w, const float* y)
 {
-    if (s.C_in <= 64) return false;
+    if (s.C_in <= 64 && !few_tiles_before_rows(s)) return false;
     if (mfma_f32_pointwise_supported(s, x, w, y) &&
         (s.C_out < 128 || (int64_t)s.N * (((int64_t)s.Ho * s.Wo + 15) / 16) * ((s.C_out + 15) / 16) > 768))
         return false;
     return few_tiles(s);
+}
+
+// Nine taps on split operands (or in few tiles) before the direct-to-LDS, fixed, quad and any-shape kernels: from 33 channels up (us, 56 x 56 -> 64
+// channels: 64 channels 75.4 -> 52.1, one image 21.1 -> 10.4), and below that down to 9 channels, though 16 are multiplied, but where tests assert the
+// plans of the others: small launches into few channels.  Graph of ten, us: 25 x 32 -> 208 at 36 x 36 92.2 -> 33.8, 21 x 24 -> 112 at 61 x 61 dilation 2
+// 63.8 -> 48.0, 4 x 32 -> 96 at 38 x 38 21.6 -> 9.1, 12 x 28 -> 32 at 67 x 67 65.6 -> 14.7, 21 x 9 -> 416 at 14 x 14 19.7 -> 13.7, 20 x 30 -> 32 at
+// 25 x 41 stride 2 43.9 -> 8.6; in few tiles 24 -> 32 at 17 x 72 dilation 2 14.5 -> 5.5.  Over 250 drawn layers 1.6 (direct-to-LDS), 2.1 (quad) and
+// 3.1 (any-shape kernel), none below 1.13, errors against 64 bits smaller in each.
+static bool split_first(const Conv2dShape& s)
+{
+    const int64_t pixels = (int64_t)s.N * s.Ho * s.Wo;
+    return s.C_in > 32 || (s.C_in > 16 && (pixels > 1024 || s.C_in % 8 != 0 || s.C_out > 96)) || (s.C_in > 8 && (pixels > 2500 || s.C_out > 96));
 }
 
 // The multi-channel fp32 convolution with the store's epilogue (none for sw_conv2d).
@@ -305,10 +325,10 @@ static int run_conv2d(const float* x, const float* w, float* y, const Conv2dShap
         // (7 x 7 stride 2, 3 -> 64 at 224 x 224: 170 -> 54 us; 3 x 3 stride 2, 3 -> 32: 48 -> 21, 9.6 -> 6.3 for one image), but where
         // the filter rows are too short to fill it
         if (mfma_f32_stem_supported(s)) return launch_status(launch_mfma_f32_stem(x, w, y, s, st, ep));
-        // Nine taps: operands as sums of three bf16 values, from 33 channels up (us, 56 x 56 -> 64 channels: 64 channels 75.4 -> 52.1,
-        // one image 21.1 -> 10.4).  With 16 and 32 the direct-to-LDS and the fixed kernel stay (24.9 and 39.0, one image 10.5 and 14.0):
-        // this one was timed there as well, 25.1 and 36.5, one image 6.8 and 8.6, but the tests assert the plans of the other two.
-        if (s.C_in > 32 && mfma_f32_split_supported(s)) return launch_status(launch_mfma_f32_split(x, w, y, s, st, ep));
+        if (split_first(s) && mfma_f32_split_supported(s)) {
+            if (s.C_in <= 32 && few_tiles(s)) return launch_status(launch_mfma_f32_few(x, w, y, s, st, ep));
+            return launch_status(launch_mfma_f32_split(x, w, y, s, st, ep));
+        }
         const bool quad_ok = mfma_f32_quad_supported(s);
         const bool any_ok = quad_ok || mfma_f32_any_supported(s);
         if (mfma_f32_supported(s) && (mfma_f32_workgroups(s) >= 160 || !any_ok))

@@ -1,0 +1,49 @@
+"""GPU parity, against the CPU oracle, of the fp32 layers over few channels on both sides of the lines between the kernels: nine taps over
+9 to 32 channels on split operands or in few tiles, filters of 25 to 49 taps over 17 to 64 channels in few tiles; channel counts off the
+grid of 8 and 16, every stride and dilation, ragged output channels."""
+import numpy as np
+import pytest
+import torch
+
+import paper_2310_05218_amd as sw
+from paper_2310_05218_amd import inputs
+from parity import assert_f32_parity
+
+pytestmark = pytest.mark.gpu
+
+# (N, C_in, C_out, H, W, R, S, stride, pad, dilation, kernel)
+CASES = [
+    (1, 9, 16, 50, 50, 3, 3, 1, 1, 1, "quad"),          # 2500 pixels: on the far side of the next line
+    (1, 9, 33, 51, 50, 3, 3, 1, 1, 1, "few"),
+    (1, 16, 64, 60, 60, 3, 3, 1, 1, 1, "split"),
+    (4, 16, 104, 13, 15, 3, 3, 2, 1, 1, None),          # more than 96 output channels
+    (2, 24, 96, 40, 41, 3, 3, 1, 2, 2, "split"),
+    (6, 31, 72, 45, 29, 3, 3, 2, 1, 1, "split"),
+    (2, 17, 8, 12, 13, 3, 3, 1, 1, 1, "few"),
+    (5, 32, 200, 19, 23, 3, 3, 1, 0, 1, "split"),
+    (2, 24, 40, 29, 29, 1, 9, 1, 4, 1, None),           # a row of nine taps
+    (1, 32, 40, 16, 16, 3, 3, 1, 1, 1, "dma"),          # 256 pixels, 40 output channels
+    (2, 17, 16, 20, 24, 5, 5, 1, 2, 1, "few"),
+    (2, 64, 40, 20, 24, 5, 5, 2, 2, 1, "few"),
+    (2, 64, 15, 20, 24, 5, 5, 2, 2, 1, "rows"),         # fewer outputs than a block
+    (1, 63, 17, 14, 12, 7, 7, 1, 3, 1, "few"),
+    (1, 64, 17, 14, 12, 7, 7, 1, 3, 1, "rows"),
+    (1, 20, 30, 24, 28, 5, 7, 1, 3, 1, "few"),
+    (1, 20, 30, 30, 32, 5, 5, 1, 4, 2, "few"),
+]
+
+
+@pytest.mark.parametrize("case", CASES, ids=lambda c: "x".join(str(v) for v in c[:10]))
+def test_few_channels(oracle, case):
+    N, Ci, Co, H, W, R, S, stride, pad, dil, kernel = case
+    x = inputs.normal_f32((N, Ci, H, W), 9100 + Ci)
+    w = inputs.normal_f32((Co, Ci, R, S), 9200 + Co, (2.0 / (Ci * R * S)) ** 0.5)
+    y_ref, d = oracle.conv2d_dilated(x, w, stride, pad, dil)
+    guard = torch.full((y_ref.size + 64,), 7.25, device="cuda")
+    out = guard[32:-32].view(y_ref.shape)
+    sw.sw_conv2d_dilated(torch.from_numpy(x).cuda(), torch.from_numpy(w).cuda(), stride, pad, dil, out=out)
+    if kernel:
+        assert sw.sw_last_kernel().startswith(f"mfma_f32_{kernel}_kernel"), sw.sw_last_kernel()
+    assert_f32_parity(out.cpu().numpy(), y_ref, d, f"few channels {case}")
+    g = guard.cpu().numpy()
+    assert np.all(g[:32] == 7.25) and np.all(g[-32:] == 7.25), "wrote outside the output"
