@@ -273,15 +273,20 @@ static bool few_tiles_before_rows(const Conv2dShape& s)
     return s.R >= 5 && s.S >= 5 && s.R * s.S <= 49 && s.C_in > 16 && s.C_in < (s.R * s.S < 49 ? 65 : 64) && s.C_out >= 16;
 }
 
-// ... in place of the kernels that come first in run_conv2d: from 65 input channels up; 1 x 1 on the pointwise kernel from 128 output channels up,
-// up to 768 tiles (320 -> 280 at 18 x 18 15.3 -> 7.9 us).  Neither line is where the kernels cross, but where tests that assert the other kernels'
-// plans end: single taps into fewer channels would gain as well (2 x 440 -> 10 at 34 x 34 19.0 and 7.8).
+// ... in place of the kernels that come first in run_conv2d: from 65 input channels up where the pointwise kernel does not have the layer; in its place
+// from 48 up, up to 640 tiles, or 1600 of 64 and more channels into 128 and more.  Graph of ten, us: 456 -> 48 at 38 x 38, 2 images 20.5 -> 13.4, 272 -> 16
+// at 16 x 16, 20 images 13.7 -> 7.3, 64 -> 40 at 36 x 36, 2 images 9.9 -> 5.7, 488 -> 120 at 24 x 24, 3 images 23.0 -> 9.6, 56 -> 104 at 20 x 20, 3
+// images 6.8 -> 5.8; of 46 drawn layers up to 640 tiles 1.1 to 3.2 x, of 24 of 800 to 1600 tiles into 128 and more channels 1.1 to 2.0 x, errors against 64 bits
+// smaller in each.  Beyond it is 0.85 to 1.25 x, into fewer channels 0.5 (144 -> 16 at 68 x 68, 7 images) to 1.6 x, and from fewer 0.8 to 1.3 x.  Fewer than 128 tiles
+// of fewer than 128 channels and 32 to 47 input channels would gain as well: tests assert the pointwise kernel's plans there.
 static bool few_tiles_first(const Conv2dShape& s, const float* x, const float* w, const float* y)
 {
-    if (s.C_in <= 64 && !few_tiles_before_rows(s)) return false;
-    if (mfma_f32_pointwise_supported(s, x, w, y) &&
-        (s.C_out < 128 || (int64_t)s.N * (((int64_t)s.Ho * s.Wo + 15) / 16) * ((s.C_out + 15) / 16) > 768))
+    if (mfma_f32_pointwise_supported(s, x, w, y)) {
+        const int64_t tiles = (int64_t)s.N * (((int64_t)s.Ho * s.Wo + 15) / 16) * ((s.C_out + 15) / 16);
+        if (s.C_in < 48 || tiles > (s.C_out >= 128 && s.C_in >= 64 ? 1600 : 640) || (tiles < 128 && s.C_out < 128)) return false;
+    } else if (s.C_in <= 64 && !few_tiles_before_rows(s)) {
         return false;
+    }
     return few_tiles(s);
 }
 

@@ -47,3 +47,23 @@ def test_few_channels(oracle, case):
     assert_f32_parity(out.cpu().numpy(), y_ref, d, f"few channels {case}")
     g = guard.cpu().numpy()
     assert np.all(g[:32] == 7.25) and np.all(g[-32:] == 7.25), "wrote outside the output"
+
+
+# (N, C_in, C_out, H, W, kernel): one tap on both sides of the few-tiles lines
+TAPS = [
+    (2, 48, 40, 36, 36, "few"), (2, 40, 40, 36, 36, "pointwise"), (10, 48, 250, 8, 8, "few"), (11, 48, 250, 8, 8, "pointwise"),
+    (18, 64, 130, 10, 14, "few"), (20, 64, 130, 10, 14, "pointwise"), (24, 64, 127, 10, 14, "pointwise"), (3, 456, 17, 20, 22, "few"),
+    (1, 456, 33, 20, 26, "pointwise"), (1, 456, 129, 6, 6, "few"),
+]
+
+
+@pytest.mark.parametrize("case", TAPS, ids=lambda c: "x".join(str(v) for v in c[:5]))
+def test_one_tap(oracle, case):
+    N, Ci, Co, H, W, kernel = case
+    x = inputs.normal_f32((N, Ci, H, W), 9300 + Ci)
+    w = inputs.normal_f32((Co, Ci, 1, 1), 9400 + Co, (2.0 / Ci) ** 0.5)
+    b = inputs.normal_f32((Co,), 9500 + Co)
+    y_ref, d = oracle.conv2d_bias_relu(x, w, b, 1, 0, True)
+    y = sw.sw_conv2d_bias_relu(torch.from_numpy(x).cuda(), torch.from_numpy(w).cuda(), torch.from_numpy(b).cuda(), 1, 0, True)
+    assert sw.sw_last_kernel().startswith(f"mfma_f32_{kernel}_"), sw.sw_last_kernel()
+    assert_f32_parity(y.cpu().numpy(), y_ref, d, f"one tap {case}")
