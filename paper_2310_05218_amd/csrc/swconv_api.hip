@@ -279,13 +279,16 @@ static bool few_tiles_before_rows(const Conv2dShape& s)
 // images 6.8 -> 5.8; of 46 drawn layers up to 640 tiles 1.1 to 3.2 x, of 24 of 800 to 1600 tiles into 128 and more channels 1.1 to 2.0 x, errors against 64 bits
 // smaller in each.  Beyond it is 0.85 to 1.25 x, into fewer channels 0.5 (144 -> 16 at 68 x 68, 7 images) to 1.6 x, and from fewer 0.8 to 1.3 x.  Fewer than 128 tiles
 // of fewer than 128 channels and 32 to 47 input channels would gain as well: tests assert the pointwise kernel's plans there.
+// Single taps that the pointwise kernel does not have (strides, odd planes), in place of the direct-to-LDS kernel, up to 1600 tiles of 32 to 64 channels,
+// 1000 into fewer than 48 (1.05 to 2.2 x of 100 drawn layers, errors smaller in each: 56 -> 424 at 11 x 11, 2 images 13.5 -> 5.8, 64 -> 64 at 97 x 97 stride 2 12.2 -> 6.0; beyond
+// 0.86 to 1.5 x; of 24 channels 0.96 to 1.6 x, some errors larger).
 static bool few_tiles_first(const Conv2dShape& s, const float* x, const float* w, const float* y)
 {
+    const int64_t tiles = (int64_t)s.N * (((int64_t)s.Ho * s.Wo + 15) / 16) * ((s.C_out + 15) / 16);
     if (mfma_f32_pointwise_supported(s, x, w, y)) {
-        const int64_t tiles = (int64_t)s.N * (((int64_t)s.Ho * s.Wo + 15) / 16) * ((s.C_out + 15) / 16);
         if (s.C_in < 48 || tiles > (s.C_out >= 128 && s.C_in >= 64 ? 1600 : 640) || (tiles < 128 && s.C_out < 128)) return false;
     } else if (s.C_in <= 64 && !few_tiles_before_rows(s)) {
-        return false;
+        if (s.R * s.S != 1 || s.C_in < 32 || tiles < 65 || tiles > (s.C_out < 48 ? 1000 : 1600)) return false;
     }
     return few_tiles(s);
 }

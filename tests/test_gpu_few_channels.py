@@ -67,3 +67,15 @@ def test_one_tap(oracle, case):
     y = sw.sw_conv2d_bias_relu(torch.from_numpy(x).cuda(), torch.from_numpy(w).cuda(), torch.from_numpy(b).cuda(), 1, 0, True)
     assert sw.sw_last_kernel().startswith(f"mfma_f32_{kernel}_"), sw.sw_last_kernel()
     assert_f32_parity(y.cpu().numpy(), y_ref, d, f"one tap {case}")
+
+
+@pytest.mark.parametrize("case", [(9, 32, 40, 21, 31, 2, "few"), (3, 64, 24, 31, 31, 1, "few"), (2, 30, 100, 30, 33, 3, "few"), (13, 64, 24, 99, 99, 2, "dma")],
+                         ids=lambda c: "x".join(str(v) for v in c[:6]))
+def test_one_tap_strided(oracle, case):
+    N, Ci, Co, H, W, stride, kernel = case
+    x = inputs.normal_f32((N, Ci, H, W), 9600 + Ci)
+    w = inputs.normal_f32((Co, Ci, 1, 1), 9700 + Co, (2.0 / Ci) ** 0.5)
+    y_ref, d = oracle.conv2d(x, w, stride, 0)
+    y = sw.sw_conv2d(torch.from_numpy(x).cuda(), torch.from_numpy(w).cuda(), stride, 0)
+    assert sw.sw_last_kernel().startswith(f"mfma_f32_{kernel}_"), sw.sw_last_kernel()
+    assert_f32_parity(y.cpu().numpy(), y_ref, d, f"one tap, stride {stride} {case}")
