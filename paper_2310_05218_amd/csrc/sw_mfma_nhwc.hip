@@ -300,7 +300,8 @@ __global__ __launch_bounds__(256) void direct_nhwc_kernel(const void* __restrict
 //
 // Measured (us, replayed graphs of ten, 3x3 at stride 2 on three channels, against one thread per output):
 // half, 4 x 210 x 198 to 64 channels 74.7 -> 10.3, 4 x 152 x 108 31.1 -> 8.4, 32 x 224 x 224 649 -> 45 (31 TFLOP/s), 7x7 on 8 x 224 x 224
-// 901 -> 62; fp32 4 x 152 x 108 33.6 -> 7.7.  Bound by the round trip in front of the barrier and, of small launches, a thread's chain of
+// 901 -> 62; fp32 4 x 152 x 108 33.6 -> 7.7.  Staging without branches, since: half 2 x 104 x 109 8.1 -> 7.1, 1.10 x over 50 layers; reading a tap's
+// operands before the products of the one before was 0.96 x, eight values in flight 1.02 x.  Bound by the round trip in front of the barrier and, of small launches, a thread's chain of
 // LDS reads and multiply-adds; of large ones by those.
 struct FewNhwcParams {
     Epilogue ep;
@@ -338,8 +339,11 @@ __global__ __launch_bounds__(256) void few_channels_nhwc_kernel(const void* __re
 #pragma unroll
         for (int u = 0; u < 4; ++u) {
             const int i = base + 256 * u, r = fast_div(i, P.by_pitch), e = i - r * P.pitch - P.pad * CI, h = o0 * P.stride - P.pad + r;
-            v[u] = i < cells && h >= 0 && h < P.H && e >= 0 && e < rowlen ? value(xv, first + (int64_t)h * rowlen + e) : 0.f;
-            f[u] = i < filters ? value(wv, i) : 0.f;
+            // (loads of the first value in place of branches around them, which would be waited for one by one)
+            const bool in = i < cells && h >= 0 && h < P.H && e >= 0 && e < rowlen;
+            const float vx = value(xv, first + (in ? (int64_t)h * rowlen + e : 0)), vw = value(wv, i < filters ? i : 0);
+            v[u] = in ? vx : 0.f;
+            f[u] = vw;
         }
 #pragma unroll
         for (int u = 0; u < 4; ++u) {
