@@ -272,7 +272,8 @@ __global__ __launch_bounds__(512, 2) void mfma_nhwc_lds_kernel(const unsigned ch
     const int apitch = FS ? P.fp2 : P.fpitch, cpt = FS ? P.NP : P.cpt;
     const unsigned char* arow = smem + (lj * apitch + kq) * 16;            // + 32 cb apitch 16 + (tap cpt + 2 ks) 16
 
-    const float floor_ = P.ep.relu ? 0.f : -__builtin_inff();              // (the rectifier as a lower bound)
+    // (the rectifier as a lower bound; without one a NaN, which the maximum with a number ignores and that with a NaN keeps)
+    const float floor_ = P.ep.relu ? 0.f : __builtin_nanf("");
 
     using Acc = std::conditional_t<(EK >= kFmtS8), intx16, floatx16>;
     Acc acc[CB][PB];
