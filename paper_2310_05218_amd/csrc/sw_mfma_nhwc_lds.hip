@@ -70,7 +70,8 @@ constexpr size_t kLdsAll = 160 * 1024;
 constexpr size_t kFilterMax = 76 * 1024;       // resident filters of a workgroup
 constexpr int kMaxWK = 12;                     // window loads per loading wavefront and stage
 constexpr int kMaxFK = 12;                     // filter loads per loading wavefront and stage (filters fetched per chunk)
-constexpr unsigned kBeyond = 0x80000000u;
+constexpr unsigned kBeyond = 0x80000000u;      // a byte offset no x or w of less than 2 GiB reaches
+constexpr unsigned kBeyondY = 0xffff0000u;     // ... and no tile of y: 256 pixels of 65535 blocks of 64 channels of four bytes
 // formats beyond Elem's: int8 operands with exact int32 sums, leaving as int32 or requantised to int8
 constexpr int kFmtS8 = 3, kFmtS8Q = 4, kFormats = 5;
 
@@ -435,7 +436,7 @@ __global__ __launch_bounds__(512, 2) void mfma_nhwc_lds_kernel(const unsigned ch
                             for (int j = 0; j < 4; ++j) f[j] = fmaxf(acc[cb][b][4 * q + j] + bias[j], floor_);
                             v = __builtin_bit_cast(intx4, f);
                         }
-                        __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(uintx4, v), yr, c + 4 * kq < co_end ? off + 4 * c : kBeyond, 0, 0);
+                        __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(uintx4, v), yr, c + 4 * kq < co_end ? off + 4 * c : kBeyondY, 0, 0);
                     }
             }
         } else {
@@ -480,20 +481,20 @@ __global__ __launch_bounds__(512, 2) void mfma_nhwc_lds_kernel(const unsigned ch
                                     const auto r0 = __builtin_amdgcn_permlane32_swap(v[2 * h][0], v[2 * h + 1][0], false, false);
                                     const auto r1 = __builtin_amdgcn_permlane32_swap(v[2 * h][1], v[2 * h + 1][1], false, false);
                                     const int c = cb * 32 + 16 * h + 8 * kq;
-                                    __builtin_amdgcn_raw_buffer_store_b128(uintx4{r0[0], r1[0], r0[1], r1[1]}, yr, c < co_end ? off + 2 * c : kBeyond, 0, 0);
+                                    __builtin_amdgcn_raw_buffer_store_b128(uintx4{r0[0], r1[0], r0[1], r1[1]}, yr, c < co_end ? off + 2 * c : kBeyondY, 0, 0);
                                 }
                             } else {
                                 // (channels 16 kq .. 16 kq + 15)
                                 const auto r0 = __builtin_amdgcn_permlane32_swap(v[0], v[2], false, false);
                                 const auto r1 = __builtin_amdgcn_permlane32_swap(v[1], v[3], false, false);
                                 const int c = cb * 32 + 16 * kq;
-                                __builtin_amdgcn_raw_buffer_store_b128(uintx4{r0[0], r0[1], r1[0], r1[1]}, yr, c < co_end ? off + c : kBeyond, 0, 0);
+                                __builtin_amdgcn_raw_buffer_store_b128(uintx4{r0[0], r0[1], r1[0], r1[1]}, yr, c < co_end ? off + c : kBeyondY, 0, 0);
                             }
                         } else {
 #pragma unroll
                             for (int q = 0; q < 4; ++q) {
                                 const int c = cb * 32 + 8 * q + 4 * kq;
-                                const unsigned at = c < co_end ? off + c * OB : kBeyond;
+                                const unsigned at = c < co_end ? off + c * OB : kBeyondY;
                                 if constexpr (OB == 2) __builtin_amdgcn_raw_buffer_store_b64(__builtin_bit_cast(uintx2, v[q]), yr, at, 0, 0);
                                 else __builtin_amdgcn_raw_buffer_store_b32((unsigned)v[q], yr, at, 0, 0);
                             }
@@ -527,7 +528,7 @@ LdsPlan search_plan(const Conv2dShape& s, int ek, const void* x, const void* w, 
     if (reinterpret_cast<uintptr_t>(x) % 16 != 0 || reinterpret_cast<uintptr_t>(w) % 16 != 0 ||
         reinterpret_cast<uintptr_t>(y) % (4 * ob) != 0)
         return best;
-    if ((int64_t)s.N * s.Ho * s.Wo * s.C_out >= (1LL << 40) || (int64_t)s.C_out * ob >= (1LL << 22)) return best;      // (256 pixels of y: 32-bit offsets)
+    if ((int64_t)s.N * s.Ho * s.Wo * s.C_out >= (1LL << 40)) return best;
     const int frow = RS * s.C_in / cpp, fpitch = frow | 1;
     const int64_t IW = (int64_t)(s.Wo - 1) * s.stride + (int64_t)(s.S - 1) * s.dil + 1;
     const int HoWo = s.Ho * s.Wo;
