@@ -496,7 +496,11 @@ PwPlan plan_pointwise(const Conv2dShape& s, const float* x, const float* w, cons
     if (HW * s.N >= (1LL << 31) - (1 << 20) || HW * s.C_in >= (1LL << 31) || reinterpret_cast<uintptr_t>(w) % 16 != 0) return a;
     const auto fits = [&](int cb) { return (size_t)cb * 32 * (s.C_in + 4) * sizeof(float) <= kPwLdsMax; };
     const auto aligned = [&](int qb) {
-        if (loose) return HW >= qb && (reinterpret_cast<uintptr_t>(x) | reinterpret_cast<uintptr_t>(y)) % 4 == 0;
+        // A plane's last group is taken whole: of 9 pixels 12 are computed in fours, 10 in pairs.  Below 26 pixels pairs are faster, unless their
+        // filters (13 steps and more of two blocks) leave a CU one workgroup.  us, fours / pairs: 72 -> 114 at 3 x 7, 2959 images 33.5 / 20.1, 40 -> 442 at
+        // 3 x 3, 1648 images 28.9 / 16.6; of 308 drawn layers of 32 to 192 channels 1.12 x
+        // (eleven 0.81 to 0.97), of 140 beyond 0.92 x; fewer channels stay where the direct-to-LDS kernel takes what would be fours
+        if (loose) return HW >= (qb == 4 && s.C_in >= 32 && s.C_in <= 192 ? 26 : qb) && (reinterpret_cast<uintptr_t>(x) | reinterpret_cast<uintptr_t>(y)) % 4 == 0;
         return HW % qb == 0 && reinterpret_cast<uintptr_t>(x) % (4 * qb) == 0 && reinterpret_cast<uintptr_t>(y) % (4 * qb) == 0;
     };
     const auto units = [&](int cb, int qb) {

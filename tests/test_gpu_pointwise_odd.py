@@ -65,3 +65,16 @@ def test_odd_planes_beyond(oracle):
     ref, _ = oracle.conv2d(x, w, 1, 0)
     assert np.array_equal(np.isnan(y), np.isnan(ref)) and np.array_equal(np.isinf(y), np.isinf(ref))
     assert np.array_equal(np.sign(y[np.isinf(ref)]), np.sign(ref[np.isinf(ref)]))
+
+
+# small planes, whose last group is a large part: pairs of pixels up to 25 and 192 channels, fours beyond
+@pytest.mark.parametrize("case", [(2959, 72, 114, 3, 7, "<2,2,1>"), (1648, 40, 442, 3, 3, "<2,2,1>"), (1600, 192, 65, 5, 5, "<2,2,1>"),
+                                  (1800, 200, 65, 5, 5, "<2,4,1>"), (1500, 56, 130, 3, 9, "<2,4,1>")], ids=lambda c: "x".join(str(v) for v in c[:5]))
+def test_small_planes(oracle, case):
+    N, Ci, Co, H, W, form = case
+    x = inputs.normal_f32((N, Ci, H, W), inputs.seed_for(8, 31 * Ci + Co))
+    w = inputs.normal_f32((Co, Ci, 1, 1), inputs.seed_for(8, 1000 + Ci), (2.0 / Ci) ** 0.5)
+    y = sw.sw_conv2d(torch.from_numpy(x).cuda(), torch.from_numpy(w).cuda(), 1, 0)
+    assert sw.sw_last_kernel() == "mfma_f32_pointwise_split_kernel" + form
+    y_ref, d = oracle.conv2d(x, w, 1, 0)
+    assert_f32_parity(y.cpu().numpy(), y_ref, d, f"pointwise, small planes {case}")
