@@ -339,6 +339,14 @@ hipError_t launch_any(const float* x, const float* w, float* y, const Conv2dShap
 
 bool mfma_f32_any_supported(const Conv2dShape& s) { return s.C_in >= 2 && plan_any(s, nullptr).ok; }
 
+// (us of nine taps from the channels that a workgroup multiplies and the rounds of 256 workgroups; fitted to 600 launches, nine in ten within 0.76 to 1.2)
+double mfma_f32_any_estimate_nine(const Conv2dShape& s, const float* w)
+{
+    const AnyPlan a = plan_any(s, w);
+    const double wgs = (double)a.tiles_x * a.tiles_y * s.N * ((s.C_out + 63) / 64);
+    return 14.8 + 0.577 * ((s.C_in + a.CK - 1) / a.CK * a.CK) * (wgs > 256 ? wgs / 256 : 1.0);
+}
+
 hipError_t launch_mfma_f32_any(const float* x, const float* w, float* y, const Conv2dShape& s, hipStream_t st,
                                const Epilogue& ep)
 {

@@ -305,6 +305,20 @@ static bool split_first(const Conv2dShape& s)
     return s.C_in > 32 || (s.C_in > 16 && (pixels > 1024 || s.C_in % 8 != 0 || s.C_out > 96)) || (s.C_in > 8 && (pixels > 2500 || s.C_out > 96));
 }
 
+// ... but of up to 32 channels not those whose windows hold many times the cells of their tiles (dilations from 3 up, nine filter rows), which
+// every block of 32 output channels fetches and splits again.  The estimates decide against the kernel that has the layer otherwise (us, that
+// kernel / the split one: 24 -> 174 at 87 x 55 9 x 1, 40 images 196 / 404, 24 -> 349 at 46 x 46 dilation 4, 16 images 88 / 165, 12 -> 370 at 70 x 70
+// dilation 3, 17 images 116 / 160; of 4042 drawn layers of 9 to 32 channels, half of them so dilated or 9 x 1, 43 were slower split, 0.49 to 0.97.
+// Left there are those of 0.81 to 0.97, where neither estimate is that good, and a few go back that were up to 1.1 x as fast split.  The fixed and
+// the quad kernel had none, 1.09 to 4 x).
+static bool split_slower(const Conv2dShape& s, const float* x, const float* w)
+{
+    if (s.C_in > 32 || (mfma_f32_supported(s) && mfma_f32_workgroups(s) >= 160)) return false;
+    // (the line between them lies higher for sums in parts, whose launches are the smaller ones)
+    if (const int parts = mfma_f32_dma_parts(s, x, w)) return mfma_f32_split_estimate(s) > (parts > 1 ? 1.2 : 1.05) * mfma_f32_dma_estimate_nine(s, x, w);
+    return !mfma_f32_quad_supported(s) && mfma_f32_any_supported(s) && mfma_f32_split_estimate(s) > 1.1 * mfma_f32_any_estimate_nine(s, w);
+}
+
 // The multi-channel fp32 convolution with the store's epilogue (none for sw_conv2d).
 static int run_conv2d(const float* x, const float* w, float* y, const Conv2dShape& s, const Epilogue& ep, hipStream_t st)
 {
@@ -335,7 +349,7 @@ static int run_conv2d(const float* x, const float* w, float* y, const Conv2dShap
         if (mfma_f32_stem_supported(s)) return launch_status(launch_mfma_f32_stem(x, w, y, s, st, ep));
         if (split_first(s) && mfma_f32_split_supported(s)) {
             if (s.C_in <= 32 && few_tiles(s)) return launch_status(launch_mfma_f32_few(x, w, y, s, st, ep));
-            return launch_status(launch_mfma_f32_split(x, w, y, s, st, ep));
+            if (!split_slower(s, x, w)) return launch_status(launch_mfma_f32_split(x, w, y, s, st, ep));
         }
         const bool quad_ok = mfma_f32_quad_supported(s);
         const bool any_ok = quad_ok || mfma_f32_any_supported(s);

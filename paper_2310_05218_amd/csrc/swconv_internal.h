@@ -192,6 +192,7 @@ hipError_t launch_sliding_plane(const float* x, const float* w, float* y, int64_
 // ---- multi-channel fp32, few taps (1x1 ... 4x4), C_in % 8 == 0, any stride / padding / dilation: both operands
 // brought into LDS by direct-to-LDS loads, two stages (16-byte aligned w, tensors below 2 GiB)
 bool       mfma_f32_dma_supported(const Conv2dShape& s, const float* x, const float* w);
+double     mfma_f32_dma_estimate_nine(const Conv2dShape& s, const float* x, const float* w);   // us, nine taps
 int        mfma_f32_dma_parts(const Conv2dShape& s, const float* x, const float* w);      // parts of its sums (0: not supported)
 hipError_t launch_mfma_f32_dma(const float* x, const float* w, float* y, const Conv2dShape& s, hipStream_t st,
                                const Epilogue& ep = Epilogue{nullptr, 0});
@@ -295,6 +296,7 @@ hipError_t launch_mfma_f32(const float* x, const float* w, float* y, const Conv2
                            const Epilogue& ep = Epilogue{nullptr, 0});
 int64_t    mfma_f32_workgroups(const Conv2dShape& s);     // of the fixed 3x3 / 5x5 kernel, one per CU at a time; 0: tiles half empty
 bool       mfma_f32_any_supported(const Conv2dShape& s);  // any extent, stride and channel count (C_in >= 2)
+double     mfma_f32_any_estimate_nine(const Conv2dShape& s, const float* w);                           // us, nine taps
 hipError_t launch_mfma_f32_any(const float* x, const float* w, float* y, const Conv2dShape& s, hipStream_t st,
                                const Epilogue& ep = Epilogue{nullptr, 0});
 bool       mfma_f32_rows_supported(const Conv2dShape& s, const float* x); // large filters: one filter row of a channel chunk at a time

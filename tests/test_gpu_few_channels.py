@@ -79,3 +79,25 @@ def test_one_tap_strided(oracle, case):
     y = sw.sw_conv2d(torch.from_numpy(x).cuda(), torch.from_numpy(w).cuda(), stride, 0)
     assert sw.sw_last_kernel().startswith(f"mfma_f32_{kernel}_"), sw.sw_last_kernel()
     assert_f32_parity(y.cpu().numpy(), y_ref, d, f"one tap, stride {stride} {case}")
+
+
+# (N, C_in, C_out, H, W, R, S, stride, pad, dilation, kernel): nine taps whose windows hold many times the cells of a tile, on both sides of the
+# line to the direct-to-LDS and the any-shape kernel; 9 and 13 channels on split operands, several tiles a workgroup
+WIDE = [
+    (40, 24, 174, 87, 55, 9, 1, 1, 1, 1, "dma"), (16, 24, 349, 46, 46, 3, 3, 1, 4, 4, "dma"), (15, 16, 36, 47, 47, 3, 3, 1, 4, 4, "dma"),
+    (17, 12, 370, 70, 70, 3, 3, 1, 0, 3, "any"), (23, 20, 303, 53, 53, 9, 1, 1, 0, 1, "any"),
+    (16, 24, 349, 46, 46, 3, 3, 1, 2, 2, "split"), (6, 24, 96, 30, 17, 9, 1, 1, 0, 1, "split"), (17, 11, 64, 70, 70, 3, 3, 1, 0, 3, "split"),
+    (12, 9, 104, 40, 44, 3, 3, 1, 1, 1, "split"), (9, 13, 200, 37, 29, 3, 3, 1, 0, 2, "split"),
+]
+
+
+@pytest.mark.parametrize("case", WIDE, ids=lambda c: "x".join(str(v) for v in c[:10]))
+def test_wide_windows(oracle, case):
+    N, Ci, Co, H, W, R, S, stride, pad, dil, kernel = case
+    x = inputs.normal_f32((N, Ci, H, W), 9800 + Ci)
+    w = inputs.normal_f32((Co, Ci, R, S), 9900 + Co, (2.0 / (Ci * R * S)) ** 0.5)
+    y = sw.sw_conv2d_dilated(torch.from_numpy(x).cuda(), torch.from_numpy(w).cuda(), stride, pad, dil)
+    assert sw.sw_last_kernel().startswith(f"mfma_f32_{kernel}_kernel"), sw.sw_last_kernel()
+    images = sorted({0, N - 1})                              # (the oracle is slow: the first and the last image)
+    y_ref, d = oracle.conv2d_dilated(np.ascontiguousarray(x[images]), w, stride, pad, dil)
+    assert_f32_parity(y.cpu().numpy()[images], y_ref, d, f"wide windows {case}")
