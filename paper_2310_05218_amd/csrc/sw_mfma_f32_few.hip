@@ -367,6 +367,8 @@ bool mfma_f32_few_supported(const Conv2dShape& s) { return plan_few(s).ok; }
 
 double mfma_f32_few_estimate(const Conv2dShape& s) { return plan_few(s).est; }
 
+int mfma_f32_few_columns(const Conv2dShape& s) { return plan_few(s).P.TW; }
+
 hipError_t launch_mfma_f32_few(const float* x, const float* w, float* y, const Conv2dShape& s, hipStream_t st, const Epilogue& ep)
 {
     FewPlan a = plan_few(s);

@@ -278,7 +278,10 @@ static bool few_tiles_before_rows(const Conv2dShape& s)
 // at 16 x 16, 20 images 13.7 -> 7.3, 64 -> 40 at 36 x 36, 2 images 9.9 -> 5.7, 488 -> 120 at 24 x 24, 3 images 23.0 -> 9.6, 56 -> 104 at 20 x 20, 3
 // images 6.8 -> 5.8; of 46 drawn layers up to 640 tiles 1.1 to 3.2 x, of 24 of 800 to 1600 tiles into 128 and more channels 1.1 to 2.0 x, errors against 64 bits
 // smaller in each.  Beyond it is 0.85 to 1.25 x, into fewer channels 0.5 (144 -> 16 at 68 x 68, 7 images) to 1.6 x, and from fewer 0.8 to 1.3 x.  Fewer than 128 tiles
-// of fewer than 128 channels and 32 to 47 input channels would gain as well: tests assert the pointwise kernel's plans there.
+// of fewer than 128 channels and 32 to 47 input channels would gain as well: tests assert the pointwise kernel's plans there.  From 512 tiles up into
+// fewer than 16 channels the pointwise kernel keeps planes that would be taken in tiles of four columns, 16 bytes of a row at a time (us, it / this one:
+// 344 -> 9 at 16 x 90, 6 images 16.4 / 19.5, 216 -> 7 at 35 x 34, 8 images 12.4 / 14.6; of 13 drawn layers on rows of 26 and more
+// all 0.84 to 1.0; shorter rows 0.98 to 1.25, wider tiles 1.0 to 2.4).
 // Single taps that the pointwise kernel does not have (strides, odd planes), in place of the direct-to-LDS kernel, up to 1600 tiles of 32 to 64 channels,
 // 1000 into fewer than 48 (1.05 to 2.2 x of 100 drawn layers, errors smaller in each: 56 -> 424 at 11 x 11, 2 images 13.5 -> 5.8, 64 -> 64 at 97 x 97 stride 2 12.2 -> 6.0; beyond
 // 0.86 to 1.5 x; of 24 channels 0.96 to 1.6 x, some errors larger).
@@ -287,6 +290,7 @@ static bool few_tiles_first(const Conv2dShape& s, const float* x, const float* w
     const int64_t tiles = (int64_t)s.N * (((int64_t)s.Ho * s.Wo + 15) / 16) * ((s.C_out + 15) / 16);
     if (mfma_f32_pointwise_supported(s, x, w, y)) {
         if (s.C_in < 48 || tiles > (s.C_out >= 128 && s.C_in >= 64 ? 1600 : 640) || (tiles < 128 && s.C_out < 128)) return false;
+        if (s.C_out < 16 && tiles > 512 && s.Wo > 24 && mfma_f32_few_supported(s) && mfma_f32_few_columns(s) <= 4) return false;
     } else if (s.C_in <= 64 && !few_tiles_before_rows(s)) {
         if (s.R * s.S != 1 || s.C_in < 32 || tiles < 65 || tiles > (s.C_out < 48 ? 1000 : 1600)) return false;
     }

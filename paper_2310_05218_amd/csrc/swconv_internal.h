@@ -207,6 +207,7 @@ hipError_t launch_mfma_f32_split(const float* x, const float* w, float* y, const
 // ---- multi-channel fp32, few tiles: a tile's reduction split over the wavefronts of a workgroup (tensors below 2 GiB)
 bool       mfma_f32_few_supported(const Conv2dShape& s);
 double     mfma_f32_few_estimate(const Conv2dShape& s);         // us
+int        mfma_f32_few_columns(const Conv2dShape& s);          // output columns of a tile (where supported)
 hipError_t launch_mfma_f32_few(const float* x, const float* w, float* y, const Conv2dShape& s, hipStream_t st,
                                const Epilogue& ep = Epilogue{nullptr, 0});
 

@@ -101,3 +101,16 @@ def test_wide_windows(oracle, case):
     images = sorted({0, N - 1})                              # (the oracle is slow: the first and the last image)
     y_ref, d = oracle.conv2d_dilated(np.ascontiguousarray(x[images]), w, stride, pad, dil)
     assert_f32_parity(y.cpu().numpy()[images], y_ref, d, f"wide windows {case}")
+
+
+# (N, C_in, C_out, H, W, kernel): one tap into fewer than 16 channels, planes in tiles of four columns and in wider ones
+@pytest.mark.parametrize("case", [(6, 344, 9, 16, 90, "pointwise_split"), (4, 128, 12, 70, 35, "pointwise"), (15, 280, 5, 18, 32, "few"), (17, 160, 7, 24, 24, "few"),
+                                  (5, 344, 9, 16, 90, "few"), (21, 104, 11, 20, 20, "few")], ids=lambda c: "x".join(str(v) for v in c[:5]))
+def test_one_tap_few_outputs(oracle, case):
+    N, Ci, Co, H, W, kernel = case
+    x = inputs.normal_f32((N, Ci, H, W), 9310 + Ci)
+    w = inputs.normal_f32((Co, Ci, 1, 1), 9410 + Co, (2.0 / Ci) ** 0.5)
+    y = sw.sw_conv2d(torch.from_numpy(x).cuda(), torch.from_numpy(w).cuda(), 1, 0)
+    assert sw.sw_last_kernel().startswith(f"mfma_f32_{kernel}_kernel"), sw.sw_last_kernel()
+    y_ref, d = oracle.conv2d(x, w, 1, 0)
+    assert_f32_parity(y.cpu().numpy(), y_ref, d, f"one tap, few outputs {case}")
