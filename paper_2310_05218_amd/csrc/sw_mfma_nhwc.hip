@@ -339,11 +339,17 @@ __global__ __launch_bounds__(256) void few_channels_nhwc_kernel(const void* __re
 #pragma unroll
         for (int u = 0; u < 4; ++u) {
             const int i = base + 256 * u, r = fast_div(i, P.by_pitch), e = i - r * P.pitch - P.pad * CI, h = o0 * P.stride - P.pad + r;
-            // (loads of the first value in place of branches around them, which would be waited for one by one)
             const bool in = i < cells && h >= 0 && h < P.H && e >= 0 && e < rowlen;
-            const float vx = value(xv, first + (in ? (int64_t)h * rowlen + e : 0)), vw = value(wv, i < filters ? i : 0);
-            v[u] = in ? vx : 0.f;
-            f[u] = vw;
+            if constexpr (EK == kElemF32) {
+                v[u] = in ? value(xv, first + (int64_t)h * rowlen + e) : 0.f;
+                f[u] = i < filters ? value(wv, i) : 0.f;
+            } else {
+                // (loads of the first value in place of branches around them, which would be waited for one by one: their halves of a register are
+                // widened behind each.  fp32 values need nothing of the kind and were 0.91 to 1.04, 0.99 on the average, as fast so)
+                const float vx = value(xv, first + (in ? (int64_t)h * rowlen + e : 0)), vw = value(wv, i < filters ? i : 0);
+                v[u] = in ? vx : 0.f;
+                f[u] = vw;
+            }
         }
 #pragma unroll
         for (int u = 0; u < 4; ++u) {
