@@ -680,6 +680,14 @@ bool mfma_s8_nhwc_lds_supported(const int8_t* x, const int8_t* w, const void* y,
     return s.dil == 1 && plan_lds(s, requant ? kFmtS8Q : kFmtS8, x, w, y).ok;
 }
 
+int mfma_nhwc_lds_stages(const void* x, const void* w, const void* y, const Conv2dShape& s, int fmt, int* tiles)
+{
+    const LdsPlan a = plan_lds(s, fmt, x, w, y);
+    if (!a.ok) return 0;
+    *tiles = (int)((a.tiles + a.gx - 1) / a.gx);
+    return a.P.stages;
+}
+
 // fmt: Elem, kFmtS8 or kFmtS8Q
 static hipError_t launch_any(const void* x, const void* w, void* y, const Conv2dShape& s, int fmt, const Epilogue& ep, const Requant& rq,
                              hipStream_t st)

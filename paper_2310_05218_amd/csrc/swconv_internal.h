@@ -235,6 +235,8 @@ hipError_t launch_mfma_nhwc_lds(const void* x, const void* w, void* y, const Con
 // the same kernel on int8 tensors: exact int32 sums, leaving as int32 (rq null) or requantised to int8 (C_in % 32 == 0)
 bool       mfma_s8_nhwc_lds_supported(const int8_t* x, const int8_t* w, const void* y, bool requant, const Conv2dShape& s);
 hipError_t launch_mfma_s8_nhwc_lds(const int8_t* x, const int8_t* w, void* y, const Requant* rq, const Conv2dShape& s, hipStream_t st);
+// window stages of its plan (0: not supported) and tiles of a workgroup; fmt: Elem, 3 int8 -> int32, 4 int8 -> int8
+int        mfma_nhwc_lds_stages(const void* x, const void* w, const void* y, const Conv2dShape& s, int fmt, int* tiles);
 // int8 requantised to int8, one tap at stride 1 over at least 128 channels (multiples of 32; C_out a multiple of 16; 16-byte
 // aligned tensors)
 bool       mfma_s8_pointwise_nhwc_supported(const int8_t* x, const int8_t* w, const int8_t* y, const Conv2dShape& s);
