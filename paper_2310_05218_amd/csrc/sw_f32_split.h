@@ -3,7 +3,7 @@
 // and a product is taken as   lh + hl + mm + mh + hm + hh,   six products of eight-bit significands that are exact in the
 // fp32 accumulators.  What is left out (ml, lm, ll) is up to 2^-24.0 of the product, as much as an fp32 rounding (both operands
 // 1 + 2^-8 - 2^-17; over random pairs 2^-27.5 in the mean square, above 2^-26 for 2.7 % of them).  A sum of a single product is off by
-// up to 1.0e-7 of it where an fp32 instruction gives 6e-8 (1.5e-7 in 1 x 1 layers, whose six products share an accumulator), and where
+// up to 1.0e-7 of it where an fp32 instruction gives 6e-8 (1.6e-7 in 1 x 1 layers, whose six products share an accumulator), and where
 // many equal operands give the left-out parts one sign they are still 2^-24 of the result.
 //
 // Why: v_mfma_f32_32x32x16_bf16 performs 8 times the multiply-adds of v_mfma_f32_32x32x2_f32 in half its time (per K step of

@@ -372,3 +372,24 @@ def test_left_out_products(torch, sw, case):
     taps = torch.nn.functional.conv2d(torch.ones(1, Ci, H, W, dtype=torch.float64), torch.ones(1, Ci, R, R, dtype=torch.float64), stride=st, padding=pad)
     ref = taps * (v * v)
     assert torch.all((y - ref).abs() <= 2.0 ** -23 * ref)
+
+
+@pytest.mark.parametrize("case", [(40, 152, 160, 25, 25, 1, "pointwise_split"), (1648, 40, 442, 3, 3, 1, "pointwise_split"), (12, 9, 104, 40, 44, 3, "split"),
+                                  (1, 16, 64, 60, 60, 3, "split"), (5, 32, 200, 19, 23, 3, "split")], ids=lambda c: "x".join(str(v) for v in c[:6]))
+def test_sums_of_a_single_product(torch, sw, case):
+    """One weight per output channel: every output is one product.  2^-24 of it may be left out, and of the five additions of its six parts three meet
+    the full magnitude at most, 2^-24 each."""
+    N, C, K, H, W, R, kernel = case
+    rng = np.random.default_rng(4100 + C)
+    x = inputs.normal_f32((N, C, H, W), 4101) * np.float32(2.0) ** rng.integers(-30, 30, (N, C, 1, 1)).astype(np.float32)
+    w = np.zeros((K, C, R, R), np.float32)
+    ci, r, s = rng.integers(0, C, K), rng.integers(0, R, K), rng.integers(0, R, K)
+    v = inputs.normal_f32((K,), 4102)
+    w[np.arange(K), ci, r, s] = v
+    y = sw.sw_conv2d(torch.from_numpy(x).cuda(), torch.from_numpy(w).cuda(), 1, R // 2).cpu().numpy()
+    assert sw.sw_last_kernel().startswith(f"mfma_f32_{kernel}_kernel"), sw.sw_last_kernel()
+    xp = np.pad(x, ((0, 0), (0, 0), (R // 2, R // 2), (R // 2, R // 2)))
+    for k in range(K):
+        ref = xp[:, ci[k], r[k]:r[k] + H, s[k]:s[k] + W].astype(np.float64) * np.float64(v[k])
+        err = np.abs(y[:, k] - ref)
+        assert np.all(err <= 4 * 2.0 ** -24 * np.abs(ref)), (k, float(np.max(err / np.maximum(np.abs(ref), 1e-300))))
