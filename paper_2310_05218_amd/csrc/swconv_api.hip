@@ -266,8 +266,9 @@ static bool few_tiles(const Conv2dShape& s)
 // Those of filters of 5 x 5 to 7 x 7 over 17 to 64 channels into whole blocks of 16, in place of the compound kernel, which has a workgroup per 256 pixels whatever
 // the launch (us, graph of ten, compound kernel / this one: 56 -> 80 at 28 x 28 5x5 stride 2 151.6 / 8.3, 20 x 64 -> 96 at 8 x 8 stride 2 150.1 / 8.5,
 // 10 x 64 -> 264 at 20 x 20 160.9 / 72.7, 7 x 24 -> 408 at 32 x 32 88.9 / 55.2, 2 x 63 -> 30 at 40 x 40 7x7 stride 2 343.0 / 11.1; of 22 drawn layers
-// 1.5 to 31 x, errors against 64 bits a third).  Fewer channels, fewer outputs, 64 channels under 7x7 and larger filters would gain as well: tests
-// assert the compound kernel's plans there.
+// 1.5 to 31 x, errors against 64 bits a third).  The lines at 16 and 64 channels and at 16 outputs are not where the kernels cross: beyond them tests assert
+// the compound kernel's plans.  Both sides, compound kernel / this one: 4 x 64 -> 29 at 8 x 8 7x7 268 / 10.4 (79 layers 2.8 to 34 x), 11 -> 47 at 44 x 44 5x7
+// 59 / 6.5 (271 of 8 to 16 channels 1.6 to 15 x), 2 x 64 -> 10 at 42 x 44 5x7 196 / 9.3 (375 into fewer than 16 outputs 5 to 34 x).
 static bool few_tiles_before_rows(const Conv2dShape& s)
 {
     return s.R >= 5 && s.S >= 5 && s.R * s.S <= 49 && s.C_in > 16 && s.C_in < (s.R * s.S < 49 ? 65 : 64) && s.C_out >= 16;
@@ -277,14 +278,16 @@ static bool few_tiles_before_rows(const Conv2dShape& s)
 // from 48 up, up to 640 tiles, or 1600 of 64 and more channels into 128 and more.  Graph of ten, us: 456 -> 48 at 38 x 38, 2 images 20.5 -> 13.4, 272 -> 16
 // at 16 x 16, 20 images 13.7 -> 7.3, 64 -> 40 at 36 x 36, 2 images 9.9 -> 5.7, 488 -> 120 at 24 x 24, 3 images 23.0 -> 9.6, 56 -> 104 at 20 x 20, 3
 // images 6.8 -> 5.8; of 46 drawn layers up to 640 tiles 1.1 to 3.2 x, of 24 of 800 to 1600 tiles into 128 and more channels 1.1 to 2.0 x, errors against 64 bits
-// smaller in each.  Beyond it is 0.85 to 1.25 x, into fewer channels 0.5 (144 -> 16 at 68 x 68, 7 images) to 1.6 x, and from fewer 0.8 to 1.3 x.  Fewer than 128 tiles
-// of fewer than 128 channels and 32 to 47 input channels would gain as well: tests assert the pointwise kernel's plans there.  From 512 tiles up into
+// smaller in each.  Beyond it is 0.85 to 1.25 x, into fewer channels 0.5 (144 -> 16 at 68 x 68, 7 images) to 1.6 x, and from fewer 0.8 to 1.3 x.  The lines at 48
+// channels and 128 tiles are not where the kernels cross: tests assert the pointwise kernel's plans there.  Both sides, it / this one: 10 x 40 -> 10 at 8 x 8
+// 5.5 / 4.5 (774 layers of 32 and 40 channels 0.94 to 1.38 x), 2 x 184 -> 13 at 10 x 10 10.4 / 5.4 (478 of fewer than 128 tiles 1.2 to 3.5 x).  From 512 tiles up into
 // fewer than 16 channels the pointwise kernel keeps planes that would be taken in tiles of four columns, 16 bytes of a row at a time (us, it / this one:
 // 344 -> 9 at 16 x 90, 6 images 16.4 / 19.5, 216 -> 7 at 35 x 34, 8 images 12.4 / 14.6; of 13 drawn layers on rows of 26 and more
 // all 0.84 to 1.0; shorter rows 0.98 to 1.25, wider tiles 1.0 to 2.4).
 // Single taps that the pointwise kernel does not have (strides, odd planes), in place of the direct-to-LDS kernel, up to 1600 tiles of 32 to 64 channels,
 // 1000 into fewer than 48 (1.05 to 2.2 x of 100 drawn layers, errors smaller in each: 56 -> 424 at 11 x 11, 2 images 13.5 -> 5.8, 64 -> 64 at 97 x 97 stride 2 12.2 -> 6.0; beyond
-// 0.86 to 1.5 x; of 24 channels 0.96 to 1.6 x, some errors larger).
+// 0.86 to 1.5 x; of 24 channels 0.96 to 1.6 x, some errors larger).  Nor do they cross at 65 tiles, where tests assert the direct-to-LDS kernel: 2 x 64 -> 28 at
+// 13 x 13 8.0 / 4.7 (196 layers 1.4 to 2.3 x).
 static bool few_tiles_first(const Conv2dShape& s, const float* x, const float* w, const float* y)
 {
     const int64_t tiles = (int64_t)s.N * (((int64_t)s.Ho * s.Wo + 15) / 16) * ((s.C_out + 15) / 16);
@@ -302,7 +305,9 @@ static bool few_tiles_first(const Conv2dShape& s, const float* x, const float* w
 // plans of the others: small launches into few channels.  Graph of ten, us: 25 x 32 -> 208 at 36 x 36 92.2 -> 33.8, 21 x 24 -> 112 at 61 x 61 dilation 2
 // 63.8 -> 48.0, 4 x 32 -> 96 at 38 x 38 21.6 -> 9.1, 12 x 28 -> 32 at 67 x 67 65.6 -> 14.7, 21 x 9 -> 416 at 14 x 14 19.7 -> 13.7, 20 x 30 -> 32 at
 // 25 x 41 stride 2 43.9 -> 8.6; in few tiles 24 -> 32 at 17 x 72 dilation 2 14.5 -> 5.5.  Over 250 drawn layers 1.6 (direct-to-LDS), 2.1 (quad) and
-// 3.1 (any-shape kernel), none below 1.13, errors against 64 bits smaller in each.
+// 3.1 (any-shape kernel), none below 1.13, errors against 64 bits smaller in each.  The lines at 1024 and 2500 pixels and 96 outputs are those of the tests' layers,
+// not where the kernels cross.  Both sides, others / split or few tiles: 6 x 32 -> 17 at 7 x 7 9.8 / 5.3 (178 layers of 17 to 32 channels 1.55 to 2.55 x), 7 x 15 -> 32
+// at 7 x 7 stride 2 11.9 / 5.0 (512 of 9 to 16 channels 1.3 to 3.3 x).
 static bool split_first(const Conv2dShape& s)
 {
     const int64_t pixels = (int64_t)s.N * s.Ho * s.Wo;
