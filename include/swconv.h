@@ -105,21 +105,26 @@ int sw_pool2d(const float* x, float* y, int N, int C, int H, int W, int R, int S
  *     y[n,co,i,j] = sum_{ci,r,s} w[co,ci,r,s] * xz[n,ci,i*stride+r-pad, j*stride+s-pad]
  * x: [N,C_in,H,W] fp32;  w: [C_out,C_in,R,S] fp32;  y: [N,C_out,H_out,W_out] fp32.
  * Supported: any shape with R,S <= 64 (SW_ERR_UNSUPPORTED beyond).  C_in >= 2
- * runs on the matrix cores.  Nine taps over more than 32 channels (stride 1, or any
- * stride while the launch is one tile per workgroup), few channels at an even stride
- * (2 to 7, rows of at most 8 taps but not so short that little of a matrix instruction
- * is filled, R * C_in <= 22) and 1x1 at stride 1 without padding (C_in % 16 == 0 or
- * >= 128, from 16 to 320 channels up by the size of the launch) take every fp32 operand
- * as a sum of three bf16 values on the bf16 matrix instructions: six of nine products,
- * fp32 sums; what is left out of a product is up to 2^-24 of it, errors of sums of N(0,1)
- * data against 64-bit sums are below those of the fp32 instructions.  Outputs that
- * meet an infinity, a NaN, an operand from about 2^104 up or a sum from 2^80 up are computed
- * on the fp32 instructions instead: the same results at up to ten times a launch's time
- * where all outputs do.  3x3 and 5x5 at stride 1 with C_in % 16 == 0,
- * C_out % 64 == 0 and 16-byte aligned w run in a large-tile fp32 kernel when the problem
- * fills the chip with such tiles, other 1x1 layers (C_in % 8 == 0, an even number of
- * pixels per plane, x and y aligned to 8 bytes, w to 16) in a kernel that reads its
- * operands straight from x, every other extent, stride, padding and channel count in
+ * runs on the matrix cores.  Operands as sums of three bf16 values on the bf16 matrix
+ * instructions (six of nine products, fp32 sums): nine taps (stride 1, or any stride
+ * while the launch is one tile per workgroup) over more than 32 channels and, in all but
+ * small launches into few channels and filters whose windows hold many times a tile's
+ * cells, down to 9 channels; few channels at an even stride (2 to 7, rows of at most 8
+ * taps but not so short that little of a matrix instruction is filled, R * C_in <= 22);
+ * 1x1 at stride 1 without padding (C_in % 8 == 0, w aligned to 16 bytes), on even planes
+ * aligned to 8 bytes with C_in % 16 == 0 or >= 128, from 16 to 320 channels up by the size
+ * of the launch, and on planes of any size at any 4-byte address from 16 or 32 channels
+ * up by its size.  What is left out of a product is up to 2^-24 of it (a sum of a single
+ * product is off by up to 1.6e-7 of it); errors of sums of N(0,1) data against 64-bit
+ * sums are below those of the fp32 instructions.  Outputs that meet an infinity, a NaN,
+ * an operand from about 2^104 up or a sum from 2^80 up are computed on the fp32
+ * instructions instead: the same results at up to ten times a launch's time where all
+ * outputs do.  All else multiplies in fp32: small launches (few tiles of 16 channels x 16
+ * pixels) in a kernel whose wavefronts share an output's products; 3x3 and 5x5 at stride 1
+ * with C_in % 16 == 0, C_out % 64 == 0 and 16-byte aligned w in a large-tile kernel when
+ * the problem fills the chip with such tiles; other 1x1 layers (C_in % 8 == 0, an even
+ * number of pixels per plane, x and y aligned to 8 bytes, w to 16) in a kernel that reads
+ * its operands straight from x; every other extent, stride, padding and channel count in
  * few-tap, compound or any-shape kernels (one thread per output only when the window or
  * filter does not fit 64 KB of LDS).  C_in == 1 runs the one-filter-per-plane kernels
  * of sw_conv2d_depthwise.

@@ -27,6 +27,9 @@
 // fp32 matrix instruction holds up the vector and LDS instructions of its SIMD: with those between them a run took 950 cycles where
 // the eight matrix instructions take 290 alone and the rest 350, so they stand in one block in front.  That, uniform loop counts and no
 // reads in branches: 1.07 x over 31 drawn layers (1.00 to 1.14), this one 11.1 -> 10.2 us, 10 x 80 -> 192 at 19 x 19 5 x 5 47.3 -> 41.5.
+// Not where eight wavefronts run two workgroups a CU over a multiple of 32 products in 585 to 768 workgroups: of 159 such layers of 4 x 8 to 8 x 8 filters
+// half take 1.1 to 1.3 times as long as before (19 -> 111 at 38 wide 8 x 8 60.3 / 76.6 us), the other half 0.9 to 1.0 times.  Neither four runs of filters
+// under way, with one workgroup a CU or two, nor three made up for it.
 // Tried and not kept: sixteen wavefronts (12.8), loads by wavefronts of their own in four chunks with a barrier each (11.3 to 16.1), the window
 // through registers by 16-byte loads (11.0, and 1 us more for the smallest layers), taps instead of runs (filters at 36-byte strides: 11.8),
 // the outputs' places computed before the products (10.7).
