@@ -28,8 +28,9 @@
 // the eight matrix instructions take 290 alone and the rest 350, so they stand in one block in front.  That, uniform loop counts and no
 // reads in branches: 1.07 x over 31 drawn layers (1.00 to 1.14), this one 11.1 -> 10.2 us, 10 x 80 -> 192 at 19 x 19 5 x 5 47.3 -> 41.5.
 // Not where eight wavefronts run two workgroups a CU over a multiple of 32 products in 585 to 768 workgroups: of 159 such layers of 4 x 8 to 8 x 8 filters
-// half take 1.1 to 1.3 times as long as before (19 -> 111 at 38 wide 8 x 8 60.3 / 76.6 us), the other half 0.9 to 1.0 times.  Neither four runs of filters
-// under way, with one workgroup a CU or two, nor three made up for it.
+// a third take 1.1 to 1.3 times as long as before (15 -> 167 at 71 x 22 8 x 8 stride 2, 32 images 49.4 / 62.2 us), the others 0.9 to 1.05 times.  Their wavefronts live as long
+// as before, but end together, two workgroups a CU, and the last ones run alone; the order of the first ones (`stagger`) mends some.  Neither four runs of
+// filters under way, with one workgroup a CU or two, nor three made up for it.
 // Tried and not kept: sixteen wavefronts (12.8), loads by wavefronts of their own in four chunks with a barrier each (11.3 to 16.1), the window
 // through registers by 16-byte loads (11.0, and 1 us more for the smallest layers), taps instead of runs (filters at 36-byte strides: 11.8),
 // the outputs' places computed before the products (10.7).
@@ -58,6 +59,7 @@ struct FewParams {
     int K, T, S, dil;               // products of an output, taps, filter columns
     int KW, CW, PW, lKW, lCW;       // wavefronts that share a tile's products; tiles of 16 channels; tiles of 16 pixels
     int KWq, KWr;                   // KW runs in whole periods of T and the rest
+    int stagger;                    // the first of two workgroups of a CU comes first
     int TH, TW, IW, cells;          // rows and columns of a pixel tile, columns and cells of its window
     int pitch, pieces, group;       // words from a channel's window to the next's; loads per channel, or channels per load
     int CC, chunks;                 // channels in LDS at a time
@@ -79,6 +81,11 @@ template <int WAVES, int MIN, int RING>
 __global__ __launch_bounds__(64 * WAVES, MIN) void mfma_f32_few_kernel(const float* __restrict__ x, const float* __restrict__ w,
                                                                                       float* __restrict__ y, const FewParams P)
 {
+    // Two workgroups of a CU that began together end together, and the third then runs alone: the first comes first where there are three turns of half a
+    // launch's (513 to 768 workgroups; us, 28 -> 142 at 98 x 38 4 x 8 dilation 3, 6 images 60.0 -> 47.9; 159 layers 1.01 in the median, 0.93 to 1.25)
+    if constexpr (WAVES == 8 && MIN == 4) {
+        if (P.stagger && (blockIdx.x >> 8 & 1) == 0) __builtin_amdgcn_s_setprio(1);
+    }
     constexpr int NA = 12;                              // accumulators: short chains of roundings
     extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
     int* tab = reinterpret_cast<int*>(smem);
@@ -381,6 +388,7 @@ hipError_t launch_mfma_f32_few(const float* x, const float* w, float* y, const C
     // -> 16 at 31 x 31, 27 images 9.7 / 8.8); with 768 workgroups or fewer all run at once as it is
     if (a.waves == 4)
         return a.grid > 768 && 4 * (a.lds + 512) <= 160 * 1024 ? launch_one<4, 4, 2>(x, w, y, a, st) : launch_one<4, 2, 4>(x, w, y, a, st);
+    a.P.stagger = a.grid > 512 && a.grid <= 768;
     // eight wavefronts: two workgroups a CU, with half the filters under way, where there are that many and LDS has room for them
     return a.grid > 256 && 2 * (a.lds + 512) <= 160 * 1024 ? launch_one<8, 4, 2>(x, w, y, a, st) : launch_one<8, 2, 4>(x, w, y, a, st);
 }

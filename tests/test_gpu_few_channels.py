@@ -114,3 +114,16 @@ def test_one_tap_few_outputs(oracle, case):
     assert sw.sw_last_kernel().startswith(f"mfma_f32_{kernel}_kernel"), sw.sw_last_kernel()
     y_ref, d = oracle.conv2d(x, w, 1, 0)
     assert_f32_parity(y.cpu().numpy(), y_ref, d, f"one tap, few outputs {case}")
+
+
+# launches of eight wavefronts, two workgroups a CU, below, in and above the range of three turns of half a launch's (405, 540, 605, 688 and 880 workgroups)
+@pytest.mark.parametrize("case", [(5, 11, 2, 53, 23, 3, 5, 1, 1, 1), (18, 2, 80, 13, 76, 4, 4, 1, 0, 1), (5, 155, 3, 46, 46, 4, 4, 1, 2, 2),
+                                  (43, 440, 8, 32, 32, 1, 1, 2, 0, 1), (5, 324, 4, 132, 132, 1, 2, 3, 0, 1)], ids=lambda c: "x".join(str(v) for v in c))
+def test_two_workgroups_a_cu(oracle, case):
+    N, Ci, Co, H, W, R, S, stride, pad, dil = case
+    x = inputs.normal_f32((N, Ci, H, W), 9950 + Ci)
+    w = inputs.normal_f32((Co, Ci, R, S), 9960 + Co, (2.0 / (Ci * R * S)) ** 0.5)
+    y = sw.sw_conv2d_dilated(torch.from_numpy(x).cuda(), torch.from_numpy(w).cuda(), stride, pad, dil)
+    assert sw.sw_last_kernel().startswith("mfma_f32_few_kernel<8,"), sw.sw_last_kernel()
+    y_ref, d = oracle.conv2d_dilated(x, w, stride, pad, dil)
+    assert_f32_parity(y.cpu().numpy(), y_ref, d, f"two workgroups a CU {case}")
