@@ -116,8 +116,8 @@ def test_one_tap_few_outputs(oracle, case):
     assert_f32_parity(y.cpu().numpy(), y_ref, d, f"one tap, few outputs {case}")
 
 
-# launches of eight wavefronts, two workgroups a CU, below, in and above the range of three turns of half a launch's (405, 540, 605, 688 and 880 workgroups)
-@pytest.mark.parametrize("case", [(5, 11, 2, 53, 23, 3, 5, 1, 1, 1), (18, 2, 80, 13, 76, 4, 4, 1, 0, 1), (5, 155, 3, 46, 46, 4, 4, 1, 2, 2),
+# launches of eight wavefronts, two workgroups a CU, below, in and above the range of three turns of half a launch's (405, 672, 605, 688 and 880 workgroups)
+@pytest.mark.parametrize("case", [(5, 11, 2, 53, 23, 3, 5, 1, 1, 1), (14, 5, 4, 81, 84, 13, 3, 1, 0, 1), (5, 155, 3, 46, 46, 4, 4, 1, 2, 2),
                                   (43, 440, 8, 32, 32, 1, 1, 2, 0, 1), (5, 324, 4, 132, 132, 1, 2, 3, 0, 1)], ids=lambda c: "x".join(str(v) for v in c))
 def test_two_workgroups_a_cu(oracle, case):
     N, Ci, Co, H, W, R, S, stride, pad, dil = case
