@@ -384,11 +384,11 @@ hipError_t launch_mfma_f32_few(const float* x, const float* w, float* y, const C
     FewPlan a = plan_few(s);
     if (!a.ok) return hipErrorInvalidValue;
     a.P.ep = ep;
+    a.P.stagger = a.grid > 512 && a.grid <= 768;
     // four wavefronts: a fourth workgroup a CU likewise (graph of ten, us, four filters under way / two: 208 -> 16 at 31 x 31, 15 images 11.7 / 10.8, 96
     // -> 16 at 31 x 31, 27 images 9.7 / 8.8); with 768 workgroups or fewer all run at once as it is
     if (a.waves == 4)
         return a.grid > 768 && 4 * (a.lds + 512) <= 160 * 1024 ? launch_one<4, 4, 2>(x, w, y, a, st) : launch_one<4, 2, 4>(x, w, y, a, st);
-    a.P.stagger = a.grid > 512 && a.grid <= 768;
     // eight wavefronts: two workgroups a CU, with half the filters under way, where there are that many and LDS has room for them
     return a.grid > 256 && 2 * (a.lds + 512) <= 160 * 1024 ? launch_one<8, 4, 2>(x, w, y, a, st) : launch_one<8, 2, 4>(x, w, y, a, st);
 }
